@@ -81,6 +81,8 @@ typedef struct {
  * debug_tune: "name=a,b,c,d;..." with name in {qkv, o, gu, down, lm}: tiles per workgroup, waves per
  * workgroup, k-major layout (0/1), interleaved k-blocks (0/1); and name in {pf_qkv, pf_o, pf_gu,
  * pf_down}: 16-row chunks per workgroup, K slices[, prefetch depth[, tiles per wave (pf_qkv: 3..5)]] of the prompt-block GEMMs;
+ * "pf_ring=V[,S]": tile shape V (0..15) of the ring kernel of bf16 prompt-block GEMMs and K slices S of its residual-add
+ * launches (default: by estimated time; a pf_* entry takes its class back to the other kernel);
  * "qkv_rows=N": tiles per QKV workgroup in passes of five rows and more (default: by balance).  A
  * layout override changes how weights are tiled in the arena, never their values.  The string is
  * copied by asd_create.

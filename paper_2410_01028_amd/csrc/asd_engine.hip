@@ -51,7 +51,7 @@ hipError_t scratch_ptr(unsigned char** out) {
 }
 
 struct GemmCfg { int TN, NW, grid, kmajor, kint; };
-struct PfCfg { int NC, KS, PD, NA; };  // prompt GEMM: 16-row chunks per workgroup, K slices, prefetch depth, tiles per wave (0: by balance)
+struct PfCfg { int NC, KS, PD, NA; bool forced; };  // prompt GEMM: 16-row chunks per workgroup, K slices, prefetch depth, tiles per wave (0: by balance); forced: given in debug_tune
 
 struct Layer {
     char *wqkv, *wo, *wg, *wu, *wd;
@@ -100,6 +100,8 @@ struct asd_engine {
     int32_t* pf_tok;
     float *pf_xres, *pf_raw, *pf_ssq, *pf_rscale, *pf_cos_rows;
     void *pf_xb, *pf_q, *pf_attn_out, *pf_hmid;
+    int pf_rows;                        // most rows of a prompt block
+    int pf_ring_tune[2] = {-1, 0};          // debug_tune "pf_ring": tile shape and K slices of the eight-wave prompt GEMM
     PfCfg pf_qkv, pf_o, pf_gu, pf_down;
     // launch shapes
     GemmCfg g_qkv, g_o, g_gu, g_down, g_lm;
@@ -256,6 +258,7 @@ struct Plan {
         argmax, tokbuf, out_tokens, st, ops, ops_bytes, staging, staging_bytes, total, qlogits;
     size_t pf_tok, pf_xres, pf_raw, pf_ssq, pf_rscale, pf_cos_rows, pf_xb, pf_q, pf_attn_out, pf_hmid;
     int es, KE, KBd, KBq, KBf, n_pages, nc_stride, qkv_tiles;
+    int pf_rows;                                    // most rows of a prompt block
     GemmCfg g_qkv, g_o, g_gu, g_down, g_lm;
 };
 
@@ -325,17 +328,35 @@ Plan make_plan(const asd_config& c) {
     if ((size_t)qd * c.d_model > biggest) biggest = (size_t)qd * c.d_model;
     p.staging_bytes = align_up(biggest * p.es + 4096);
     p.staging = take(p.staging_bytes);
-    // prompt-block workspace: PF_ROWS rows as PF_CHUNKS chunks of 16
-    p.pf_tok = take((size_t)PF_ROWS * 4);
-    p.pf_xres = take((size_t)PF_ROWS * c.d_model * 4);
-    p.pf_raw = take((size_t)PF_MAX_KSPLIT * PF_ROWS * c.d_model * 4);
-    p.pf_ssq = take((size_t)PF_ROWS * 4);
-    p.pf_rscale = take((size_t)PF_ROWS * 4);
-    p.pf_cos_rows = take((size_t)2 * c.n_layers * PF_ROWS * 4);
-    p.pf_xb = take((size_t)PF_CHUNKS * p.KBd * frag * NPL);
-    p.pf_q = take((size_t)PF_CHUNKS * p.KBq * frag * NPL);
-    p.pf_attn_out = take((size_t)PF_CHUNKS * p.KBq * frag * NPL);
-    p.pf_hmid = take((size_t)PF_CHUNKS * p.KBf * frag * NPL);
+    // Prompt-block workspace of R rows as R / 16 chunks of 16.  512 rows have their own place behind the staging region.
+    // Longer blocks (fewer, better balanced launches) are laid out over the staging region too, which only a weight
+    // upload or read-back uses, and only if they fit into what 512 rows and the staging region take anyway (the arena does
+    // not grow) and no activation has k padding (padding is cleared once, when the engine is created, and an upload
+    // would leave other bytes there).
+    auto take_pf = [&](size_t R) {
+        p.pf_rows = (int)R;
+        p.pf_tok = take(R * 4);
+        p.pf_xres = take(R * c.d_model * 4);
+        p.pf_raw = take((size_t)PF_RAW_ROWS * c.d_model * 4);
+        p.pf_ssq = take(R * 4);
+        p.pf_rscale = take(R * 4);
+        p.pf_cos_rows = take((size_t)2 * c.n_layers * R * 4);
+        p.pf_xb = take(R / 16 * p.KBd * frag * NPL);
+        p.pf_q = take(R / 16 * p.KBq * frag * NPL);
+        p.pf_attn_out = take(R / 16 * p.KBq * frag * NPL);
+        p.pf_hmid = take(R / 16 * p.KBf * frag * NPL);
+    };
+    take_pf(PF_MIN_ROWS);
+    const size_t end = off;
+    if (c.dtype == ASD_DT_BF16 && c.d_model % kblk == 0 && qd % kblk == 0 && c.d_ffn % kblk == 0)
+        for (size_t R = PF_MAX_ROWS; R > PF_MIN_ROWS; R /= 2) {
+            const Plan keep = p;
+            off = p.staging;
+            take_pf(R);
+            if (off <= end) break;
+            p = keep;
+        }
+    off = end;
     p.total = off;
     return p;
 }
@@ -714,10 +735,10 @@ void destroy_host(asd_engine* e) {
 // Launch shape of a prompt GEMM class: NC 16-row chunks per workgroup and K slices (slices only for the two
 // residual-add GEMMs).  The configuration's debug_tune (development aid) overrides, e.g. "pf_qkv=8,1;pf_o=8,2;pf_gu=4,1;pf_down=8,4".
 PfCfg pf_pick(const char* tune, const char* name, int nc, int ks) {
-    PfCfg g{nc, ks, 2, 0};
+    PfCfg g{nc, ks, 2, 0, false};
     int v[4] = {0, 0, 1, 0};
     const int n = tune_entry(tune, name, v, 4);
-    if (n >= 2 && (v[0] == 2 || v[0] == 4 || v[0] == 8) && v[1] >= 1 && v[1] <= PF_MAX_KSPLIT && v[2] >= 1 && v[2] <= 4) { g.NC = v[0]; g.KS = v[1]; g.PD = v[2]; }
+    if (n >= 2 && (v[0] == 2 || v[0] == 4 || v[0] == 8) && v[1] >= 1 && v[1] <= PF_MAX_KSPLIT && v[2] >= 1 && v[2] <= 4) { g.NC = v[0]; g.KS = v[1]; g.PD = v[2]; g.forced = true; }
     if (n == 4 && v[3] >= 3 && v[3] <= 5) g.NA = v[3];
     return g;
 }
@@ -725,11 +746,16 @@ PfCfg pf_pick(const char* tune, const char* name, int nc, int ks) {
 constexpr int PF_NW = 4;                 // waves per workgroup of a prompt GEMM
 template <int EPI> constexpr int pf_na() { return EPI == PF_GU ? 2 : 4; }     // weight tiles per wave (gate and up each, for PF_GU)
 
+// K slices of the four-wave kernel's residual-add launches: as configured, no more than k-blocks or than the buffer holds
+int pf_old_slices(const PfCfg& g, int KB, int n_chunks) {
+    const int most = PF_RAW_ROWS / (n_chunks * 16);
+    int ks = g.KS < KB ? g.KS : KB;
+    return ks < most ? ks : most;
+}
 template <class T, int EPI, int NA> bool launch_pf_gemm_na(hipStream_t s, const PfCfg& g, PfArgs a, int n_chunks) {
     a.n_fb = (a.n_tiles + PF_NW * NA - 1) / (PF_NW * NA);
     a.n_rb = (n_chunks + g.NC - 1) / g.NC;
-    a.ksplit = EPI == PF_RAW ? g.KS : 1;
-    if (a.ksplit > a.KB) a.ksplit = a.KB;
+    a.ksplit = EPI == PF_RAW ? pf_old_slices(g, a.KB, n_chunks) : 1;
     const unsigned grid = (unsigned)((a.n_fb + 7) / 8 * 8 * a.n_rb * a.ksplit);
 #define PFK(nc, pd) if (g.NC == nc && g.PD == pd) { pf_gemm_kernel<T, EPI, NA, nc, PF_NW, pd><<<grid, PF_NW * 64, 0, s>>>(a); return true; }
     if constexpr (NA == pf_na<EPI>()) { PFK(2, 1) PFK(4, 1) PFK(8, 1) PFK(2, 2) PFK(4, 2) PFK(8, 2) PFK(2, 3) PFK(4, 3) PFK(2, 4) PFK(4, 4) }
@@ -762,7 +788,84 @@ template <class T, int EPI> bool launch_pf_gemm_t(hipStream_t s, const PfCfg& g,
     }
     return launch_pf_gemm_na<T, EPI, pf_na<EPI>()>(s, g, a, n_chunks);
 }
+
+// Tile shapes of pf_ring_kernel: output tiles (for gate/up: pairs of tiles) and chunks per workgroup, and the time of a
+// k-block where the products set it (the large shapes, at the clock the card keeps under them; measured).
+struct PfRingTile { int FT, RC; float us_kb; };
+constexpr PfRingTile kPfRing[] = {{12, 8, 0.68f}, {16, 8, 0.76f}, {24, 8, 1.10f}, {16, 16, 1.32f},
+                                  {3, 2, 0.f}, {3, 3, 0.f}, {3, 4, 0.f}, {4, 2, 0.f}, {4, 3, 0.f}, {4, 4, 0.f}, {4, 6, 0.f}, {4, 8, 0.f},
+                                  {8, 2, 0.f}, {8, 3, 0.f}, {8, 4, 0.f}, {8, 8, 0.f}};
+constexpr int kPfRings = sizeof kPfRing / sizeof kPfRing[0], kPfBig = 4;      // the first kPfBig: gate/up tiles counted singly
+struct PfRingPick { int tile, ks; };                                          // tile -1: pf_gemm_kernel
+// The kernel and shape with the least estimated time.  pf_ring_kernel: rounds of workgroups (one to a compute unit) on the
+// busiest XCD, times a workgroup's k-blocks at the rate a compute unit takes fragments in, about 43 KiB per us whichever cache level
+// they come from (7 to 32 KiB per k-block measured 0.18 to 0.71 us), plus 4 us per round for filling the ring and the
+// epilogue.  pf_gemm_kernel: up to three workgroups share a compute unit, which then takes in about 57 KiB per us, but one alone
+// needs 0.5 us per k-block (its prefetch is two k-blocks deep).  It stays the better one where its small tile leaves
+// less of the chip idle: O / down of the 13B shape at 300 rows 44 / 100 us against 57 / 125 us.  Split-K launches: the
+// partial sums' way through memory (written and read back, about 5 TB/s).  Up to PF_FIXED_SLICES chunks the K slices are the
+// same whatever the choice: such blocks need them all to give every compute unit work, and a result then depends neither
+// on the shape nor on the block's length.  Longer blocks fill the chip with fewer (13B at 1003 rows, O and down: 94 and 227 us
+// with two slices, 120 and 300 us with four).
+constexpr int PF_FIXED_SLICES = 40;
+PfRingPick pf_ring_pick(const asd_engine* e, int epi, const PfCfg& g, int n_tiles, int KB, int n_chunks) {
+    const int units = device_units() / 8 > 0 ? device_units() / 8 : 1;
+    const int ks4 = pf_old_slices(g, KB, n_chunks);
+    auto raw_us = [&](int ks) { return epi == PF_RAW ? ks * (2.f * n_chunks * 16 * n_tiles * 16 * 4 / 5e6f) : 0.f; };
+    PfRingPick best{-1, epi == PF_RAW ? ks4 : 1};
+    float best_us = 3e38f;
+    if (e->pf_ring_tune[0] < 0 && e->pf_ring_tune[1] == 0) {
+        const int na = epi == PF_GU ? 2 : epi == PF_QKV ? pf_qkv_na(g, n_tiles, n_chunks) : 4, per = 4 * na;
+        const float wgs = (float)(((n_tiles + per - 1) / per + 7) / 8 * ((n_chunks + g.NC - 1) / g.NC) * best.ks) / units;
+        const float on_unit = wgs > 2.f ? wgs : ceilf(wgs), frags = 4 * (epi == PF_GU ? 2 * na : na) + 2 * g.NC;
+        best_us = (float)KB / best.ks * fmaxf(0.5f, on_unit * frags / 57.f) + 4.f + raw_us(best.ks);
+    }
+    for (int v = 0; v < kPfRings; ++v) {
+        const PfRingTile& T = kPfRing[v];
+        if (e->pf_ring_tune[0] >= 0 && e->pf_ring_tune[0] != v) continue;
+        const int per = epi == PF_GU && v < kPfBig ? T.FT / 2 : T.FT, n_fb = (n_tiles + per - 1) / per, n_rb = (n_chunks + T.RC - 1) / T.RC;
+        const int frags = (epi == PF_GU ? 2 * per : per) + 2 * T.RC;
+        for (int ks = 1; ks <= PF_MAX_KSPLIT; ++ks) {
+            if (ks > 1 && (epi != PF_RAW || ks * n_chunks * 16 > PF_RAW_ROWS || ks > KB)) break;
+            if (epi == PF_RAW && (e->pf_ring_tune[1] > 0 ? ks != e->pf_ring_tune[1] : n_chunks <= PF_FIXED_SLICES && ks != ks4)) continue;
+            const int rounds = ((n_fb + 7) / 8 * n_rb * ks + units - 1) / units;
+            const float us = rounds * ((float)KB / ks * fmaxf(T.us_kb, frags / 43.f) + 4.f) + raw_us(ks);
+            if (us < best_us) { best = {v, ks}; best_us = us; }
+        }
+    }
+    return best;
+}
+template <int EPI> bool launch_pf_ring(hipStream_t s, const PfRingPick& p, PfArgs a, int n_chunks) {
+    const PfRingTile& T = kPfRing[p.tile];
+    const int per = EPI == PF_GU && p.tile < kPfBig ? T.FT / 2 : T.FT;
+    a.n_fb = (a.n_tiles + per - 1) / per;
+    a.n_rb = (n_chunks + T.RC - 1) / T.RC;
+    a.ksplit = p.ks;
+    const unsigned grid = (unsigned)((a.n_fb + 7) / 8 * 8 * a.n_rb * a.ksplit);
+    constexpr int N1 = EPI == PF_GU ? 2 : 1;            // one output tile per wave
+    constexpr auto ring = [](int nf) { return 159 / nf < 16 ? 159 / nf / 2 * 2 : 16; };      // stages the LDS holds (an even number)
+    switch (p.tile) {
+#define PFR(v, nt, nc, fw, rw, st, pf) case v: pf_ring_kernel<EPI, nt, nc, fw, rw, st, pf><<<grid, fw * rw * 64, 0, s>>>(a); return true;
+        PFR(0, 6, 2, 2, 4, 5, true) PFR(1, 4, 4, 4, 2, 4, true) PFR(2, 6, 4, 4, 2, 4, true) PFR(3, 8, 4, 2, 4, 3, false)
+#define PFN(v, nc, fw) PFR(v, N1, nc, fw, 1, ring(N1 * fw + 2 * nc), true)
+        PFN(4, 2, 3) PFN(5, 3, 3) PFN(6, 4, 3) PFN(7, 2, 4) PFN(8, 3, 4) PFN(9, 4, 4) PFN(10, 6, 4) PFN(11, 8, 4)
+        PFN(12, 2, 8) PFN(13, 3, 8) PFN(14, 4, 8) PFN(15, 8, 8)
+#undef PFN
+#undef PFR
+    }
+    return false;
+}
+PfRingPick pf_use(const asd_engine* e, const PfCfg& g, int epi, int n_tiles, int KB, int n_chunks) {
+    if (e->c.dtype != ASD_DT_BF16 || BF16::NP != 2 || g.forced) return {-1, pf_old_slices(g, KB, n_chunks)};
+    return pf_ring_pick(e, epi, g, n_tiles, KB, n_chunks);
+}
+// K slices of a residual-add GEMM's launch (what pf_resid_kernel has to add up)
+int pf_slices(const asd_engine* e, const PfCfg& g, int n_tiles, int KB, int n_chunks) {
+    return pf_use(e, g, PF_RAW, n_tiles, KB, n_chunks).ks;
+}
 template <int EPI> bool launch_pf_gemm(asd_engine* e, const PfCfg& g, const PfArgs& a, int n_chunks) {
+    const PfRingPick p = pf_use(e, g, EPI, a.n_tiles, a.KB, n_chunks);
+    if (p.tile >= 0) return launch_pf_ring<EPI>(e->stream, p, a, n_chunks);
     return e->c.dtype == ASD_DT_BF16 ? launch_pf_gemm_t<BF16, EPI>(e->stream, g, a, n_chunks) : launch_pf_gemm_t<F32, EPI>(e->stream, g, a, n_chunks);
 }
 
@@ -777,13 +880,13 @@ template <class T> void launch_pf_attn_t(asd_engine* e, const PfAttnArgs& a, int
 template <class T> void launch_pf_rows_t(asd_engine* e, int what, int rows, int n_chunks, int ksplit, const float* gain, float* cos_row, int tail_row) {
     const asd_config& c = e->c;
     using El = typename T::elem;
-    const int64_t xb_plane = (int64_t)PF_CHUNKS * e->KBd * 64 * e->KE, xb_chunk = (int64_t)e->KBd * 64 * e->KE;
+    const int64_t xb_plane = (int64_t)(e->pf_rows / 16) * e->KBd * 64 * e->KE, xb_chunk = (int64_t)e->KBd * 64 * e->KE;
     const float inv_d = 1.f / (float)c.d_model;
     if (what == 0)
         pf_embed_kernel<T><<<n_chunks * 16, 256, 0, e->stream>>>((const El*)e->embed, e->pf_tok, rows, c.d_model, gain, e->pf_xres, e->pf_xb,
                                                                  xb_plane, xb_chunk, e->pf_ssq, e->pf_rscale, inv_d, c.rms_eps);
     else if (what == 1)
-        pf_resid_kernel<T><<<rows, 256, 0, e->stream>>>(e->pf_raw, ksplit, c.d_model, e->pf_xres, e->pf_xb, xb_plane, xb_chunk, gain, e->pf_ssq,
+        pf_resid_kernel<T><<<rows, 256, 0, e->stream>>>(e->pf_raw, n_chunks * 16, ksplit, c.d_model, e->pf_xres, e->pf_xb, xb_plane, xb_chunk, gain, e->pf_ssq,
                                                         e->pf_rscale, cos_row, inv_d, c.rms_eps);
     else
         pf_tail_kernel<T><<<1, 256, 0, e->stream>>>(e->pf_xres, e->pf_ssq, tail_row, c.d_model, e->g_final, e->xres, e->xb,
@@ -804,9 +907,13 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
     auto wl = [&](PfArgs& a, const GemmCfg& cfg, int total_tiles, int KB) {
         a.n_tiles = total_tiles; a.KB = KB; a.w_tile_stride = cfg.kmajor ? 1 : KB; a.w_kb_stride = cfg.kmajor ? total_tiles : 1;
     };
+    // as few blocks as the workspace allows, of equal length in whole 128-row steps (a workgroup's chunks)
+    const int n_blocks = (n + e->pf_rows - 1) / e->pf_rows;
+    const int block = e->pf_rows == PF_MIN_ROWS ? PF_MIN_ROWS : ((n + n_blocks - 1) / n_blocks + 127) / 128 * 128;
+    const int64_t cap = e->pf_rows / 16;                // chunks per activation plane
     int rows = 0;
     for (int r0 = 0; r0 < n; r0 += rows) {
-        rows = n - r0 < PF_ROWS ? n - r0 : PF_ROWS;
+        rows = n - r0 < block ? n - r0 : block;
         const int n_chunks = (rows + 15) / 16;
         CK(e, hipMemcpyAsync(e->pf_tok, tokens + r0, (size_t)rows * 4, hipMemcpyHostToDevice, e->stream));
         set_state_kernel<<<1, 1, 0, e->stream>>>(e->st, r0, 0, 0, 0);
@@ -817,16 +924,16 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
         const double fl_row = 2.0 * rows, ctx_sum = (double)rows * r0 + 0.5 * rows * (rows + 1.0);
 
         PfArgs base{};
-        base.rows = rows; base.rscale = e->pf_rscale; base.raw = e->pf_raw;
+        base.rows = rows; base.raw_rows = n_chunks * 16; base.rscale = e->pf_rscale; base.raw = e->pf_raw;
         base.pos0 = r0; base.rope = e->rope; base.q = e->pf_q; base.page_table = e->page_table;
-        base.q_plane = (int64_t)PF_CHUNKS * e->KBq * 64 * KE; base.q_chunk = (int64_t)e->KBq * 64 * KE;
+        base.q_plane = cap * e->KBq * 64 * KE; base.q_chunk = (int64_t)e->KBq * 64 * KE;
         base.n_h = c.n_heads; base.n_kv = c.n_kv_heads; base.h = c.head_dim; base.page_tokens = c.page_tokens;
-        base.hmid = e->pf_hmid; base.hmid_plane = (int64_t)PF_CHUNKS * e->KBf * 64 * KE; base.hmid_chunk = (int64_t)e->KBf * 64 * KE;
+        base.hmid = e->pf_hmid; base.hmid_plane = cap * e->KBf * 64 * KE; base.hmid_chunk = (int64_t)e->KBf * 64 * KE;
         for (int l = 0; l < L; ++l) {
             const Layer& ly = e->layers[l];
             bool ok = true;
             PfArgs a = base;
-            a.W = (const u32x4*)ly.wqkv; a.X = (const u32x4*)e->pf_xb; a.x_plane = (int64_t)PF_CHUNKS * e->KBd * 64; a.x_chunk = (int64_t)e->KBd * 64;
+            a.W = (const u32x4*)ly.wqkv; a.X = (const u32x4*)e->pf_xb; a.x_plane = cap * e->KBd * 64; a.x_chunk = (int64_t)e->KBd * 64;
             wl(a, e->g_qkv, e->qkv_tiles, e->KBd);
             a.kv = e->kv + (size_t)l * e->kv_layer_bytes;
             pr.begin(ASD_PK_QKV, fl_row * c.d_model * (qd + 2 * kvd));
@@ -843,13 +950,13 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
             pr.end();
 
             PfArgs o = base;
-            o.W = (const u32x4*)ly.wo; o.X = (const u32x4*)e->pf_attn_out; o.x_plane = (int64_t)PF_CHUNKS * e->KBq * 64; o.x_chunk = (int64_t)e->KBq * 64;
+            o.W = (const u32x4*)ly.wo; o.X = (const u32x4*)e->pf_attn_out; o.x_plane = cap * e->KBq * 64; o.x_chunk = (int64_t)e->KBq * 64;
             wl(o, e->g_o, c.d_model / 16, e->KBq);
             pr.begin(ASD_PK_OPROJ, fl_row * qd * c.d_model);
             ok = ok && launch_pf_gemm<PF_RAW>(e, e->pf_o, o, n_chunks);
             pr.end();
             pr.begin(ASD_PK_ROWS, 0);
-            launch_pf_rows(e, 1, rows, n_chunks, e->pf_o.KS < e->KBq ? e->pf_o.KS : e->KBq, ly.g_mlp, e->pf_cos_rows + (size_t)(2 * l) * PF_ROWS, 0);
+            launch_pf_rows(e, 1, rows, n_chunks, pf_slices(e, e->pf_o, c.d_model / 16, e->KBq, n_chunks), ly.g_mlp, e->pf_cos_rows + (size_t)(2 * l) * e->pf_rows, 0);
             pr.end();
 
             PfArgs gu = base;
@@ -860,18 +967,18 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
             pr.end();
 
             PfArgs dn = base;
-            dn.W = (const u32x4*)ly.wd; dn.X = (const u32x4*)e->pf_hmid; dn.x_plane = (int64_t)PF_CHUNKS * e->KBf * 64; dn.x_chunk = (int64_t)e->KBf * 64;
+            dn.W = (const u32x4*)ly.wd; dn.X = (const u32x4*)e->pf_hmid; dn.x_plane = cap * e->KBf * 64; dn.x_chunk = (int64_t)e->KBf * 64;
             wl(dn, e->g_down, c.d_model / 16, e->KBf);
             pr.begin(ASD_PK_DOWN, fl_row * (double)c.d_model * c.d_ffn);
             ok = ok && launch_pf_gemm<PF_RAW>(e, e->pf_down, dn, n_chunks);
             pr.end();
             pr.begin(ASD_PK_ROWS, 0);
-            launch_pf_rows(e, 1, rows, n_chunks, e->pf_down.KS < e->KBf ? e->pf_down.KS : e->KBf, l + 1 < L ? e->layers[l + 1].g_attn : e->g_final,
-                           e->pf_cos_rows + (size_t)(2 * l + 1) * PF_ROWS, 0);
+            launch_pf_rows(e, 1, rows, n_chunks, pf_slices(e, e->pf_down, c.d_model / 16, e->KBf, n_chunks), l + 1 < L ? e->layers[l + 1].g_attn : e->g_final,
+                           e->pf_cos_rows + (size_t)(2 * l + 1) * e->pf_rows, 0);
             pr.end();
             if (!ok) return fail(e, ASD_E_STATE, "no prompt GEMM instance for this launch shape");
         }
-        pf_cos_sum_kernel<<<2 * L, 256, 0, e->stream>>>(e->pf_cos_rows, rows, e->cos_acc);
+        pf_cos_sum_kernel<<<2 * L, 256, 0, e->stream>>>(e->pf_cos_rows, e->pf_rows, rows, e->cos_acc);
         e->kv_len = r0 + rows;
     }
     // the last prompt row through the final norm and the LM head, as row 0 of a one-row pass
@@ -941,10 +1048,12 @@ int asd_create(const asd_config* cfg, void* device_arena, size_t arena_bytes, vo
     e->pf_tok = (int32_t*)(A + p.pf_tok); e->pf_xres = (float*)(A + p.pf_xres); e->pf_raw = (float*)(A + p.pf_raw);
     e->pf_ssq = (float*)(A + p.pf_ssq); e->pf_rscale = (float*)(A + p.pf_rscale); e->pf_cos_rows = (float*)(A + p.pf_cos_rows);
     e->pf_xb = A + p.pf_xb; e->pf_q = A + p.pf_q; e->pf_attn_out = A + p.pf_attn_out; e->pf_hmid = A + p.pf_hmid;
+    e->pf_rows = p.pf_rows;
     e->tune = cfg->debug_tune ? cfg->debug_tune : "";
     e->c.debug_tune = nullptr;              // (the caller's string is not kept; e->tune is the copy)
     const char* tune = e->tune.empty() ? nullptr : e->tune.c_str();
     e->pf_qkv = pf_pick(tune, "pf_qkv", 4, 1); e->pf_o = pf_pick(tune, "pf_o", 4, 4);
+    { int v[2]; const int nv = tune_entry(tune, "pf_ring", v, 2); if (nv >= 1 && v[0] >= 0 && v[0] < kPfRings) { e->pf_ring_tune[0] = v[0]; if (nv == 2 && v[1] >= 1 && v[1] <= PF_MAX_KSPLIT) e->pf_ring_tune[1] = v[1]; } }
     e->pf_gu = pf_pick(tune, "pf_gu", 4, 1); e->pf_down = pf_pick(tune, "pf_down", 4, 4);
     e->g_qkv = p.g_qkv; e->g_o = p.g_o; e->g_gu = p.g_gu; e->g_down = p.g_down; e->g_lm = p.g_lm;
     e->g_qkv_rows = pick_qkv_rows(e->g_qkv, e->qkv_tiles, tune);

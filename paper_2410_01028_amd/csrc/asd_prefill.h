@@ -1,13 +1,15 @@
 // Prompt processing as large-M contractions: the pass that fills the KV cache and measures the prompt's
 // average cosine similarity per sublayer (Section 3.2, the definition of C_l) before the draft / verify loop starts.
 //
-// The prompt is processed in blocks of up to PF_ROWS rows, layer by layer, so every weight is read once per
+// The prompt is processed in blocks of up to 2048 rows, layer by layer, so every weight is read once per
 // block instead of once per 16 rows.  Activations of a block are kept as 16-row chunks, each chunk in the same
 // tiled layout the decode kernels use with a row stride of 16 ([K/KE][16][KE], hi and lo planes for bf16):
 // one (chunk, k-block) fragment is one contiguous KiB that a wave loads with one instruction, and the decode
 // attention kernel runs unchanged on a chunk.
 //
-// pf_gemm_kernel: a workgroup of NW waves owns NW*NA weight tiles (16 output features each) x NC chunks of
+// pf_ring_kernel (bf16): eight waves, a tile of up to 24 weight tiles x 8 chunks (16 x 16 for long blocks), both operands
+// brought into an LDS ring by direct-to-LDS loads; see its own comment.
+// pf_gemm_kernel (fp32, short bf16 blocks): a workgroup of NW waves owns NW*NA weight tiles (16 output features each) x NC chunks of
 // rows and, with a K split, one slice of K.  Per k-block the waves stage the NC chunks' activation fragments
 // in LDS (double buffered, one barrier per k-block); each wave streams its own NA weight fragments from
 // global memory and feeds NA*NC accumulators.  Workgroups that share weights (same features, other rows)
@@ -21,9 +23,12 @@
 #include <type_traits>
 #include "asd_gemm.h"
 
-#define PF_ROWS 512                    // rows per prompt block
-#define PF_CHUNKS (PF_ROWS / 16)
+// A block holds up to 512, 1024 or 2048 rows, whatever the engine's workspace has room for (PF_MIN_ROWS always fits);
+// the raw partial sums of a block take slices x rows <= PF_RAW_ROWS rows of d_model.
+#define PF_MIN_ROWS 512
+#define PF_MAX_ROWS 2048
 #define PF_MAX_KSPLIT 8
+#define PF_RAW_ROWS (PF_MAX_KSPLIT * PF_MIN_ROWS)
 
 enum { PF_QKV = 0, PF_RAW = 1, PF_GU = 2 };
 
@@ -34,8 +39,9 @@ struct PfArgs {
     int64_t w_tile_stride, w_kb_stride;
     int32_t n_fb, n_rb, ksplit;      // feature blocks (NW*NA tiles each), row blocks (NC chunks each), K slices
     int32_t rows;                    // valid rows of this prompt block
-    const float* rscale;             // [PF_ROWS] RMSNorm scale of each row (PF_QKV, PF_GU)
-    float* raw;                      // PF_RAW: [ksplit][PF_ROWS][16 * n_tiles]
+    int32_t raw_rows;                // row stride between the K slices of raw
+    const float* rscale;             // [rows] RMSNorm scale of each row (PF_QKV, PF_GU)
+    float* raw;                      // PF_RAW: [ksplit][raw_rows][16 * n_tiles]
     // PF_QKV
     int32_t pos0;                    // cache position of row 0
     const float* rope;
@@ -56,16 +62,105 @@ template <class T> __device__ __forceinline__ void store_elem4(typename T::elem*
     }
 }
 
+// Epilogues of the prompt GEMMs, straight from the accumulators: lane 16g + m holds features 4g..4g+3 of each tile for
+// row m of each chunk.  PF_GU: acc[0 .. NA-1] gate, acc[NA .. 2NA-1] up.
+template <class T, int EPI, int NA, int NAT, int NC>
+__device__ __forceinline__ void pf_epilogue(const PfArgs& a, const f32x4 (&acc)[NAT][NC], const int (&tile)[NA], const bool (&tval)[NA],
+                                            const int chunk0, const int ks, const int lane) {
+    using E = typename T::elem;
+    const int g = lane >> 4, m = lane & 15;
+    int row[NC];
+    bool rv[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) { row[c] = (chunk0 + c) * 16 + m; rv[c] = row[c] < a.rows; }
+
+    if constexpr (EPI == PF_RAW) {
+        const int N = a.n_tiles * 16;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (!rv[c]) continue;
+            float* dst = a.raw + ((size_t)ks * a.raw_rows + row[c]) * N + 4 * g;
+#pragma unroll
+            for (int s = 0; s < NA; ++s)
+                if (tval[s]) *(f32x4*)(dst + tile[s] * 16) = acc[s][c];
+        }
+    }
+
+    if constexpr (EPI == PF_GU) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (!rv[c]) continue;
+            const float rs = a.rscale[row[c]];
+#pragma unroll
+            for (int s = 0; s < NA; ++s) {
+                if (!tval[s]) continue;
+                float v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float gt = acc[s][c][j] * rs, up = acc[NA + s][c][j] * rs;
+                    v[j] = gt / (1.f + __expf(-gt)) * up;
+                }
+                store_act4<T>(a.hmid, a.hmid_plane, (int64_t)(chunk0 + c) * a.hmid_chunk, tile[s] * 16 + 4 * g, m, v);
+            }
+        }
+    }
+
+    if constexpr (EPI == PF_QKV) {
+        // tile j of a head: rows 0..7 = head dims 8j..8j+7, rows 8..15 = the same dims + h/2 (rotary partners):
+        // lane groups 0,1 hold the first halves, groups 2,3 their partners, 32 lanes away
+        const int hpt = a.h / 16, hh = a.h / 2;
+#pragma unroll
+        for (int s = 0; s < NA; ++s) {
+            if (!tval[s]) continue;                   // wave-uniform
+            const int head = tile[s] / hpt, jt = tile[s] % hpt;
+            const int i0 = jt * 8 + 4 * (g & 1), dim = i0 + (g >= 2 ? hh : 0);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const float rs = rv[c] ? a.rscale[row[c]] : 0.f;
+                float own[4], oth[4], v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { own[j] = acc[s][c][j] * rs; oth[j] = __shfl_xor(own[j], 32); }
+                if (!rv[c]) continue;
+                const int pos = a.pos0 + row[c];
+                if (head < a.n_h + a.n_kv) {
+                    const float* rp = a.rope + ((size_t)pos * hh + i0) * 2;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float cs = rp[2 * j], sn = rp[2 * j + 1];
+                        v[j] = g < 2 ? own[j] * cs - oth[j] * sn : own[j] * cs + oth[j] * sn;
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[j] = own[j];
+                }
+                if (head < a.n_h) {
+                    store_act4<T>(a.q, a.q_plane, (int64_t)(chunk0 + c) * a.q_chunk, head * a.h + dim, m, v);
+                } else {
+                    const bool isk = head < a.n_h + a.n_kv;
+                    const int kvh = isk ? head - a.n_h : head - a.n_h - a.n_kv;
+                    const int PT = a.page_tokens, page = a.page_table[pos / PT], slot = pos % PT;
+                    E* base = (E*)a.kv + ((size_t)page * a.n_kv + kvh) * 2 * PT * a.h;
+                    if (isk) {                   // dim is a multiple of 4: the four values stay inside one lane's KE elements
+                        store_elem4<T>(base + kv_k_off<T>(slot, dim, a.h), v);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) base[kv_v_off<T>(slot, dim + j, a.h)] = T::from_f32(v[j]);
+                    }
+                }
+            }
+        }
+    }
+}
+
 template <class T, int EPI, int NA, int NC, int NW, int PD>
 __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const PfArgs a) {
-    using E = typename T::elem;
     constexpr int NP = T::NP;
     constexpr int NAT = (EPI == PF_GU) ? 2 * NA : NA;
     constexpr int XF = NC * NP;                       // activation fragments per k-block of this row block
     constexpr int XW = (XF + NW - 1) / NW;            // ... staged by each wave
     __shared__ u32x4 xs[2][XF][64];
 
-    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, m = lane & 15;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // workgroup -> (feature block, row block, K slice): consecutive workgroup ids go to the 8 XCDs in turn, so the
     // XCD is the low 3 bits; on one XCD the row blocks and K slices of a feature block follow each other.
     const int L = blockIdx.x, inner = a.n_rb * a.ksplit;
@@ -145,88 +240,172 @@ __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const
     for (int p = 0; p + 1 < PD; ++p)                    // the last, partial round: nothing further to request
         if (kb0 + n_full + p < kb1) k_block(p, kb0 + n_full + p, std::false_type{});
 
-    // ---- epilogues, straight from the accumulators: lane 16g + m holds features 4g..4g+3 of each tile for row m
-    int row[NC];
-    bool rv[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) { row[c] = (chunk0 + c) * 16 + m; rv[c] = row[c] < a.rows; }
+    pf_epilogue<T, EPI, NA, NAT, NC>(a, acc, tile, tval, chunk0, ks, lane);
+}
 
-    if constexpr (EPI == PF_RAW) {
-        const int N = a.n_tiles * 16;
+// ---- the eight-wave kernel of the bf16 prompt GEMMs
+// One fragment (1 KiB: a weight tile's or a chunk plane's k-block) from global memory into LDS, 16 bytes per lane, without
+// passing through registers.  p, the number of bytes that may be read from there (0: nothing is read, zeros come back) and
+// the LDS address are wave-uniform.
+__device__ __forceinline__ void frag_to_lds(const char* p, uint32_t bytes, u32x4* lds, int lane) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)p, 0, bytes, 0x00020000),
+                                             (__attribute__((address_space(3))) void*)lds, 16, lane * 16, 0, 0, 0);
+}
+// wait until at most N vector-memory requests are outstanding; LGKM: and every LDS read has returned
+template <int N, bool LGKM> __device__ __forceinline__ void wait_vm() {
+    __builtin_amdgcn_s_waitcnt((LGKM ? 0x0070 : 0x0f70) | (N & 15) | ((N >> 4) << 14));
+}
+
+// What bounds the large prompt GEMMs is the card's power, not the issue of matrix-core work: a loop of matrix-core
+// instructions on random operands in registers runs at 2.1 GHz and 2.1 PFLOP/s, and every byte moved per product takes its
+// share of the clock.  So both operands are read once per workgroup into LDS (no fragment passes through a register on
+// its way there), the tile per workgroup is as large as the launch's balance allows, and a wave's tile (NT weight tiles x
+// NC chunks, both planes) reads NT + 2 NC fragments for 2 NT NC products.
+//   FW x RW waves share a k-block, FW over the weight tiles, RW over the chunks.  An output is one wave's sum over its K
+//   slice in k-block order, hi plane before lo plane, as in pf_gemm_kernel: the tile shape does not enter a result.
+// A stage is one k-block; S stages form a ring.  Per stage: wait for this wave's requests of the stage to come, one
+// barrier (everybody's have arrived, and nobody reads the slot to be refilled any more), then the requests of a later stage
+// spread between the products: a direct-to-LDS load holds up its wave for about 64 cycles, which the SIMD's other wave
+// fills with products; issued back to back they cost more than the products themselves.  PF: the next stage's fragments are read into a second
+// set of registers during this stage's products (all tiles but the largest, whose accumulators leave no room).
+// Products run with one weight fragment held over NC chunks in alternating direction (2 % less time than the other
+// order).  Measured (two planes counted, 7B): QKV 512 rows 95 -> 83 us, gate/up 158 -> 146 us (1.26 PFLOP/s), down 79 -> 74 us;
+// 2048 rows: gate/up 4 x 158 -> 540 us (1.37 PFLOP/s), QKV 4 x 95 -> 295 us, down 4 x 79 -> 262 us (1.41 PFLOP/s, which
+// is what the vendor library's largest square product reaches here).
+template <int NT, int NC, int FW, int RW, int S> struct PfRing {
+    static constexpr int W = FW * RW;                               // waves
+    static constexpr int FT = FW * NT, RC = RW * NC;                // weight tiles and chunks per workgroup
+    static constexpr int NF = FT + 2 * RC;                          // fragments per k-block
+    // requests per wave and stage, the same number from every wave (the wait counts depend on it): where they do not come
+    // out even, some waves' last request reads nothing (into a spare KiB)
+    static constexpr int L = (NF + W - 1) / W, LDS = S * NF + (NF % W ? 1 : 0);
+    static_assert(LDS <= 160 && (S - 1) * L < 64, "LDS, and what the request counter can hold");
+};
+template <int EPI, int NT, int NC, int FW, int RW, int S, bool PF>
+__global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kernel(const PfArgs a) {
+    using SH = PfRing<NT, NC, FW, RW, S>;
+    constexpr int W = SH::W, FT = SH::FT, RC = SH::RC, NF = SH::NF, L = SH::L;
+    constexpr int NA = EPI == PF_GU ? NT / 2 : NT;                  // output tiles per wave
+    __shared__ u32x4 sm[SH::LDS * 64];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fw = w % FW, rw = w / FW;
+    // workgroup -> (feature block, row block, K slice), XCD-first as in pf_gemm_kernel
+    const int Lb = blockIdx.x, inner = a.n_rb * a.ksplit;
+    const int fb = ((Lb >> 3) / inner) * 8 + (Lb & 7), in = (Lb >> 3) % inner, rb = in % a.n_rb, ks = in / a.n_rb;
+    if (fb >= a.n_fb) return;
+    const int kb0 = (int)((long)ks * a.KB / a.ksplit), n = (int)((long)(ks + 1) * a.KB / a.ksplit) - kb0;
+
+    // This wave's requests of a stage: fragments w, w + W, ... of the stage's FT weight and 2 RC chunk fragments.  A tile
+    // beyond the last re-reads the last one, a chunk beyond the rows holds whatever it holds: their products are never
+    // looked at.
+    const char* src[L];
+    int64_t step[L];
+    int dst[L];                                                     // fragment of slot 0
+    uint32_t bytes[L];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if (!rv[c]) continue;
-            float* dst = a.raw + ((size_t)ks * PF_ROWS + row[c]) * N + 4 * g;
-#pragma unroll
-            for (int s = 0; s < NA; ++s)
-                if (tval[s]) *(f32x4*)(dst + tile[s] * 16) = acc[s][c];
+    for (int i = 0; i < L; ++i) {
+        const int f = (w + W * i) % NF, s = f % NT, x = f - FT;
+        const bool real = w + W * i < NF;
+        dst[i] = real ? f : S * NF;
+        bytes[i] = real ? 0xffffffffu : 0u;
+        if (f < FT) {
+            const bool up = EPI == PF_GU && s >= NA;
+            int t = (fb * FW + f / NT) * NA + (up ? s - NA : s);
+            if (t >= a.n_tiles) t = a.n_tiles - 1;
+            src[i] = (const char*)(up ? a.W2 : a.W) + ((int64_t)t * a.w_tile_stride + (int64_t)kb0 * a.w_kb_stride) * 1024;
+            step[i] = a.w_kb_stride * 1024;
+        } else {
+            src[i] = (const char*)a.X + ((int64_t)(x & 1) * a.x_plane + (int64_t)(rb * RC + (x >> 1)) * a.x_chunk) * 16 + (int64_t)kb0 * 1024;
+            step[i] = 1024;
         }
     }
+    int asked = 0;
+    auto issue = [&](const int slot) {
+#pragma unroll
+        for (int i = 0; i < L; ++i) frag_to_lds(src[i], bytes[i], &sm[(dst[i] + (NF % W == 0 || bytes[i] ? slot * NF : 0)) * 64], lane);
+        ++asked;                                                    // past the last stage it is asked for again
+#pragma unroll
+        for (int i = 0; i < L; ++i) src[i] += asked < n ? step[i] : 0;
+    };
 
-    if constexpr (EPI == PF_GU) {
+    f32x4 acc[NT][NC];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if (!rv[c]) continue;
-            const float rs = a.rscale[row[c]];
+    for (int s = 0; s < NT; ++s)
 #pragma unroll
-            for (int s = 0; s < NA; ++s) {
-                if (!tval[s]) continue;
-                float v[4];
+        for (int c = 0; c < NC; ++c) acc[s][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 fa[PF ? 2 : 1][NT], fx[PF ? 2 : 1][2 * NC];
+    auto read = [&](const int slot, const int r) {
+        const u32x4* p = &sm[slot * NF * 64 + lane];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float gt = acc[s][c][j] * rs, up = acc[NA + s][c][j] * rs;
-                    v[j] = gt / (1.f + __expf(-gt)) * up;
+        for (int b = 0; b < 2 * NC; ++b) fx[r][b] = p[(FT + rw * 2 * NC + b) * 64];
+#pragma unroll
+        for (int s = 0; s < NT; ++s) fa[r][s] = p[(fw * NT + s) * 64];
+    };
+    auto products = [&](const int r) {
+#pragma unroll
+        for (int s = 0; s < NT; ++s)
+#pragma unroll
+            for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                for (int cc = 0; cc < NC; ++cc) {
+                    const int c = ((2 * s + pl) & 1) ? NC - 1 - cc : cc;
+                    mma16<BF16>(acc[s][c], fa[r][s], fx[r][2 * c + pl]);
                 }
-                store_act4<T>(a.hmid, a.hmid_plane, (int64_t)(chunk0 + c) * a.hmid_chunk, tile[s] * 16 + 4 * g, m, v);
+    };
+    constexpr int NM = 2 * NT * NC, ND = NT + 2 * NC, TAIL = NM > 16 ? 6 : 0;     // products and fragment reads per stage
+    auto stage = [&](const int slot, const int r) {
+        wait_vm<(S - 2) * L, true>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (PF) {
+            issue(slot);                                            // its fragments are in registers since the last stage
+            read((slot + 1) % S, r ^ 1);
+            products(r);
+#pragma unroll
+            for (int j = 0; j < NM; ++j) {
+                if (j < NM - TAIL && (j * ND) / (NM - TAIL) != ((j - 1) * ND + NM - TAIL) / (NM - TAIL) - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                if ((j * L) / NM != ((j - 1) * L + NM) / NM - 1) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            }
+        } else {
+            read(slot, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            issue((slot + S - 1) % S);
+            products(0);
+#pragma unroll
+            for (int j = 0; j < NM; ++j) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                if ((j * L) / NM != ((j - 1) * L + NM) / NM - 1) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+    };
+#pragma unroll
+    for (int b = 0; b < (PF ? S : S - 1); ++b) issue(b);
+    if constexpr (PF) {
+        wait_vm<(S - 1) * L, false>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read(0, 0);
     }
+    constexpr int U = PF && S % 2 ? 2 * S : S;                      // stages until slot and register set repeat
+    int i = 0;
+    for (; i + U <= n; i += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) stage(u % S, PF ? u & 1 : 0);
+    }
+#pragma unroll
+    for (int u = 0; u + 1 < U; ++u)
+        if (i + u < n) stage(u % S, PF ? u & 1 : 0);
+    wait_vm<0, true>();                                             // no request may outlive the workgroup's LDS
 
-    if constexpr (EPI == PF_QKV) {
-        // tile j of a head: rows 0..7 = head dims 8j..8j+7, rows 8..15 = the same dims + h/2 (rotary partners):
-        // lane groups 0,1 hold the first halves, groups 2,3 their partners, 32 lanes away
-        const int hpt = a.h / 16, hh = a.h / 2;
+    int tile[NA];
+    bool tval[NA];
 #pragma unroll
-        for (int s = 0; s < NA; ++s) {
-            if (!tval[s]) continue;                   // wave-uniform
-            const int head = tile[s] / hpt, jt = tile[s] % hpt;
-            const int i0 = jt * 8 + 4 * (g & 1), dim = i0 + (g >= 2 ? hh : 0);
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const float rs = rv[c] ? a.rscale[row[c]] : 0.f;
-                float own[4], oth[4], v[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) { own[j] = acc[s][c][j] * rs; oth[j] = __shfl_xor(own[j], 32); }
-                if (!rv[c]) continue;
-                const int pos = a.pos0 + row[c];
-                if (head < a.n_h + a.n_kv) {
-                    const float* rp = a.rope + ((size_t)pos * hh + i0) * 2;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float cs = rp[2 * j], sn = rp[2 * j + 1];
-                        v[j] = g < 2 ? own[j] * cs - oth[j] * sn : own[j] * cs + oth[j] * sn;
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) v[j] = own[j];
-                }
-                if (head < a.n_h) {
-                    store_act4<T>(a.q, a.q_plane, (int64_t)(chunk0 + c) * a.q_chunk, head * a.h + dim, m, v);
-                } else {
-                    const bool isk = head < a.n_h + a.n_kv;
-                    const int kvh = isk ? head - a.n_h : head - a.n_h - a.n_kv;
-                    const int PT = a.page_tokens, page = a.page_table[pos / PT], slot = pos % PT;
-                    E* base = (E*)a.kv + ((size_t)page * a.n_kv + kvh) * 2 * PT * a.h;
-                    if (isk) {                   // dim is a multiple of 4: the four values stay inside one lane's KE elements
-                        store_elem4<T>(base + kv_k_off<T>(slot, dim, a.h), v);
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) base[kv_v_off<T>(slot, dim + j, a.h)] = T::from_f32(v[j]);
-                    }
-                }
-            }
-        }
-    }
+    for (int s = 0; s < NA; ++s) { tile[s] = (fb * FW + fw) * NA + s; tval[s] = tile[s] < a.n_tiles; }
+    pf_epilogue<BF16, EPI, NA, NT, NC>(a, acc, tile, tval, rb * RC + rw * NC, ks, lane);
 }
 
 // ---------------------------------------------------------------- rows of a block: embedding, residual add + cosine tap
@@ -272,7 +451,7 @@ __global__ __launch_bounds__(256) void pf_embed_kernel(const typename T::elem* E
 // grid = valid rows: y = x + sum of the K slices (slice order), residual stream, normed copy for the next sublayer,
 // the row's cosine(x, y) (the summand of C_l, Section 3.2) and the statistics of y
 template <class T>
-__global__ __launch_bounds__(256) void pf_resid_kernel(const float* raw, int ksplit, int d, float* xres, void* xb, int64_t xb_plane,
+__global__ __launch_bounds__(256) void pf_resid_kernel(const float* raw, int raw_rows, int ksplit, int d, float* xres, void* xb, int64_t xb_plane,
                                                        int64_t xb_chunk, const float* g_next, float* ssq, float* rscale, float* cos_row,
                                                        float inv_d, float eps) {
     __shared__ float red[256];
@@ -292,7 +471,7 @@ __global__ __launch_bounds__(256) void pf_resid_kernel(const float* raw, int ksp
                 gn[q] = *(const float4*)&g_next[n0];
 #pragma unroll
                 for (int k = 1; k < PF_MAX_KSPLIT; ++k)
-                    if (k < ksplit) t4[q][k - 1] = *(const float4*)&raw[((size_t)k * PF_ROWS + r) * d + n0];
+                    if (k < ksplit) t4[q][k - 1] = *(const float4*)&raw[((size_t)k * raw_rows + r) * d + n0];
             }
         }
 #pragma unroll
@@ -325,11 +504,11 @@ __global__ __launch_bounds__(256) void pf_resid_kernel(const float* raw, int ksp
 }
 
 // grid = sublayers: adds the block's rows' cosines (fixed order, double) to the running sums of C_l (Section 3.2)
-__global__ __launch_bounds__(256) void pf_cos_sum_kernel(const float* cos_rows /* [sublayers][PF_ROWS] */, int rows, double* cos_acc) {
+__global__ __launch_bounds__(256) void pf_cos_sum_kernel(const float* cos_rows /* [sublayers][stride] */, int stride, int rows, double* cos_acc) {
     __shared__ double red[256];
     const int j = blockIdx.x, tid = threadIdx.x;
     double s = 0.0;
-    for (int r = tid; r < rows; r += 256) s += (double)cos_rows[(size_t)j * PF_ROWS + r];
+    for (int r = tid; r < rows; r += 256) s += (double)cos_rows[(size_t)j * stride + r];
     red[tid] = s;
     __syncthreads();
     for (int st = 128; st > 0; st >>= 1) {

@@ -1,0 +1,75 @@
+"""The ring kernel of the prompt GEMMs: every tile shape and K split against the chunked prompt pass (the decode kernels).
+
+The shape has output widths that no tile divides (feature blocks with a partly filled last tile, and fewer blocks than
+XCDs), and K ranges shorter than the ring; the prompts end inside a 16-row chunk, inside a workgroup's 8 (16) chunks, and inside a second block.  Both paths
+hold activations as two bf16 planes and sum in fp32; they differ in the order of the sums, and K / V values next to a bf16
+rounding boundary then differ by one unit: TOL of the parity tests."""
+import numpy as np
+import pytest
+
+import asd_inputs as si
+import paper_2410_01028_amd as asd
+from test_gpu_parity import COS_TOL, TOL, rel_err
+
+pytestmark = pytest.mark.gpu
+
+# 24 QKV tiles, 14 residual tiles, 21 gate/up pairs; k-blocks 7 (odd), 6, 11 (odd, the last half padding)
+RAGGED = si.Shape("ragged", 2, 224, 6, 3, 32, 336, 320, si.DT_BF16, 8, 8, 2)
+EVEN = si.Shape("even", 2, 320, 4, 2, 64, 512, 320, si.DT_BF16, 8, 8, 2)
+CASES = [(RAGGED, "pf_ring=0", 81), (RAGGED, "pf_ring=1", 130), (RAGGED, "pf_ring=2,2", 97), (RAGGED, "pf_ring=3", 300), (RAGGED, "pf_ring=0,7", 200),
+         (RAGGED, "pf_ring=4", 17), (RAGGED, "pf_ring=5", 45), (RAGGED, "pf_ring=6", 63), (RAGGED, "pf_ring=7,1", 100), (RAGGED, "pf_ring=8", 33),
+         (RAGGED, "pf_ring=9,3", 49), (RAGGED, "pf_ring=10", 81), (RAGGED, "pf_ring=11", 128), (RAGGED, "pf_ring=12", 32), (RAGGED, "pf_ring=13", 40),
+         (RAGGED, "pf_ring=14", 64), (RAGGED, "pf_ring=15,5", 144), (EVEN, None, 18), (EVEN, None, 300), (EVEN, "pf_ring=1,8", 500),
+         (EVEN, "pf_ring=2,1", 144), (EVEN, "pf_ring=3,2", 1000), (EVEN, None, 2049), (EVEN, "pf_ring=3,1", 2300), (EVEN, "pf_o=4,4,2", 1500)]
+
+
+@pytest.mark.parametrize("shape,tune,n", CASES, ids=[f"{s.name}-{t}-{n}" for s, t, n in CASES])
+def test_prompt_gemm_tiles_agree_with_the_chunked_pass(shape, tune, n):
+    W = list(si.all_tensors(shape, 6, 0.1))
+    eng = asd.Engine(asd.make_config(shape, n + 16, debug_tune=tune)).load(W)
+    ref = asd.Engine(asd.make_config(shape, n + 16)).load(W)
+    toks = si.prompt(n, n + 3, shape.vocab)
+    _, acs, lg = eng.prefill(toks[:n], want_logits=True)
+    _, acs2, lg2 = ref.prefill(toks[:n], want_logits=True, chunked=True)
+    assert eng.kv_len == n and np.abs(acs - acs2).max() < COS_TOL
+    assert rel_err(lg, lg2) < TOL[shape.dtype]
+    a = eng.forward(toks[n:n + 3], n)["logits"]
+    b = ref.forward(toks[n:n + 3], n)["logits"]
+    assert rel_err(a, b).max() < TOL[shape.dtype]
+    for l in range(shape.n_layers):
+        k, v = eng.get_kv(l, 0, n)
+        k2, v2 = ref.get_kv(l, 0, n)
+        for x, y in ((k, k2), (v, v2)):
+            assert np.abs(x - y).max() <= 2 ** -7 * np.abs(y).max()          # one bf16 unit at the largest value
+            assert np.linalg.norm(x - y) < 1e-3 * np.linalg.norm(y)
+    eng.close(); ref.close()
+
+
+@pytest.mark.parametrize("n", [17, 45, 100, 520, 640])
+def test_tile_shape_does_not_enter_the_bits(n):
+    """With equal K slices (up to 640 rows) a prompt's logits, cosines and cache are the same bits in every tile shape and in
+    the four-wave kernel."""
+    toks = si.prompt(n, n, RAGGED.vocab)
+    W = list(si.all_tensors(RAGGED, 2, 0.1))
+    got = []
+    for tune in ("pf_qkv=4,1,2;pf_o=4,4,2;pf_gu=4,1,2;pf_down=4,4,2", None, "pf_ring=0,4", "pf_ring=2,4", "pf_ring=3,4", "pf_ring=5,4", "pf_ring=11,4"):
+        eng = asd.Engine(asd.make_config(RAGGED, n + 16, debug_tune=tune)).load(W)
+        got.append((*eng.prefill(toks, want_logits=True), *eng.get_kv(1, 0, n)))
+        eng.close()
+    for g in got[1:]:
+        assert all(np.array_equal(x, y) for x, y in zip(got[0], g))
+
+
+def test_weights_survive_prompt_blocks_laid_over_the_staging_region():
+    """Long blocks share memory with the region weight uploads go through: uploads and read-backs between prompt passes
+    leave each other's results alone."""
+    W = list(si.all_tensors(EVEN, 3))
+    eng = asd.Engine(asd.make_config(EVEN, 1100)).load(W)
+    toks = si.prompt(1, 1050, EVEN.vocab)
+    a = eng.prefill(toks, want_logits=True)
+    for t, l, arr in W:
+        assert np.array_equal(eng.get_weight(t, l, arr.shape, arr.dtype), arr)
+    eng.load(W)
+    b = eng.prefill(toks, want_logits=True)
+    assert a[0] == b[0] and np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
+    eng.close()
