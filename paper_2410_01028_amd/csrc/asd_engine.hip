@@ -877,31 +877,30 @@ template <class T> void launch_pf_attn_t(asd_engine* e, const PfAttnArgs& a, int
     if (H == 128) pf_attn_kernel<T, 128><<<grid, 256, 0, e->stream>>>(a);
 }
 
-template <class T> void launch_pf_rows_t(asd_engine* e, int what, int rows, int n_chunks, int ksplit, const float* gain, float* cos_row, int tail_row) {
+template <class T> void launch_pf_embed_t(asd_engine* e, int rows, int n_chunks) {
     const asd_config& c = e->c;
-    using El = typename T::elem;
-    const int64_t xb_plane = (int64_t)(e->pf_rows / 16) * e->KBd * 64 * e->KE, xb_chunk = (int64_t)e->KBd * 64 * e->KE;
-    const float inv_d = 1.f / (float)c.d_model;
-    if (what == 0)
-        pf_embed_kernel<T><<<n_chunks * 16, 256, 0, e->stream>>>((const El*)e->embed, e->pf_tok, rows, c.d_model, gain, e->pf_xres, e->pf_xb,
-                                                                 xb_plane, xb_chunk, e->pf_ssq, e->pf_rscale, inv_d, c.rms_eps);
-    else if (what == 1)
-        pf_resid_kernel<T><<<rows, 256, 0, e->stream>>>(e->pf_raw, n_chunks * 16, ksplit, c.d_model, e->pf_xres, e->pf_xb, xb_plane, xb_chunk, gain, e->pf_ssq,
-                                                        e->pf_rscale, cos_row, inv_d, c.rms_eps);
-    else
-        pf_tail_kernel<T><<<1, 256, 0, e->stream>>>(e->pf_xres, e->pf_ssq, tail_row, c.d_model, e->g_final, e->xres, e->xb,
-                                                    (int64_t)e->KBd * 64 * e->KE, e->part);
+    pf_embed_kernel<T><<<pf_row_grid(n_chunks), 256, 0, e->stream>>>((const typename T::elem*)e->embed, e->pf_tok, rows, n_chunks, c.d_model, e->layers[0].g_attn,
+        e->pf_xres, e->pf_xb, (int64_t)(e->pf_rows / 16) * e->KBd * 64 * e->KE, (int64_t)e->KBd * 64 * e->KE, e->pf_ssq, e->pf_rscale,
+        1.f / (float)c.d_model, c.rms_eps);
 }
-void launch_pf_rows(asd_engine* e, int what, int rows, int n_chunks, int ksplit, const float* gain, float* cos_row, int tail_row) {
-    if (e->c.dtype == ASD_DT_BF16) launch_pf_rows_t<BF16>(e, what, rows, n_chunks, ksplit, gain, cos_row, tail_row);
-    else launch_pf_rows_t<F32>(e, what, rows, n_chunks, ksplit, gain, cos_row, tail_row);
+template <class T> void launch_pf_resid_t(asd_engine* e, int rows, int n_chunks, int ksplit, const float* gain, float* cos_row) {
+    const asd_config& c = e->c;
+#define PFS(ks) case ks: pf_resid_kernel<T, ks><<<pf_row_grid(n_chunks), 256, 0, e->stream>>>(e->pf_raw, n_chunks * 16, rows, c.d_model, e->pf_xres, e->pf_xb, \
+        (int64_t)(e->pf_rows / 16) * e->KBd * 64 * e->KE, (int64_t)e->KBd * 64 * e->KE, gain, e->pf_ssq, e->pf_rscale, cos_row, 1.f / (float)c.d_model, c.rms_eps); break;
+    switch (ksplit) { PFS(1) PFS(2) PFS(3) PFS(4) PFS(5) PFS(6) PFS(7) PFS(8) }
+#undef PFS
 }
-
+template <class T> void launch_pf_tail_t(asd_engine* e, int rows) {
+    const asd_config& c = e->c;
+    pf_tail_kernel<T><<<2 * c.n_layers + (c.d_model + 255) / 256, 256, 0, e->stream>>>(e->pf_cos_rows, e->pf_rows, rows, e->cos_acc, 2 * c.n_layers, e->pf_xres,
+        e->pf_ssq, c.d_model, e->g_final, e->xres, e->xb, (int64_t)e->KBd * 64 * e->KE, e->part);
+}
 // The whole prompt, block by block and layer by layer; leaves the last row's logits / greedy token in row 0 of the
 // decode buffers and the cosine sums of all rows in cos_acc (the caller cleared it).  Enqueue only.
 int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profiler = nullptr) {
     const asd_config& c = e->c;
     const int L = c.n_layers, KE = e->KE;
+    const bool bf = c.dtype == ASD_DT_BF16;
     const double qd = (double)c.n_heads * c.head_dim, kvd = (double)c.n_kv_heads * c.head_dim;
     Prof pr{profiler, e->stream};
     auto wl = [&](PfArgs& a, const GemmCfg& cfg, int total_tiles, int KB) {
@@ -918,7 +917,7 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
         CK(e, hipMemcpyAsync(e->pf_tok, tokens + r0, (size_t)rows * 4, hipMemcpyHostToDevice, e->stream));
         set_state_kernel<<<1, 1, 0, e->stream>>>(e->st, r0, 0, 0, 0);
         pr.begin(ASD_PK_ROWS, 0);
-        launch_pf_rows(e, 0, rows, n_chunks, 1, e->layers[0].g_attn, nullptr, 0);
+        if (bf) launch_pf_embed_t<BF16>(e, rows, n_chunks); else launch_pf_embed_t<F32>(e, rows, n_chunks);
         pr.end();
         // flops of each contraction over this block's rows (every weight multiply-add counted once), causal attention
         const double fl_row = 2.0 * rows, ctx_sum = (double)rows * r0 + 0.5 * rows * (rows + 1.0);
@@ -929,6 +928,10 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
         base.q_plane = cap * e->KBq * 64 * KE; base.q_chunk = (int64_t)e->KBq * 64 * KE;
         base.n_h = c.n_heads; base.n_kv = c.n_kv_heads; base.h = c.head_dim; base.page_tokens = c.page_tokens;
         base.hmid = e->pf_hmid; base.hmid_plane = cap * e->KBf * 64 * KE; base.hmid_chunk = (int64_t)e->KBf * 64 * KE;
+        auto resid = [&](int ksplit, const float* gain, int sub) {
+            float* cr = e->pf_cos_rows + (size_t)sub * e->pf_rows;
+            if (bf) launch_pf_resid_t<BF16>(e, rows, n_chunks, ksplit, gain, cr); else launch_pf_resid_t<F32>(e, rows, n_chunks, ksplit, gain, cr);
+        };
         for (int l = 0; l < L; ++l) {
             const Layer& ly = e->layers[l];
             bool ok = true;
@@ -956,7 +959,7 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
             ok = ok && launch_pf_gemm<PF_RAW>(e, e->pf_o, o, n_chunks);
             pr.end();
             pr.begin(ASD_PK_ROWS, 0);
-            launch_pf_rows(e, 1, rows, n_chunks, pf_slices(e, e->pf_o, c.d_model / 16, e->KBq, n_chunks), ly.g_mlp, e->pf_cos_rows + (size_t)(2 * l) * e->pf_rows, 0);
+            resid(pf_slices(e, e->pf_o, c.d_model / 16, e->KBq, n_chunks), ly.g_mlp, 2 * l);
             pr.end();
 
             PfArgs gu = base;
@@ -973,17 +976,16 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
             ok = ok && launch_pf_gemm<PF_RAW>(e, e->pf_down, dn, n_chunks);
             pr.end();
             pr.begin(ASD_PK_ROWS, 0);
-            launch_pf_rows(e, 1, rows, n_chunks, pf_slices(e, e->pf_down, c.d_model / 16, e->KBf, n_chunks), l + 1 < L ? e->layers[l + 1].g_attn : e->g_final,
-                           e->pf_cos_rows + (size_t)(2 * l + 1) * e->pf_rows, 0);
+            resid(pf_slices(e, e->pf_down, c.d_model / 16, e->KBf, n_chunks), l + 1 < L ? e->layers[l + 1].g_attn : e->g_final, 2 * l + 1);
             pr.end();
             if (!ok) return fail(e, ASD_E_STATE, "no prompt GEMM instance for this launch shape");
         }
-        pf_cos_sum_kernel<<<2 * L, 256, 0, e->stream>>>(e->pf_cos_rows, e->pf_rows, rows, e->cos_acc);
+        if (r0 + rows < n) pf_cos_sum_kernel<<<2 * L, 256, 0, e->stream>>>(e->pf_cos_rows, e->pf_rows, rows, e->cos_acc);      // (the last block's: pf_tail_kernel)
         e->kv_len = r0 + rows;
     }
     // the last prompt row through the final norm and the LM head, as row 0 of a one-row pass
     pr.begin(ASD_PK_LMHEAD, 2.0 * c.d_model * c.vocab);
-    launch_pf_rows(e, 2, rows, 0, 1, nullptr, nullptr, rows - 1);
+    if (bf) launch_pf_tail_t<BF16>(e, rows); else launch_pf_tail_t<F32>(e, rows);
     std::vector<PassOp> ops;
     build_pass(e, 1, 0, nullptr, n, chunks_for(n - 1), engine_out(e), ops);
     for (PassOp& op : ops) {

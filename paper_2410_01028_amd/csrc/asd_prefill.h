@@ -409,79 +409,104 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
 }
 
 // ---------------------------------------------------------------- rows of a block: embedding, residual add + cosine tap
-// fixed-order sum of one value per thread (blockDim.x a power of two <= 256); result valid in thread 0
-__device__ __forceinline__ float pf_block_sum(float v, float* red) {
+// What bounds these kernels is memory (per row and sublayer the K slices, the residual row both ways and its normed copy), and two
+// things kept them from its rate: a normed copy leaves a row as 16-byte pieces 256 bytes apart, so the rows of one
+// chunk share every cache line; and each row's sums went through LDS level by level.  So the 16 rows of a chunk go to
+// workgroups of one XCD that follow each other (consecutive workgroup ids go to the 8 XCDs in turn), whose L2 puts the
+// lines together, all requests of a row are made before the first use, and the two sums take one pass through LDS
+// and shuffles, in the order the level-by-level sum had.  7B: residual add 15.4 -> 12.1 us at 512 rows (four slices, 4.8 TB/s), 45 -> 33 us at 2048 rows;
+// embedding 18.6 -> 8.4 us and 66 -> 32 us.
+__device__ __forceinline__ int pf_row_of_block(int b) { return ((b >> 7) * 8 + (b & 7)) * 16 + ((b >> 3) & 15); }
+inline unsigned pf_row_grid(int n_chunks) { return (unsigned)((n_chunks + 7) / 8 * 128); }
+
+// sums of one value pair per thread of a 256-thread workgroup, each in the order of a halving tree (t, t + 128), (t, t + 64),
+// ...; valid in thread 0
+__device__ __forceinline__ void pf_block_sum2(float& u, float& v, float2* red) {
     const int tid = threadIdx.x;
-    red[tid] = v;
+    red[tid] = float2{u, v};
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (tid < s) red[tid] += red[tid + s];
-        __syncthreads();
+    if (tid < 64) {
+        const float2 a = red[tid], b = red[tid + 128], c = red[tid + 64], d = red[tid + 192];
+        u = (a.x + b.x) + (c.x + d.x);
+        v = (a.y + b.y) + (c.y + d.y);
+        for (int s = 32; s > 0; s >>= 1) { u += __shfl_down(u, s); v += __shfl_down(v, s); }
     }
-    const float r = red[0];
-    __syncthreads();
-    return r;
 }
 
-// grid = chunk-padded rows; rows at or beyond `rows` are zero-filled
+// grid = pf_row_grid; rows of the last chunk at or beyond `rows` are zero-filled
 template <class T>
-__global__ __launch_bounds__(256) void pf_embed_kernel(const typename T::elem* E, const int32_t* tokens, int rows, int d, const float* g_first,
+__global__ __launch_bounds__(256) void pf_embed_kernel(const typename T::elem* E, const int32_t* tokens, int rows, int n_chunks, int d, const float* g_first,
                                                        float* xres, void* xb, int64_t xb_plane, int64_t xb_chunk, float* ssq, float* rscale,
                                                        float inv_d, float eps) {
-    __shared__ float red[256];
-    const int r = blockIdx.x, tid = threadIdx.x;
+    using El = typename T::elem;
+    __shared__ float2 red[256];
+    const int r = pf_row_of_block(blockIdx.x), tid = threadIdx.x;
+    if (r >= n_chunks * 16) return;
     const bool valid = r < rows;
-    const typename T::elem* src = E + (size_t)(valid ? tokens[r] : 0) * d;
-    float ss = 0.f;
-    for (int n0 = tid * 4; n0 < d; n0 += 1024) {
-        float x[4], v[4];
+    const El* src = E + (size_t)(valid ? tokens[r] : 0) * d;
+    float ss = 0.f, none = 0.f;
+    constexpr int PB = 4;
+    struct alignas(4 * sizeof(El)) Four { El e[4]; };
+    for (int base = tid * 4; base < d; base += PB * 1024) {
+        Four e4[PB];
+        float4 g4[PB];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            x[j] = valid ? T::to_f32(src[n0 + j]) : 0.f;
-            v[j] = x[j] * g_first[n0 + j];
-            ss += x[j] * x[j];
+        for (int q = 0; q < PB; ++q) {
+            const int n0 = base + q * 1024;
+            if (n0 < d) { e4[q] = *(const Four*)(src + n0); g4[q] = *(const float4*)&g_first[n0]; }
         }
-        *(float4*)&xres[(size_t)r * d + n0] = float4{x[0], x[1], x[2], x[3]};
-        store_act4<T>(xb, xb_plane, (int64_t)(r / 16) * xb_chunk, n0, r % 16, v);
+#pragma unroll
+        for (int q = 0; q < PB; ++q) {
+            const int n0 = base + q * 1024;
+            if (n0 < d) {
+                const float gg[4] = {g4[q].x, g4[q].y, g4[q].z, g4[q].w};
+                float x[4], v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    x[j] = valid ? T::to_f32(e4[q].e[j]) : 0.f;
+                    v[j] = x[j] * gg[j];
+                    ss += x[j] * x[j];
+                }
+                *(float4*)&xres[(size_t)r * d + n0] = float4{x[0], x[1], x[2], x[3]};
+                store_act4<T>(xb, xb_plane, (int64_t)(r / 16) * xb_chunk, n0, r % 16, v);
+            }
+        }
     }
-    const float tot = pf_block_sum(ss, red);
-    if (tid == 0) { ssq[r] = tot; rscale[r] = rsqrtf(tot * inv_d + eps); }
+    pf_block_sum2(ss, none, red);
+    if (tid == 0) { ssq[r] = ss; rscale[r] = rsqrtf(ss * inv_d + eps); }
 }
 
-// grid = valid rows: y = x + sum of the K slices (slice order), residual stream, normed copy for the next sublayer,
-// the row's cosine(x, y) (the summand of C_l, Section 3.2) and the statistics of y
-template <class T>
-__global__ __launch_bounds__(256) void pf_resid_kernel(const float* raw, int raw_rows, int ksplit, int d, float* xres, void* xb, int64_t xb_plane,
+// grid = pf_row_grid: y = x + sum of the K slices (slice order), residual stream, normed copy for the next sublayer,
+// the row's cosine(x, y) (the summand of C_l, Section 3.2) and the statistics of y.  KS = number of K slices.
+template <class T, int KS>
+__global__ __launch_bounds__(256) void pf_resid_kernel(const float* raw, int raw_rows, int rows, int d, float* xres, void* xb, int64_t xb_plane,
                                                        int64_t xb_chunk, const float* g_next, float* ssq, float* rscale, float* cos_row,
                                                        float inv_d, float eps) {
-    __shared__ float red[256];
-    const int r = blockIdx.x, tid = threadIdx.x;
+    __shared__ float2 red[256];
+    const int r = pf_row_of_block(blockIdx.x), tid = threadIdx.x;
+    if (r >= rows) return;
     float sxy = 0.f, syy = 0.f;
-    // four 4-element pieces per thread and trip, every load of a trip requested before the first use: with two
-    // workgroups per compute unit there is little else to hide the latency of a piece-by-piece walk
     constexpr int PB = 4;
     for (int base = tid * 4; base < d; base += PB * 1024) {
-        float4 x4[PB], s4[PB], gn[PB], t4[PB][PF_MAX_KSPLIT - 1];
+        float4 x4[PB], gn[PB], t4[PB][KS];
 #pragma unroll
         for (int q = 0; q < PB; ++q) {
             const int n0 = base + q * 1024;
             if (n0 < d) {
                 x4[q] = *(const float4*)&xres[(size_t)r * d + n0];
-                s4[q] = *(const float4*)&raw[(size_t)r * d + n0];
                 gn[q] = *(const float4*)&g_next[n0];
 #pragma unroll
-                for (int k = 1; k < PF_MAX_KSPLIT; ++k)
-                    if (k < ksplit) t4[q][k - 1] = *(const float4*)&raw[((size_t)k * raw_rows + r) * d + n0];
+                for (int k = 0; k < KS; ++k) t4[q][k] = *(const float4*)&raw[((size_t)k * raw_rows + r) * d + n0];
             }
         }
 #pragma unroll
         for (int q = 0; q < PB; ++q) {
             const int n0 = base + q * 1024;
             if (n0 < d) {
+                float4 s4 = t4[q][0];
 #pragma unroll
-                for (int k = 1; k < PF_MAX_KSPLIT; ++k)
-                    if (k < ksplit) { s4[q].x += t4[q][k - 1].x; s4[q].y += t4[q][k - 1].y; s4[q].z += t4[q][k - 1].z; s4[q].w += t4[q][k - 1].w; }
-                const float x[4] = {x4[q].x, x4[q].y, x4[q].z, x4[q].w}, sv[4] = {s4[q].x, s4[q].y, s4[q].z, s4[q].w};
+                for (int k = 1; k < KS; ++k) { s4.x += t4[q][k].x; s4.y += t4[q][k].y; s4.z += t4[q][k].z; s4.w += t4[q][k].w; }
+                const float x[4] = {x4[q].x, x4[q].y, x4[q].z, x4[q].w}, sv[4] = {s4.x, s4.y, s4.z, s4.w};
                 const float gg[4] = {gn[q].x, gn[q].y, gn[q].z, gn[q].w};
                 float y[4], v[4];
 #pragma unroll
@@ -491,42 +516,53 @@ __global__ __launch_bounds__(256) void pf_resid_kernel(const float* raw, int raw
             }
         }
     }
-    const float xy = pf_block_sum(sxy, red);
-    const float yy = pf_block_sum(syy, red);
+    pf_block_sum2(sxy, syy, red);
     if (tid == 0) {
         const float xx = ssq[r];
-        float c = xy * rsqrtf(fmaxf(xx, 1e-16f) * fmaxf(yy, 1e-16f));
+        float c = sxy * rsqrtf(fmaxf(xx, 1e-16f) * fmaxf(syy, 1e-16f));
         c = fminf(1.f, fmaxf(-1.f, c));
         cos_row[r] = c;
-        ssq[r] = yy;
-        rscale[r] = rsqrtf(yy * inv_d + eps);
+        ssq[r] = syy;
+        rscale[r] = rsqrtf(syy * inv_d + eps);
     }
 }
 
-// grid = sublayers: adds the block's rows' cosines (fixed order, double) to the running sums of C_l (Section 3.2)
-__global__ __launch_bounds__(256) void pf_cos_sum_kernel(const float* cos_rows /* [sublayers][stride] */, int stride, int rows, double* cos_acc) {
-    __shared__ double red[256];
-    const int j = blockIdx.x, tid = threadIdx.x;
+// one sublayer's row cosines of a block (fixed order, double) added to the running sum of C_l (Section 3.2); 256 threads
+__device__ __forceinline__ void pf_cos_sum(const float* row, int rows, double* acc, double* red) {
+    const int tid = threadIdx.x;
     double s = 0.0;
-    for (int r = tid; r < rows; r += 256) s += (double)cos_rows[(size_t)j * stride + r];
+    for (int r = tid; r < rows; r += 256) s += (double)row[r];
     red[tid] = s;
     __syncthreads();
     for (int st = 128; st > 0; st >>= 1) {
         if (tid < st) red[tid] += red[tid + st];
         __syncthreads();
     }
-    if (tid == 0) cos_acc[j] += red[0];
+    if (tid == 0) *acc += red[0];
+}
+// grid = sublayers
+__global__ __launch_bounds__(256) void pf_cos_sum_kernel(const float* cos_rows /* [sublayers][stride] */, int stride, int rows, double* cos_acc) {
+    __shared__ double red[256];
+    pf_cos_sum(cos_rows + (size_t)blockIdx.x * stride, rows, cos_acc + blockIdx.x, red);
 }
 
-// one workgroup: hand row r of the block to the single-row decode buffers (residual, normed copy under the final
-// norm's gain, ||x||^2 as the one partial the LM-head kernel sums), so that the LM head runs on it as row 0
+// The end of the prompt's last block, grid = sublayers + ceil(d / 256): the block's cosine sums, and row r handed to the
+// single-row decode buffers (residual, normed copy under the final norm's gain, ||x||^2 as the one partial the LM-head
+// kernel sums), so that the LM head runs on it as row 0.
 template <class T>
-__global__ __launch_bounds__(256) void pf_tail_kernel(const float* xres_pf, const float* ssq_pf, int r, int d, const float* g_final,
-                                                      float* xres, void* xb, int64_t xb_plane, float* part) {
-    for (int i = threadIdx.x; i < d; i += 256) {
+__global__ __launch_bounds__(256) void pf_tail_kernel(const float* cos_rows, int stride, int rows, double* cos_acc, int sublayers, const float* xres_pf,
+                                                      const float* ssq_pf, int d, const float* g_final, float* xres, void* xb, int64_t xb_plane, float* part) {
+    __shared__ double red[256];
+    const int r = rows - 1, b = (int)blockIdx.x - sublayers;
+    if (b < 0) {
+        pf_cos_sum(cos_rows + (size_t)blockIdx.x * stride, rows, cos_acc + blockIdx.x, red);
+        return;
+    }
+    const int i = b * 256 + threadIdx.x;
+    if (i < d) {
         const float y = xres_pf[(size_t)r * d + i];
         xres[i] = y;
         store_act<T>(xb, (size_t)xb_plane, 1, i, 0, y * g_final[i]);
     }
-    if (threadIdx.x == 0) { part[0] = 0.f; part[1] = ssq_pf[r]; }
+    if (b == 0 && threadIdx.x == 0) { part[0] = 0.f; part[1] = ssq_pf[r]; }
 }
