@@ -587,3 +587,160 @@ __global__ __launch_bounds__(256, 1) void pf_attn_kernel(const PfAttnArgs a) {
         __syncthreads();
     }
 }
+
+// The same attention for blocks with enough rows to give every compute unit a workgroup (bf16).  pf_attn_kernel above loads
+// every K / V^T fragment per wave and 32 rows, which is what fills its time (a compute unit takes in about 45-57 KiB per
+// us), and needs a SIMD's whole register file per wave, so that nothing runs beside a wave's softmax.  Here a workgroup
+// takes 128 rows, 32 to each of four waves, all walking the keys together: a chunk's fragments come into LDS once
+// (direct-to-LDS loads) for four waves' products, and two workgroups fit on a compute unit, one's products beside
+// the other's exponentials.  The LDS ring holds five half-chunks (K, V^T, K, ...: 16 KiB each at head dim 128, so two rings
+// fill the compute unit's 160 KiB); a step waits for its half, one barrier, asks for the half four steps on (its slot was last
+// read one step ago) and computes.  Workgroups are numbered longest row block first; a KV head's workgroups get ids of one
+// residue mod 8, i.e. one XCD's L2, where the number of KV heads is a multiple of 8.
+// 7B, 8192-token prompt, per 2048-row block on average: 480 -> 285 us (0.97 PFLOP/s, two planes counted); 13B, 1003 rows: 90 -> 55 us; 70B,
+// 2048 rows: 373 -> 163 us.
+#define PF_ATT_LONG_ROWS 128
+template <int H>
+__global__ __launch_bounds__(256, 2) void pf_attn_long_kernel(const PfAttnArgs a) {
+    using T = BF16;
+    constexpr int KE = T::KE, HS = H / (4 * KE), HT = H / 16, KST = 64 / (4 * KE), NP = T::NP, NT = 2;
+    constexpr int HF = 4 * HS, LH = HF / 4, SLOTS = 5;        // fragments of a half-chunk, requests per wave and half
+    static_assert(HT * KST == HF, "K and V^T halves have the same size");
+    __shared__ u32x4 sm[SLOTS * HF * 64];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, m = lane & 15;
+    const int n_units = (a.rows + PF_ATT_LONG_ROWS - 1) / PF_ATT_LONG_ROWS, G = a.n_h / a.n_kv;
+    const int rank = (int)blockIdx.x / a.n_h, rem = (int)blockIdx.x % a.n_h;
+    const int u = n_units - 1 - rank, kvh = rem % a.n_kv, head = kvh * G + rem / a.n_kv, PT = a.page_tokens;
+    const int row0 = PF_ATT_LONG_ROWS * u + 32 * w, n_rows = max(0, min(32, a.rows - row0));      // this wave's rows
+    const int p0 = a.pos0 + row0;
+    const int n_kc = (a.pos0 + min(PF_ATT_LONG_ROWS * (u + 1), a.rows) - 1) / ASD_CHUNK + 1;      // chunks the workgroup walks
+    const int n_my = n_rows > 0 ? (p0 + n_rows - 1) / ASD_CHUNK + 1 : 0;                          // ... this wave has products for
+
+    // half-chunk i of the ring: K of chunk i / 2 (i even) or its V^T; past the end the last one is asked for again
+    auto issue = [&](const int i_) {
+        const int i = min(i_, 2 * n_kc - 1), kc = i >> 1, slot = i_ % SLOTS;
+        typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
+        const int page = ((const_i32_ptr)(uintptr_t)a.page_table)[(kc * ASD_CHUNK) / PT], slot0 = (kc * ASD_CHUNK) % PT;
+        const uint16_t* src = (const uint16_t*)a.kv + ((size_t)page * a.n_kv + kvh) * 2 * PT * H + kv_chunk_off<T>(slot0 / ASD_CHUNK, H) +
+                              (i & 1) * (size_t)ASD_CHUNK * H;
+#pragma unroll
+        for (int q = 0; q < LH; ++q) frag_to_lds((const char*)src + (w + 4 * q) * 1024, 0xffffffffu, &sm[(slot * HF + w + 4 * q) * 64], lane);
+    };
+
+    u32x4 qf[NT][HS][NP];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const uint16_t* qp = (const uint16_t*)a.q + (size_t)(row0 / 16 + t) * a.q_chunk + (size_t)head * H * 16;
+#pragma unroll
+        for (int hs = 0; hs < HS; ++hs)
+#pragma unroll
+            for (int pl = 0; pl < NP; ++pl)
+                qf[t][hs][pl] = 16 * t + m < n_rows ? *(const u32x4*)(qp + pl * a.q_plane + ((size_t)(hs * 4 + g) * 16 + m) * KE) : u32x4{0u, 0u, 0u, 0u};
+    }
+    f32x4 o[NT][HT];
+    float mx[NT], l[NT];                                      // running maximum of the raw scores; this lane's share of the sum
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        mx[t] = -INFINITY; l[t] = 0.f;
+#pragma unroll
+        for (int ht = 0; ht < HT; ++ht) o[t][ht] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const float c2 = a.scale * 1.44269504088896340736f;      // exp(scale (s - max)) = exp2(c2 s - c2 max)
+    wait_vm<0, true>();                                       // the query fragments: from here on only the ring's requests count
+#pragma unroll
+    for (int i = 0; i < SLOTS - 1; ++i) issue(i);
+    auto step = [&](const int i) {
+        wait_vm<(SLOTS - 2) * LH, true>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        issue(i + SLOTS - 1);
+    };
+    for (int kc = 0; kc < n_kc; ++kc) {
+        f32x4 s[NT][4];
+        u32x4 pf[NT][KST][NP];
+        step(2 * kc);
+        if (kc < n_my) {
+            const u32x4* kp = &sm[(2 * kc) % SLOTS * HF * 64 + lane];
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) s[t][kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int hs = 0; hs < HS; ++hs) {
+                    const u32x4 kf = kp[(kt * HS + hs) * 64];
+#pragma unroll
+                    for (int pl = 0; pl < NP; ++pl)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) mma16<T>(s[t][kt], kf, qf[t][hs][pl]);
+                }
+            }
+            const bool diagonal = kc * ASD_CHUNK + ASD_CHUNK - 1 > p0;          // some of this wave's rows see only part of the chunk
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                if (diagonal) {
+                    const int row_pos = p0 + 16 * t + m;
+#pragma unroll
+                    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (kc * ASD_CHUNK + score_key<T>(kt, 4 * g + j) > row_pos) s[t][kt][j] = -INFINITY;
+                }
+                float cm = s[t][0][0];
+#pragma unroll
+                for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) cm = fmaxf(cm, s[t][kt][j]);
+                cm = fmaxf(cm, __shfl_xor(cm, 16));
+                cm = fmaxf(cm, __shfl_xor(cm, 32));
+                // (a row's first chunk holds its key 0, so its maximum is finite from then on)
+                if (__any(cm > mx[t])) {
+                    const float mn = fmaxf(mx[t], cm), alpha = __builtin_amdgcn_exp2f((mx[t] - mn) * c2);
+                    mx[t] = mn;
+                    l[t] *= alpha;
+#pragma unroll
+                    for (int ht = 0; ht < HT; ++ht) { o[t][ht][0] *= alpha; o[t][ht][1] *= alpha; o[t][ht][2] *= alpha; o[t][ht][3] *= alpha; }
+                }
+                const float off = -mx[t] * c2;
+#pragma unroll
+                for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float p = __builtin_amdgcn_exp2f(fmaf(s[t][kt][j], c2, off));
+                        s[t][kt][j] = p;
+                        l[t] += p;
+                    }
+                att_pfrags<T>(s[t], pf[t]);
+            }
+        }
+        step(2 * kc + 1);
+        if (kc < n_my) {
+            const u32x4* vp = &sm[(2 * kc + 1) % SLOTS * HF * 64 + lane];
+#pragma unroll
+            for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+                for (int ks = 0; ks < KST; ++ks) {
+                    const u32x4 vf = vp[(ht * KST + ks) * 64];
+#pragma unroll
+                    for (int pl = 0; pl < NP; ++pl)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) mma16<T>(o[t][ht], vf, pf[t][ks][pl]);
+                }
+        }
+    }
+    wait_vm<0, true>();                                       // no request may outlive the workgroup's LDS
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        float z = l[t];
+        z += __shfl_xor(z, 16);
+        z += __shfl_xor(z, 32);
+        const float inv = 1.f / z;
+        if (16 * t + m < n_rows) {
+#pragma unroll
+            for (int ht = 0; ht < HT; ++ht) {
+                const float v[4] = {o[t][ht][0] * inv, o[t][ht][1] * inv, o[t][ht][2] * inv, o[t][ht][3] * inv};
+                store_act4<T>(a.out, a.q_plane, (int64_t)(row0 / 16 + t) * a.q_chunk, head * H + ht * 16 + 4 * g, m, v);
+            }
+        }
+    }
+}

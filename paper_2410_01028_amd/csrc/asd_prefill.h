@@ -244,18 +244,6 @@ __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const
 }
 
 // ---- the eight-wave kernel of the bf16 prompt GEMMs
-// One fragment (1 KiB: a weight tile's or a chunk plane's k-block) from global memory into LDS, 16 bytes per lane, without
-// passing through registers.  p, the number of bytes that may be read from there (0: nothing is read, zeros come back) and
-// the LDS address are wave-uniform.
-__device__ __forceinline__ void frag_to_lds(const char* p, uint32_t bytes, u32x4* lds, int lane) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)p, 0, bytes, 0x00020000),
-                                             (__attribute__((address_space(3))) void*)lds, 16, lane * 16, 0, 0, 0);
-}
-// wait until at most N vector-memory requests are outstanding; LGKM: and every LDS read has returned
-template <int N, bool LGKM> __device__ __forceinline__ void wait_vm() {
-    __builtin_amdgcn_s_waitcnt((LGKM ? 0x0070 : 0x0f70) | (N & 15) | ((N >> 4) << 14));
-}
-
 // What bounds the large prompt GEMMs is the card's power, not the issue of matrix-core work: a loop of matrix-core
 // instructions on random operands in registers runs at 2.1 GHz and 2.1 PFLOP/s, and every byte moved per product takes its
 // share of the clock.  So both operands are read once per workgroup into LDS (no fragment passes through a register on

@@ -60,6 +60,40 @@ def test_tile_shape_does_not_enter_the_bits(n):
         assert all(np.array_equal(x, y) for x, y in zip(got[0], g))
 
 
+# head_dim, heads, KV heads, prompt: blocks with at least three 128-row attention workgroups to four compute units (256); prompts that
+# end inside a 16-row chunk, a wave's 32 rows, a workgroup's 128, and in a second block
+LONG = [(32, 32, 8, 1030), (64, 48, 6, 900), (128, 32, 32, 2100), (32, 64, 64, 513), (128, 64, 8, 2177)]
+
+
+@pytest.mark.parametrize("h,n_h,n_kv,n", LONG, ids=lambda v: str(v))
+def test_long_block_attention_agrees_with_the_chunked_pass(h, n_h, n_kv, n):
+    shape = si.Shape("wide", 2, 256, n_h, n_kv, h, 256, 256, si.DT_BF16, 8, 8, 2)
+    W = list(si.all_tensors(shape, 11, 0.1))
+    # larger q and k weights: scores of several units, so that running maxima move and rows have few heavy keys
+    W = [(t, l, si_scale(a, 3.0) if t in (si.T_WQ, si.T_WK) else a) for t, l, a in W]
+    eng = asd.Engine(asd.make_config(shape, n + 16)).load(W)
+    ref = asd.Engine(asd.make_config(shape, n + 16)).load(W)
+    pages = -(-(n + 16) // 64)
+    for e in (eng, ref):
+        e.set_page_table(np.random.default_rng(n).permutation(pages))
+    toks = si.prompt(n, n + 3, shape.vocab)
+    _, acs, lg = eng.prefill(toks[:n], want_logits=True)
+    _, acs2, lg2 = ref.prefill(toks[:n], want_logits=True, chunked=True)
+    assert np.abs(acs - acs2).max() < COS_TOL
+    assert rel_err(lg, lg2) < TOL[shape.dtype]
+    k, v = eng.get_kv(1, 0, n)          # the second layer's cache carries every row's attention output of the first
+    k2, v2 = ref.get_kv(1, 0, n)
+    for x, y in ((k, k2), (v, v2)):
+        assert np.linalg.norm(x - y) < 1e-3 * np.linalg.norm(y)
+    eng.close(); ref.close()
+
+
+def si_scale(a, f):
+    """bf16 bit patterns times f, rounded to nearest even."""
+    x = (si.bf16_to_f32(a) * np.float32(f)).view(np.uint32)
+    return ((x + 0x7fff + ((x >> 16) & 1)) >> 16).astype(np.uint16)
+
+
 def test_weights_survive_prompt_blocks_laid_over_the_staging_region():
     """Long blocks share memory with the region weight uploads go through: uploads and read-backs between prompt passes
     leave each other's results alone."""
