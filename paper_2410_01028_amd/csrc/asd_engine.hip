@@ -89,7 +89,7 @@ struct asd_engine {
     int last_logits_row;                // row of `logits` holding the last prompt row after a prompt pass
     unsigned* arrivals;
     void *xb, *q, *attn_out, *hmid;
-    unsigned* counters;
+    double* pstat;                      // [16][2] softmax statistics of a verification pass's rows (sampled decoding)
     double* cos_acc;
     AmaxPart* amax_part;
     int32_t *argmax, *tokbuf, *out_tokens;
@@ -254,7 +254,7 @@ GemmCfg pick_qkv_rows(const GemmCfg& base, int tiles, const char* tune) {
 struct Plan {
     size_t embed, lm, g_final, layer0, layer_stride, wqkv, wo, wg, wu, wd, g_attn, g_mlp;
     size_t kv, kv_layer, page_table;
-    size_t xres, ssq, part, cos_rows, logits, o_part, rope, ml_part, arrivals, xb, q, attn_out, hmid, counters, cos_acc, amax_part,
+    size_t xres, ssq, part, cos_rows, logits, o_part, rope, ml_part, arrivals, xb, q, attn_out, hmid, pstat, cos_acc, amax_part,
         argmax, tokbuf, out_tokens, st, ops, ops_bytes, staging, staging_bytes, total, qlogits;
     size_t pf_tok, pf_xres, pf_raw, pf_ssq, pf_rscale, pf_cos_rows, pf_xb, pf_q, pf_attn_out, pf_hmid;
     int es, KE, KBd, KBq, KBf, n_pages, nc_stride, qkv_tiles;
@@ -316,7 +316,7 @@ Plan make_plan(const asd_config& c) {
     p.q = take((size_t)c.n_heads * c.head_dim * ASD_ROWS * p.es * NPL);
     p.attn_out = take((size_t)p.KBq * frag * NPL);
     p.hmid = take((size_t)p.KBf * frag * NPL);
-    p.counters = take(256);
+    p.pstat = take(ASD_ROWS * 2 * sizeof(double));
     p.cos_acc = take((size_t)2 * c.n_layers * 8);
     p.amax_part = take((size_t)p.g_lm.grid * ASD_ROWS * sizeof(AmaxPart));
     p.argmax = take(ASD_ROWS * 4);
@@ -1055,7 +1055,7 @@ int asd_create(const asd_config* cfg, void* device_arena, size_t arena_bytes, vo
     e->cos_rows = (float*)(A + p.cos_rows); e->logits = (float*)(A + p.logits); e->qlogits = (float*)(A + p.qlogits); e->last_logits_row = 0; e->o_part = (float*)(A + p.o_part);
     e->rope = (float*)(A + p.rope); e->ml_part = (float*)(A + p.ml_part); e->arrivals = (unsigned*)(A + p.arrivals);
     e->xb = A + p.xb; e->q = A + p.q; e->attn_out = A + p.attn_out; e->hmid = A + p.hmid;
-    e->counters = (unsigned*)(A + p.counters); e->cos_acc = (double*)(A + p.cos_acc);
+    e->pstat = (double*)(A + p.pstat); e->cos_acc = (double*)(A + p.cos_acc);
     e->amax_part = (AmaxPart*)(A + p.amax_part); e->argmax = (int32_t*)(A + p.argmax);
     e->tokbuf = (int32_t*)(A + p.tokbuf); e->out_tokens = (int32_t*)(A + p.out_tokens); e->st = (DevState*)(A + p.st);
     e->staging = A + p.staging; e->staging_bytes = p.staging_bytes;
@@ -1506,26 +1506,32 @@ static SampleArgs sample_args(asd_engine* e, float temperature, uint64_t seed) {
     SampleArgs a{};
     a.logits = e->logits; a.qlogits = e->qlogits; a.V = e->c.vocab; a.inv_T = 1.f / temperature;
     a.qstat = (double*)(e->qlogits + (size_t)ASD_ROWS * e->c.vocab);
+    a.pstat = e->pstat;
     a.stream = h_stream(seed, 102u, 0u);
     a.st = e->st; a.tokbuf = e->tokbuf; a.out = e->out_tokens;
     return a;
 }
 
-// The sampling kernels hold a thread's share of a logit row in registers when the vocabulary allows it
+// The sampling kernels hold a wave's tiles of a logit row in registers when the vocabulary allows it
 // (ASD_DBG_SAMPLE_MEM, a test aid, forces the variant that re-reads memory: same arithmetic, same draws).
 static bool sample_in_registers(const asd_engine* e) {
-    return !e->sample_mem && e->c.vocab <= SAMPLE_SEG * SAMPLE_THREADS;
+    return !e->sample_mem && e->c.vocab <= SAMPLE_REG_MAX;
 }
 static void launch_sample_draft(asd_engine* e, const SampleArgs& sa, int j) {
-    if (sample_in_registers(e)) sample_draft_kernel<SAMPLE_SEG><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, j);
+    if (sample_in_registers(e)) sample_draft_kernel<SAMPLE_TILES><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, j);
     else sample_draft_kernel<0><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, j);
 }
 static void launch_sample_accept(asd_engine* e, const SampleArgs& sa, int kk) {
-    if (sample_in_registers(e)) sample_accept_kernel<SAMPLE_SEG><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, kk);
-    else sample_accept_kernel<0><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, kk);
+    if (sample_in_registers(e)) {
+        sample_stats_kernel<SAMPLE_TILES><<<kk + 1, SAMPLE_THREADS, 0, e->stream>>>(sa);
+        sample_accept_kernel<SAMPLE_TILES><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, kk);
+    } else {
+        sample_stats_kernel<0><<<kk + 1, SAMPLE_THREADS, 0, e->stream>>>(sa);
+        sample_accept_kernel<0><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, kk);
+    }
 }
 static void launch_sample_plain(asd_engine* e, const SampleArgs& sa, int row, int64_t index) {
-    if (sample_in_registers(e)) sample_plain_kernel<SAMPLE_SEG><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, row, index);
+    if (sample_in_registers(e)) sample_plain_kernel<SAMPLE_TILES><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, row, index);
     else sample_plain_kernel<0><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, row, index);
 }
 

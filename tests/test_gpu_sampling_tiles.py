@@ -1,0 +1,37 @@
+"""The sampling kernels at vocabulary sizes around their 256-value tiles and 16-wave split, and at both ends of the register
+variant, against the oracle's rule on identical logits (draws within MARGIN of a threshold are left out: either outcome is
+right there), and the two variants against each other draw for draw."""
+import numpy as np
+import pytest
+
+import asd_inputs as si
+import paper_2410_01028_amd as asd
+from test_gpu_sampling import MARGIN, oracle_step
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("V", [16, 256, 272, 4080, 4112, 32768, 32784])
+def test_draws_at_the_edges_of_the_tiles(V):
+    shape = si.Shape("v", 1, 64, 2, 2, 32, 64, V, si.DT_F32, 4, 4, 2)
+    engines = [asd.Engine(asd.make_config(shape, 64, debug_flags=f)) for f in (0, asd.DBG_SAMPLE_MEM)]
+    rng = np.random.default_rng(V)
+    compared = 0
+    for trial in range(24):
+        kk = int(rng.integers(0, 6))
+        p = rng.normal(0, 2.0, (kk + 1, V)).astype(np.float32)
+        q = (p[:kk] + rng.normal(0, float(rng.choice([0.1, 1.0])), (kk, V))).astype(np.float32)
+        if trial % 4 == 3:                    # all weight in the last / first few values, the rest far below
+            p -= 200.0
+            p[:, -3:] += 200.0
+            q[:, :2] += 300.0
+        seed, index0 = int(rng.integers(0, 2 ** 40)), int(rng.integers(0, 1000))
+        got = [e.spec_sample(q, p, 0.8, seed, index0) for e in engines]
+        assert np.array_equal(got[0][0], got[1][0]) and got[0][1:] == got[1][1:]
+        wd, wa, wn, mg = oracle_step(q.astype(np.float64), p.astype(np.float64), 0.8, seed, index0)
+        if mg >= MARGIN:
+            compared += 1
+            assert np.array_equal(got[0][0], wd) and got[0][1] == wa and got[0][2] == wn, (trial, kk, mg)
+    assert compared >= 12
+    for e in engines:
+        e.close()
