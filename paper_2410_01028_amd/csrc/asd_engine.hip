@@ -97,7 +97,6 @@ struct asd_engine {
     char* staging;
     size_t staging_bytes;
     // prompt-block workspace
-    int32_t* pf_tok;
     float *pf_xres, *pf_raw, *pf_ssq, *pf_rscale, *pf_cos_rows;
     void *pf_xb, *pf_q, *pf_attn_out, *pf_hmid;
     int pf_rows;                        // most rows of a prompt block
@@ -112,7 +111,12 @@ struct asd_engine {
     std::vector<double> acs_sum;         // per sublayer: sum of the prompt rows' cosines
     int acs_rows;
     bool acs_valid;
-    DevState* h_st;                     // pinned
+    // pinned host memory the device writes results into and reads prompts from
+    char* h_pin;
+    DevState* h_st;
+    int32_t *h_argmax, *h_tok;          // [16]; [capacity] prompt tokens going in, decoded tokens coming out
+    double* h_cos_acc;                  // [2L]
+    float *h_cos_rows, *h_logits;       // [2L][16]; [max_rows][vocab]
     std::map<std::vector<int>, hipGraphExec_t> graphs;
     std::vector<uint8_t> graph_mask;
     unsigned char* scratch = nullptr;   // this device's copy of the static scratch array (asd_forward_noalloc)
@@ -256,7 +260,7 @@ struct Plan {
     size_t kv, kv_layer, page_table;
     size_t xres, ssq, part, cos_rows, logits, o_part, rope, ml_part, arrivals, xb, q, attn_out, hmid, pstat, cos_acc, amax_part,
         argmax, tokbuf, out_tokens, st, ops, ops_bytes, staging, staging_bytes, total, qlogits;
-    size_t pf_tok, pf_xres, pf_raw, pf_ssq, pf_rscale, pf_cos_rows, pf_xb, pf_q, pf_attn_out, pf_hmid;
+    size_t pf_xres, pf_raw, pf_ssq, pf_rscale, pf_cos_rows, pf_xb, pf_q, pf_attn_out, pf_hmid;
     int es, KE, KBd, KBq, KBf, n_pages, nc_stride, qkv_tiles;
     int pf_rows;                                    // most rows of a prompt block
     GemmCfg g_qkv, g_o, g_gu, g_down, g_lm;
@@ -335,7 +339,6 @@ Plan make_plan(const asd_config& c) {
     // would leave other bytes there).
     auto take_pf = [&](size_t R) {
         p.pf_rows = (int)R;
-        p.pf_tok = take(R * 4);
         p.pf_xres = take(R * c.d_model * 4);
         p.pf_raw = take((size_t)PF_RAW_ROWS * c.d_model * 4);
         p.pf_ssq = take(R * 4);
@@ -553,9 +556,10 @@ struct PassOut {
     unsigned* arrivals;
     AmaxPart* amax_part;
     int nc_stride;       // groups per head in o_part / ml_part
+    float* d_cos;        // [2L] the mean cosines, for a caller's device buffer (else NULL)
 };
 PassOut engine_out(const asd_engine* e) {
-    return PassOut{e->logits, e->argmax, e->ssq, e->part, e->cos_rows, e->cos_acc, e->o_part, e->ml_part, e->arrivals, e->amax_part, e->nc_stride};
+    return PassOut{e->logits, e->argmax, e->ssq, e->part, e->cos_rows, e->cos_acc, e->o_part, e->ml_part, e->arrivals, e->amax_part, e->nc_stride, nullptr};
 }
 
 // The steps of one forward pass of M rows (first row at cache position st->pos + pos_off) under a skip mask:
@@ -673,6 +677,13 @@ int launch_steps(asd_engine* e, const std::vector<PassOp>& ops, const int32_t* d
             case OP_LM: ok = launch_gemm<EPI_LM>(e, e->g_lm, op.g); break;
             case OP_ATTN: launch_attn(e, op.t); break;
             case OP_FINISH:
+                if (out.d_cos) {
+                    MaskBits mb{};
+                    for (int j = 0; j < 2 * c.n_layers; ++j) if (mask && mask[j]) mb.w[j >> 5] |= 1u << (j & 31);
+                    finish_cos_kernel<<<1, 64 * M, 0, e->stream>>>((const AmaxCand*)out.amax_part, e->g_lm.grid, M, c.vocab, out.argmax, e->st, out.cos_acc,
+                                                                   2 * c.n_layers, mb, out.d_cos);
+                    break;
+                }
                 finish_kernel<<<1, 64 * M, 0, e->stream>>>((const AmaxCand*)out.amax_part, e->g_lm.grid, M, c.vocab, out.argmax, fin_mode, fin_arg,
                                                            e->st, e->tokbuf, e->out_tokens);
                 break;
@@ -700,11 +711,34 @@ bool weights_ready(asd_engine* e) {
 
 int chunks_for(int last_pos) { return last_pos / ASD_CHUNK + 1; }
 
+// Device arrays (whole words) on their way to pinned host memory, up to TO_HOST_MAX of them in one launch: with a copy per
+// array, most of them to pageable memory, a prompt pass spent about 50 us on handing its results over
+struct HostCopies {
+    ToHost a{};
+    int k = 0, most = 0;
+    void add(const void* src, void* dst, size_t bytes) {
+        a.src[k] = (const uint32_t*)src; a.dst[k] = (uint32_t*)dst; a.n[k] = (int32_t)(bytes / 4);
+        if (a.n[k] > most) most = a.n[k];
+        ++k;
+    }
+    void launch(hipStream_t s) const {
+        const int blocks = (most + 1023) / 1024;
+        to_host_kernel<<<blocks < 1 ? 1 : blocks > 256 ? 256 : blocks, 256, 0, s>>>(a);
+    }
+};
+// Enqueue what a call starts with: state, zeroed words, at most 16 tokens
+void launch_begin(asd_engine* e, int pos, int target = 0, int reset_counts = 0, int index_base = 0, void* zero = nullptr, int n_zero = 0,
+                  const int32_t* tok = nullptr, int n_tok = 0) {
+    BeginArgs a{};
+    a.st = e->st; a.pos = pos; a.target = target; a.reset_counts = reset_counts; a.index_base = index_base;
+    a.zero = (uint32_t*)zero; a.n_zero = n_zero; a.tokbuf = e->tokbuf; a.n_tok = n_tok;
+    for (int i = 0; i < n_tok; ++i) a.tok[i] = tok[i];
+    begin_kernel<<<n_zero > 256 ? (n_zero + 255) / 256 : 1, 256, 0, e->stream>>>(a);
+}
+
 // After a synchronisation: did a kernel meet a token id outside the vocabulary, or a row of logits without a finite
-// maximum?  (st: a host copy of the decoding state, or NULL to fetch it.)
-int check_pass_error(asd_engine* e, const DevState* st = nullptr) {
-    DevState tmp;
-    if (!st) { CK(e, hipMemcpy(&tmp, e->st, sizeof tmp, hipMemcpyDeviceToHost)); st = &tmp; }
+// maximum?  (st: a host copy of the decoding state.)
+int check_pass_error(asd_engine* e, const DevState* st) {
     if (st->err & DEV_ERR_TOKEN) return fail(e, ASD_E_INVAL, "a token id outside the vocabulary reached the embedding");
     if (st->err & DEV_ERR_LOGITS) return fail(e, ASD_E_STATE, "a row of logits had no finite maximum (non-finite weights?)");
     return ASD_OK;
@@ -727,7 +761,7 @@ int capacity(const asd_engine* e) { return e->n_pages * e->c.page_tokens; }
 void destroy_host(asd_engine* e) {
     drop_graphs(e);
     for (hipEvent_t ev : e->ev) if (ev) hipEventDestroy(ev);
-    if (e->h_st) hipHostFree(e->h_st);
+    if (e->h_pin) hipHostFree(e->h_pin);
     delete e;
 }
 
@@ -889,9 +923,9 @@ template <class T> void launch_pf_attn_t(asd_engine* e, const PfAttnArgs& a, int
     if (H == 128) pf_attn_kernel<T, 128><<<grid, 256, 0, e->stream>>>(a);
 }
 
-template <class T> void launch_pf_embed_t(asd_engine* e, int rows, int n_chunks) {
+template <class T> void launch_pf_embed_t(asd_engine* e, const int32_t* tokens, int rows, int n_chunks) {
     const asd_config& c = e->c;
-    pf_embed_kernel<T><<<pf_row_grid(n_chunks), 256, 0, e->stream>>>((const typename T::elem*)e->embed, e->pf_tok, rows, n_chunks, c.d_model, e->layers[0].g_attn,
+    pf_embed_kernel<T><<<pf_row_grid(n_chunks), 256, 0, e->stream>>>((const typename T::elem*)e->embed, tokens, rows, n_chunks, c.d_model, e->layers[0].g_attn,
         e->pf_xres, e->pf_xb, (int64_t)(e->pf_rows / 16) * e->KBd * 64 * e->KE, (int64_t)e->KBd * 64 * e->KE, e->pf_ssq, e->pf_rscale,
         1.f / (float)c.d_model, c.rms_eps);
 }
@@ -922,14 +956,14 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
     const int n_blocks = (n + e->pf_rows - 1) / e->pf_rows;
     const int block = e->pf_rows == PF_MIN_ROWS ? PF_MIN_ROWS : ((n + n_blocks - 1) / n_blocks + 127) / 128 * 128;
     const int64_t cap = e->pf_rows / 16;                // chunks per activation plane
+    memcpy(e->h_tok, tokens, (size_t)n * 4);             // (the embedding reads them from there; n <= capacity)
+    launch_begin(e, 0, 0, 0, 0, e->cos_acc, 4 * L);
     int rows = 0;
     for (int r0 = 0; r0 < n; r0 += rows) {
         rows = n - r0 < block ? n - r0 : block;
         const int n_chunks = (rows + 15) / 16;
-        CK(e, hipMemcpyAsync(e->pf_tok, tokens + r0, (size_t)rows * 4, hipMemcpyHostToDevice, e->stream));
-        set_state_kernel<<<1, 1, 0, e->stream>>>(e->st, r0, 0, 0, 0);
         pr.begin(ASD_PK_ROWS, 0);
-        if (bf) launch_pf_embed_t<BF16>(e, rows, n_chunks); else launch_pf_embed_t<F32>(e, rows, n_chunks);
+        if (bf) launch_pf_embed_t<BF16>(e, e->h_tok + r0, rows, n_chunks); else launch_pf_embed_t<F32>(e, e->h_tok + r0, rows, n_chunks);
         pr.end();
         // flops of each contraction over this block's rows (every weight multiply-add counted once), causal attention
         const double fl_row = 2.0 * rows, ctx_sum = (double)rows * r0 + 0.5 * rows * (rows + 1.0);
@@ -1059,7 +1093,7 @@ int asd_create(const asd_config* cfg, void* device_arena, size_t arena_bytes, vo
     e->amax_part = (AmaxPart*)(A + p.amax_part); e->argmax = (int32_t*)(A + p.argmax);
     e->tokbuf = (int32_t*)(A + p.tokbuf); e->out_tokens = (int32_t*)(A + p.out_tokens); e->st = (DevState*)(A + p.st);
     e->staging = A + p.staging; e->staging_bytes = p.staging_bytes;
-    e->pf_tok = (int32_t*)(A + p.pf_tok); e->pf_xres = (float*)(A + p.pf_xres); e->pf_raw = (float*)(A + p.pf_raw);
+    e->pf_xres = (float*)(A + p.pf_xres); e->pf_raw = (float*)(A + p.pf_raw);
     e->pf_ssq = (float*)(A + p.pf_ssq); e->pf_rscale = (float*)(A + p.pf_rscale); e->pf_cos_rows = (float*)(A + p.pf_cos_rows);
     e->pf_xb = A + p.pf_xb; e->pf_q = A + p.pf_q; e->pf_attn_out = A + p.pf_attn_out; e->pf_hmid = A + p.pf_hmid;
     e->pf_rows = p.pf_rows;
@@ -1080,13 +1114,20 @@ int asd_create(const asd_config* cfg, void* device_arena, size_t arena_bytes, vo
     e->acs_sum.assign(2 * (size_t)cfg->n_layers, 0.0);
     e->acs_rows = 0;
     e->acs_valid = false;
-    e->h_st = nullptr;
+    e->h_pin = nullptr;
 
     {   // the static scratch of asd_forward_noalloc: resolve this device's address now, not in the middle of a caller's loop
         const hipError_t rs = scratch_ptr(&e->scratch);
         if (rs != hipSuccess) { delete e; return fail(nullptr, ASD_E_HIP, "hipGetSymbolAddress(scratch): %s", hipGetErrorString(rs)); }
     }
-    hipError_t r = hipHostMalloc((void**)&e->h_st, sizeof(DevState), hipHostMallocDefault);
+    size_t pin = 0;
+    auto pinned = [&](size_t bytes) { const size_t o = pin; pin = align_up(pin + bytes); return o; };
+    const size_t o_st = pinned(sizeof(DevState)), o_am = pinned(ASD_ROWS * 4), o_acc = pinned((size_t)2 * cfg->n_layers * 8),
+                 o_rows = pinned((size_t)2 * cfg->n_layers * ASD_ROWS * 4), o_tok = pinned((size_t)capacity(e) * 4),
+                 o_lg = pinned((size_t)cfg->max_rows * cfg->vocab * 4);
+    hipError_t r = hipHostMalloc((void**)&e->h_pin, pin, hipHostMallocCoherent);
+    e->h_st = (DevState*)(e->h_pin + o_st); e->h_argmax = (int32_t*)(e->h_pin + o_am); e->h_cos_acc = (double*)(e->h_pin + o_acc);
+    e->h_cos_rows = (float*)(e->h_pin + o_rows); e->h_tok = (int32_t*)(e->h_pin + o_tok); e->h_logits = (float*)(e->h_pin + o_lg);
     if (r != hipSuccess) { delete e; return fail(nullptr, ASD_E_HIP, "hipHostMalloc: %s", hipGetErrorString(r)); }
     for (int i = 0; i < 3 && r == hipSuccess; ++i) r = hipEventCreate(&e->ev[i]);
     if (r != hipSuccess) { destroy_host(e); return fail(nullptr, ASD_E_HIP, "hipEventCreate: %s", hipGetErrorString(r)); }
@@ -1326,11 +1367,10 @@ int asd_admg(const float* C, int32_t L, float alpha, int32_t m, int32_t n, int32
     return asd_admg2(c2.data(), L, alpha, m, n, use_cs, 0.f, 0, mask);
 }
 
-// run rows [tokens, tokens+n) at the current cache end; results stay on the device
-static int forward_rows(asd_engine* e, const int32_t* tokens, int n, const uint8_t* mask, Profiler* prof) {
-    CK(e, hipMemcpyAsync(e->tokbuf, tokens, (size_t)n * 4, hipMemcpyHostToDevice, e->stream));
-    set_state_kernel<<<1, 1, 0, e->stream>>>(e->st, e->kv_len, 0, 0, 0);
-    return enqueue_forward(e, e->tokbuf, n, 0, mask, chunks_for(e->kv_len + n - 1), prof, e->kv_len + n);
+// run rows [tokens, tokens+n) at the current cache end; results stay on the device (first: the running cosine sums start anew)
+static int forward_rows(asd_engine* e, const int32_t* tokens, int n, const uint8_t* mask, bool first) {
+    launch_begin(e, e->kv_len, 0, 0, 0, e->cos_acc, first ? 4 * e->c.n_layers : 0, tokens, n);
+    return enqueue_forward(e, e->tokbuf, n, 0, mask, chunks_for(e->kv_len + n - 1), nullptr, e->kv_len + n);
 }
 
 int asd_forward(asd_engine* e, const int32_t* tokens, int32_t n_rows, int32_t pos0, const uint8_t* mask, int32_t commit,
@@ -1344,30 +1384,27 @@ int asd_forward(asd_engine* e, const int32_t* tokens, int32_t n_rows, int32_t po
     int rc = check_tokens(e, tokens, n_rows);
     if (rc) return rc;
     const int L2 = 2 * e->c.n_layers;
-    CK(e, hipMemsetAsync(e->cos_acc, 0, (size_t)L2 * 8, e->stream));
-    rc = forward_rows(e, tokens, n_rows, mask, nullptr);
+    rc = forward_rows(e, tokens, n_rows, mask, true);
     if (rc) return rc;
-    std::vector<double> acc(L2);
-    std::vector<float> rows((size_t)L2 * ASD_ROWS);
-    std::vector<int32_t> am(ASD_ROWS);
-    std::vector<float> lg;
-    CK(e, hipMemcpyAsync(acc.data(), e->cos_acc, (size_t)L2 * 8, hipMemcpyDeviceToHost, e->stream));
-    CK(e, hipMemcpyAsync(rows.data(), e->cos_rows, rows.size() * 4, hipMemcpyDeviceToHost, e->stream));
-    CK(e, hipMemcpyAsync(am.data(), e->argmax, ASD_ROWS * 4, hipMemcpyDeviceToHost, e->stream));
-    if (logits) {
-        lg.resize((size_t)n_rows * e->c.vocab);
-        CK(e, hipMemcpyAsync(lg.data(), e->logits, lg.size() * 4, hipMemcpyDeviceToHost, e->stream));
-    }
+    HostCopies out;
+    out.add(e->st, e->h_st, sizeof(DevState));
+    out.add(e->argmax, e->h_argmax, ASD_ROWS * 4);
+    out.add(e->cos_rows, e->h_cos_rows, (size_t)L2 * ASD_ROWS * 4);
+    out.add(e->cos_acc, e->h_cos_acc, (size_t)L2 * 8);
+    if (logits) out.add(e->logits, e->h_logits, (size_t)n_rows * e->c.vocab * 4);
+    out.launch(e->stream);
     CK(e, hipStreamSynchronize(e->stream));
-    rc = check_pass_error(e);
+    rc = check_pass_error(e, e->h_st);
     if (rc) return rc;
-    if (logits) memcpy(logits, lg.data(), lg.size() * 4);
+    if (logits) memcpy(logits, e->h_logits, (size_t)n_rows * e->c.vocab * 4);
+    const double* acc = e->h_cos_acc;
+    const float* rows = e->h_cos_rows;
     for (int j = 0; j < L2; ++j) {
         const bool skipped = mask && mask[j];
         if (cos) cos[j] = skipped ? 1.f : (float)(acc[j] / n_rows);
         if (cos_rows) for (int r = 0; r < n_rows; ++r) cos_rows[(size_t)r * L2 + j] = skipped ? 1.f : rows[(size_t)j * ASD_ROWS + r];
     }
-    if (argmax) memcpy(argmax, am.data(), (size_t)n_rows * 4);
+    if (argmax) memcpy(argmax, e->h_argmax, (size_t)n_rows * 4);
     if (commit) e->kv_len = pos0 + n_rows;
     return ASD_OK;
 }
@@ -1412,15 +1449,10 @@ int asd_forward_noalloc(asd_engine* e, const int32_t* d_tokens, int32_t n_rows, 
     if (d_argmax) out.argmax = d_argmax;
     // what must start at zero: the running cosine sums and the heads' arrival counters (neighbours in the layout)
     const int nz = (int)(((unsigned char*)out.amax_part - (unsigned char*)out.cos_acc) / 4);
-    zero_words_kernel<<<(nz + 255) / 256, 256, 0, e->stream>>>((uint32_t*)out.cos_acc, nz);
-    set_state_kernel<<<1, 1, 0, e->stream>>>(e->st, e->kv_len, 0, 0, 0);
+    launch_begin(e, e->kv_len, 0, 0, 0, out.cos_acc, nz);
+    out.d_cos = d_cos;
     const int rc = enqueue_forward(e, d_tokens, n_rows, 0, mask, chunks_for(e->kv_len + n_rows - 1), nullptr, e->kv_len + n_rows, FIN_NONE, 0, &out);
     if (rc) return rc;
-    if (d_cos) {
-        MaskBits mb{};
-        for (int j = 0; j < L2; ++j) if (mask && mask[j]) mb.w[j >> 5] |= 1u << (j & 31);
-        cos_mean_kernel<<<(L2 + 255) / 256, 256, 0, e->stream>>>(out.cos_acc, L2, n_rows, mb, d_cos);
-    }
     const hipError_t r = hipGetLastError();
     if (r != hipSuccess) return fail(e, ASD_E_HIP, "kernel launch: %s", hipGetErrorString(r));
     if (commit) e->kv_len = pos0 + n_rows;
@@ -1429,8 +1461,11 @@ int asd_forward_noalloc(asd_engine* e, const int32_t* d_tokens, int32_t n_rows, 
 
 int asd_check(asd_engine* e) {
     if (!e) return ASD_E_INVAL;
+    HostCopies out;
+    out.add(e->st, e->h_st, sizeof(DevState));
+    out.launch(e->stream);
     CK(e, hipStreamSynchronize(e->stream));
-    return check_pass_error(e);
+    return check_pass_error(e, e->h_st);
 }
 
 static int prefill_impl(asd_engine* e, const int32_t* tokens, int32_t n, int32_t* first_token, float* cos_out, float* last_logits, bool blocks) {
@@ -1442,7 +1477,6 @@ static int prefill_impl(asd_engine* e, const int32_t* tokens, int32_t n, int32_t
     if (rc) return rc;
     const int L2 = 2 * e->c.n_layers;
     e->kv_len = 0; e->acs_valid = false;
-    CK(e, hipMemsetAsync(e->cos_acc, 0, (size_t)L2 * 8, e->stream));
     int last_row = 0;
     if (blocks) {
         rc = prefill_blocks(e, tokens, n);
@@ -1451,31 +1485,29 @@ static int prefill_impl(asd_engine* e, const int32_t* tokens, int32_t n, int32_t
         int rows = 0;
         for (int p = 0; p < n; p += rows) {
             rows = n - p < e->c.max_rows ? n - p : e->c.max_rows;
-            rc = forward_rows(e, tokens + p, rows, nullptr, nullptr);
+            rc = forward_rows(e, tokens + p, rows, nullptr, p == 0);
             if (rc) return rc;
             e->kv_len = p + rows;
         }
         last_row = rows - 1;
     }
     e->last_logits_row = last_row;
-    std::vector<double> acc(L2);
-    int32_t am[ASD_ROWS];
-    CK(e, hipMemcpyAsync(acc.data(), e->cos_acc, (size_t)L2 * 8, hipMemcpyDeviceToHost, e->stream));
-    CK(e, hipMemcpyAsync(am, e->argmax, ASD_ROWS * 4, hipMemcpyDeviceToHost, e->stream));
-    std::vector<float> lg;
-    if (last_logits) {
-        lg.resize(e->c.vocab);
-        CK(e, hipMemcpyAsync(lg.data(), e->logits + (size_t)last_row * e->c.vocab, lg.size() * 4, hipMemcpyDeviceToHost, e->stream));
-    }
+    HostCopies out;
+    out.add(e->st, e->h_st, sizeof(DevState));
+    out.add(e->argmax, e->h_argmax, ASD_ROWS * 4);
+    out.add(e->cos_acc, e->h_cos_acc, (size_t)L2 * 8);
+    if (last_logits) out.add(e->logits + (size_t)last_row * e->c.vocab, e->h_logits, (size_t)e->c.vocab * 4);
+    out.launch(e->stream);
     CK(e, hipStreamSynchronize(e->stream));
-    rc = check_pass_error(e);
+    rc = check_pass_error(e, e->h_st);
     if (rc) return rc;
+    const double* acc = e->h_cos_acc;
     for (int j = 0; j < L2; ++j) { e->acs[j] = (float)(acc[j] / n); e->acs_sum[j] = acc[j]; }
     e->acs_rows = n;
     e->acs_valid = true;
     if (cos_out) memcpy(cos_out, e->acs.data(), (size_t)L2 * 4);
-    if (last_logits) memcpy(last_logits, lg.data(), lg.size() * 4);
-    *first_token = am[last_row];
+    if (last_logits) memcpy(last_logits, e->h_logits, (size_t)e->c.vocab * 4);
+    *first_token = e->h_argmax[last_row];
     return ASD_OK;
 }
 
@@ -1561,7 +1593,7 @@ int asd_spec_sample(asd_engine* e, const float* q_logits, const float* p_logits,
     if (index0 < 0 || index0 > (1 << 30)) return fail(e, ASD_E_INVAL, "index0 out of range");
     const size_t V = e->c.vocab;
     const SampleArgs sa = sample_args(e, temperature, seed);
-    set_state_kernel<<<1, 1, 0, e->stream>>>(e->st, e->kv_len, 0, kk + 1, 1, (int)index0);
+    launch_begin(e, e->kv_len, kk + 1, 1, (int)index0);
     for (int j = 0; j < kk; ++j) {                 // each draft row takes the place a draft step's logits would have
         CK(e, hipMemcpyAsync(e->logits, q_logits + (size_t)j * V, V * 4, hipMemcpyHostToDevice, e->stream));
         launch_sample_draft(e, sa, j);
@@ -1650,8 +1682,7 @@ int asd_decode(asd_engine* e, int32_t last_token, int32_t n_more, const asd_gen_
     const auto t0 = std::chrono::steady_clock::now();
     const bool sampled = p->temperature > 0.f;
     const SampleArgs sa = sampled ? sample_args(e, p->temperature, p->seed) : SampleArgs{};
-    set_state_kernel<<<1, 1, 0, e->stream>>>(e->st, e->kv_len, 0, n_more, 1, sampled ? (int)p->sample_index0 : 0);
-    set_token_kernel<<<1, 1, 0, e->stream>>>(e->tokbuf, last_token);
+    launch_begin(e, e->kv_len, n_more, 1, sampled ? (int)p->sample_index0 : 0, nullptr, 0, &last_token, 1);
     const bool graphs = p->use_graphs != 0;
     if (sampled && (e->graph_T != p->temperature || e->graph_seed != p->seed)) {        // both are baked into captured launches
         drop_graphs(e); e->graph_T = p->temperature; e->graph_seed = p->seed;
@@ -1704,7 +1735,9 @@ int asd_decode(asd_engine* e, int32_t last_token, int32_t n_more, const asd_gen_
                                   [&] { return enqueue_forward(e, e->tokbuf + d, 1, d, mask.data(), nc, nullptr, ctx, FIN_DRAFT, d); });
                 if (rc) return rc;
                 ++d;
-                CK(e, hipMemcpyAsync(e->h_st, e->st, sizeof(DevState), hipMemcpyDeviceToHost, e->stream));
+                HostCopies step;
+                step.add(e->st, e->h_st, sizeof(DevState));
+                step.launch(e->stream);
                 CK(e, hipStreamSynchronize(e->stream));
                 if ((double)e->h_st->conf < gamma) break;
             }
@@ -1716,7 +1749,13 @@ int asd_decode(asd_engine* e, int32_t last_token, int32_t n_more, const asd_gen_
         CK(e, hipEventRecord(e->ev[2], e->stream));
         for (int j = 0; j < d; ++j) add_bytes(bytes_draft, mask.data(), e->kv_len + ahead + j + 1);
         add_bytes(bytes_verify, nullptr, e->kv_len + ahead + d + 1);
-        CK(e, hipMemcpyAsync(e->h_st, e->st, sizeof(DevState), hipMemcpyDeviceToHost, e->stream));
+        // the state, and the tokens this trip may have emitted (fewer than asked for where drafts were rejected: the next
+        // trip brings those places again)
+        HostCopies trip;
+        const int most = ahead + d + 1 < n_more - emitted ? ahead + d + 1 : n_more - emitted;
+        trip.add(e->st, e->h_st, sizeof(DevState));
+        trip.add(e->out_tokens + emitted, e->h_tok + emitted, (size_t)most * 4);
+        trip.launch(e->stream);
         if (refresh) CK(e, hipMemcpyAsync(cr.data(), e->cos_rows, cr.size() * 4, hipMemcpyDeviceToHost, e->stream));
         CK(e, hipStreamSynchronize(e->stream));
         {
@@ -1749,9 +1788,8 @@ int asd_decode(asd_engine* e, int32_t last_token, int32_t n_more, const asd_gen_
             if (mnew != mask) { mask = mnew; ++mask_changes; drop_graphs(e); e->graph_mask = mask; }
         }
     }
-    CK(e, hipMemcpyAsync(out, e->out_tokens, (size_t)n_more * 4, hipMemcpyDeviceToHost, e->stream));
-    CK(e, hipStreamSynchronize(e->stream));
-    { const int rc2 = check_pass_error(e); if (rc2) return rc2; }
+    { const int rc2 = check_pass_error(e, e->h_st); if (rc2) return rc2; }
+    memcpy(out, e->h_tok, (size_t)n_more * 4);
     const auto t1 = std::chrono::steady_clock::now();
     if (stats) {
         stats->cycles = e->h_st->cycles; stats->drafted = e->h_st->drafted; stats->accepted = e->h_st->accepted;
@@ -1804,8 +1842,7 @@ int asd_generate(asd_engine* e, const int32_t* prompt, int32_t n_prompt, int32_t
 static int bench_tokens(asd_engine* e, int n_rows) {
     int32_t t[ASD_ROWS];
     for (int i = 0; i < n_rows; ++i) t[i] = (int32_t)((1 + 7919 * i) % e->c.vocab);
-    CK(e, hipMemcpyAsync(e->tokbuf, t, (size_t)n_rows * 4, hipMemcpyHostToDevice, e->stream));
-    set_state_kernel<<<1, 1, 0, e->stream>>>(e->st, e->kv_len, 0, 0, 0);
+    launch_begin(e, e->kv_len, 0, 0, 0, nullptr, 0, t, n_rows);
     CK(e, hipStreamSynchronize(e->stream));
     return ASD_OK;
 }
@@ -1905,11 +1942,9 @@ int asd_profile_prefill(asd_engine* e, const int32_t* tokens, int32_t n, asd_pre
     if (rc) return rc;
     const int L2 = 2 * e->c.n_layers;
     e->kv_len = 0; e->acs_valid = false;
-    CK(e, hipMemsetAsync(e->cos_acc, 0, (size_t)L2 * 8, e->stream));
     rc = prefill_blocks(e, tokens, n);                 // warm-up
     if (rc) return rc;
     e->kv_len = 0;
-    CK(e, hipMemsetAsync(e->cos_acc, 0, (size_t)L2 * 8, e->stream));
     Profiler pf;
     rc = prefill_blocks(e, tokens, n, &pf);
     hipError_t r2 = hipStreamSynchronize(e->stream);

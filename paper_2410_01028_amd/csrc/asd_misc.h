@@ -46,11 +46,39 @@ __global__ __launch_bounds__(EMBED_THREADS) void embed_kernel(const typename T::
 }
 
 // ---------------------------------------------------------------- decoding state
-__global__ void set_state_kernel(DevState* st, int pos, int emitted, int target, int reset_counts, int index_base = 0) {
-    st->pos = pos; st->emitted = emitted; st->target = target; st->index_base = index_base; st->err = 0;
-    if (reset_counts) { st->cycles = 0; st->drafted = 0; st->accepted = 0; }
+// What a call sets up before its first pass, in one launch: the decoding state, the words that must start at zero (running
+// cosine sums, arrival counters; a kernel, not a memset, so that a caller may record the call into a HIP graph) and up
+// to 16 token ids, which come as kernel arguments.
+struct BeginArgs {
+    DevState* st;
+    int32_t pos, emitted, target, reset_counts, index_base;
+    uint32_t* zero;
+    int32_t n_zero;
+    int32_t* tokbuf;
+    int32_t n_tok, tok[16];
+};
+__global__ __launch_bounds__(256) void begin_kernel(const BeginArgs a) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < a.n_zero) a.zero[i] = 0u;
+    if (blockIdx.x != 0) return;
+    if (i < a.n_tok) a.tokbuf[i] = a.tok[i];
+    if (i == 0) {
+        DevState* st = a.st;
+        st->pos = a.pos; st->emitted = a.emitted; st->target = a.target; st->index_base = a.index_base; st->err = 0;
+        if (a.reset_counts) { st->cycles = 0; st->drafted = 0; st->accepted = 0; }
+    }
 }
-__global__ void set_token_kernel(int32_t* tokbuf, int32_t tok) { tokbuf[0] = tok; }
+
+// What a call hands back to the host, in one launch: up to five arrays of words, written straight into pinned host memory
+// (one launch and one wait instead of a copy per array)
+#define TO_HOST_MAX 5
+struct ToHost { const uint32_t* src[TO_HOST_MAX]; uint32_t* dst[TO_HOST_MAX]; int32_t n[TO_HOST_MAX]; };
+__global__ __launch_bounds__(256) void to_host_kernel(const ToHost a) {
+    const int step = (int)gridDim.x * 256, first = (int)blockIdx.x * 256 + (int)threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < TO_HOST_MAX; ++k)
+        for (int i = first; i < a.n[k]; i += step) a.dst[k][i] = a.src[k][i];
+}
 
 // After the LM head: pick each row's greedy token from the per-workgroup candidates (largest
 // logit, lowest index on ties), then, by mode,
@@ -144,19 +172,16 @@ __global__ __launch_bounds__(1024) void finish_kernel(const AmaxCand* cand, int 
     finish_block(cand, P, M, V, argmax, mode, j_or_kk, st, tokbuf, out, win);
 }
 
-// ---------------------------------------------------------------- helpers of the entry point that allocates nothing
-// clears n 32-bit words (counters and running sums that must start at zero; a kernel, not a memset, so that a caller
-// may record the call into a HIP graph)
-__global__ void zero_words_kernel(uint32_t* p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
-}
 // one bit per sublayer of a skip mask, passed to a kernel by value
 struct MaskBits { uint32_t w[128]; };
-// mean over the rows of every sublayer's cosine (a removed sublayer reports exactly 1), to a caller's device buffer
-__global__ void cos_mean_kernel(const double* cos_acc, int n_sub, int rows, MaskBits skip, float* out) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < n_sub) out[j] = ((skip.w[j >> 5] >> (j & 31)) & 1u) ? 1.f : (float)(cos_acc[j] / (double)rows);
+// The end of a pass whose results stay on the device: as finish_kernel (FIN_NONE), and the mean over the rows of every
+// sublayer's cosine (a removed sublayer reports exactly 1) to a caller's device buffer.
+__global__ __launch_bounds__(1024) void finish_cos_kernel(const AmaxCand* cand, int P, int M, int V, int32_t* argmax, DevState* st,
+                                                          const double* cos_acc, int n_sub, MaskBits skip, float* cos) {
+    __shared__ int win[16];
+    for (int j = threadIdx.x; j < n_sub; j += (int)blockDim.x)
+        cos[j] = ((skip.w[j >> 5] >> (j & 31)) & 1u) ? 1.f : (float)(cos_acc[j] / (double)M);
+    finish_block(cand, P, M, V, argmax, FIN_NONE, 0, st, nullptr, nullptr, win);
 }
 
 // ---------------------------------------------------------------- rotary table: cos/sin(pos * theta^(-2i/h)) in double
