@@ -399,7 +399,7 @@ __global__ __launch_bounds__(ATT_GW * 64, 4) void attn_kernel_w4(ATT_HOT_PARAMS,
 }
 
 // ---------------------------------------------------------------- prompt blocks: causal attention
-// 16 * PF_ATT_NT query rows of a prompt block (cache positions pos0 + ...) of one query head against all keys up to
+// Query rows of a prompt block (cache positions pos0 + ...) of one query head against all keys up to
 // their own positions.  Same fragments and key order as the decode kernel above.  Workgroups are numbered longest
 // row block first.
 struct PfAttnArgs {
@@ -413,22 +413,20 @@ struct PfAttnArgs {
     float scale;
 };
 
-#ifndef PF_ATT_NT
-#define PF_ATT_NT 2            // 16-row chunks of query rows per workgroup of pf_attn_kernel
-#endif
-// A workgroup takes 32 query rows (two 16-row chunks) and splits the keys over its four waves: wave w walks the
-// 64-key chunks w, w + 4, ... with a running maximum and sum per row (the output accumulator is rescaled when the
+// A workgroup takes one 16-row chunk of query rows and splits the keys over its four waves: wave w walks the 64-key
+// chunks w, w + 4, ... with a running maximum and sum per row (the output accumulator is rescaled when the
 // maximum grows), and the four partial results are merged through LDS in wave order at the end, so the result has
-// one fixed order.  A chunk's K and V^T fragments are loaded once per 32 query rows and feed two column tiles of
-// matrix-core work (with one tile per load the loads, not the products, fill the time: 1.8x slower at 8K context);
-// the next chunk's K fragments are requested as soon as the score products have consumed the current ones, the
-// next V^T fragments right after the output products, into the same registers (the scheduler is fenced at those
-// points: without the fences, or with three column tiles, the kernel is slower).  Needs a SIMD's whole register
-// file per wave.
+// one fixed order.  The next chunk's K fragments are requested as soon as the score products have consumed the current ones,
+// the next V^T fragments right after the output products, into the same registers (the scheduler is fenced at those
+// points: without the fences the kernel is slower).  This is the kernel of short blocks and few heads, where a launch lasts as long as one
+// workgroup's chain of loads, products and merge: a wave of 16 rows fits twice on a SIMD and has half the products to wait
+// for, where 32 rows per wave need a SIMD's whole register file and halve the fragment loads, which nothing here is
+// short of.  32 -> 16 rows: 7B 45 rows 10.7 -> 7.6 us, 512 rows 30.8 -> 24.8 us; four heads x 128 at 6000 rows 44 -> 27 us per block.
 template <class T, int H>
-__global__ __launch_bounds__(256, 1) void pf_attn_kernel(const PfAttnArgs a) {
+__global__ __launch_bounds__(256, sizeof(typename T::elem) == 4 && H == 128 ? 1 : 2) void pf_attn_kernel(const PfAttnArgs a) {
     using E = typename T::elem;
-    constexpr int KE = T::KE, HS = H / (4 * KE), HT = H / 16, KST = 64 / (4 * KE), NP = T::NP, NT = PF_ATT_NT, NWV = 4;
+    constexpr int KE = T::KE, HS = H / (4 * KE), HT = H / 16, KST = 64 / (4 * KE), NP = T::NP, NWV = 4;
+    constexpr int NT = 1;             // 16-row chunks per workgroup
     __shared__ float so[NWV][16][H];
     __shared__ float sml[NWV][NT][16][2];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, m = lane & 15, r = lane & 15;

@@ -843,7 +843,8 @@ struct PfRingPick { int tile, ks; };                                          //
 // with two slices, 120 and 300 us with four).
 constexpr int PF_FIXED_SLICES = 40;
 PfRingPick pf_ring_pick(const asd_engine* e, int epi, const PfCfg& g, int n_tiles, int KB, int n_chunks) {
-    const int units = device_units() / 8 > 0 ? device_units() / 8 : 1;
+    const int units = device_units() / 8 > 0 ? device_units() / 8 : 1, np = e->c.dtype == ASD_DT_BF16 ? BF16::NP : F32::NP;
+    const bool f32 = e->c.dtype == ASD_DT_F32;
     const int ks4 = pf_old_slices(g, KB, n_chunks);
     auto raw_us = [&](int ks) { return epi == PF_RAW ? ks * (2.f * n_chunks * 16 * n_tiles * 16 * 4 / 5e6f) : 0.f; };
     PfRingPick best{-1, epi == PF_RAW ? ks4 : 1};
@@ -851,37 +852,38 @@ PfRingPick pf_ring_pick(const asd_engine* e, int epi, const PfCfg& g, int n_tile
     if (e->pf_ring_tune[0] < 0 && e->pf_ring_tune[1] == 0) {
         const int na = epi == PF_GU ? 2 : epi == PF_QKV ? pf_qkv_na(g, n_tiles, n_chunks) : 4, per = 4 * na;
         const float wgs = (float)(((n_tiles + per - 1) / per + 7) / 8 * ((n_chunks + g.NC - 1) / g.NC) * best.ks) / units;
-        const float on_unit = wgs > 2.f ? wgs : ceilf(wgs), frags = 4 * (epi == PF_GU ? 2 * na : na) + 2 * g.NC;
-        best_us = (float)KB / best.ks * fmaxf(0.5f, on_unit * frags / 57.f) + 4.f + raw_us(best.ks);
+        const float on_unit = wgs > 2.f ? wgs : ceilf(wgs), frags = 4 * (epi == PF_GU ? 2 * na : na) + np * g.NC;
+        best_us = (float)KB / best.ks * fmaxf(f32 ? 1.1f : 0.5f, on_unit * frags / 57.f) + 4.f + raw_us(best.ks);
     }
     for (int v = 0; v < kPfRings; ++v) {
         const PfRingTile& T = kPfRing[v];
         if (e->pf_ring_tune[0] >= 0 && e->pf_ring_tune[0] != v) continue;
         const int per = epi == PF_GU && v < kPfBig ? T.FT / 2 : T.FT, n_fb = (n_tiles + per - 1) / per, n_rb = (n_chunks + T.RC - 1) / T.RC;
-        const int frags = (epi == PF_GU ? 2 * per : per) + 2 * T.RC;
+        const int tiles = epi == PF_GU ? 2 * per : per, frags = tiles + np * T.RC;
+        const float us_kb = f32 ? tiles * T.RC * 0.061f / (v < kPfBig ? 8 : T.FT) : T.us_kb;      // a fragment product: 128 cycles of one SIMD
         for (int ks = 1; ks <= PF_MAX_KSPLIT; ++ks) {
             if (ks > 1 && (epi != PF_RAW || ks * n_chunks * 16 > PF_RAW_ROWS || ks > KB)) break;
             if (epi == PF_RAW && (e->pf_ring_tune[1] > 0 ? ks != e->pf_ring_tune[1] : n_chunks <= PF_FIXED_SLICES && ks != ks4)) continue;
             const int rounds = ((n_fb + 7) / 8 * n_rb * ks + units - 1) / units;
-            const float us = rounds * ((float)KB / ks * fmaxf(T.us_kb, frags / 43.f) + 4.f) + raw_us(ks);
+            const float us = rounds * ((float)KB / ks * fmaxf(us_kb, frags / 43.f) + 4.f) + raw_us(ks);
             if (us < best_us) { best = {v, ks}; best_us = us; }
         }
     }
     return best;
 }
-template <int EPI> bool launch_pf_ring(hipStream_t s, const PfRingPick& p, PfArgs a, int n_chunks) {
-    const PfRingTile& T = kPfRing[p.tile];
-    const int per = EPI == PF_GU && p.tile < kPfBig ? T.FT / 2 : T.FT;
+template <class T, int EPI> bool launch_pf_ring(hipStream_t s, const PfRingPick& p, PfArgs a, int n_chunks) {
+    const PfRingTile& R = kPfRing[p.tile];
+    const int per = EPI == PF_GU && p.tile < kPfBig ? R.FT / 2 : R.FT;
     a.n_fb = (a.n_tiles + per - 1) / per;
-    a.n_rb = (n_chunks + T.RC - 1) / T.RC;
+    a.n_rb = (n_chunks + R.RC - 1) / R.RC;
     a.ksplit = p.ks;
     const unsigned grid = (unsigned)((a.n_fb + 7) / 8 * 8 * a.n_rb * a.ksplit);
     constexpr int N1 = EPI == PF_GU ? 2 : 1;            // one output tile per wave
     constexpr auto ring = [](int nf) { return 159 / nf < 16 ? 159 / nf / 2 * 2 : 16; };      // stages the LDS holds (an even number)
     switch (p.tile) {
-#define PFR(v, nt, nc, fw, rw, st, pf) case v: pf_ring_kernel<EPI, nt, nc, fw, rw, st, pf><<<grid, fw * rw * 64, 0, s>>>(a); return true;
+#define PFR(v, nt, nc, fw, rw, st, pf) case v: pf_ring_kernel<T, EPI, nt, nc, fw, rw, st, pf><<<grid, fw * rw * 64, 0, s>>>(a); return true;
         PFR(0, 6, 2, 2, 4, 5, true) PFR(1, 4, 4, 4, 2, 4, true) PFR(2, 6, 4, 4, 2, 4, true) PFR(3, 8, 4, 2, 4, 3, false)
-#define PFN(v, nc, fw) PFR(v, N1, nc, fw, 1, ring(N1 * fw + 2 * nc), true)
+#define PFN(v, nc, fw) PFR(v, N1, nc, fw, 1, ring(N1 * fw + T::NP * nc), true)
         PFN(4, 2, 3) PFN(5, 3, 3) PFN(6, 4, 3) PFN(7, 2, 4) PFN(8, 3, 4) PFN(9, 4, 4) PFN(10, 6, 4) PFN(11, 8, 4)
         PFN(12, 2, 8) PFN(13, 3, 8) PFN(14, 4, 8) PFN(15, 8, 8)
 #undef PFN
@@ -890,7 +892,7 @@ template <int EPI> bool launch_pf_ring(hipStream_t s, const PfRingPick& p, PfArg
     return false;
 }
 PfRingPick pf_use(const asd_engine* e, const PfCfg& g, int epi, int n_tiles, int KB, int n_chunks) {
-    if (e->c.dtype != ASD_DT_BF16 || BF16::NP != 2 || g.forced) return {-1, pf_old_slices(g, KB, n_chunks)};
+    if (g.forced) return {-1, pf_old_slices(g, KB, n_chunks)};
     return pf_ring_pick(e, epi, g, n_tiles, KB, n_chunks);
 }
 // K slices of a residual-add GEMM's launch (what pf_resid_kernel has to add up)
@@ -899,15 +901,15 @@ int pf_slices(const asd_engine* e, const PfCfg& g, int n_tiles, int KB, int n_ch
 }
 template <int EPI> bool launch_pf_gemm(asd_engine* e, const PfCfg& g, const PfArgs& a, int n_chunks) {
     const PfRingPick p = pf_use(e, g, EPI, a.n_tiles, a.KB, n_chunks);
-    if (p.tile >= 0) return launch_pf_ring<EPI>(e->stream, p, a, n_chunks);
+    if (p.tile >= 0) return e->c.dtype == ASD_DT_BF16 ? launch_pf_ring<BF16, EPI>(e->stream, p, a, n_chunks) : launch_pf_ring<F32, EPI>(e->stream, p, a, n_chunks);
     return e->c.dtype == ASD_DT_BF16 ? launch_pf_gemm_t<BF16, EPI>(e->stream, g, a, n_chunks) : launch_pf_gemm_t<F32, EPI>(e->stream, g, a, n_chunks);
 }
 
 template <class T> void launch_pf_attn_t(asd_engine* e, const PfAttnArgs& a, int n_chunks) {
     const int H = e->c.head_dim;
     // From three 128-row workgroups to four compute units on, the kernel that shares a chunk's fragments among 128 rows;
-    // with fewer, units stand idle and the 32-row workgroups are as fast or faster (7B: 192 workgroups at 700 rows 39 us
-    // against 46 us, 128 at 512 rows 31 against 32 us, 64 at 256 rows 20 against 15 us).
+    // with fewer, units stand idle (7B: 192 workgroups at 700 rows 39 us; 128 at 512 rows 31 us against 25 us of the 16-row
+    // workgroups, 64 at 256 rows 20 against 14 us).
     if constexpr (std::is_same_v<T, BF16> && BF16::NP == 2) {
         const int wgs = (a.rows + PF_ATT_LONG_ROWS - 1) / PF_ATT_LONG_ROWS * a.n_h;
         if (4 * wgs >= 3 * device_units()) {
@@ -917,7 +919,7 @@ template <class T> void launch_pf_attn_t(asd_engine* e, const PfAttnArgs& a, int
             return;
         }
     }
-    const dim3 grid((n_chunks + PF_ATT_NT - 1) / PF_ATT_NT, e->c.n_heads);
+    const dim3 grid(n_chunks, e->c.n_heads);
     if (H == 32) pf_attn_kernel<T, 32><<<grid, 256, 0, e->stream>>>(a);
     if (H == 64) pf_attn_kernel<T, 64><<<grid, 256, 0, e->stream>>>(a);
     if (H == 128) pf_attn_kernel<T, 128><<<grid, 256, 0, e->stream>>>(a);

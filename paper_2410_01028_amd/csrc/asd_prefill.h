@@ -244,7 +244,7 @@ __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const
 }
 
 // ---- the eight-wave kernel of the bf16 prompt GEMMs
-// What bounds the large prompt GEMMs is the card's power, not the issue of matrix-core work: a loop of matrix-core
+// What bounds the large bf16 prompt GEMMs is the card's power, not the issue of matrix-core work: a loop of matrix-core
 // instructions on random operands in registers runs at 2.1 GHz and 2.1 PFLOP/s, and every byte moved per product takes its
 // share of the clock.  So both operands are read once per workgroup into LDS (no fragment passes through a register on
 // its way there), the tile per workgroup is as large as the launch's balance allows, and a wave's tile (NT weight tiles x
@@ -260,18 +260,19 @@ __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const
 // order).  Measured (two planes counted, 7B): QKV 512 rows 95 -> 83 us, gate/up 158 -> 146 us (1.26 PFLOP/s), down 79 -> 74 us;
 // 2048 rows: gate/up 4 x 158 -> 540 us (1.37 PFLOP/s), QKV 4 x 95 -> 295 us, down 4 x 79 -> 262 us (1.41 PFLOP/s, which
 // is what the vendor library's largest square product reaches here).
-template <int NT, int NC, int FW, int RW, int S> struct PfRing {
+template <int NP, int NT, int NC, int FW, int RW, int S> struct PfRing {
     static constexpr int W = FW * RW;                               // waves
     static constexpr int FT = FW * NT, RC = RW * NC;                // weight tiles and chunks per workgroup
-    static constexpr int NF = FT + 2 * RC;                          // fragments per k-block
+    static constexpr int NF = FT + NP * RC;                          // fragments per k-block
     // requests per wave and stage, the same number from every wave (the wait counts depend on it): where they do not come
     // out even, some waves' last request reads nothing (into a spare KiB)
     static constexpr int L = (NF + W - 1) / W, LDS = S * NF + (NF % W ? 1 : 0);
     static_assert(LDS <= 160 && (S - 1) * L < 64, "LDS, and what the request counter can hold");
 };
-template <int EPI, int NT, int NC, int FW, int RW, int S, bool PF>
+template <class T, int EPI, int NT, int NC, int FW, int RW, int S, bool PF>
 __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kernel(const PfArgs a) {
-    using SH = PfRing<NT, NC, FW, RW, S>;
+    constexpr int NP = T::NP;
+    using SH = PfRing<NP, NT, NC, FW, RW, S>;
     constexpr int W = SH::W, FT = SH::FT, RC = SH::RC, NF = SH::NF, L = SH::L;
     constexpr int NA = EPI == PF_GU ? NT / 2 : NT;                  // output tiles per wave
     __shared__ u32x4 sm[SH::LDS * 64];
@@ -283,7 +284,7 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
     if (fb >= a.n_fb) return;
     const int kb0 = (int)((long)ks * a.KB / a.ksplit), n = (int)((long)(ks + 1) * a.KB / a.ksplit) - kb0;
 
-    // This wave's requests of a stage: fragments w, w + W, ... of the stage's FT weight and 2 RC chunk fragments.  A tile
+    // This wave's requests of a stage: fragments w, w + W, ... of the stage's FT weight and NP RC chunk fragments.  A tile
     // beyond the last re-reads the last one, a chunk beyond the rows holds whatever it holds: their products are never
     // looked at.
     const char* src[L];
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
             src[i] = (const char*)(up ? a.W2 : a.W) + ((int64_t)t * a.w_tile_stride + (int64_t)kb0 * a.w_kb_stride) * 1024;
             step[i] = a.w_kb_stride * 1024;
         } else {
-            src[i] = (const char*)a.X + ((int64_t)(x & 1) * a.x_plane + (int64_t)(rb * RC + (x >> 1)) * a.x_chunk) * 16 + (int64_t)kb0 * 1024;
+            src[i] = (const char*)a.X + ((int64_t)(x % NP) * a.x_plane + (int64_t)(rb * RC + x / NP) * a.x_chunk) * 16 + (int64_t)kb0 * 1024;
             step[i] = 1024;
         }
     }
@@ -321,11 +322,11 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
     for (int s = 0; s < NT; ++s)
 #pragma unroll
         for (int c = 0; c < NC; ++c) acc[s][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    u32x4 fa[PF ? 2 : 1][NT], fx[PF ? 2 : 1][2 * NC];
+    u32x4 fa[PF ? 2 : 1][NT], fx[PF ? 2 : 1][NP * NC];
     auto read = [&](const int slot, const int r) {
         const u32x4* p = &sm[slot * NF * 64 + lane];
 #pragma unroll
-        for (int b = 0; b < 2 * NC; ++b) fx[r][b] = p[(FT + rw * 2 * NC + b) * 64];
+        for (int b = 0; b < NP * NC; ++b) fx[r][b] = p[(FT + rw * NP * NC + b) * 64];
 #pragma unroll
         for (int s = 0; s < NT; ++s) fa[r][s] = p[(fw * NT + s) * 64];
     };
@@ -333,14 +334,14 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
 #pragma unroll
         for (int s = 0; s < NT; ++s)
 #pragma unroll
-            for (int pl = 0; pl < 2; ++pl)
+            for (int pl = 0; pl < NP; ++pl)
 #pragma unroll
                 for (int cc = 0; cc < NC; ++cc) {
-                    const int c = ((2 * s + pl) & 1) ? NC - 1 - cc : cc;
-                    mma16<BF16>(acc[s][c], fa[r][s], fx[r][2 * c + pl]);
+                    const int c = ((NP * s + pl) & 1) ? NC - 1 - cc : cc;
+                    mma16<T>(acc[s][c], fa[r][s], fx[r][NP * c + pl]);
                 }
     };
-    constexpr int NM = 2 * NT * NC, ND = NT + 2 * NC, TAIL = NM > 16 ? 6 : 0;     // products and fragment reads per stage
+    constexpr int NM = NP * NT * NC * (sizeof(typename T::elem) == 4 ? 4 : 1), ND = NT + NP * NC, TAIL = NM > 16 ? 6 : 0;     // products and fragment reads per stage
     auto stage = [&](const int slot, const int r) {
         wait_vm<(S - 2) * L, true>();
         __builtin_amdgcn_s_barrier();
@@ -393,7 +394,7 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
     bool tval[NA];
 #pragma unroll
     for (int s = 0; s < NA; ++s) { tile[s] = (fb * FW + fw) * NA + s; tval[s] = tile[s] < a.n_tiles; }
-    pf_epilogue<BF16, EPI, NA, NT, NC>(a, acc, tile, tval, rb * RC + rw * NC, ks, lane);
+    pf_epilogue<T, EPI, NA, NT, NC>(a, acc, tile, tval, rb * RC + rw * NC, ks, lane);
 }
 
 // ---------------------------------------------------------------- rows of a block: embedding, residual add + cosine tap

@@ -107,3 +107,25 @@ def test_weights_survive_prompt_blocks_laid_over_the_staging_region():
     b = eng.prefill(toks, want_logits=True)
     assert a[0] == b[0] and np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
     eng.close()
+
+
+F32_RAGGED = si.Shape("f32-ragged", 2, 176, 6, 3, 32, 272, 320, si.DT_F32, 8, 8, 2)
+
+
+@pytest.mark.parametrize("n", [17, 33, 100, 300, 513])
+def test_fp32_tile_shapes_give_the_same_bits(n):
+    """The ring kernel on fp32 weights (k-blocks of 16, one plane): all tile shapes against the four-wave kernel bit for bit, and
+    that against the chunked pass."""
+    toks = si.prompt(n, n, F32_RAGGED.vocab)
+    W = list(si.all_tensors(F32_RAGGED, 2, 0.1))
+    got = []
+    for tune in ("pf_qkv=4,1,2;pf_o=4,4,2;pf_gu=4,1,2;pf_down=4,4,2", None, "pf_ring=0,4", "pf_ring=1,4", "pf_ring=2,4", "pf_ring=3,4", "pf_ring=4,4",
+                 "pf_ring=8,4", "pf_ring=11,4", "pf_ring=14,4"):
+        eng = asd.Engine(asd.make_config(F32_RAGGED, n + 16, debug_tune=tune)).load(W)
+        got.append((*eng.prefill(toks, want_logits=True), *eng.get_kv(1, 0, n)))
+        if tune is None:
+            ref = eng.prefill(toks, want_logits=True, chunked=True)
+        eng.close()
+    for g in got[1:]:
+        assert all(np.array_equal(x, y) for x, y in zip(got[0], g))
+    assert np.abs(got[0][1] - ref[1]).max() < COS_TOL and rel_err(got[0][2], ref[2]) < TOL[si.DT_F32]
