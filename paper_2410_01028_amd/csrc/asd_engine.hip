@@ -652,9 +652,10 @@ void build_pass(asd_engine* e, int M, int pos_off, const uint8_t* mask, int ctx_
     push(OP_FINISH, ASD_K_FINISH, 1, 0);
 }
 
-// Run a pass as one launch per step.
+// Run a pass as one launch per step.  embedded: the launch before left this pass's embedding; embed_next: the pass is a draft
+// step (FIN_DRAFT) and its last launch embeds the drafted token for the step that follows under the same mask.
 int launch_steps(asd_engine* e, const std::vector<PassOp>& ops, const int32_t* d_tokens, int M, const uint8_t* mask,
-                 Profiler* profiler, int fin_mode, int fin_arg, const PassOut& out) {
+                 Profiler* profiler, int fin_mode, int fin_arg, const PassOut& out, bool embedded = false, bool embed_next = false) {
     const asd_config& c = e->c;
     Prof pr{profiler, e->stream};
     const int RS = row_stride(e, M);
@@ -663,6 +664,7 @@ int launch_steps(asd_engine* e, const std::vector<PassOp>& ops, const int32_t* d
         bool ok = true;
         switch (op.type) {
             case OP_EMBED:
+                if (embedded) break;
                 if (c.dtype == ASD_DT_BF16)
                     embed_kernel<BF16><<<dim3(EMBED_SPLIT, M), EMBED_THREADS, 0, e->stream>>>((const uint16_t*)e->embed, d_tokens, c.d_model, c.vocab, e->st,
                         next_gain(e, mask, -1), e->xres, e->xb, (size_t)e->KBd * 64 * e->KE, RS, out.part);
@@ -677,11 +679,21 @@ int launch_steps(asd_engine* e, const std::vector<PassOp>& ops, const int32_t* d
             case OP_LM: ok = launch_gemm<EPI_LM>(e, e->g_lm, op.g); break;
             case OP_ATTN: launch_attn(e, op.t); break;
             case OP_FINISH:
+                if (fin_mode == FIN_SKIP) break;
                 if (out.d_cos) {
                     MaskBits mb{};
                     for (int j = 0; j < 2 * c.n_layers; ++j) if (mask && mask[j]) mb.w[j >> 5] |= 1u << (j & 31);
                     finish_cos_kernel<<<1, 64 * M, 0, e->stream>>>((const AmaxCand*)out.amax_part, e->g_lm.grid, M, c.vocab, out.argmax, e->st, out.cos_acc,
                                                                    2 * c.n_layers, mb, out.d_cos);
+                    break;
+                }
+                if (embed_next) {
+                    if (c.dtype == ASD_DT_BF16)
+                        finish_embed_kernel<BF16><<<EMBED_SPLIT, EMBED_THREADS, 0, e->stream>>>((const AmaxCand*)out.amax_part, e->g_lm.grid, out.argmax, fin_arg, e->tokbuf,
+                            (const uint16_t*)e->embed, c.d_model, c.vocab, e->st, next_gain(e, mask, -1), e->xres, e->xb, (size_t)e->KBd * 64 * e->KE, out.part);
+                    else
+                        finish_embed_kernel<F32><<<EMBED_SPLIT, EMBED_THREADS, 0, e->stream>>>((const AmaxCand*)out.amax_part, e->g_lm.grid, out.argmax, fin_arg, e->tokbuf,
+                            (const float*)e->embed, c.d_model, c.vocab, e->st, next_gain(e, mask, -1), e->xres, e->xb, (size_t)e->KBd * 64 * e->KE, out.part);
                     break;
                 }
                 finish_kernel<<<1, 64 * M, 0, e->stream>>>((const AmaxCand*)out.amax_part, e->g_lm.grid, M, c.vocab, out.argmax, fin_mode, fin_arg,
@@ -697,11 +709,12 @@ int launch_steps(asd_engine* e, const std::vector<PassOp>& ops, const int32_t* d
 }
 
 int enqueue_forward(asd_engine* e, const int32_t* d_tokens, int M, int pos_off, const uint8_t* mask, int nc,
-                    Profiler* profiler, int ctx_for_bytes, int fin_mode = FIN_NONE, int fin_arg = 0, const PassOut* out_or_null = nullptr) {
+                    Profiler* profiler, int ctx_for_bytes, int fin_mode = FIN_NONE, int fin_arg = 0, const PassOut* out_or_null = nullptr,
+                    bool embedded = false, bool embed_next = false) {
     const PassOut out = out_or_null ? *out_or_null : engine_out(e);
     std::vector<PassOp> ops;
     build_pass(e, M, pos_off, mask, ctx_for_bytes, nc, out, ops);
-    return launch_steps(e, ops, d_tokens, M, mask, profiler, fin_mode, fin_arg, out);
+    return launch_steps(e, ops, d_tokens, M, mask, profiler, fin_mode, fin_arg, out, embedded, embed_next);
 }
 
 bool weights_ready(asd_engine* e) {
@@ -1526,7 +1539,7 @@ int asd_prefill_chunked(asd_engine* e, const int32_t* tokens, int32_t n, int32_t
 
 static int enqueue_drafts(asd_engine* e, int kk, const uint8_t* mask, int nc, int32_t ctx) {
     for (int j = 0; j < kk; ++j) {
-        int rc = enqueue_forward(e, e->tokbuf + j, 1, j, mask, nc, nullptr, ctx, FIN_DRAFT, j);
+        int rc = enqueue_forward(e, e->tokbuf + j, 1, j, mask, nc, nullptr, ctx, FIN_DRAFT, j, nullptr, j > 0, j + 1 < kk);
         if (rc) return rc;
     }
     return ASD_OK;
@@ -1572,14 +1585,14 @@ static void launch_sample_plain(asd_engine* e, const SampleArgs& sa, int row, in
 // one sampled draft / verify / accept cycle, enqueue only
 static int enqueue_sampled_drafts(asd_engine* e, int kk, const uint8_t* mask, int nc, int32_t ctx, const SampleArgs& sa) {
     for (int j = 0; j < kk; ++j) {
-        int rc = enqueue_forward(e, e->tokbuf + j, 1, j, mask, nc, nullptr, ctx, FIN_NONE, 0);
+        int rc = enqueue_forward(e, e->tokbuf + j, 1, j, mask, nc, nullptr, ctx, FIN_SKIP, 0);
         if (rc) return rc;
         launch_sample_draft(e, sa, j);
     }
     return ASD_OK;
 }
 static int enqueue_sampled_verify(asd_engine* e, int kk, int nc, int32_t ctx, const SampleArgs& sa) {
-    int rc = enqueue_forward(e, e->tokbuf, kk + 1, 0, nullptr, nc, nullptr, ctx, FIN_NONE, 0);
+    int rc = enqueue_forward(e, e->tokbuf, kk + 1, 0, nullptr, nc, nullptr, ctx, FIN_SKIP, 0);
     if (rc) return rc;
     launch_sample_accept(e, sa, kk);
     return ASD_OK;

@@ -396,9 +396,8 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, const int bid, Gem
             if (best.v != -INFINITY)
                 for (int s = 0; s < NA; ++s)
                     for (int nl = 0; nl < 16; ++nl) se += __expf(epi_a[s * 256 + tid * 16 + nl] - best.v);
-            a.amax_part[(size_t)bid * 16 + tid].v = best.v;
-            a.amax_part[(size_t)bid * 16 + tid].i = best.i;
-            a.amax_part[(size_t)bid * 16 + tid].s = se;
+            best.s = se;
+            if (tid < a.M) a.amax_part[(size_t)bid * 16 + tid] = best;
         }
     }
 }

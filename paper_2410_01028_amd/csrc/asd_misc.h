@@ -10,12 +10,13 @@
 #define EMBED_THREADS 256
 template <class T>
 __device__ __forceinline__ void embed_block(const typename T::elem* E, const int32_t* tokens, int d, int vocab, DevState* st, const float* g_first,
-                                            float* xres, void* xb, size_t xb_plane, int rs, float* part, const int sp, const int m, float* red) {
+                                            float* xres, void* xb, size_t xb_plane, int rs, float* part, const int sp, const int m, float* red,
+                                            const int token = 0) {
     using El = typename T::elem;
     const int tid = threadIdx.x, nt = EMBED_THREADS;
     // a token id that is not a row of the table (possible when the ids come from device memory the host never saw)
     // must not become an address: it reads row 0 and raises the state's error bit
-    int tok = tokens[m];
+    int tok = tokens ? tokens[m] : token;
     if ((unsigned)tok >= (unsigned)vocab) {
         tok = 0;
         if (tid == 0 && sp == 0) __hip_atomic_fetch_or(&st->err, (int)DEV_ERR_TOKEN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -82,16 +83,59 @@ __global__ __launch_bounds__(256) void to_host_kernel(const ToHost a) {
 
 // After the LM head: pick each row's greedy token from the per-workgroup candidates (largest
 // logit, lowest index on ties), then, by mode,
-//   FIN_NONE    nothing more;
+//   FIN_NONE    nothing more (FIN_SKIP: not even that, the launch is left out: a sampled pass draws its own tokens);
 //   FIN_DRAFT   draft step j: the drafted token becomes row j+1 of the coming verification pass, and its
 //               softmax probability goes to the decoding state (what an adaptive draft exit looks at);
 //   FIN_ACCEPT  accept / rollback after a verification pass over rows [last, d_1..d_kk], g_i = the
 //               full model's choice after row i: a = length of the longest prefix with
 //               d_{i+1} == g_i; emit d_1..d_a, g_a; the cache keeps pos + a + 1 positions; g_a is
 //               the next cycle's first row.
-enum { FIN_NONE = 0, FIN_DRAFT = 1, FIN_ACCEPT = 2 };
-struct AmaxCand { float v; int32_t i; float s; float pad; };
+enum { FIN_NONE = 0, FIN_DRAFT = 1, FIN_ACCEPT = 2, FIN_SKIP = 3 };
+struct AmaxCand { float v; int32_t i; float s; float pad; };      // (the LM-head kernel's AmaxPart)
+__device__ __forceinline__ AmaxCand amax_load(const AmaxCand* p) {
+    const float4 x = *(const float4*)p;
+    return AmaxCand{x.x, __float_as_int(x.y), x.z, 0.f};
+}
 __device__ __forceinline__ bool amax_better(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
+// One wave: the greedy token of a row from its P candidates (16 apart), and, with conf, the softmax probability of that token
+// (1 / sum_i exp(logit_i - max), from the per-workgroup sums).  A row without a finite maximum (NaN weights) leaves no candidate:
+// its token must still be a valid id, because the next pass uses it as an address into the embedding table.
+__device__ __forceinline__ int row_winner(const AmaxCand* cand, int P, int V, DevState* st, bool flag, float* conf) {
+    const int lane = threadIdx.x & 63;
+    float v = -INFINITY; int idx = 0x7fffffff;
+    // eight candidates per lane and trip, all requested before the first is looked at (one memory round trip per
+    // trip instead of one per candidate); a lane past the end re-reads the last candidate, which changes nothing
+    for (int p0 = lane; p0 < P; p0 += 64 * 8) {
+        AmaxCand c[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c[u] = amax_load(cand + (size_t)(p0 + 64 * u < P ? p0 + 64 * u : P - 1) * 16);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (amax_better(c[u].v, c[u].i, v, idx)) { v = c[u].v; idx = c[u].i; }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(v, o); const int oi = __shfl_xor(idx, o);
+        if (amax_better(ov, oi, v, idx)) { v = ov; idx = oi; }
+    }
+    if ((unsigned)idx >= (unsigned)V) {
+        idx = 0;
+        if (lane == 0 && flag) __hip_atomic_fetch_or(&st->err, (int)DEV_ERR_LOGITS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (conf) {
+        float se = 0.f;
+        for (int p0 = lane; p0 < P; p0 += 64 * 8) {          // ascending p per lane; requests batched
+            AmaxCand c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c[u] = amax_load(cand + (size_t)(p0 + 64 * u < P ? p0 + 64 * u : P - 1) * 16);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (p0 + 64 * u < P) se += c[u].s * __expf(c[u].v - v);
+        }
+        for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o);
+        *conf = 1.f / se;
+    }
+    return idx;
+}
 // one workgroup; wave w handles rows w, w + (waves), ...; candidates are [workgroup][16 rows]
 __device__ __forceinline__ void finish_block(const AmaxCand* cand, int P, int M, int V, int32_t* argmax, int mode, int j_or_kk,
                                              DevState* st, int32_t* tokbuf, int32_t* out, int* win) {
@@ -104,49 +148,12 @@ __device__ __forceinline__ void finish_block(const AmaxCand* cand, int P, int M,
         st_emitted = st->emitted; st_target = st->target;
     }
     for (int m = tid >> 6; m < M; m += nw) {
-        float v = -INFINITY; int idx = 0x7fffffff;
-        // eight candidates per lane and trip, all requested before the first is looked at (one memory round trip per
-        // trip instead of one per candidate); a lane past the end re-reads the last candidate, which changes nothing
-        for (int p0 = lane; p0 < P; p0 += 64 * 8) {
-            float cv[8]; int ci[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int p = p0 + 64 * u < P ? p0 + 64 * u : P - 1;
-                cv[u] = cand[(size_t)p * 16 + m].v;
-                ci[u] = cand[(size_t)p * 16 + m].i;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (amax_better(cv[u], ci[u], v, idx)) { v = cv[u]; idx = ci[u]; }
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            const float ov = __shfl_xor(v, o); const int oi = __shfl_xor(idx, o);
-            if (amax_better(ov, oi, v, idx)) { v = ov; idx = oi; }
-        }
-        // a row without a finite maximum (NaN weights) leaves no candidate: its token must still be a valid id,
-        // because the next pass uses it as an address into the embedding table
-        if ((unsigned)idx >= (unsigned)V) {
-            idx = 0;
-            if (lane == 0) __hip_atomic_fetch_or(&st->err, (int)DEV_ERR_LOGITS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        if (lane == 0) { win[m] = idx; argmax[m] = idx; }
-        if (mode == FIN_DRAFT && m == 0) {
-            // confidence of the drafted token: 1 / sum_i exp(logit_i - max), from the per-workgroup sums
-            float se = 0.f;
-            for (int p0 = lane; p0 < P; p0 += 64 * 8) {          // ascending p per lane, as before; requests batched
-                float cs[8], cv[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int p = p0 + 64 * u < P ? p0 + 64 * u : P - 1;
-                    cs[u] = cand[(size_t)p * 16].s;
-                    cv[u] = cand[(size_t)p * 16].v;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (p0 + 64 * u < P) se += cs[u] * __expf(cv[u] - v);
-            }
-            for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o);
-            if (lane == 0) st->conf = 1.f / se;
+        float conf;
+        const bool first_draft = mode == FIN_DRAFT && m == 0;
+        const int idx = row_winner(cand + m, P, V, st, true, first_draft ? &conf : nullptr);
+        if (lane == 0) {
+            win[m] = idx; argmax[m] = idx;
+            if (first_draft) st->conf = conf;
         }
     }
     __syncthreads();
@@ -170,6 +177,28 @@ __global__ __launch_bounds__(1024) void finish_kernel(const AmaxCand* cand, int 
                                                       DevState* st, int32_t* tokbuf, int32_t* out) {
     __shared__ int win[16];
     finish_block(cand, P, M, V, argmax, mode, j_or_kk, st, tokbuf, out, win);
+}
+
+// Between two draft steps: finish_kernel (FIN_DRAFT, one row, draft j) and the embedding of the token it finds, in one launch of
+// EMBED_SPLIT workgroups, each of which looks through the candidates for itself (one launch less per draft
+// step; tiny shape: 2.8 + 2.9 us and the gap between them -> 3.5 us).
+template <class T>
+__global__ __launch_bounds__(EMBED_THREADS) void finish_embed_kernel(const AmaxCand* cand, int P, int32_t* argmax, int j, int32_t* tokbuf,
+                                                                     const typename T::elem* E, int d, int vocab, DevState* st, const float* g_first, float* xres,
+                                                                     void* xb, size_t xb_plane, float* part) {
+    __shared__ float red[EMBED_THREADS];
+    __shared__ int win;
+    const bool writer = blockIdx.x == 0;
+    if (threadIdx.x < 64) {
+        float conf;
+        const int idx = row_winner(cand, P, vocab, st, writer, writer ? &conf : nullptr);
+        if (threadIdx.x == 0) {
+            win = idx;
+            if (writer) { argmax[0] = idx; tokbuf[j + 1] = idx; st->conf = conf; }
+        }
+    }
+    __syncthreads();
+    embed_block<T>(E, nullptr, d, vocab, st, g_first, xres, xb, xb_plane, 1, part, blockIdx.x, 0, red, win);
 }
 
 // one bit per sublayer of a skip mask, passed to a kernel by value

@@ -142,10 +142,12 @@ __device__ __forceinline__ void tile_sums(const RowTiles<TILES>& r, F w, TileSum
 // softmax statistics of a logit row at temperature 1/inv_T: the maximum, and Z = sum exp((l - max) * inv_T) of whose terms
 // the sums are left in s
 template <int TILES>
-__device__ __forceinline__ void row_stats(const RowTiles<TILES>& r, float inv_T, float* mx, double* Z, TileSums<TILES>& s, double* red) {
+__device__ __forceinline__ void row_stats(const RowTiles<TILES>& r, float inv_T, float* mx, double* Z, TileSums<TILES>& s, double* red, DevState* st) {
     float m = -INFINITY;
     r.each([&](int, float4 x) { m = fmaxf(fmaxf(m, fmaxf(x.x, x.y)), fmaxf(x.z, x.w)); });
     const float mxv = blk_max(m, red);
+    // a row without a maximum (every logit NaN or -inf) is reported as the greedy pass reports it
+    if (mxv == -INFINITY && threadIdx.x == 0) __hip_atomic_fetch_or(&st->err, (int)DEV_ERR_LOGITS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     tile_sums(r, [&](int, const float4& x) { return softmax_weights(x, mxv, inv_T); }, s);
     *mx = mxv;
     *Z = blk_sum(s.all, red);
@@ -232,7 +234,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_draft_kernel(const Samp
     float mx; double Z;
     const float inv_T = a.inv_T;
     TileSums<TILES> s;
-    row_stats(r, inv_T, &mx, &Z, s, red);
+    row_stats(r, inv_T, &mx, &Z, s, red, a.st);
     const int tok = max(0, blk_sample(r, [&](int, const float4& x) { return softmax_weights(x, mx, inv_T); }, s, sample_uniform(a.stream, index, 0), red, ired));
     if (threadIdx.x == 0) { a.tokbuf[j + 1] = tok; a.qstat[2 * j] = (double)mx; a.qstat[2 * j + 1] = Z; }
 }
@@ -247,7 +249,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_plain_kernel(const Samp
     float mx; double Z;
     const float inv_T = a.inv_T;
     TileSums<TILES> s;
-    row_stats(r, inv_T, &mx, &Z, s, red);
+    row_stats(r, inv_T, &mx, &Z, s, red, a.st);
     const int tok = max(0, blk_sample(r, [&](int, const float4& x) { return softmax_weights(x, mx, inv_T); }, s, sample_uniform(a.stream, index, 2), red, ired));
     if (threadIdx.x == 0) a.tokbuf[0] = tok;
 }
@@ -260,7 +262,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_stats_kernel(const Samp
     r.load(a.logits + (size_t)blockIdx.x * a.V, a.V);
     float mx; double Z;
     TileSums<TILES> s;
-    row_stats(r, a.inv_T, &mx, &Z, s, red);
+    row_stats(r, a.inv_T, &mx, &Z, s, red, a.st);
     if (threadIdx.x == 0) { a.pstat[2 * blockIdx.x] = (double)mx; a.pstat[2 * blockIdx.x + 1] = Z; }
 }
 
