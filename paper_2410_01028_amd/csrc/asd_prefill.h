@@ -286,8 +286,8 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
     const int kb0 = (int)((long)ks * a.KB / a.ksplit), n = (int)((long)(ks + 1) * a.KB / a.ksplit) - kb0;
 
     // This wave's requests of a stage: fragments w, w + W, ... of the stage's FT weight and NP RC chunk fragments.  A tile
-    // beyond the last re-reads the last one, a chunk beyond the rows holds whatever it holds: their products are never
-    // looked at.
+    // beyond the last re-reads the last one, a chunk beyond the block's last re-reads that one (the buffers end with it where
+    // the block is full and RC does not divide it): their products are never looked at.
     const char* src[L];
     int64_t step[L];
     int dst[L];                                                     // fragment of slot 0
@@ -305,7 +305,8 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
             src[i] = (const char*)(up ? a.W2 : a.W) + ((int64_t)t * a.w_tile_stride + (int64_t)kb0 * a.w_kb_stride) * 1024;
             step[i] = a.w_kb_stride * 1024;
         } else {
-            src[i] = (const char*)a.X + ((int64_t)(x % NP) * a.x_plane + (int64_t)(rb * RC + x / NP) * a.x_chunk) * 16 + (int64_t)kb0 * 1024;
+            const int chunk = min(rb * RC + x / NP, (a.rows + 15) / 16 - 1);
+            src[i] = (const char*)a.X + ((int64_t)(x % NP) * a.x_plane + (int64_t)chunk * a.x_chunk) * 16 + (int64_t)kb0 * 1024;
             step[i] = 1024;
         }
     }
