@@ -365,7 +365,7 @@ def main():
         planes = 2 if shape.dtype else 1
         out["prefill"]["roofline"] = {"bound": "mfma", "achieved": round(tf, 1), "peak": 2500.0 if shape.dtype else 157.3, "unit": "TFLOP/s",
                                       "frac": round(tf / (2500.0 if shape.dtype else 157.3), 4),
-                                      "kernel": "pf_gemm_kernel<PF_GU> (prompt-block gate/up projection + SiLU*mul)",
+                                      "kernel": "pf_ring_kernel<BF16, PF_GU> (prompt-block gate/up projection + SiLU*mul)",
                                       "flops_per_launch": gu["flops"] / gu["launches"], "avg_launch_us": round(gu["ms"] / gu["launches"] * 1e3, 2),
                                       "matrix_core_issue_frac": round(tf * planes / (2500.0 if shape.dtype else 157.3), 4)}
 

@@ -269,8 +269,8 @@ int asd_check(asd_engine* e);
  * sublayer over the n rows (cos_out [2L], optional) and the logits of the last row
  * (last_logits [vocab], optional).  The ACS is kept in the engine for a following
  * asd_decode with mask_mode 0.  Prompts longer than max_rows are processed in blocks
- * of up to 512 rows, layer by layer, with large-M matrix-core contractions (every
- * weight is read once per block); shorter ones as one pass of the decode kernels.
+ * of up to 2048 rows (as many as the arena has room for, never fewer than 512), layer by
+ * layer, with large-M matrix-core contractions (every weight is read once per block); shorter ones as one pass of the decode kernels.
  * asd_prefill_chunked always takes the decode kernels, max_rows rows at a time (the
  * same results up to rounding; kept for cross-checks and as the reference for timing).
  * All pointers are host memory.

@@ -587,8 +587,9 @@ __global__ __launch_bounds__(256, sizeof(typename T::elem) == 4 && H == 128 ? 1 
 }
 
 // The same attention for blocks with enough rows to give every compute unit a workgroup (bf16).  pf_attn_kernel above loads
-// every K / V^T fragment per wave and 32 rows, which is what fills its time (a compute unit takes in about 45-57 KiB per
-// us), and needs a SIMD's whole register file per wave, so that nothing runs beside a wave's softmax.  Here a workgroup
+// every K / V^T fragment per wave and 16 rows, which is what would fill its time here (a compute unit takes in about 45-57
+// KiB per us; with 32 rows per wave the loads halve, but a wave needs a SIMD's whole register file and nothing runs beside
+// its softmax: that is the first figure of each pair below).  Here a workgroup
 // takes 128 rows, 32 to each of four waves, all walking the keys together: a chunk's fragments come into LDS once
 // (direct-to-LDS loads) for four waves' products, and two workgroups fit on a compute unit, one's products beside
 // the other's exponentials.  The LDS ring holds five half-chunks (K, V^T, K, ...: 16 KiB each at head dim 128, so two rings

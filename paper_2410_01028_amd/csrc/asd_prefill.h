@@ -7,9 +7,10 @@
 // one (chunk, k-block) fragment is one contiguous KiB that a wave loads with one instruction, and the decode
 // attention kernel runs unchanged on a chunk.
 //
-// pf_ring_kernel (bf16): eight waves, a tile of up to 24 weight tiles x 8 chunks (16 x 16 for long blocks), both operands
-// brought into an LDS ring by direct-to-LDS loads; see its own comment.
-// pf_gemm_kernel (fp32, short bf16 blocks): a workgroup of NW waves owns NW*NA weight tiles (16 output features each) x NC chunks of
+// pf_ring_kernel: a tile of up to 24 weight tiles x 8 chunks (16 x 16 for long blocks) per workgroup, both operands brought
+// into an LDS ring by direct-to-LDS loads; see its own comment.  The kernel and tile of a launch are the ones with the
+// smallest estimated time.
+// pf_gemm_kernel (where the estimate of the ring's tiles is no better): a workgroup of NW waves owns NW*NA weight tiles (16 output features each) x NC chunks of
 // rows and, with a K split, one slice of K.  Per k-block the waves stage the NC chunks' activation fragments
 // in LDS (double buffered, one barrier per k-block); each wave streams its own NA weight fragments from
 // global memory and feeds NA*NC accumulators.  Workgroups that share weights (same features, other rows)
@@ -243,7 +244,7 @@ __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const
     pf_epilogue<T, EPI, NA, NAT, NC>(a, acc, tile, tval, chunk0, ks, lane);
 }
 
-// ---- the eight-wave kernel of the bf16 prompt GEMMs
+// ---- the LDS ring kernel of the prompt GEMMs
 // What bounds the large bf16 prompt GEMMs is the card's power, not the issue of matrix-core work: a loop of matrix-core
 // instructions on random operands in registers runs at 2.1 GHz and 2.1 PFLOP/s, and every byte moved per product takes its
 // share of the clock.  So both operands are read once per workgroup into LDS (no fragment passes through a register on

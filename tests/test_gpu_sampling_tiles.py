@@ -35,3 +35,19 @@ def test_draws_at_the_edges_of_the_tiles(V):
     assert compared >= 12
     for e in engines:
         e.close()
+
+
+@pytest.mark.parametrize("drafts", [0, 3])
+def test_sampled_decoding_reports_rows_without_a_maximum(drafts):
+    """Sampled passes run without the greedy finish: the sampling kernels report such rows in its place."""
+    s = si.SHAPES["tiny"]
+    eng = asd.Engine(asd.make_config(s, 128))
+    eng.init_synthetic(0)
+    first = eng.prefill([1, 2, 3, 4])[0]
+    kw = dict(temperature=0.8, seed=1, fixed_mask=np.zeros(2 * s.n_layers, np.uint8))
+    eng.decode(first, 4, drafts, **kw)
+    eng.set_weight(si.T_FINAL_NORM, 0, np.full(s.d_model, np.nan, np.float32))
+    with pytest.raises(asd.AsdError) as ei:
+        eng.decode(first, 4, drafts, **kw)
+    assert ei.value.code == asd.E_STATE
+    eng.close()
