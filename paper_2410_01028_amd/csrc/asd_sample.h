@@ -153,10 +153,44 @@ __device__ __forceinline__ void row_stats(const RowTiles<TILES>& r, float inv_T,
     *Z = blk_sum(s.all, red);
 }
 
+// ---- where a point of a running sum falls (plain functions: the CPU tests compile and run them too)
+#define SAMPLE_HD __host__ __device__ __forceinline__
+// Intervals laid end to end from `run`, visited in order: the first whose end exceeds t, and the running sum before it.  Where
+// rounding leaves none (a level's sums are added in another order than the level above added them), the last interval
+// with a positive sum, and a running sum that stays below every t: all levels inside it then take their last one as well.
+struct IntervalSearch {
+    double t, run, before;
+    int hit, last;
+    SAMPLE_HD IntervalSearch(double t_, double run_) : t(t_), run(run_), before(-(double)INFINITY), hit(-1), last(0) {}
+    SAMPLE_HD void visit(int i, double sum) {
+        if (hit < 0 && t < run + sum) { hit = i; before = run; }
+        if (sum > 0.0) last = i;
+        run += sum;
+    }
+    SAMPLE_HD int index() const { return hit >= 0 ? hit : last; }
+};
+// The lane of a tile: over: lanes whose inclusive running sum exceeds t; some: lanes with a positive sum.  The scan adds in
+// a different order for every lane, so `over` may begin at a lane without any weight: only lanes with some are asked.
+SAMPLE_HD int sample_lane(uint64_t over, uint64_t some) {
+    over &= some;
+    return over ? __builtin_ctzll(over) : some ? 63 - __builtin_clzll(some) : 0;
+}
+// The value of a lane's four, z = running sum before them: the first that carries it past t, else the last positive one
+SAMPLE_HD int sample_of_four(const float (&e)[4], double z, double t) {
+    int pick = -1, pos = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        z += (double)e[j];
+        if (pick < 0 && e[j] > 0.f && z > t) pick = j;
+        if (e[j] > 0.f) pos = j;
+    }
+    return pick >= 0 ? pick : pos;
+}
+
 // Inverse-CDF draw from the non-negative weights w(index, values) of a row's tiles, whose sums are in s: an index whose interval of
 // the running sum holds u * total (the smallest index whose running sum exceeds it, sums taken tile by tile); where
-// rounding leaves none, the last index with a positive weight.  Every thread returns the drawn index, or -1 if no
-// weight is positive.
+// rounding leaves none at some level (wave, tile, lane, value), the last positive one of that level.  The drawn index never has
+// weight zero.  Every thread returns the drawn index, or -1 if no weight is positive.
 template <int TILES, class F>
 __device__ __forceinline__ int blk_sample(const RowTiles<TILES>& r, F w, const TileSums<TILES>& s, double u, double* red, int* ired) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -166,54 +200,30 @@ __device__ __forceinline__ int blk_sample(const RowTiles<TILES>& r, F w, const T
     for (int i = 0; i < SAMPLE_WAVES; ++i) total += red[i];
     if (!(total > 0.0)) return -1;
     const double t = u * total;
-    // the wave whose interval holds t, else the last one with any weight
-    int mine = -1, last = 0;
-    double base = 0.0, cum = 0.0;
+    IntervalSearch waves(t, 0.0);
 #pragma unroll
-    for (int i = 0; i < SAMPLE_WAVES; ++i) {
-        const double v = red[i];
-        if (mine < 0 && t < cum + v) { mine = i; base = cum; }
-        if (v > 0.0) last = i;
-        cum += v;
-    }
-    if (mine < 0) { mine = last; base = cum; }
-    if (wave == mine) {
-        // likewise the tile, c = running sum before it
-        double c = base, run = base;
-        int kt = -1, kl = 0;
-        auto visit = [&](int k, double sum) {
-            if (kt < 0 && t < run + sum) { kt = k; c = run; }
-            if (sum > 0.0) kl = k;
-            run += sum;
-        };
+    for (int i = 0; i < SAMPLE_WAVES; ++i) waves.visit(i, red[i]);
+    if (wave == waves.index()) {
+        IntervalSearch tiles(t, waves.before);
         if constexpr (TILES > 0) {
             double sum[TILES];
 #pragma unroll
             for (int k = 0; k < TILES; ++k) sum[k] = wave_sum(s.tile[k]);
 #pragma unroll
-            for (int k = 0; k < TILES; ++k) visit(k, sum[k]);
+            for (int k = 0; k < TILES; ++k) tiles.visit(k, sum[k]);
         } else {
-            for (int k = 0; k < r.n; ++k) visit(k, wave_sum(lane_sum(w(r.index(k), r.at(k)))));
+            for (int k = 0; k < r.n; ++k) tiles.visit(k, wave_sum(lane_sum(w(r.index(k), r.at(k)))));
         }
-        if (kt < 0) { kt = kl; c = run; }
+        const int kt = tiles.index();
         const float4 q = w(r.index(kt), r.tile(kt));
         const double sl = lane_sum(q);
         double incl = sl;                                             // running sum over the lanes
         for (int o = 1; o < 64; o <<= 1) { const double up = __shfl_up(incl, o); if (lane >= o) incl += up; }
         const double before = __shfl_up(incl, 1);
-        const unsigned long long over = __ballot(t < c + incl), some = __ballot(sl > 0.0);
-        const int hit = over ? __ffsll((long long)over) - 1 : some ? 63 - __clzll((long long)some) : 0;
+        const int hit = sample_lane(__ballot(t < tiles.before + incl), __ballot(sl > 0.0));
         if (lane == hit) {
             const float e[4] = {q.x, q.y, q.z, q.w};
-            double z = c + (lane ? before : 0.0);
-            int pick = -1, pos = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                z += (double)e[j];
-                if (pick < 0 && z > t) pick = j;
-                if (e[j] > 0.f) pos = j;
-            }
-            ired[0] = r.index(kt) + (pick >= 0 ? pick : pos);         // (adding the lane's values one by one may fall short)
+            ired[0] = r.index(kt) + sample_of_four(e, tiles.before + (lane ? before : 0.0), t);
         }
     }
     __syncthreads();
