@@ -187,10 +187,28 @@ SAMPLE_HD int sample_of_four(const float (&e)[4], double z, double t) {
     return pick >= 0 ? pick : pos;
 }
 
+// The last index with a positive weight, or -1 (every thread)
+template <int TILES, class F>
+__device__ __forceinline__ int blk_last_positive(const RowTiles<TILES>& r, F w, double* red) {
+    int best = -1;
+#pragma unroll 1
+    for (int k = 0; k < r.n; ++k) {
+        const float4 q = w(r.index(k), r.at(k));
+        const int i = r.index(k), j = q.w > 0.f ? 3 : q.z > 0.f ? 2 : q.y > 0.f ? 1 : q.x > 0.f ? 0 : -1;
+        if (j >= 0) best = i + j;
+    }
+    for (int o = 32; o > 0; o >>= 1) best = max(best, __shfl_xor(best, o));
+    share_waves(best, (int*)red);
+#pragma unroll
+    for (int i = 0; i < SAMPLE_WAVES; ++i) best = max(best, ((int*)red)[i]);
+    return best;
+}
+
 // Inverse-CDF draw from the non-negative weights w(index, values) of a row's tiles, whose sums are in s: an index whose interval of
 // the running sum holds u * total (the smallest index whose running sum exceeds it, sums taken tile by tile); where
 // rounding leaves none at some level (wave, tile, lane, value), the last positive one of that level.  The drawn index never has
-// weight zero.  Every thread returns the drawn index, or -1 if no weight is positive.
+// weight zero.  A row with a NaN among its weights has no running sum: its last index with a positive weight.  Every thread
+// returns the drawn index, or -1 if no weight is positive.
 template <int TILES, class F>
 __device__ __forceinline__ int blk_sample(const RowTiles<TILES>& r, F w, const TileSums<TILES>& s, double u, double* red, int* ired) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -198,7 +216,7 @@ __device__ __forceinline__ int blk_sample(const RowTiles<TILES>& r, F w, const T
     double total = 0.0;
 #pragma unroll
     for (int i = 0; i < SAMPLE_WAVES; ++i) total += red[i];
-    if (!(total > 0.0)) return -1;
+    if (!(total > 0.0)) return total == 0.0 ? -1 : blk_last_positive(r, w, red);
     const double t = u * total;
     IntervalSearch waves(t, 0.0);
 #pragma unroll

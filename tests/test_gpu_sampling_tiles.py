@@ -51,3 +51,28 @@ def test_sampled_decoding_reports_rows_without_a_maximum(drafts):
         eng.decode(first, 4, drafts, **kw)
     assert ei.value.code == asd.E_STATE
     eng.close()
+
+
+@pytest.mark.parametrize("V", [16, 272, 32768, 32784])
+def test_rows_with_nan_draw_their_last_positive_weight(V):
+    """A row with a NaN has no running sum: draft draws, extra draws and replacements then take the last index with a positive
+    weight (masked -inf logits have none), in both variants of the kernels."""
+    shape = si.Shape("v", 1, 64, 2, 2, 32, 64, V, si.DT_F32, 4, 4, 2)
+    rng = np.random.default_rng(V)
+    p = rng.normal(0, 2.0, (3, V)).astype(np.float32)
+    q = p[:2] + rng.normal(0, 0.5, (2, V)).astype(np.float32)
+    clean = p[2:].copy()
+    for rows in (p, q):
+        rows[:, V // 3] = np.nan
+        rows[:, V - 2:] = -np.inf
+    q[1, V - 5:] = -np.inf
+    for flags in (0, asd.DBG_SAMPLE_MEM):
+        eng = asd.Engine(asd.make_config(shape, 64, debug_flags=flags))
+        drafts, acc, nxt = eng.spec_sample(q, p, 0.8, 5, 0)
+        assert list(drafts) == [V - 3, V - 6] and acc == 0 and nxt == V - 3      # a NaN ratio keeps no draft
+        assert eng.spec_sample(np.zeros((0, V), np.float32), p[:1], 0.8, 5, 0)[2] == V - 3
+        assert eng.spec_sample(np.zeros((0, V), np.float32), np.full((1, V), np.nan, np.float32), 0.8, 5, 0)[2] == 0
+        masked = clean.copy()
+        masked[:, 3:] = -np.inf                                                   # ordinary masked rows: only what is left
+        assert all(eng.spec_sample(np.zeros((0, V), np.float32), masked, 0.8, s, 0)[2] < 3 for s in range(20))
+        eng.close()
