@@ -692,15 +692,16 @@ __global__ __launch_bounds__(256, 2) void pf_attn_long_kernel(const PfAttnArgs a
                     for (int j = 0; j < 4; ++j) cm = fmaxf(cm, s[t][kt][j]);
                 cm = fmaxf(cm, __shfl_xor(cm, 16));
                 cm = fmaxf(cm, __shfl_xor(cm, 32));
-                // (a row's first chunk holds its key 0, so its maximum is finite from then on)
+                // A row's maximum is -inf until its first key with a score above that (scores may overflow to -inf): such a
+                // chunk counts for nothing, so the exponents are taken against 0 then, not against -inf
                 if (__any(cm > mx[t])) {
-                    const float mn = fmaxf(mx[t], cm), alpha = __builtin_amdgcn_exp2f((mx[t] - mn) * c2);
+                    const float mn = fmaxf(mx[t], cm), alpha = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mx[t] - mn) * c2);
                     mx[t] = mn;
                     l[t] *= alpha;
 #pragma unroll
                     for (int ht = 0; ht < HT; ++ht) { o[t][ht][0] *= alpha; o[t][ht][1] *= alpha; o[t][ht][2] *= alpha; o[t][ht][3] *= alpha; }
                 }
-                const float off = -mx[t] * c2;
+                const float off = mx[t] == -INFINITY ? 0.f : -mx[t] * c2;
 #pragma unroll
                 for (int kt = 0; kt < 4; ++kt)
 #pragma unroll

@@ -88,6 +88,36 @@ def test_long_block_attention_agrees_with_the_chunked_pass(h, n_h, n_kv, n):
     eng.close(); ref.close()
 
 
+def test_rows_whose_first_keys_all_score_minus_infinity():
+    """Scores that overflow to -inf count for nothing, whichever attention kernel takes the row: 70 tokens A, then tokens B whose
+    scores against every A are -inf and against every B zero, so that the first key chunk of every B row holds nothing.  192
+    workgroups of 128 rows: the long-block kernel."""
+    n, n_a = 450, 70
+    shape = si.Shape("wide", 2, 256, 48, 48, 32, 256, 256, si.DT_BF16, 8, 8, 2)
+    W = {(t, l): a.copy() for t, l, a in si.all_tensors(shape, 5, 0.1)}
+    bf16 = lambda x: np.uint16(np.float32(x).view(np.uint32) >> 16)
+    emb = W[si.T_EMBED, 0]
+    emb[:2] = 0
+    emb[0, 0] = emb[1, 1] = bf16(1.0)                      # token 0 (A) is feature 0, token 1 (B) feature 1; 16 each behind the norm
+    W[si.T_ATTN_NORM, 0][:] = 1.0
+    for t, col, val in ((si.T_WQ, 1, -1e19), (si.T_WK, 0, 1e19)):
+        w = W[t, 0]
+        w[:, :2] = 0
+        w[15::32, col] = bf16(val)                         # the slowest rotary pair: 0.08 radians over the prompt
+    toks = np.where(np.arange(n + 3) < n_a, 0, 1).astype(np.int32)
+    got = []
+    for chunked in (False, True):
+        eng = asd.Engine(asd.make_config(shape, n + 16)).load([(t, l, a) for (t, l), a in W.items()])
+        _, acs, lg = eng.prefill(toks[:n], want_logits=True, chunked=chunked)
+        got.append((acs, lg, *eng.get_kv(1, 0, n), eng.forward(toks[n:], n)["logits"]))
+        eng.close()
+    a, b = got
+    assert all(np.isfinite(x).all() for x in a) and np.abs(a[0] - b[0]).max() < COS_TOL
+    assert rel_err(a[1], b[1]) < TOL[shape.dtype] and rel_err(a[4], b[4]).max() < TOL[shape.dtype]
+    for x, y in zip(a[2:4], b[2:4]):
+        assert np.linalg.norm(x - y) < 1e-3 * np.linalg.norm(y)
+
+
 def si_scale(a, f):
     """bf16 bit patterns times f, rounded to nearest even."""
     x = (si.bf16_to_f32(a) * np.float32(f)).view(np.uint32)
