@@ -734,9 +734,11 @@ struct HostCopies {
         if (a.n[k] > most) most = a.n[k];
         ++k;
     }
-    void launch(hipStream_t s) const {
+    // (the launch's own status: were it lost, a call would hand over what the last one left in the pinned memory)
+    hipError_t launch(hipStream_t s) {
         const int blocks = (most + 1023) / 1024;
-        to_host_kernel<<<blocks < 1 ? 1 : blocks > 256 ? 256 : blocks, 256, 0, s>>>(a);
+        void* args[] = {&a};
+        return hipLaunchKernel((const void*)to_host_kernel, dim3(blocks < 1 ? 1 : blocks > 256 ? 256 : blocks), dim3(256), args, 0, s);
     }
 };
 // Enqueue what a call starts with: state, zeroed words, at most 16 tokens
@@ -1407,7 +1409,7 @@ int asd_forward(asd_engine* e, const int32_t* tokens, int32_t n_rows, int32_t po
     out.add(e->cos_rows, e->h_cos_rows, (size_t)L2 * ASD_ROWS * 4);
     out.add(e->cos_acc, e->h_cos_acc, (size_t)L2 * 8);
     if (logits) out.add(e->logits, e->h_logits, (size_t)n_rows * e->c.vocab * 4);
-    out.launch(e->stream);
+    CK(e, out.launch(e->stream));
     CK(e, hipStreamSynchronize(e->stream));
     rc = check_pass_error(e, e->h_st);
     if (rc) return rc;
@@ -1478,7 +1480,7 @@ int asd_check(asd_engine* e) {
     if (!e) return ASD_E_INVAL;
     HostCopies out;
     out.add(e->st, e->h_st, sizeof(DevState));
-    out.launch(e->stream);
+    CK(e, out.launch(e->stream));
     CK(e, hipStreamSynchronize(e->stream));
     return check_pass_error(e, e->h_st);
 }
@@ -1512,7 +1514,7 @@ static int prefill_impl(asd_engine* e, const int32_t* tokens, int32_t n, int32_t
     out.add(e->argmax, e->h_argmax, ASD_ROWS * 4);
     out.add(e->cos_acc, e->h_cos_acc, (size_t)L2 * 8);
     if (last_logits) out.add(e->logits + (size_t)last_row * e->c.vocab, e->h_logits, (size_t)e->c.vocab * 4);
-    out.launch(e->stream);
+    CK(e, out.launch(e->stream));
     CK(e, hipStreamSynchronize(e->stream));
     rc = check_pass_error(e, e->h_st);
     if (rc) return rc;
@@ -1752,7 +1754,7 @@ int asd_decode(asd_engine* e, int32_t last_token, int32_t n_more, const asd_gen_
                 ++d;
                 HostCopies step;
                 step.add(e->st, e->h_st, sizeof(DevState));
-                step.launch(e->stream);
+                CK(e, step.launch(e->stream));
                 CK(e, hipStreamSynchronize(e->stream));
                 if ((double)e->h_st->conf < gamma) break;
             }
@@ -1770,7 +1772,7 @@ int asd_decode(asd_engine* e, int32_t last_token, int32_t n_more, const asd_gen_
         const int most = ahead + d + 1 < n_more - emitted ? ahead + d + 1 : n_more - emitted;
         trip.add(e->st, e->h_st, sizeof(DevState));
         trip.add(e->out_tokens + emitted, e->h_tok + emitted, (size_t)most * 4);
-        trip.launch(e->stream);
+        CK(e, trip.launch(e->stream));
         if (refresh) CK(e, hipMemcpyAsync(cr.data(), e->cos_rows, cr.size() * 4, hipMemcpyDeviceToHost, e->stream));
         CK(e, hipStreamSynchronize(e->stream));
         {
