@@ -81,8 +81,9 @@ typedef struct {
  * debug_tune: "name=a,b,c,d;..." with name in {qkv, o, gu, down, lm}: tiles per workgroup, waves per
  * workgroup, k-major layout (0/1), interleaved k-blocks (0/1); and name in {pf_qkv, pf_o, pf_gu,
  * pf_down}: 16-row chunks per workgroup, K slices[, prefetch depth[, tiles per wave (pf_qkv: 3..5)]] of the prompt-block GEMMs;
- * "pf_ring=V[,S]": tile shape V (0..15) of the ring kernel of bf16 prompt-block GEMMs and K slices S of its residual-add
- * launches (default: by estimated time; a pf_* entry takes its class back to the other kernel);
+ * "pf_ring=V[,S]": tile shape V (0..15) of the ring kernel of the prompt-block GEMMs and K slices S of its residual-add
+ * launches (default: by estimated time; a pf_* entry takes its class back to the other kernel, and so does an S that a
+ * launch cannot have: more slices than k-blocks, or more than the partial-sum buffer holds, 4096 rows over all slices);
  * "qkv_rows=N": tiles per QKV workgroup in passes of five rows and more (default: by balance).  A
  * layout override changes how weights are tiled in the arena, never their values.  The string is
  * copied by asd_create.
@@ -270,7 +271,11 @@ int asd_check(asd_engine* e);
  * (last_logits [vocab], optional).  The ACS is kept in the engine for a following
  * asd_decode with mask_mode 0.  Prompts longer than max_rows are processed in blocks
  * of up to 2048 rows (as many as the arena has room for, never fewer than 512), layer by
- * layer, with large-M matrix-core contractions (every weight is read once per block); shorter ones as one pass of the decode kernels.
+ * layer, with large-M matrix-core contractions (every weight is read once per block);
+ * shorter ones as one pass of the decode kernels.  Blocks, K slices and attention kernel
+ * follow the prompt's length, and with them the order of the sums: the same prompt gives
+ * the same bits, but the cached rows (and ACS) of a prefix that two prompts of different length share agree
+ * up to rounding only.
  * asd_prefill_chunked always takes the decode kernels, max_rows rows at a time (the
  * same results up to rounding; kept for cross-checks and as the reference for timing).
  * All pointers are host memory.
@@ -359,6 +364,20 @@ int asd_profile_forward(asd_engine* e, int32_t n_rows, const uint8_t* skip_mask,
 int asd_time_step_class(asd_engine* e, int32_t cls, int32_t n_rows, int32_t reps, double* us_avg, double* bytes_per_launch);
 int asd_profile_prefill(asd_engine* e, const int32_t* tokens, int32_t n, asd_prefill_times* out);
 int asd_copy_bench(asd_engine* e, size_t nbytes, int32_t reps, double* ms_avg);
+
+/*
+ * How asd_prefill runs a prompt of n tokens under a configuration (host arithmetic, no engine; for the compute units of the
+ * current device, 256 where none is visible): block number
+ * `block` (0 ..) of n_blocks, its first row and rows, the query rows per attention workgroup (16 or 128: two kernels), and
+ * for the layer's contractions QKV, O, gate/up, down the tile shape of the ring kernel (-1: the four-wave kernel) and
+ * the K slices.  n <= max_rows: n_blocks is 0 (one pass of the decode kernels).  ASD_E_INVAL: no such block, n outside
+ * [1, capacity], or an invalid configuration.
+ */
+typedef struct {
+    int32_t n_blocks, row0, rows, attn_rows;
+    int32_t tile[4], slices[4];
+} asd_prompt_block;
+int asd_plan_prompt(const asd_config* cfg, int32_t n, int32_t block, asd_prompt_block* out);
 
 #ifdef __cplusplus
 }

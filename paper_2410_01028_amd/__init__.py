@@ -61,6 +61,11 @@ class PrefillTimes(ctypes.Structure):
                 ("ms_total", ctypes.c_double)]
 
 
+class PromptBlock(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("n_blocks", "row0", "rows", "attn_rows")] + \
+               [("tile", ctypes.c_int32 * 4), ("slices", ctypes.c_int32 * 4)]
+
+
 class KernelTimes(ctypes.Structure):
     _fields_ = [("ms", ctypes.c_double * 8), ("launches", ctypes.c_int32 * 8), ("bytes", ctypes.c_double * 8),
                 ("ms_total", ctypes.c_double)]
@@ -80,6 +85,7 @@ def lib():
         cfgp = ctypes.POINTER(Config)
         L.asd_arena_bytes.restype = sz
         L.asd_arena_bytes.argtypes = [cfgp]
+        L.asd_plan_prompt.argtypes = [cfgp, i32, i32, ctypes.POINTER(PromptBlock)]
         L.asd_create.argtypes = [cfgp, vp, sz, vp, ctypes.POINTER(vp)]
         L.asd_destroy.argtypes = [vp]
         L.asd_destroy.restype = None
@@ -123,6 +129,26 @@ def make_config(shape, max_seq: int, page_tokens: int = 64, max_rows: int = MAX_
 
 def arena_bytes(cfg: Config) -> int:
     return int(lib().asd_arena_bytes(ctypes.byref(cfg)))
+
+
+PROMPT_GEMMS = ("qkv", "oproj", "gateup", "down")
+
+
+def plan_prompt(cfg: Config, n: int) -> list[dict]:
+    """How Engine.prefill runs a prompt of n tokens: one dict per block (row0, rows, attn_rows, and per contraction of
+    PROMPT_GEMMS the ring kernel's tile shape, -1 for the four-wave kernel, and the K slices); [] for a prompt that the
+    decode kernels take as one pass."""
+    blocks, b = [], PromptBlock()
+    while True:
+        rc = lib().asd_plan_prompt(ctypes.byref(cfg), n, len(blocks), ctypes.byref(b))
+        if rc:
+            raise AsdError(rc, "asd_plan_prompt: invalid configuration or prompt length")
+        if b.n_blocks == 0:
+            return []
+        blocks.append({"row0": b.row0, "rows": b.rows, "attn_rows": b.attn_rows, "tile": dict(zip(PROMPT_GEMMS, b.tile)),
+                       "slices": dict(zip(PROMPT_GEMMS, b.slices))})
+        if len(blocks) == b.n_blocks:
+            return blocks
 
 
 def admg(c_attn, alpha: float, m: int, n: int, use_cs: bool = True) -> np.ndarray:

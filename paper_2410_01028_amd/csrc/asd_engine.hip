@@ -52,6 +52,17 @@ hipError_t scratch_ptr(unsigned char** out) {
 
 struct GemmCfg { int TN, NW, grid, kmajor, kint; };
 struct PfCfg { int NC, KS, PD, NA; bool forced; };  // prompt GEMM: 16-row chunks per workgroup, K slices, prefetch depth, tiles per wave (0: by balance); forced: given in debug_tune
+enum { PF_C_QKV = 0, PF_C_O = 1, PF_C_GU = 2, PF_C_DOWN = 3, PF_CLASSES = 4 };      // the prompt GEMMs of a layer
+// What the launch rules of the prompt pass look at
+struct PfRules {
+    int dtype, n_heads, rows;                       // rows: the most a block may have
+    int n_tiles[PF_CLASSES], KB[PF_CLASSES];        // output tiles (pairs for gate/up), k-blocks
+    PfCfg cfg[PF_CLASSES];
+    int ring_tile, ring_ks;                         // debug_tune "pf_ring": tile shape and K slices of pf_ring_kernel (-1, 0: by estimate)
+};
+struct PfPick { int tile, ks; };                    // tile shape of pf_ring_kernel (-1: pf_gemm_kernel) and K slices
+// One block's launches; decided once per block, so that a GEMM and the kernel that adds its K slices go by the same numbers
+struct PfBlock { PfPick gemm[PF_CLASSES]; bool long_attn; };
 
 struct Layer {
     char *wqkv, *wo, *wg, *wu, *wd;
@@ -100,8 +111,7 @@ struct asd_engine {
     float *pf_xres, *pf_raw, *pf_ssq, *pf_rscale, *pf_cos_rows;
     void *pf_xb, *pf_q, *pf_attn_out, *pf_hmid;
     int pf_rows;                        // most rows of a prompt block
-    int pf_ring_tune[2] = {-1, 0};          // debug_tune "pf_ring": tile shape and K slices of the eight-wave prompt GEMM
-    PfCfg pf_qkv, pf_o, pf_gu, pf_down;
+    PfRules pf;
     // launch shapes
     GemmCfg g_qkv, g_o, g_gu, g_down, g_lm;
     GemmCfg g_qkv_rows;                 // QKV launch shape of passes of at least QKV_ROWS_MIN rows (same layout, same bits)
@@ -801,10 +811,10 @@ int pf_old_slices(const PfCfg& g, int KB, int n_chunks) {
     int ks = g.KS < KB ? g.KS : KB;
     return ks < most ? ks : most;
 }
-template <class T, int EPI, int NA> bool launch_pf_gemm_na(hipStream_t s, const PfCfg& g, PfArgs a, int n_chunks) {
+template <class T, int EPI, int NA> bool launch_pf_gemm_na(hipStream_t s, const PfCfg& g, int ks, PfArgs a, int n_chunks) {
     a.n_fb = (a.n_tiles + PF_NW * NA - 1) / (PF_NW * NA);
     a.n_rb = (n_chunks + g.NC - 1) / g.NC;
-    a.ksplit = EPI == PF_RAW ? pf_old_slices(g, a.KB, n_chunks) : 1;
+    a.ksplit = ks;
     const unsigned grid = (unsigned)((a.n_fb + 7) / 8 * 8 * a.n_rb * a.ksplit);
 #define PFK(nc, pd) if (g.NC == nc && g.PD == pd) { pf_gemm_kernel<T, EPI, NA, nc, PF_NW, pd><<<grid, PF_NW * 64, 0, s>>>(a); return true; }
     if constexpr (NA == pf_na<EPI>()) { PFK(2, 1) PFK(4, 1) PFK(8, 1) PFK(2, 2) PFK(4, 2) PFK(8, 2) PFK(2, 3) PFK(4, 3) PFK(2, 4) PFK(4, 4) }
@@ -829,13 +839,13 @@ static int pf_qkv_na(const PfCfg& g, int n_tiles, int n_chunks) {
     }
     return best;
 }
-template <class T, int EPI> bool launch_pf_gemm_t(hipStream_t s, const PfCfg& g, PfArgs a, int n_chunks) {
+template <class T, int EPI> bool launch_pf_gemm_t(hipStream_t s, const PfCfg& g, int ks, PfArgs a, int n_chunks) {
     if constexpr (EPI == PF_QKV) {
         const int na = pf_qkv_na(g, a.n_tiles, n_chunks);
-        if (na == 3) return launch_pf_gemm_na<T, EPI, 3>(s, g, a, n_chunks);
-        if (na == 5) return launch_pf_gemm_na<T, EPI, 5>(s, g, a, n_chunks);
+        if (na == 3) return launch_pf_gemm_na<T, EPI, 3>(s, g, ks, a, n_chunks);
+        if (na == 5) return launch_pf_gemm_na<T, EPI, 5>(s, g, ks, a, n_chunks);
     }
-    return launch_pf_gemm_na<T, EPI, pf_na<EPI>()>(s, g, a, n_chunks);
+    return launch_pf_gemm_na<T, EPI, pf_na<EPI>()>(s, g, ks, a, n_chunks);
 }
 
 // Tile shapes of pf_ring_kernel: output tiles (for gate/up: pairs of tiles) and chunks per workgroup, and the time of a
@@ -845,7 +855,6 @@ constexpr PfRingTile kPfRing[] = {{12, 8, 0.68f}, {16, 8, 0.76f}, {24, 8, 1.10f}
                                   {3, 2, 0.f}, {3, 3, 0.f}, {3, 4, 0.f}, {4, 2, 0.f}, {4, 3, 0.f}, {4, 4, 0.f}, {4, 6, 0.f}, {4, 8, 0.f},
                                   {8, 2, 0.f}, {8, 3, 0.f}, {8, 4, 0.f}, {8, 8, 0.f}};
 constexpr int kPfRings = sizeof kPfRing / sizeof kPfRing[0], kPfBig = 4;      // the first kPfBig: gate/up tiles counted singly
-struct PfRingPick { int tile, ks; };                                          // tile -1: pf_gemm_kernel
 // The kernel and shape with the least estimated time.  pf_ring_kernel: rounds of workgroups (one to a compute unit) on the
 // busiest XCD, times a workgroup's k-blocks at the rate a compute unit takes fragments in, about 43 KiB per us whichever cache level
 // they come from (7 to 32 KiB per k-block measured 0.18 to 0.71 us), plus 4 us per round for filling the ring and the
@@ -857,14 +866,17 @@ struct PfRingPick { int tile, ks; };                                          //
 // on the shape nor on the block's length.  Longer blocks fill the chip with fewer (13B at 1003 rows, O and down: 94 and 227 us
 // with two slices, 120 and 300 us with four).
 constexpr int PF_FIXED_SLICES = 40;
-PfRingPick pf_ring_pick(const asd_engine* e, int epi, const PfCfg& g, int n_tiles, int KB, int n_chunks) {
-    const int units = device_units() / 8 > 0 ? device_units() / 8 : 1, np = e->c.dtype == ASD_DT_BF16 ? BF16::NP : F32::NP;
-    const bool f32 = e->c.dtype == ASD_DT_F32;
-    const int ks4 = pf_old_slices(g, KB, n_chunks);
+PfPick pf_pick_gemm(const PfRules& r, int cls, int n_chunks) {
+    const PfCfg& g = r.cfg[cls];
+    const int epi = cls == PF_C_QKV ? PF_QKV : cls == PF_C_GU ? PF_GU : PF_RAW, n_tiles = r.n_tiles[cls], KB = r.KB[cls];
+    const bool f32 = r.dtype == ASD_DT_F32;
+    const int units = device_units() / 8 > 0 ? device_units() / 8 : 1, np = f32 ? F32::NP : BF16::NP;
+    const int ks4 = epi == PF_RAW ? pf_old_slices(g, KB, n_chunks) : 1;
+    if (g.forced) return {-1, ks4};
     auto raw_us = [&](int ks) { return epi == PF_RAW ? ks * (2.f * n_chunks * 16 * n_tiles * 16 * 4 / 5e6f) : 0.f; };
-    PfRingPick best{-1, epi == PF_RAW ? ks4 : 1};
+    PfPick best{-1, ks4};
     float best_us = 3e38f;
-    if (e->pf_ring_tune[0] < 0 && e->pf_ring_tune[1] == 0) {
+    if (r.ring_tile < 0) {
         const int na = epi == PF_GU ? 2 : epi == PF_QKV ? pf_qkv_na(g, n_tiles, n_chunks) : 4, per = 4 * na;
         const float wgs = (float)(((n_tiles + per - 1) / per + 7) / 8 * ((n_chunks + g.NC - 1) / g.NC) * best.ks) / units;
         const float on_unit = wgs > 2.f ? wgs : ceilf(wgs), frags = 4 * (epi == PF_GU ? 2 * na : na) + np * g.NC;
@@ -872,13 +884,13 @@ PfRingPick pf_ring_pick(const asd_engine* e, int epi, const PfCfg& g, int n_tile
     }
     for (int v = 0; v < kPfRings; ++v) {
         const PfRingTile& T = kPfRing[v];
-        if (e->pf_ring_tune[0] >= 0 && e->pf_ring_tune[0] != v) continue;
+        if (r.ring_tile >= 0 && r.ring_tile != v) continue;
         const int per = epi == PF_GU && v < kPfBig ? T.FT / 2 : T.FT, n_fb = (n_tiles + per - 1) / per, n_rb = (n_chunks + T.RC - 1) / T.RC;
         const int tiles = epi == PF_GU ? 2 * per : per, frags = tiles + np * T.RC;
         const float us_kb = f32 ? tiles * T.RC * 0.061f / (v < kPfBig ? 8 : T.FT) : T.us_kb;      // a fragment product: 128 cycles of one SIMD
         for (int ks = 1; ks <= PF_MAX_KSPLIT; ++ks) {
             if (ks > 1 && (epi != PF_RAW || ks * n_chunks * 16 > PF_RAW_ROWS || ks > KB)) break;
-            if (epi == PF_RAW && (e->pf_ring_tune[1] > 0 ? ks != e->pf_ring_tune[1] : n_chunks <= PF_FIXED_SLICES && ks != ks4)) continue;
+            if (epi == PF_RAW && (r.ring_ks > 0 ? ks != r.ring_ks : n_chunks <= PF_FIXED_SLICES && ks != ks4)) continue;
             const int rounds = ((n_fb + 7) / 8 * n_rb * ks + units - 1) / units;
             const float us = rounds * ((float)KB / ks * fmaxf(us_kb, frags / 43.f) + 4.f) + raw_us(ks);
             if (us < best_us) { best = {v, ks}; best_us = us; }
@@ -886,7 +898,7 @@ PfRingPick pf_ring_pick(const asd_engine* e, int epi, const PfCfg& g, int n_tile
     }
     return best;
 }
-template <class T, int EPI> bool launch_pf_ring(hipStream_t s, const PfRingPick& p, PfArgs a, int n_chunks) {
+template <class T, int EPI> bool launch_pf_ring(hipStream_t s, const PfPick& p, PfArgs a, int n_chunks) {
     const PfRingTile& R = kPfRing[p.tile];
     const int per = EPI == PF_GU && p.tile < kPfBig ? R.FT / 2 : R.FT;
     a.n_fb = (a.n_tiles + per - 1) / per;
@@ -906,28 +918,47 @@ template <class T, int EPI> bool launch_pf_ring(hipStream_t s, const PfRingPick&
     }
     return false;
 }
-PfRingPick pf_use(const asd_engine* e, const PfCfg& g, int epi, int n_tiles, int KB, int n_chunks) {
-    if (g.forced) return {-1, pf_old_slices(g, KB, n_chunks)};
-    return pf_ring_pick(e, epi, g, n_tiles, KB, n_chunks);
-}
-// K slices of a residual-add GEMM's launch (what pf_resid_kernel has to add up)
-int pf_slices(const asd_engine* e, const PfCfg& g, int n_tiles, int KB, int n_chunks) {
-    return pf_use(e, g, PF_RAW, n_tiles, KB, n_chunks).ks;
-}
-template <int EPI> bool launch_pf_gemm(asd_engine* e, const PfCfg& g, const PfArgs& a, int n_chunks) {
-    const PfRingPick p = pf_use(e, g, EPI, a.n_tiles, a.KB, n_chunks);
+template <int EPI> bool launch_pf_gemm(asd_engine* e, const PfCfg& g, const PfPick& p, const PfArgs& a, int n_chunks) {
     if (p.tile >= 0) return e->c.dtype == ASD_DT_BF16 ? launch_pf_ring<BF16, EPI>(e->stream, p, a, n_chunks) : launch_pf_ring<F32, EPI>(e->stream, p, a, n_chunks);
-    return e->c.dtype == ASD_DT_BF16 ? launch_pf_gemm_t<BF16, EPI>(e->stream, g, a, n_chunks) : launch_pf_gemm_t<F32, EPI>(e->stream, g, a, n_chunks);
+    return e->c.dtype == ASD_DT_BF16 ? launch_pf_gemm_t<BF16, EPI>(e->stream, g, p.ks, a, n_chunks) : launch_pf_gemm_t<F32, EPI>(e->stream, g, p.ks, a, n_chunks);
 }
 
-template <class T> void launch_pf_attn_t(asd_engine* e, const PfAttnArgs& a, int n_chunks) {
+// From three 128-row workgroups to four compute units on, the attention kernel that shares a chunk's fragments among 128 rows;
+// with fewer, units stand idle (7B: 192 workgroups at 700 rows 39 us; 128 at 512 rows 31 us against 25 us of the 16-row
+// workgroups, 64 at 256 rows 20 against 14 us).
+bool pf_attn_is_long(const PfRules& r, int rows) {
+    return r.dtype == ASD_DT_BF16 && BF16::NP == 2 && 4 * ((rows + PF_ATT_LONG_ROWS - 1) / PF_ATT_LONG_ROWS * r.n_heads) >= 3 * device_units();
+}
+PfRules pf_rules(const asd_config& c, const Plan& p) {
+    const char* tune = c.debug_tune;
+    PfRules r{c.dtype, c.n_heads, p.pf_rows, {p.qkv_tiles, c.d_model / 16, c.d_ffn / 16, c.d_model / 16}, {p.KBd, p.KBq, p.KBd, p.KBf},
+              {pf_pick(tune, "pf_qkv", 4, 1), pf_pick(tune, "pf_o", 4, 4), pf_pick(tune, "pf_gu", 4, 1), pf_pick(tune, "pf_down", 4, 4)}, -1, 0};
+    int v[2];
+    const int nv = tune_entry(tune, "pf_ring", v, 2);
+    if (nv >= 1 && v[0] >= 0 && v[0] < kPfRings) {
+        r.ring_tile = v[0];
+        if (nv == 2 && v[1] >= 1 && v[1] <= PF_MAX_KSPLIT) r.ring_ks = v[1];
+    }
+    return r;
+}
+PfBlock pf_block(const PfRules& r, int rows) {
+    PfBlock b;
+    for (int cls = 0; cls < PF_CLASSES; ++cls) b.gemm[cls] = pf_pick_gemm(r, cls, (rows + 15) / 16);
+    b.long_attn = pf_attn_is_long(r, rows);
+    return b;
+}
+// Rows of every block but the last of an n-row prompt: as few blocks as the workspace allows, of equal length in whole
+// 128-row steps (a workgroup's chunks); 512-row workspaces take 512 at a time
+int pf_block_rows(const PfRules& r, int n) {
+    const int n_blocks = (n + r.rows - 1) / r.rows;
+    return r.rows == PF_MIN_ROWS ? PF_MIN_ROWS : ((n + n_blocks - 1) / n_blocks + 127) / 128 * 128;
+}
+
+template <class T> void launch_pf_attn_t(asd_engine* e, const PfAttnArgs& a, int n_chunks, bool long_rows) {
     const int H = e->c.head_dim;
-    // From three 128-row workgroups to four compute units on, the kernel that shares a chunk's fragments among 128 rows;
-    // with fewer, units stand idle (7B: 192 workgroups at 700 rows 39 us; 128 at 512 rows 31 us against 25 us of the 16-row
-    // workgroups, 64 at 256 rows 20 against 14 us).
     if constexpr (std::is_same_v<T, BF16> && BF16::NP == 2) {
-        const int wgs = (a.rows + PF_ATT_LONG_ROWS - 1) / PF_ATT_LONG_ROWS * a.n_h;
-        if (4 * wgs >= 3 * device_units()) {
+        if (long_rows) {
+            const int wgs = (a.rows + PF_ATT_LONG_ROWS - 1) / PF_ATT_LONG_ROWS * a.n_h;
             if (H == 32) pf_attn_long_kernel<32><<<wgs, 256, 0, e->stream>>>(a);
             if (H == 64) pf_attn_long_kernel<64><<<wgs, 256, 0, e->stream>>>(a);
             if (H == 128) pf_attn_long_kernel<128><<<wgs, 256, 0, e->stream>>>(a);
@@ -959,7 +990,7 @@ template <class T> void launch_pf_tail_t(asd_engine* e, int rows) {
         e->pf_ssq, c.d_model, e->g_final, e->xres, e->xb, (int64_t)e->KBd * 64 * e->KE, e->part);
 }
 // The whole prompt, block by block and layer by layer; leaves the last row's logits / greedy token in row 0 of the
-// decode buffers and the cosine sums of all rows in cos_acc (the caller cleared it).  Enqueue only.
+// decode buffers and the cosine sums of all rows in cos_acc.  Enqueue only.
 int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profiler = nullptr) {
     const asd_config& c = e->c;
     const int L = c.n_layers, KE = e->KE;
@@ -969,9 +1000,7 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
     auto wl = [&](PfArgs& a, const GemmCfg& cfg, int total_tiles, int KB) {
         a.n_tiles = total_tiles; a.KB = KB; a.w_tile_stride = cfg.kmajor ? 1 : KB; a.w_kb_stride = cfg.kmajor ? total_tiles : 1;
     };
-    // as few blocks as the workspace allows, of equal length in whole 128-row steps (a workgroup's chunks)
-    const int n_blocks = (n + e->pf_rows - 1) / e->pf_rows;
-    const int block = e->pf_rows == PF_MIN_ROWS ? PF_MIN_ROWS : ((n + n_blocks - 1) / n_blocks + 127) / 128 * 128;
+    const int block = pf_block_rows(e->pf, n);
     const int64_t cap = e->pf_rows / 16;                // chunks per activation plane
     memcpy(e->h_tok, tokens, (size_t)n * 4);             // (the embedding reads them from there; n <= capacity)
     launch_begin(e, 0, 0, 0, 0, e->cos_acc, 4 * L);
@@ -979,6 +1008,7 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
     for (int r0 = 0; r0 < n; r0 += rows) {
         rows = n - r0 < block ? n - r0 : block;
         const int n_chunks = (rows + 15) / 16;
+        const PfBlock how = pf_block(e->pf, rows);
         pr.begin(ASD_PK_ROWS, 0);
         if (bf) launch_pf_embed_t<BF16>(e, e->h_tok + r0, rows, n_chunks); else launch_pf_embed_t<F32>(e, e->h_tok + r0, rows, n_chunks);
         pr.end();
@@ -1003,7 +1033,7 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
             wl(a, e->g_qkv, e->qkv_tiles, e->KBd);
             a.kv = e->kv + (size_t)l * e->kv_layer_bytes;
             pr.begin(ASD_PK_QKV, fl_row * c.d_model * (qd + 2 * kvd));
-            ok = ok && launch_pf_gemm<PF_QKV>(e, e->pf_qkv, a, n_chunks);
+            ok = ok && launch_pf_gemm<PF_QKV>(e, e->pf.cfg[PF_C_QKV], how.gemm[PF_C_QKV], a, n_chunks);
             pr.end();
 
             PfAttnArgs t{};
@@ -1012,34 +1042,34 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
             t.n_h = c.n_heads; t.n_kv = c.n_kv_heads; t.h = c.head_dim; t.page_tokens = c.page_tokens;
             t.scale = 1.f / sqrtf((float)c.head_dim);
             pr.begin(ASD_PK_ATTN, 4.0 * qd * ctx_sum);
-            if (c.dtype == ASD_DT_BF16) launch_pf_attn_t<BF16>(e, t, n_chunks); else launch_pf_attn_t<F32>(e, t, n_chunks);
+            if (c.dtype == ASD_DT_BF16) launch_pf_attn_t<BF16>(e, t, n_chunks, how.long_attn); else launch_pf_attn_t<F32>(e, t, n_chunks, how.long_attn);
             pr.end();
 
             PfArgs o = base;
             o.W = (const u32x4*)ly.wo; o.X = (const u32x4*)e->pf_attn_out; o.x_plane = cap * e->KBq * 64; o.x_chunk = (int64_t)e->KBq * 64;
             wl(o, e->g_o, c.d_model / 16, e->KBq);
             pr.begin(ASD_PK_OPROJ, fl_row * qd * c.d_model);
-            ok = ok && launch_pf_gemm<PF_RAW>(e, e->pf_o, o, n_chunks);
+            ok = ok && launch_pf_gemm<PF_RAW>(e, e->pf.cfg[PF_C_O], how.gemm[PF_C_O], o, n_chunks);
             pr.end();
             pr.begin(ASD_PK_ROWS, 0);
-            resid(pf_slices(e, e->pf_o, c.d_model / 16, e->KBq, n_chunks), ly.g_mlp, 2 * l);
+            resid(how.gemm[PF_C_O].ks, ly.g_mlp, 2 * l);
             pr.end();
 
             PfArgs gu = base;
             gu.W = (const u32x4*)ly.wg; gu.W2 = (const u32x4*)ly.wu; gu.X = (const u32x4*)e->pf_xb; gu.x_plane = a.x_plane; gu.x_chunk = a.x_chunk;
             wl(gu, e->g_gu, c.d_ffn / 16, e->KBd);
             pr.begin(ASD_PK_GATEUP, fl_row * 2.0 * c.d_model * c.d_ffn);
-            ok = ok && launch_pf_gemm<PF_GU>(e, e->pf_gu, gu, n_chunks);
+            ok = ok && launch_pf_gemm<PF_GU>(e, e->pf.cfg[PF_C_GU], how.gemm[PF_C_GU], gu, n_chunks);
             pr.end();
 
             PfArgs dn = base;
             dn.W = (const u32x4*)ly.wd; dn.X = (const u32x4*)e->pf_hmid; dn.x_plane = cap * e->KBf * 64; dn.x_chunk = (int64_t)e->KBf * 64;
             wl(dn, e->g_down, c.d_model / 16, e->KBf);
             pr.begin(ASD_PK_DOWN, fl_row * (double)c.d_model * c.d_ffn);
-            ok = ok && launch_pf_gemm<PF_RAW>(e, e->pf_down, dn, n_chunks);
+            ok = ok && launch_pf_gemm<PF_RAW>(e, e->pf.cfg[PF_C_DOWN], how.gemm[PF_C_DOWN], dn, n_chunks);
             pr.end();
             pr.begin(ASD_PK_ROWS, 0);
-            resid(pf_slices(e, e->pf_down, c.d_model / 16, e->KBf, n_chunks), l + 1 < L ? e->layers[l + 1].g_attn : e->g_final, 2 * l + 1);
+            resid(how.gemm[PF_C_DOWN].ks, l + 1 < L ? e->layers[l + 1].g_attn : e->g_final, 2 * l + 1);
             pr.end();
             if (!ok) return fail(e, ASD_E_STATE, "no prompt GEMM instance for this launch shape");
         }
@@ -1071,6 +1101,30 @@ extern "C" {
 size_t asd_arena_bytes(const asd_config* cfg) {
     if (!config_ok(cfg, nullptr)) return 0;
     return make_plan(*cfg).total;
+}
+
+int asd_plan_prompt(const asd_config* cfg, int32_t n, int32_t block, asd_prompt_block* out) {
+    if (!out || !config_ok(cfg, nullptr)) return ASD_E_INVAL;
+    const Plan p = make_plan(*cfg);
+    if (n < 1 || n > p.n_pages * cfg->page_tokens || block < 0) return ASD_E_INVAL;
+    asd_prompt_block b{};
+    if (n <= cfg->max_rows) {                          // one pass of the decode kernels
+        if (block) return ASD_E_INVAL;
+        b.rows = n;
+        *out = b;
+        return ASD_OK;
+    }
+    const PfRules r = pf_rules(*cfg, p);
+    const int most = pf_block_rows(r, n);
+    b.n_blocks = (n + most - 1) / most;
+    if (block >= b.n_blocks) return ASD_E_INVAL;
+    b.row0 = block * most;
+    b.rows = n - b.row0 < most ? n - b.row0 : most;
+    const PfBlock how = pf_block(r, b.rows);
+    b.attn_rows = how.long_attn ? PF_ATT_LONG_ROWS : 16;
+    for (int i = 0; i < PF_CLASSES; ++i) { b.tile[i] = how.gemm[i].tile; b.slices[i] = how.gemm[i].ks; }
+    *out = b;
+    return ASD_OK;
 }
 
 const char* asd_last_error(const asd_engine* e) { return e ? e->err.c_str() : g_create_error.c_str(); }
@@ -1117,9 +1171,7 @@ int asd_create(const asd_config* cfg, void* device_arena, size_t arena_bytes, vo
     e->tune = cfg->debug_tune ? cfg->debug_tune : "";
     e->c.debug_tune = nullptr;              // (the caller's string is not kept; e->tune is the copy)
     const char* tune = e->tune.empty() ? nullptr : e->tune.c_str();
-    e->pf_qkv = pf_pick(tune, "pf_qkv", 4, 1); e->pf_o = pf_pick(tune, "pf_o", 4, 4);
-    { int v[2]; const int nv = tune_entry(tune, "pf_ring", v, 2); if (nv >= 1 && v[0] >= 0 && v[0] < kPfRings) { e->pf_ring_tune[0] = v[0]; if (nv == 2 && v[1] >= 1 && v[1] <= PF_MAX_KSPLIT) e->pf_ring_tune[1] = v[1]; } }
-    e->pf_gu = pf_pick(tune, "pf_gu", 4, 1); e->pf_down = pf_pick(tune, "pf_down", 4, 4);
+    e->pf = pf_rules(*cfg, p);
     e->g_qkv = p.g_qkv; e->g_o = p.g_o; e->g_gu = p.g_gu; e->g_down = p.g_down; e->g_lm = p.g_lm;
     e->g_qkv_rows = pick_qkv_rows(e->g_qkv, e->qkv_tiles, tune);
     e->att_gh1 = (cfg->debug_flags & ASD_DBG_ATT_GH1) != 0;

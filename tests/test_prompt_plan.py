@@ -1,0 +1,70 @@
+"""How a prompt is cut into blocks and which launches a block gets (asd_plan_prompt: host arithmetic): what every launch relies on
+holds over the lengths and shapes a cache can hold, not only at the benchmark's."""
+import pytest
+
+import asd_inputs as si
+import paper_2410_01028_amd as asd
+
+SMALL = si.Shape("small", 2, 256, 4, 2, 64, 256, 256, si.DT_BF16, 8, 8, 2)
+PADDED = si.Shape("padded", 2, 224, 6, 3, 32, 336, 320, si.DT_BF16, 8, 8, 2)      # d_model and d_ffn no multiples of 32
+SHAPES = [si.SHAPES["tiny"], si.SHAPES["7b"], si.SHAPES["13b"], si.SHAPES["70b"], SMALL, SMALL.with_(vocab=6016), SMALL.with_(vocab=16000),
+          PADDED, PADDED.with_(vocab=32000), SMALL.with_(d_ffn=16, vocab=16000), SMALL.with_(dtype=si.DT_F32, vocab=16000)]
+LENGTHS = sorted({17, 18, 31, 32, 33, 100, 511, 512, 513, 640, 641, 656, 1003, 1024, 1025, 1360, 2047, 2048, 2049, 2300, 4096, 4097, 8191, 8192}
+                 | set(range(19, 8192, 97)))
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"{s.name}-{s.d_ffn}-{s.vocab}-{s.dtype}")
+def test_blocks_cover_the_prompt_and_their_launches_fit(shape):
+    cfg = asd.make_config(shape, 8192)
+    kb = 32 if shape.dtype else 16
+    k_blocks = {"qkv": -(-shape.d_model // kb), "oproj": -(-shape.q_dim // kb), "gateup": -(-shape.d_model // kb), "down": -(-shape.d_ffn // kb)}
+    longest = max(b["rows"] for n in LENGTHS for b in asd.plan_prompt(cfg, n))
+    assert longest in (512, 1024, 2048)
+    for n in LENGTHS:
+        blocks = asd.plan_prompt(cfg, n)
+        assert [b["row0"] for b in blocks] == [sum(x["rows"] for x in blocks[:i]) for i in range(len(blocks))] and sum(b["rows"] for b in blocks) == n
+        assert len(blocks) == -(-n // longest) and all(1 <= b["rows"] <= longest for b in blocks)
+        assert all(b["rows"] == blocks[0]["rows"] and b["rows"] % 128 == 0 for b in blocks[:-1]) and blocks[-1]["rows"] <= blocks[0]["rows"]
+        if longest > 512 and len(blocks) > 1:
+            assert blocks[0]["rows"] < n / len(blocks) + 128                       # equal blocks, up to the 128-row step
+        for b in blocks:
+            chunks = -(-b["rows"] // 16)
+            assert b["slices"]["qkv"] == b["slices"]["gateup"] == 1
+            for g in ("oproj", "down"):
+                assert 1 <= b["slices"][g] <= min(8, k_blocks[g]) and b["slices"][g] * chunks * 16 <= 4096
+                if chunks <= 40:
+                    assert b["slices"][g] == min(4, k_blocks[g])                   # up to 640 rows one count for all
+            assert all(-1 <= t <= 15 for t in b["tile"].values())
+            assert b["attn_rows"] == (128 if shape.dtype and 4 * -(-b["rows"] // 128) * shape.n_heads >= 3 * 256 else 16)
+
+
+def test_long_blocks_need_room_in_the_staging_region_and_no_padding():
+    most = lambda s: max(b["rows"] for b in asd.plan_prompt(asd.make_config(s, 8192), 8192))
+    assert [most(s) for s in SHAPES] == [512, 2048, 2048, 2048, 512, 1024, 2048, 512, 512, 512, 512]
+
+
+def test_overrides_are_honoured_or_fall_back_as_stated():
+    plan = lambda shape, n, tune: asd.plan_prompt(asd.make_config(shape, n, debug_tune=tune), n)[0]
+    for v in range(16):
+        b = plan(SMALL, 300, f"pf_ring={v}")
+        assert set(b["tile"].values()) == {v} and b["slices"]["down"] == 4
+    b = plan(SMALL, 300, "pf_ring=3,8")
+    assert set(b["tile"].values()) == {3} and b["slices"]["oproj"] == b["slices"]["down"] == 8
+    b = plan(PADDED, 200, "pf_ring=0,7")               # six k-blocks do not make seven slices: O goes to the other kernel
+    assert b["tile"] == {"qkv": 0, "oproj": -1, "gateup": 0, "down": 0} and b["slices"]["oproj"] == 4 and b["slices"]["down"] == 7
+    b = plan(SMALL.with_(vocab=16000), 2048, "pf_ring=3,4")      # 4 x 2048 rows of partial sums do not fit
+    assert b["tile"]["oproj"] == b["tile"]["down"] == -1 and b["slices"]["down"] == 2
+    b = plan(SMALL.with_(vocab=16000), 1003, "pf_o=4,4,2")
+    assert b["tile"]["oproj"] == -1 and b["slices"]["oproj"] == 4 and b["tile"]["down"] >= -1
+    assert plan(SMALL.with_(vocab=16000), 2048, "pf_o=4,4,2")["slices"]["oproj"] == 2
+
+
+def test_short_prompts_and_bad_lengths():
+    cfg = asd.make_config(SMALL, 1000)                  # capacity 1024
+    assert asd.plan_prompt(cfg, 1) == [] and asd.plan_prompt(cfg, 16) == [] and len(asd.plan_prompt(cfg, 17)) == 1
+    for n in (0, -1, 1025):
+        with pytest.raises(asd.AsdError):
+            asd.plan_prompt(cfg, n)
+    cfg.d_model = 100
+    with pytest.raises(asd.AsdError):
+        asd.plan_prompt(cfg, 20)
