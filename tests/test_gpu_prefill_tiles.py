@@ -1,8 +1,9 @@
 """The ring kernel of the prompt GEMMs: every tile shape and K split against the chunked prompt pass (the decode kernels).
 
-The shape has output widths that no tile divides (feature blocks with a partly filled last tile, and fewer blocks than
-XCDs), and K ranges shorter than the ring; the prompts end inside a 16-row chunk, inside a workgroup's 8 (16) chunks, and inside a second block.  Both paths
-hold activations as two bf16 planes and sum in fp32; they differ in the order of the sums, and K / V values next to a bf16
+The first two shapes have output widths that no tile divides (feature blocks with a partly filled last tile, and fewer blocks than
+XCDs), and K ranges shorter than the ring; their workspace holds 512 rows.  The other two have a vocabulary large enough for the
+staging region to hold blocks of 1024 and 2048 rows.  The prompts end inside a 16-row chunk, inside a workgroup's 8 (16) chunks,
+and inside the first, second and third block.  Both paths hold activations as two bf16 planes and sum in fp32; they differ in the order of the sums, and K / V values next to a bf16
 rounding boundary then differ by one unit: TOL of the parity tests."""
 import numpy as np
 import pytest
@@ -16,17 +17,32 @@ pytestmark = pytest.mark.gpu
 # 24 QKV tiles, 14 residual tiles, 21 gate/up pairs; k-blocks 7 (odd), 6, 11 (odd, the last half padding)
 RAGGED = si.Shape("ragged", 2, 224, 6, 3, 32, 336, 320, si.DT_BF16, 8, 8, 2)
 EVEN = si.Shape("even", 2, 320, 4, 2, 64, 512, 320, si.DT_BF16, 8, 8, 2)
-CASES = [(RAGGED, "pf_ring=0", 81), (RAGGED, "pf_ring=1", 130), (RAGGED, "pf_ring=2,2", 97), (RAGGED, "pf_ring=3", 300), (RAGGED, "pf_ring=0,7", 200),
+LONG_1K = si.Shape("long-1k", 2, 256, 4, 2, 64, 256, 6016, si.DT_BF16, 8, 8, 2)
+LONG_2K = si.Shape("long-2k", 2, 256, 12, 4, 32, 256, 18944, si.DT_BF16, 8, 8, 2)       # from 1921 rows: the long-block attention
+LONGEST = {"ragged": 512, "even": 512, "long-1k": 1024, "long-2k": 2048}
+CASES = [(RAGGED, "pf_ring=0", 81), (RAGGED, "pf_ring=1", 130), (RAGGED, "pf_ring=2,2", 97), (RAGGED, "pf_ring=3", 300), (RAGGED, "pf_ring=0,6", 200),
          (RAGGED, "pf_ring=4", 17), (RAGGED, "pf_ring=5", 45), (RAGGED, "pf_ring=6", 63), (RAGGED, "pf_ring=7,1", 100), (RAGGED, "pf_ring=8", 33),
          (RAGGED, "pf_ring=9,3", 49), (RAGGED, "pf_ring=10", 81), (RAGGED, "pf_ring=11", 128), (RAGGED, "pf_ring=12", 32), (RAGGED, "pf_ring=13", 40),
          (RAGGED, "pf_ring=14", 64), (RAGGED, "pf_ring=15,5", 144), (EVEN, None, 18), (EVEN, None, 300), (EVEN, "pf_ring=1,8", 500),
-         (EVEN, "pf_ring=2,1", 144), (EVEN, "pf_ring=3,2", 1000), (EVEN, None, 2049), (EVEN, "pf_ring=3,1", 2300), (EVEN, "pf_o=4,4,2", 1500)]
+         (EVEN, "pf_ring=2,1", 144), (EVEN, "pf_ring=3,2", 1000), (EVEN, None, 2049), (EVEN, "pf_ring=3,1", 2300), (EVEN, "pf_o=4,4,2", 1500),
+         (LONG_1K, None, 641), (LONG_1K, None, 1003), (LONG_1K, None, 1025), (LONG_1K, None, 2300), (LONG_1K, "pf_ring=1,4", 1009),
+         (LONG_1K, "pf_o=4,4,2;pf_down=8,3,2;pf_qkv=4,1,2;pf_gu=4,1,2", 1700), (LONG_2K, None, 641), (LONG_2K, None, 1003), (LONG_2K, None, 2041),
+         (LONG_2K, None, 2049), (LONG_2K, None, 4001), (LONG_2K, None, 4200), (LONG_2K, "pf_ring=3,2", 2035), (LONG_2K, "pf_ring=2,1", 2300), (LONG_2K, "pf_ring=15,3", 1345),
+         (LONG_2K, "pf_ring=13", 700), (LONG_2K, "pf_o=4,4,2;pf_down=4,4,2;pf_qkv=4,1,2;pf_gu=4,1,2", 1985)]
 
 
 @pytest.mark.parametrize("shape,tune,n", CASES, ids=[f"{s.name}-{t}-{n}" for s, t, n in CASES])
 def test_prompt_gemm_tiles_agree_with_the_chunked_pass(shape, tune, n):
     W = list(si.all_tensors(shape, 6, 0.1))
-    eng = asd.Engine(asd.make_config(shape, n + 16, debug_tune=tune)).load(W)
+    cfg = asd.make_config(shape, n + 16, debug_tune=tune)
+    plan = asd.plan_prompt(cfg, n)
+    assert len(plan) == -(-n // LONGEST[shape.name])
+    if tune and tune.startswith("pf_ring"):
+        want = tune[len("pf_ring="):].split(",")
+        assert all(set(b["tile"].values()) == {int(want[0])} for b in plan)
+        assert len(want) == 1 or all(b["slices"][g] == int(want[1]) for b in plan for g in ("oproj", "down"))
+    assert shape is not LONG_2K or [b["attn_rows"] for b in plan] == [128 if b["rows"] > 1920 else 16 for b in plan]
+    eng = asd.Engine(cfg).load(W)
     ref = asd.Engine(asd.make_config(shape, n + 16)).load(W)
     toks = si.prompt(n, n + 3, shape.vocab)
     _, acs, lg = eng.prefill(toks[:n], want_logits=True)
@@ -45,29 +61,36 @@ def test_prompt_gemm_tiles_agree_with_the_chunked_pass(shape, tune, n):
     eng.close(); ref.close()
 
 
-@pytest.mark.parametrize("n", [17, 45, 100, 520, 640])
-def test_tile_shape_does_not_enter_the_bits(n):
-    """With equal K slices (up to 640 rows) a prompt's logits, cosines and cache are the same bits in every tile shape and in
+@pytest.mark.parametrize("shape,n", [(RAGGED, 17), (RAGGED, 45), (RAGGED, 100), (RAGGED, 520), (RAGGED, 640), (LONG_2K, 517), (LONG_2K, 640)],
+                         ids=lambda v: getattr(v, "name", str(v)))
+def test_tile_shape_does_not_enter_the_bits(shape, n):
+    """With equal K slices (blocks of up to 640 rows) a prompt's logits, cosines and cache are the same bits in every tile shape and in
     the four-wave kernel."""
-    toks = si.prompt(n, n, RAGGED.vocab)
-    W = list(si.all_tensors(RAGGED, 2, 0.1))
+    toks = si.prompt(n, n, shape.vocab)
+    W = list(si.all_tensors(shape, 2, 0.1))
     got = []
     for tune in ("pf_qkv=4,1,2;pf_o=4,4,2;pf_gu=4,1,2;pf_down=4,4,2", None, "pf_ring=0,4", "pf_ring=2,4", "pf_ring=3,4", "pf_ring=5,4", "pf_ring=11,4"):
-        eng = asd.Engine(asd.make_config(RAGGED, n + 16, debug_tune=tune)).load(W)
+        cfg = asd.make_config(shape, n + 16, debug_tune=tune)
+        assert all(b["slices"]["oproj"] == b["slices"]["down"] == 4 for b in asd.plan_prompt(cfg, n))
+        eng = asd.Engine(cfg).load(W)
         got.append((*eng.prefill(toks, want_logits=True), *eng.get_kv(1, 0, n)))
         eng.close()
     for g in got[1:]:
         assert all(np.array_equal(x, y) for x, y in zip(got[0], g))
 
 
-# head_dim, heads, KV heads, prompt: blocks with at least three 128-row attention workgroups to four compute units (256); prompts that
-# end inside a 16-row chunk, a wave's 32 rows, a workgroup's 128, and in a second block
-LONG = [(32, 32, 8, 1030), (64, 48, 6, 900), (128, 32, 32, 2100), (32, 64, 64, 513), (128, 64, 8, 2177)]
+# head_dim, heads, KV heads, prompt, query rows per attention workgroup in each (512-row) block: 128 from 192 such workgroups on.
+# Every head dim with and without grouped queries, last blocks that end inside a 16-row chunk, a wave's 32 rows and a
+# workgroup's 128, and blocks too short for the long-block kernel behind long ones
+LONG = [(32, 48, 48, 902, [128, 128]), (32, 64, 8, 949, [128, 128]), (64, 48, 6, 900, [128, 128]), (64, 56, 56, 985, [128, 128]),
+        (128, 48, 48, 911, [128, 128]), (128, 64, 8, 1001, [128, 128]), (128, 48, 8, 1412, [128, 128, 128]), (32, 64, 64, 513, [128, 16]),
+        (128, 64, 8, 2177, [128] * 4 + [16]), (32, 32, 8, 1030, [16, 16, 16])]
 
 
-@pytest.mark.parametrize("h,n_h,n_kv,n", LONG, ids=lambda v: str(v))
-def test_long_block_attention_agrees_with_the_chunked_pass(h, n_h, n_kv, n):
+@pytest.mark.parametrize("h,n_h,n_kv,n,attn_rows", LONG, ids=lambda v: str(v))
+def test_long_block_attention_agrees_with_the_chunked_pass(h, n_h, n_kv, n, attn_rows):
     shape = si.Shape("wide", 2, 256, n_h, n_kv, h, 256, 256, si.DT_BF16, 8, 8, 2)
+    assert [b["attn_rows"] for b in asd.plan_prompt(asd.make_config(shape, n + 16), n)] == attn_rows
     W = list(si.all_tensors(shape, 11, 0.1))
     # larger q and k weights: scores of several units, so that running maxima move and rows have few heavy keys
     W = [(t, l, si_scale(a, 3.0) if t in (si.T_WQ, si.T_WK) else a) for t, l, a in W]
@@ -94,6 +117,7 @@ def test_rows_whose_first_keys_all_score_minus_infinity():
     workgroups of 128 rows: the long-block kernel."""
     n, n_a = 450, 70
     shape = si.Shape("wide", 2, 256, 48, 48, 32, 256, 256, si.DT_BF16, 8, 8, 2)
+    assert [b["attn_rows"] for b in asd.plan_prompt(asd.make_config(shape, n + 16), n)] == [128]
     W = {(t, l): a.copy() for t, l, a in si.all_tensors(shape, 5, 0.1)}
     bf16 = lambda x: np.uint16(np.float32(x).view(np.uint32) >> 16)
     emb = W[si.T_EMBED, 0]
@@ -124,18 +148,24 @@ def si_scale(a, f):
     return ((x + 0x7fff + ((x >> 16) & 1)) >> 16).astype(np.uint16)
 
 
-def test_weights_survive_prompt_blocks_laid_over_the_staging_region():
+@pytest.mark.parametrize("shape,n", [(LONG_1K, 1021), (LONG_1K, 1500), (LONG_2K, 2043), (LONG_2K, 2600)], ids=lambda v: getattr(v, "name", str(v)))
+def test_weights_survive_prompt_blocks_laid_over_the_staging_region(shape, n):
     """Long blocks share memory with the region weight uploads go through: uploads and read-backs between prompt passes
     leave each other's results alone."""
-    W = list(si.all_tensors(EVEN, 3))
-    eng = asd.Engine(asd.make_config(EVEN, 1100)).load(W)
-    toks = si.prompt(1, 1050, EVEN.vocab)
-    a = eng.prefill(toks, want_logits=True)
+    W = list(si.all_tensors(shape, 3))
+    cfg = asd.make_config(shape, n + 16)
+    assert asd.plan_prompt(cfg, n)[0]["rows"] > 512
+    eng = asd.Engine(cfg).load(W)
+    toks = si.prompt(1, n, shape.vocab)
+    run = lambda: (*eng.prefill(toks, want_logits=True), *eng.get_kv(1, 0, n))
+    a = run()
     for t, l, arr in W:
         assert np.array_equal(eng.get_weight(t, l, arr.shape, arr.dtype), arr)
+    b = run()
     eng.load(W)
-    b = eng.prefill(toks, want_logits=True)
-    assert a[0] == b[0] and np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
+    c = run()
+    for x, y, z in zip(a, b, c):
+        assert np.array_equal(x, y) and np.array_equal(x, z)
     eng.close()
 
 
