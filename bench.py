@@ -363,9 +363,12 @@ def main():
         gu = pf_prof["gateup"]
         tf = gu["flops"] / gu["ms"] / 1e9
         planes = 2 if shape.dtype else 1
+        # (the kernel of most of the prompt's blocks)
+        ring = [b["tile"]["gateup"] >= 0 for b in asd.plan_prompt(eng.cfg, P)]
+        kernel = "pf_ring_kernel" if 2 * sum(ring) >= len(ring) else "pf_gemm_kernel"
         out["prefill"]["roofline"] = {"bound": "mfma", "achieved": round(tf, 1), "peak": 2500.0 if shape.dtype else 157.3, "unit": "TFLOP/s",
                                       "frac": round(tf / (2500.0 if shape.dtype else 157.3), 4),
-                                      "kernel": "pf_ring_kernel<BF16, PF_GU> (prompt-block gate/up projection + SiLU*mul)",
+                                      "kernel": f"{kernel}<{'BF16' if shape.dtype else 'F32'}, PF_GU> (prompt-block gate/up projection + SiLU*mul)",
                                       "flops_per_launch": gu["flops"] / gu["launches"], "avg_launch_us": round(gu["ms"] / gu["launches"] * 1e3, 2),
                                       "matrix_core_issue_frac": round(tf * planes / (2500.0 if shape.dtype else 157.3), 4)}
 
