@@ -596,8 +596,8 @@ __global__ __launch_bounds__(256, sizeof(typename T::elem) == 4 && H == 128 ? 1 
 // fill the compute unit's 160 KiB); a step waits for its half, one barrier, asks for the half four steps on (its slot was last
 // read one step ago) and computes.  Workgroups are numbered longest row block first; a KV head's workgroups get ids of one
 // residue mod 8, i.e. one XCD's L2, where the number of KV heads is a multiple of 8.
-// 7B, 8192-token prompt, per 2048-row block on average: 480 -> 285 us (0.97 PFLOP/s, two planes counted); 13B, 1003 rows: 90 -> 55 us; 70B,
-// 2048 rows: 373 -> 163 us.
+// 7B, 8192-token prompt, per 2048-row block on average: 480 -> 277 us (1.0 PFLOP/s, two planes counted; matrix cores busy in 45 % of the
+// cycles at 2.2 GHz); 13B, 1003 rows: 90 -> 55 us; 70B, 2048 rows: 373 -> 159 us.
 #define PF_ATT_LONG_ROWS 128
 template <int H>
 __global__ __launch_bounds__(256, 2) void pf_attn_long_kernel(const PfAttnArgs a) {

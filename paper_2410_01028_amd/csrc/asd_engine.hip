@@ -848,8 +848,9 @@ template <class T, int EPI> bool launch_pf_gemm_t(hipStream_t s, const PfCfg& g,
     return launch_pf_gemm_na<T, EPI, pf_na<EPI>()>(s, g, ks, a, n_chunks);
 }
 
-// Tile shapes of pf_ring_kernel: output tiles (for gate/up: pairs of tiles) and chunks per workgroup, and the time of a
-// k-block where the products set it (the large shapes, at the clock the card keeps under them; measured).
+// Tile shapes of pf_ring_kernel: output tiles (for gate/up: pairs of tiles) and chunks per workgroup, and the bf16 time of a
+// k-block of the large shapes, whose products set it (at the clock the card keeps under them; measured).  The others are priced by
+// what they take in, which is also what sets their time: gate/up on the last shape 0.74 us per k-block estimated and measured.
 struct PfRingTile { int FT, RC; float us_kb; };
 constexpr PfRingTile kPfRing[] = {{12, 8, 0.68f}, {16, 8, 0.76f}, {24, 8, 1.10f}, {16, 16, 1.32f},
                                   {3, 2, 0.f}, {3, 3, 0.f}, {3, 4, 0.f}, {4, 2, 0.f}, {4, 3, 0.f}, {4, 4, 0.f}, {4, 6, 0.f}, {4, 8, 0.f},
@@ -860,11 +861,19 @@ constexpr int kPfRings = sizeof kPfRing / sizeof kPfRing[0], kPfBig = 4;      //
 // they come from (7 to 32 KiB per k-block measured 0.18 to 0.71 us), plus 4 us per round for filling the ring and the
 // epilogue.  pf_gemm_kernel: up to three workgroups share a compute unit, which then takes in about 57 KiB per us, but one alone
 // needs 0.5 us per k-block (its prefetch is two k-blocks deep).  It stays the better one where its small tile leaves
-// less of the chip idle: O / down of the 13B shape at 300 rows 44 / 100 us against 57 / 125 us.  Split-K launches: the
-// partial sums' way through memory (written and read back, about 5 TB/s).  Up to PF_FIXED_SLICES chunks the K slices are the
-// same whatever the choice: such blocks need them all to give every compute unit work, and a result then depends neither
-// on the shape nor on the block's length.  Longer blocks fill the chip with fewer (13B at 1003 rows, O and down: 94 and 227 us
-// with two slices, 120 and 300 us with four).
+// less of the chip idle, between whole rounds of the ring's tiles: 7B gate/up at 272 rows 105 us against 118 of the ring's best tile
+// and at 700 rows 203 against 228, 13B O / down at 300 rows 44 / 98 against 47 / 103, 70B gate/up at 272 rows 481 against 509.
+// Split-K launches: the partial sums' way through memory (written and read back, about 5 TB/s).
+// The estimate is a few per cent off at most lengths and misses more at some: 7B QKV at 800 rows takes the four-wave kernel, 193 us, where
+// the third tile needs 148; 13B gate/up at 300 rows likewise, 182 against 155.  In fp32 two waves on one SIMD are priced as if
+// each had it alone, and the four-wave kernel's constant (1.1 us per k-block) is that of one workgroup to a unit: from 100 rows on the choice costs up
+// to half again what the best tile would (7B down at 144 rows 167 us against 115), and at 200 rows QKV takes 244 us where the four-wave
+// kernel needs 216; a whole prompt is faster at every length measured (17 to 1100 rows) than it was on the four-wave kernel alone.
+// Up to PF_FIXED_SLICES chunks (640 rows) the K slices are the four-wave kernel's for every choice, so that the order of the sums,
+// hence every bit, of a contraction depends neither on the kernel nor on its tile, and the contractions of such blocks kept their bits
+// when the ring kernel came in.  It is not the fastest count everywhere: 13B down at 48 rows 39 us, with six slices 32, at
+// 80 rows 61, with three 44; 7B down at 48 rows 24 us, with eight 22.5, at 300 rows 63 us and nothing better.  Longer blocks take what the estimate says
+// (13B at 1003 rows, O and down: 94 and 227 us with two slices, 120 and 300 us with four).
 constexpr int PF_FIXED_SLICES = 40;
 PfPick pf_pick_gemm(const PfRules& r, int cls, int n_chunks) {
     const PfCfg& g = r.cfg[cls];

@@ -37,7 +37,7 @@ struct GemmArgs {
     int64_t w_tile_stride, w_kb_stride;   // fragment (KiB) strides of the weight layout: tile-major {KB, 1}, k-major {1, tiles}
     int32_t k_interleave;    // how the waves of a workgroup split K
     int32_t M;               // rows in use
-    int32_t RS;              // row stride of every activation buffer in this pass (power of two >= M)
+    int32_t RS;              // row stride of every activation buffer in this pass (>= M)
     float* ssq;              // [16] ||residual row||^2 as of the last finished cosine tap
     float inv_d, eps;
     // input side of QKV / GU / LM: partials of the kernel that produced the residual

@@ -4,13 +4,13 @@
 // The prompt is processed in blocks of up to 2048 rows, layer by layer, so every weight is read once per
 // block instead of once per 16 rows.  Activations of a block are kept as 16-row chunks, each chunk in the same
 // tiled layout the decode kernels use with a row stride of 16 ([K/KE][16][KE], hi and lo planes for bf16):
-// one (chunk, k-block) fragment is one contiguous KiB that a wave loads with one instruction, and the decode
-// attention kernel runs unchanged on a chunk.
+// one (chunk, k-block) fragment is one contiguous KiB that a wave loads with one instruction, and the prompt attention kernels
+// use the decode kernel's fragments.
 //
 // pf_ring_kernel: a tile of up to 24 weight tiles x 8 chunks (16 x 16 for long blocks) per workgroup, both operands brought
 // into an LDS ring by direct-to-LDS loads; see its own comment.  The kernel and tile of a launch are the ones with the
 // smallest estimated time.
-// pf_gemm_kernel (where the estimate of the ring's tiles is no better): a workgroup of NW waves owns NW*NA weight tiles (16 output features each) x NC chunks of
+// pf_gemm_kernel (where the ring's tiles are estimated no better, between whole rounds of their workgroups): a workgroup of NW waves owns NW*NA weight tiles (16 output features each) x NC chunks of
 // rows and, with a K split, one slice of K.  Per k-block the waves stage the NC chunks' activation fragments
 // in LDS (double buffered, one barrier per k-block); each wave streams its own NA weight fragments from
 // global memory and feeds NA*NC accumulators.  Workgroups that share weights (same features, other rows)
@@ -245,9 +245,10 @@ __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const
 }
 
 // ---- the LDS ring kernel of the prompt GEMMs
-// What bounds the large bf16 prompt GEMMs is the card's power, not the issue of matrix-core work: a loop of matrix-core
-// instructions on random operands in registers runs at 2.1 GHz and 2.1 PFLOP/s, and every byte moved per product takes its
-// share of the clock.  So both operands are read once per workgroup into LDS (no fragment passes through a register on
+// What bounds the large bf16 prompt GEMMs: the clock the card keeps under them, and the cycles in which no product issues.  A loop of
+// matrix-core instructions on random operands in registers, nothing else, runs at 2.06 GHz and 2.1 PFLOP/s (on zeros: 2.4 GHz, 2.46
+// PFLOP/s); this kernel keeps the matrix cores busy in 57 to 72 % of the cycles at 2.15 to 1.8 GHz, the busier the lower the clock (2048 rows:
+// 7B gate/up 61 % at 2.15 GHz, 70B gate/up 72 % at 1.84 GHz).  Both are served by moving fewer bytes per product.  So both operands are read once per workgroup into LDS (no fragment passes through a register on
 // its way there), the tile per workgroup is as large as the launch's balance allows, and a wave's tile (NT weight tiles x
 // NC chunks, both planes) reads NT + 2 NC fragments for 2 NT NC products.
 //   FW x RW waves share a k-block, FW over the weight tiles, RW over the chunks.  An output is one wave's sum over its K
@@ -258,9 +259,9 @@ __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const
 // fills with products; issued back to back they cost more than the products themselves.  PF: the next stage's fragments are read into a second
 // set of registers during this stage's products (all tiles but the largest, whose accumulators leave no room).
 // Products run with one weight fragment held over NC chunks in alternating direction (2 % less time than the other
-// order).  Measured (two planes counted, 7B): QKV 512 rows 95 -> 83 us, gate/up 158 -> 146 us (1.26 PFLOP/s), down 79 -> 74 us;
-// 2048 rows: gate/up 4 x 158 -> 540 us (1.37 PFLOP/s), QKV 4 x 95 -> 295 us, down 4 x 79 -> 262 us (1.41 PFLOP/s, which
-// is what the vendor library's largest square product reaches here).
+// order).  Measured (two planes counted, 7B): QKV 512 rows 95 -> 91 us, gate/up 158 -> 143 us (1.29 PFLOP/s), down 79 -> 71 us;
+// 2048 rows: gate/up 4 x 158 -> 537 us (1.38 PFLOP/s), QKV 4 x 95 -> 305 us, down 4 x 79 -> 250 us (1.48 PFLOP/s; the
+// vendor library's largest square product reaches 1.40 here).
 template <int NP, int NT, int NC, int FW, int RW, int S> struct PfRing {
     static constexpr int W = FW * RW;                               // waves
     static constexpr int FT = FW * NT, RC = RW * NC;                // weight tiles and chunks per workgroup
