@@ -19,19 +19,20 @@ RAGGED = si.Shape("ragged", 2, 224, 6, 3, 32, 336, 320, si.DT_BF16, 8, 8, 2)
 EVEN = si.Shape("even", 2, 320, 4, 2, 64, 512, 320, si.DT_BF16, 8, 8, 2)
 LONG_1K = si.Shape("long-1k", 2, 256, 4, 2, 64, 256, 6016, si.DT_BF16, 8, 8, 2)
 LONG_2K = si.Shape("long-2k", 2, 256, 12, 4, 32, 256, 18944, si.DT_BF16, 8, 8, 2)       # from 1921 rows: the long-block attention
-LONGEST = {"ragged": 512, "even": 512, "long-1k": 1024, "long-2k": 2048}
+LEAST = si.Shape("least", 1, 16, 1, 1, 32, 16, 16, si.DT_BF16, 8, 8, 2)      # one tile, one k-block, half of it padding
+LONGEST = {"least": 512, "ragged": 512, "even": 512, "long-1k": 1024, "long-2k": 2048}
 CASES = [(RAGGED, "pf_ring=0", 81), (RAGGED, "pf_ring=1", 130), (RAGGED, "pf_ring=2,2", 97), (RAGGED, "pf_ring=3", 300), (RAGGED, "pf_ring=0,6", 200),
          (RAGGED, "pf_ring=4", 17), (RAGGED, "pf_ring=5", 45), (RAGGED, "pf_ring=6", 63), (RAGGED, "pf_ring=7,1", 100), (RAGGED, "pf_ring=8", 33),
          (RAGGED, "pf_ring=9,3", 49), (RAGGED, "pf_ring=10", 81), (RAGGED, "pf_ring=11", 128), (RAGGED, "pf_ring=12", 32), (RAGGED, "pf_ring=13", 40),
          (RAGGED, "pf_ring=14", 64), (RAGGED, "pf_ring=15,5", 144), (EVEN, None, 18), (EVEN, None, 300), (EVEN, "pf_ring=1,8", 500),
          (EVEN, "pf_ring=2,1", 144), (EVEN, "pf_ring=3,2", 1000), (EVEN, None, 2049), (EVEN, "pf_ring=3,1", 2300), (EVEN, "pf_o=4,4,2", 1500),
-         (LONG_1K, None, 641), (LONG_1K, None, 1003), (LONG_1K, None, 1025), (LONG_1K, None, 2300), (LONG_1K, "pf_ring=1,4", 1009),
+         (LEAST, None, 17), (LEAST, None, 600), (LEAST.with_(dtype=si.DT_F32), None, 45), (LONG_1K, None, 641), (LONG_1K, None, 1003), (LONG_1K, None, 1025), (LONG_1K, None, 2300), (LONG_1K, "pf_ring=1,4", 1009),
          (LONG_1K, "pf_o=4,4,2;pf_down=8,3,2;pf_qkv=4,1,2;pf_gu=4,1,2", 1700), (LONG_2K, None, 641), (LONG_2K, None, 1003), (LONG_2K, None, 2041),
          (LONG_2K, None, 2049), (LONG_2K, None, 4001), (LONG_2K, None, 4200), (LONG_2K, "pf_ring=3,2", 2035), (LONG_2K, "pf_ring=2,1", 2300), (LONG_2K, "pf_ring=15,3", 1345),
          (LONG_2K, "pf_ring=13", 700), (LONG_2K, "pf_o=4,4,2;pf_down=4,4,2;pf_qkv=4,1,2;pf_gu=4,1,2", 1985)]
 
 
-@pytest.mark.parametrize("shape,tune,n", CASES, ids=[f"{s.name}-{t}-{n}" for s, t, n in CASES])
+@pytest.mark.parametrize("shape,tune,n", CASES, ids=[f"{s.name}-{s.dtype}-{t}-{n}" for s, t, n in CASES])
 def test_prompt_gemm_tiles_agree_with_the_chunked_pass(shape, tune, n):
     W = list(si.all_tensors(shape, 6, 0.1))
     cfg = asd.make_config(shape, n + 16, debug_tune=tune)
@@ -151,7 +152,7 @@ def si_scale(a, f):
 @pytest.mark.parametrize("shape,n", [(LONG_1K, 1021), (LONG_1K, 1500), (LONG_2K, 2043), (LONG_2K, 2600)], ids=lambda v: getattr(v, "name", str(v)))
 def test_weights_survive_prompt_blocks_laid_over_the_staging_region(shape, n):
     """Long blocks share memory with the region weight uploads go through: uploads and read-backs between prompt passes
-    leave each other's results alone."""
+    leave each other's results alone, and so does whatever the arena held before (rows past the prompt's end stay unread)."""
     W = list(si.all_tensors(shape, 3))
     cfg = asd.make_config(shape, n + 16)
     assert asd.plan_prompt(cfg, n)[0]["rows"] > 512
@@ -164,8 +165,11 @@ def test_weights_survive_prompt_blocks_laid_over_the_staging_region(shape, n):
     b = run()
     eng.load(W)
     c = run()
-    for x, y, z in zip(a, b, c):
-        assert np.array_equal(x, y) and np.array_equal(x, z)
+    eng.close()
+    eng = asd.Engine(cfg, arena_fill=0xFF).load(W)
+    d = run()
+    for x, *others in zip(a, b, c, d):
+        assert all(np.array_equal(x, y) for y in others)
     eng.close()
 
 
