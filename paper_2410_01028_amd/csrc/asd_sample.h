@@ -17,8 +17,8 @@
 // at once (a thread-contiguous split touched 64 lines per load); sums go through shuffles and one LDS exchange of the 16
 // waves' totals instead of a halving tree with a barrier per level; only the one wave that the drawn point falls into
 // walks its tiles again.  The softmax statistics of a verification pass's rows are a launch of their own, one
-// workgroup per row, instead of one workgroup walking row after row.  7B vocabulary (32000): draft draw 33 -> 12 us, acceptance of four
-// drafts 92 -> 7 + 16 us.
+// workgroup per row, instead of one workgroup walking row after row.  7B vocabulary (32000): draft draw 33 -> 13 us, acceptance of four
+// drafts 92 -> 7 + 15 us.
 #pragma once
 #include "asd_common.h"
 #include "asd_misc.h"
@@ -187,9 +187,12 @@ SAMPLE_HD int sample_of_four(const float (&e)[4], double z, double t) {
     return pick >= 0 ? pick : pos;
 }
 
-// The last index with a positive weight, or -1 (every thread)
-template <int TILES, class F>
-__device__ __forceinline__ int blk_last_positive(const RowTiles<TILES>& r, F w, double* red) {
+// The last index with a positive weight, or -1 (every thread).  Off the usual path: the row is read anew, because keeping the caller's tiles for
+// it spilled registers of the usual path (draft draw 13.1 -> 14.3 us).
+template <class F>
+__device__ __forceinline__ int blk_last_positive(const float* row, int V, F w, double* red) {
+    RowTiles<0> r;
+    r.load(row, V);
     int best = -1;
 #pragma unroll 1
     for (int k = 0; k < r.n; ++k) {
@@ -216,7 +219,8 @@ __device__ __forceinline__ int blk_sample(const RowTiles<TILES>& r, F w, const T
     double total = 0.0;
 #pragma unroll
     for (int i = 0; i < SAMPLE_WAVES; ++i) total += red[i];
-    if (!(total > 0.0)) return total == 0.0 ? -1 : blk_last_positive(r, w, red);
+    if (total == 0.0) return -1;
+    if (__builtin_expect(!(total > 0.0), 0)) return blk_last_positive(r.row, r.V, w, red);
     const double t = u * total;
     IntervalSearch waves(t, 0.0);
 #pragma unroll
