@@ -86,8 +86,10 @@ for n_layers in (1, 4, 7, 32, 80):
         asd.admg2(rng.uniform(0.9, 1, 2 * n_layers).astype(np.float32), 0.95, 3, 1, True, 0.97, True)
 for name in ("tiny", "7b", "13b", "7b-long", "70b"):
     s = si.SHAPES[name]
-    for tune in (None, "qkv=1,8,1,1;o=1,16,0,0", "qkv_rows=2;pf_gu=4,1,2", "garbage", "qkv=,,,", ";;=;", "lm=2,8,1,1" * 40):
+    for tune in (None, "qkv=1,8,1,1;o=1,16,0,0", "qkv_rows=2;pf_gu=4,1,2", "garbage", "pf_ring=3,8", "pf_ring=,", "pf_ring=99,99", "qkv=,,,", ";;=;", "lm=2,8,1,1" * 40):
         assert asd.arena_bytes(asd.make_config(s, 4096, 64, debug_tune=tune)) > 0
+        for n in (1, 16, 17, 640, 641, 2049, 4096):
+            assert sum(b["rows"] for b in asd.plan_prompt(asd.make_config(s, 4096, 64, debug_tune=tune), n)) in (0, n)
 assert asd.arena_bytes(asd.make_config(si.SHAPES["tiny"], asd.MAX_SEQ + 64, 64)) == 0
 assert asd.arena_bytes(asd.make_config(si.SHAPES["tiny"], 64, 48)) == 0
 h = ctypes.c_void_p()
