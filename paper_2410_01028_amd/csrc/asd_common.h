@@ -104,10 +104,10 @@ template <> __device__ __forceinline__ void mma16<F32>(f32x4& acc, const u32x4& 
 
 // One fragment (1 KiB: a weight tile's or a chunk plane's k-block, a K or V^T fragment of the cache) from global memory into LDS, 16 bytes per lane, without
 // passing through registers.  p, the number of bytes that may be read from there (0: nothing is read, zeros come back) and
-// the LDS address are wave-uniform.
-__device__ __forceinline__ void frag_to_lds(const char* p, uint32_t bytes, u32x4* lds, int lane) {
+// the LDS address are wave-uniform.  ONCE: nobody else reads the fragment (a non-temporal load).
+template <bool ONCE = false> __device__ __forceinline__ void frag_to_lds(const char* p, uint32_t bytes, u32x4* lds, int lane) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)p, 0, bytes, 0x00020000),
-                                             (__attribute__((address_space(3))) void*)lds, 16, lane * 16, 0, 0, 0);
+                                             (__attribute__((address_space(3))) void*)lds, 16, lane * 16, 0, 0, ONCE ? 2 : 0);
 }
 // wait until at most N vector-memory requests are outstanding; LGKM: and every LDS read has returned
 template <int N, bool LGKM> __device__ __forceinline__ void wait_vm() {

@@ -111,6 +111,7 @@ struct asd_engine {
     float *pf_xres, *pf_raw, *pf_ssq, *pf_rscale, *pf_cos_rows;
     void *pf_xb, *pf_q, *pf_attn_out, *pf_hmid;
     int pf_rows;                        // most rows of a prompt block
+    int64_t cf_d, cf_q, cf_f;           // fragments from a chunk's activations to the next chunk's
     PfRules pf;
     // launch shapes
     GemmCfg g_qkv, g_o, g_gu, g_down, g_lm;
@@ -273,6 +274,7 @@ struct Plan {
     size_t pf_xres, pf_raw, pf_ssq, pf_rscale, pf_cos_rows, pf_xb, pf_q, pf_attn_out, pf_hmid;
     int es, KE, KBd, KBq, KBf, n_pages, nc_stride, qkv_tiles;
     int pf_rows;                                    // most rows of a prompt block
+    int cf_d, cf_q, cf_f;                           // fragments from a chunk's activations to the next chunk's
     GemmCfg g_qkv, g_o, g_gu, g_down, g_lm;
 };
 
@@ -347,28 +349,37 @@ Plan make_plan(const asd_config& c) {
     // upload or read-back uses, and only if they fit into what 512 rows and the staging region take anyway (the arena does
     // not grow) and no activation has k padding (padding is cleared once, when the engine is created, and an upload
     // would leave other bytes there).
-    auto take_pf = [&](size_t R) {
+    // Fragments (KiB) from a chunk to the next: the k-blocks, made odd.  A workgroup asks for the same k-block of all its chunks
+    // at once, and an XCD's L2 spreads addresses over its channels every 4 KiB: with 128 or 256 k-blocks between chunks
+    // (d_model 4096, 8192) all of them fall on the same quarter of the channels.  QKV at 512 rows, tile 15 and tile 12: 70B 135 -> 138 and
+    // 144 -> 126 us, 7B at 300 rows with tile 11 73 -> 62 us.  Long blocks that fit only without the extra KiB do without.
+    // In fp32, whose products hide the requests, it gains nothing (256 k values, 4 layers, 30 rows: 173 us with it, 168 without).
+    auto take_pf = [&](size_t R, int odd) {
         p.pf_rows = (int)R;
+        p.cf_d = p.KBd | odd; p.cf_q = p.KBq | odd; p.cf_f = p.KBf | odd;
         p.pf_xres = take(R * c.d_model * 4);
         p.pf_raw = take((size_t)PF_RAW_ROWS * c.d_model * 4);
         p.pf_ssq = take(R * 4);
         p.pf_rscale = take(R * 4);
         p.pf_cos_rows = take((size_t)2 * c.n_layers * R * 4);
-        p.pf_xb = take(R / 16 * p.KBd * frag * NPL);
-        p.pf_q = take(R / 16 * p.KBq * frag * NPL);
-        p.pf_attn_out = take(R / 16 * p.KBq * frag * NPL);
-        p.pf_hmid = take(R / 16 * p.KBf * frag * NPL);
+        p.pf_xb = take(R / 16 * p.cf_d * frag * NPL);
+        p.pf_q = take(R / 16 * p.cf_q * frag * NPL);
+        p.pf_attn_out = take(R / 16 * p.cf_q * frag * NPL);
+        p.pf_hmid = take(R / 16 * p.cf_f * frag * NPL);
     };
-    take_pf(PF_MIN_ROWS);
+    take_pf(PF_MIN_ROWS, c.dtype == ASD_DT_BF16);
     const size_t end = off;
-    if (c.dtype == ASD_DT_BF16 && c.d_model % kblk == 0 && qd % kblk == 0 && c.d_ffn % kblk == 0)
-        for (size_t R = PF_MAX_ROWS; R > PF_MIN_ROWS; R /= 2) {
-            const Plan keep = p;
-            off = p.staging;
-            take_pf(R);
-            if (off <= end) break;
-            p = keep;
-        }
+    if (c.dtype == ASD_DT_BF16 && c.d_model % kblk == 0 && qd % kblk == 0 && c.d_ffn % kblk == 0) {
+        bool fits = false;
+        for (size_t R = PF_MAX_ROWS; R > PF_MIN_ROWS && !fits; R /= 2)
+            for (int odd = 1; odd >= 0 && !fits; --odd) {
+                const Plan keep = p;
+                off = p.staging;
+                take_pf(R, odd);
+                fits = off <= end;
+                if (!fits) p = keep;
+            }
+    }
     off = end;
     p.total = off;
     return p;
@@ -848,83 +859,92 @@ template <class T, int EPI> bool launch_pf_gemm_t(hipStream_t s, const PfCfg& g,
     return launch_pf_gemm_na<T, EPI, pf_na<EPI>()>(s, g, ks, a, n_chunks);
 }
 
-// Tile shapes of pf_ring_kernel: output tiles (for gate/up: pairs of tiles) and chunks per workgroup, and the bf16 time of a
-// k-block of the large shapes, whose products set it (at the clock the card keeps under them; measured).  The others are priced by
-// what they take in, which is also what sets their time: gate/up on the last shape 0.74 us per k-block estimated and measured.
-struct PfRingTile { int FT, RC; float us_kb; };
-constexpr PfRingTile kPfRing[] = {{12, 8, 0.68f}, {16, 8, 0.76f}, {24, 8, 1.10f}, {16, 16, 1.32f},
-                                  {3, 2, 0.f}, {3, 3, 0.f}, {3, 4, 0.f}, {4, 2, 0.f}, {4, 3, 0.f}, {4, 4, 0.f}, {4, 6, 0.f}, {4, 8, 0.f},
-                                  {8, 2, 0.f}, {8, 3, 0.f}, {8, 4, 0.f}, {8, 8, 0.f}};
-constexpr int kPfRings = sizeof kPfRing / sizeof kPfRing[0], kPfBig = 4;      // the first kPfBig: gate/up tiles counted singly
-// The kernel and shape with the least estimated time.  pf_ring_kernel: rounds of workgroups (one to a compute unit) on the
-// busiest XCD, times a workgroup's k-blocks at the rate a compute unit takes fragments in, about 43 KiB per us whichever cache level
-// they come from (7 to 32 KiB per k-block measured 0.18 to 0.71 us), plus 4 us per round for filling the ring and the
-// epilogue.  pf_gemm_kernel: up to three workgroups share a compute unit, which then takes in about 57 KiB per us, but one alone
-// needs 0.5 us per k-block (its prefetch is two k-blocks deep).  It stays the better one where its small tile leaves
-// less of the chip idle, between whole rounds of the ring's tiles: 7B gate/up at 272 rows 105 us against 118 of the ring's best tile
-// and at 700 rows 203 against 228, 13B O / down at 300 rows 44 / 98 against 47 / 103, 70B gate/up at 272 rows 481 against 509.
-// Split-K launches: the partial sums' way through memory (written and read back, about 5 TB/s).
-// The estimate is a few per cent off at most lengths and misses more at some: 7B QKV at 800 rows takes the four-wave kernel, 193 us, where
-// the third tile needs 148; 13B gate/up at 300 rows likewise, 182 against 155.  In fp32 two waves on one SIMD are priced as if
-// each had it alone, and the four-wave kernel's constant (1.1 us per k-block) is that of one workgroup to a unit: from 100 rows on the choice costs up
-// to half again what the best tile would (7B down at 144 rows 167 us against 115), and at 200 rows QKV takes 244 us where the four-wave
+// pf_ring_kernel's shapes on the host: output tiles (for gate/up pairs of tiles) and chunks per workgroup, and the time of a
+// k-block: us0 + us1 x the share of the chip that is busy (the clock falls and L2 fills with the workgroups that run).
+struct PfRingTile { int FT, RC; float us0, us1; };
+constexpr int kPfRings = 16;
+constexpr float kPfRawUs[kPfRings][2] = {{0.477f, 0.217f}, {0.300f, 0.222f}, {0.864f, 0.368f}, {0.104f, 0.f}, {0.106f, 0.023f}, {0.127f, 0.026f},
+                                         {0.209f, 0.f}, {0.197f, 0.053f}, {0.193f, 0.f}, {0.199f, 0.124f}, {0.224f, 0.171f}, {0.262f, 0.230f},
+                                         {0.298f, 0.154f}, {0.333f, 0.208f}, {0.253f, 0.158f}, {0.327f, 0.181f}};
+constexpr float kPfPairUs[kPfRings][2] = {{0.520f, 0.180f}, {0.785f, 0.227f}, {0.837f, 0.443f}, {0.233f, 0.060f}, {0.180f, 0.f}, {0.212f, 0.f},
+                                          {0.174f, 0.f}, {0.246f, 0.f}, {0.386f, 0.f}, {0.229f, 0.087f}, {0.263f, 0.115f}, {0.293f, 0.166f},
+                                          {0.396f, 0.003f}, {0.425f, 0.073f}, {0.426f, 0.027f}, {0.410f, 0.110f}};
+#define PFR(v, nt, nc, fw, rw, nl, pf) {nt * fw, nc * rw, kPfRawUs[v][0], kPfRawUs[v][1]},
+constexpr PfRingTile kPfRing[kPfRings] = {PF_RING_SHAPES(PFR)};
+#undef PFR
+#define PFR(v, nt, nc, fw, rw, nl, pf) {nt * fw / 2, nc * rw, kPfPairUs[v][0], kPfPairUs[v][1]},
+constexpr PfRingTile kPfRingPairs[kPfRings] = {PF_RING_PAIR_SHAPES(PFR)};
+#undef PFR
+// fp32: what the products take (128 cycles of a SIMD each, eight times a bf16 pair), or what a compute unit takes in
+#define PFR(v, nt, nc, fw, rw, nl, pf) {nt * fw, nc * rw, pf_f32_us(nt * fw, nc * rw, fw * rw), 0.f},
+constexpr float pf_f32_us(int tiles, int chunks, int waves) {
+    const float mfma = tiles * chunks * 0.061f / waves, in = (tiles + F32::NP * chunks) / 43.f;
+    return mfma > in ? mfma : in;
+}
+constexpr PfRingTile kPfRingF32[kPfRings] = {PF_RING_F32_SHAPES(PFR, 1)};
+#undef PFR
+#define PFR(v, nt, nc, fw, rw, nl, pf) {nt * fw / 2, nc * rw, pf_f32_us(nt * fw, nc * rw, fw * rw), 0.f},
+constexpr PfRingTile kPfRingPairsF32[kPfRings] = {PF_RING_F32_SHAPES(PFR, 2)};
+#undef PFR
+const PfRingTile& pf_ring_tile(bool f32, bool pairs, int v) { return f32 ? (pairs ? kPfRingPairsF32 : kPfRingF32)[v] : (pairs ? kPfRingPairs : kPfRing)[v]; }
+// The kernel, shape and K slices with the least estimated time.  pf_ring_kernel: rounds of workgroups (one to a compute unit) on the busiest XCD, times
+// a workgroup's k-blocks at the shape's rate, but no less than the weights take from HBM at 6.1 TB/s; 4 us per round for filling the ring and the epilogue; for
+// split-K launches the partial sums, 0.5 us per MB (written, read back).  pf_gemm_kernel: up to three workgroups share a compute unit, so its time grows with the load
+// and not by rounds, which is where it has the better of the ring: between whole rounds of the larger tiles (7B gate/up at 300 rows 108 us against 117,
+// at 700 rows 197 against 204; 13B O at 448 rows 49 against 55).  The bf16 rates are fitted to some 8000 measurements on the 7B, 13B and 70B matrices (20 to 256 rows: each shape by itself; 272 to 2048 rows: inside prompt passes that
+// follow each other, at the clock that such passes keep): near the best time the estimate is off by 3 to 10 %, and what it takes costs 1 % more than the best on average, at worst 18 %
+// (7B gate/up, 300 rows: 127 us against 108; 13B down, 160 rows: 68 against 58; 1700 rows: 440 against 381).
+// In fp32 two waves on one SIMD are priced as if each had it alone, and the four-wave kernel's constant (1.1 us per k-block) is that of one workgroup to a unit: from
+// 100 rows on the choice costs up to half again what the best tile would (7B down at 144 rows 167 us against 115), and at 200 rows QKV takes 244 us where the four-wave
 // kernel needs 216; a whole prompt is faster at every length measured (17 to 1100 rows) than it was on the four-wave kernel alone.
-// Up to PF_FIXED_SLICES chunks (640 rows) the K slices are the four-wave kernel's for every choice, so that the order of the sums,
-// hence every bit, of a contraction depends neither on the kernel nor on its tile, and the contractions of such blocks kept their bits
-// when the ring kernel came in.  It is not the fastest count everywhere: 13B down at 48 rows 39 us, with six slices 32, at
+// Up to PF_FIXED_SLICES chunks (640 rows) the K slices are the same for every choice, so that the order of the sums,
+// hence every bit, of a contraction depends neither on the kernel nor on its tile.  It is not the fastest count everywhere: 13B down at 48 rows 39 us, with six slices 32, at
 // 80 rows 61, with three 44; 7B down at 48 rows 24 us, with eight 22.5, at 300 rows 63 us and nothing better.  Longer blocks take what the estimate says
 // (13B at 1003 rows, O and down: 94 and 227 us with two slices, 120 and 300 us with four).
 constexpr int PF_FIXED_SLICES = 40;
 PfPick pf_pick_gemm(const PfRules& r, int cls, int n_chunks) {
     const PfCfg& g = r.cfg[cls];
-    const int epi = cls == PF_C_QKV ? PF_QKV : cls == PF_C_GU ? PF_GU : PF_RAW, n_tiles = r.n_tiles[cls], KB = r.KB[cls];
-    const bool f32 = r.dtype == ASD_DT_F32;
-    const int units = device_units() / 8 > 0 ? device_units() / 8 : 1, np = f32 ? F32::NP : BF16::NP;
-    const int ks4 = epi == PF_RAW ? pf_old_slices(g, KB, n_chunks) : 1;
+    const bool pairs = cls == PF_C_GU, raw = cls == PF_C_O || cls == PF_C_DOWN, f32 = r.dtype == ASD_DT_F32;
+    const int n_tiles = r.n_tiles[cls], KB = r.KB[cls], units = device_units() / 8 > 0 ? device_units() / 8 : 1;
+    const int ks4 = raw ? pf_old_slices(g, KB, n_chunks) : 1;
     if (g.forced) return {-1, ks4};
-    auto raw_us = [&](int ks) { return epi == PF_RAW ? ks * (2.f * n_chunks * 16 * n_tiles * 16 * 4 / 5e6f) : 0.f; };
+    const float hbm_us = (float)n_tiles * (pairs ? 2 : 1) * KB * 1024 / 6.1e6f, slice_us = raw ? (f32 ? 4e-7f : 5e-7f) * n_chunks * 16 * n_tiles * 16 * 4 : 0.f;
     PfPick best{-1, ks4};
     float best_us = 3e38f;
     if (r.ring_tile < 0) {
-        const int na = epi == PF_GU ? 2 : epi == PF_QKV ? pf_qkv_na(g, n_tiles, n_chunks) : 4, per = 4 * na;
-        const float wgs = (float)(((n_tiles + per - 1) / per + 7) / 8 * ((n_chunks + g.NC - 1) / g.NC) * best.ks) / units;
-        const float on_unit = wgs > 2.f ? wgs : ceilf(wgs), frags = 4 * (epi == PF_GU ? 2 * na : na) + np * g.NC;
-        best_us = (float)KB / best.ks * fmaxf(f32 ? 1.1f : 0.5f, on_unit * frags / 57.f) + 4.f + raw_us(best.ks);
+        const int na = pairs ? 2 : cls == PF_C_QKV ? pf_qkv_na(g, n_tiles, n_chunks) : 4, per = PF_NW * na;
+        const float load = (float)(((n_tiles + per - 1) / per + 7) / 8 * ((n_chunks + g.NC - 1) / g.NC) * ks4) / units;
+        const float on_unit = load > 2.f ? load : ceilf(load), frags = PF_NW * (pairs ? 2 * na : na) + F32::NP * g.NC;
+        const float kb_us = f32 ? fmaxf(1.1f, on_unit * frags / 57.f) : pairs ? 0.154f + 0.390f * fmaxf(load, 1.f) : 0.08f + 0.096f * na * fmaxf(load, 1.f);
+        best_us = 4.f + fmaxf((float)KB / ks4 * kb_us, hbm_us) + ks4 * slice_us;
     }
     for (int v = 0; v < kPfRings; ++v) {
-        const PfRingTile& T = kPfRing[v];
+        const PfRingTile& T = pf_ring_tile(f32, pairs, v);
         if (r.ring_tile >= 0 && r.ring_tile != v) continue;
-        const int per = epi == PF_GU && v < kPfBig ? T.FT / 2 : T.FT, n_fb = (n_tiles + per - 1) / per, n_rb = (n_chunks + T.RC - 1) / T.RC;
-        const int tiles = epi == PF_GU ? 2 * per : per, frags = tiles + np * T.RC;
-        const float us_kb = f32 ? tiles * T.RC * 0.061f / (v < kPfBig ? 8 : T.FT) : T.us_kb;      // a fragment product: 128 cycles of one SIMD
+        const int n_fb = (n_tiles + T.FT - 1) / T.FT, n_rb = (n_chunks + T.RC - 1) / T.RC;
         for (int ks = 1; ks <= PF_MAX_KSPLIT; ++ks) {
-            if (ks > 1 && (epi != PF_RAW || ks * n_chunks * 16 > PF_RAW_ROWS || ks > KB)) break;
-            if (epi == PF_RAW && (r.ring_ks > 0 ? ks != r.ring_ks : n_chunks <= PF_FIXED_SLICES && ks != ks4)) continue;
-            const int rounds = ((n_fb + 7) / 8 * n_rb * ks + units - 1) / units;
-            const float us = rounds * ((float)KB / ks * fmaxf(us_kb, frags / 43.f) + 4.f) + raw_us(ks);
+            if (ks > 1 && (!raw || ks * n_chunks * 16 > PF_RAW_ROWS || ks > KB)) break;
+            if (raw && (r.ring_ks > 0 ? ks != r.ring_ks : n_chunks <= PF_FIXED_SLICES && ks != ks4)) continue;
+            const int wgs = (n_fb + 7) / 8 * n_rb * ks, full = wgs / units, rest = wgs % units;
+            const float kb_us = full * (T.us0 + T.us1) + (rest ? T.us0 + T.us1 * rest / units : 0.f);
+            const float us = (full + (rest ? 1 : 0)) * 4.f + fmaxf((float)KB / ks * kb_us, hbm_us) + ks * slice_us;
             if (us < best_us) { best = {v, ks}; best_us = us; }
         }
     }
     return best;
 }
 template <class T, int EPI> bool launch_pf_ring(hipStream_t s, const PfPick& p, PfArgs a, int n_chunks) {
-    const PfRingTile& R = kPfRing[p.tile];
-    const int per = EPI == PF_GU && p.tile < kPfBig ? R.FT / 2 : R.FT;
-    a.n_fb = (a.n_tiles + per - 1) / per;
+    constexpr bool f32 = std::is_same_v<T, F32>;
+    const PfRingTile& R = pf_ring_tile(f32, EPI == PF_GU, p.tile);
+    a.n_fb = (a.n_tiles + R.FT - 1) / R.FT;
     a.n_rb = (n_chunks + R.RC - 1) / R.RC;
     a.ksplit = p.ks;
     const unsigned grid = (unsigned)((a.n_fb + 7) / 8 * 8 * a.n_rb * a.ksplit);
-    constexpr int N1 = EPI == PF_GU ? 2 : 1;            // one output tile per wave
-    constexpr auto ring = [](int nf) { return 159 / nf < 16 ? 159 / nf / 2 * 2 : 16; };      // stages the LDS holds (an even number)
-    switch (p.tile) {
-#define PFR(v, nt, nc, fw, rw, st, pf) case v: pf_ring_kernel<T, EPI, nt, nc, fw, rw, st, pf><<<grid, fw * rw * 64, 0, s>>>(a); return true;
-        PFR(0, 6, 2, 2, 4, 5, true) PFR(1, 4, 4, 4, 2, 4, true) PFR(2, 6, 4, 4, 2, 4, true) PFR(3, 8, 4, 2, 4, 3, false)
-#define PFN(v, nc, fw) PFR(v, N1, nc, fw, 1, ring(N1 * fw + T::NP * nc), true)
-        PFN(4, 2, 3) PFN(5, 3, 3) PFN(6, 4, 3) PFN(7, 2, 4) PFN(8, 3, 4) PFN(9, 4, 4) PFN(10, 6, 4) PFN(11, 8, 4)
-        PFN(12, 2, 8) PFN(13, 3, 8) PFN(14, 4, 8) PFN(15, 8, 8)
-#undef PFN
+#define PFR(v, nt, nc, fw, rw, nl, pf) case v: pf_ring_kernel<T, EPI, nt, nc, fw, rw, nl, pf><<<grid, (fw * rw + nl) * 64, 0, s>>>(a); return true;
+    if constexpr (f32) { switch (p.tile) { PF_RING_F32_SHAPES(PFR, EPI == PF_GU ? 2 : 1) } }
+    else if constexpr (EPI == PF_GU) { switch (p.tile) { PF_RING_PAIR_SHAPES(PFR) } }
+    else { switch (p.tile) { PF_RING_SHAPES(PFR) } }
 #undef PFR
-    }
     return false;
 }
 template <int EPI> bool launch_pf_gemm(asd_engine* e, const PfCfg& g, const PfPick& p, const PfArgs& a, int n_chunks) {
@@ -983,13 +1003,13 @@ template <class T> void launch_pf_attn_t(asd_engine* e, const PfAttnArgs& a, int
 template <class T> void launch_pf_embed_t(asd_engine* e, const int32_t* tokens, int rows, int n_chunks) {
     const asd_config& c = e->c;
     pf_embed_kernel<T><<<pf_row_grid(n_chunks), 256, 0, e->stream>>>((const typename T::elem*)e->embed, tokens, rows, n_chunks, c.d_model, e->layers[0].g_attn,
-        e->pf_xres, e->pf_xb, (int64_t)(e->pf_rows / 16) * e->KBd * 64 * e->KE, (int64_t)e->KBd * 64 * e->KE, e->pf_ssq, e->pf_rscale,
+        e->pf_xres, e->pf_xb, (e->pf_rows / 16) * e->cf_d * 64 * e->KE, e->cf_d * 64 * e->KE, e->pf_ssq, e->pf_rscale,
         1.f / (float)c.d_model, c.rms_eps);
 }
 template <class T> void launch_pf_resid_t(asd_engine* e, int rows, int n_chunks, int ksplit, const float* gain, float* cos_row) {
     const asd_config& c = e->c;
 #define PFS(ks) case ks: pf_resid_kernel<T, ks><<<pf_row_grid(n_chunks), 256, 0, e->stream>>>(e->pf_raw, n_chunks * 16, rows, c.d_model, e->pf_xres, e->pf_xb, \
-        (int64_t)(e->pf_rows / 16) * e->KBd * 64 * e->KE, (int64_t)e->KBd * 64 * e->KE, gain, e->pf_ssq, e->pf_rscale, cos_row, 1.f / (float)c.d_model, c.rms_eps); break;
+        (e->pf_rows / 16) * e->cf_d * 64 * e->KE, e->cf_d * 64 * e->KE, gain, e->pf_ssq, e->pf_rscale, cos_row, 1.f / (float)c.d_model, c.rms_eps); break;
     switch (ksplit) { PFS(1) PFS(2) PFS(3) PFS(4) PFS(5) PFS(6) PFS(7) PFS(8) }
 #undef PFS
 }
@@ -1027,9 +1047,9 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
         PfArgs base{};
         base.rows = rows; base.raw_rows = n_chunks * 16; base.rscale = e->pf_rscale; base.raw = e->pf_raw;
         base.pos0 = r0; base.rope = e->rope; base.q = e->pf_q; base.page_table = e->page_table;
-        base.q_plane = cap * e->KBq * 64 * KE; base.q_chunk = (int64_t)e->KBq * 64 * KE;
+        base.q_plane = cap * e->cf_q * 64 * KE; base.q_chunk = e->cf_q * 64 * KE;
         base.n_h = c.n_heads; base.n_kv = c.n_kv_heads; base.h = c.head_dim; base.page_tokens = c.page_tokens;
-        base.hmid = e->pf_hmid; base.hmid_plane = cap * e->KBf * 64 * KE; base.hmid_chunk = (int64_t)e->KBf * 64 * KE;
+        base.hmid = e->pf_hmid; base.hmid_plane = cap * e->cf_f * 64 * KE; base.hmid_chunk = e->cf_f * 64 * KE;
         auto resid = [&](int ksplit, const float* gain, int sub) {
             float* cr = e->pf_cos_rows + (size_t)sub * e->pf_rows;
             if (bf) launch_pf_resid_t<BF16>(e, rows, n_chunks, ksplit, gain, cr); else launch_pf_resid_t<F32>(e, rows, n_chunks, ksplit, gain, cr);
@@ -1038,7 +1058,7 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
             const Layer& ly = e->layers[l];
             bool ok = true;
             PfArgs a = base;
-            a.W = (const u32x4*)ly.wqkv; a.X = (const u32x4*)e->pf_xb; a.x_plane = cap * e->KBd * 64; a.x_chunk = (int64_t)e->KBd * 64;
+            a.W = (const u32x4*)ly.wqkv; a.X = (const u32x4*)e->pf_xb; a.x_plane = cap * e->cf_d * 64; a.x_chunk = e->cf_d * 64;
             wl(a, e->g_qkv, e->qkv_tiles, e->KBd);
             a.kv = e->kv + (size_t)l * e->kv_layer_bytes;
             pr.begin(ASD_PK_QKV, fl_row * c.d_model * (qd + 2 * kvd));
@@ -1055,7 +1075,7 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
             pr.end();
 
             PfArgs o = base;
-            o.W = (const u32x4*)ly.wo; o.X = (const u32x4*)e->pf_attn_out; o.x_plane = cap * e->KBq * 64; o.x_chunk = (int64_t)e->KBq * 64;
+            o.W = (const u32x4*)ly.wo; o.X = (const u32x4*)e->pf_attn_out; o.x_plane = cap * e->cf_q * 64; o.x_chunk = e->cf_q * 64;
             wl(o, e->g_o, c.d_model / 16, e->KBq);
             pr.begin(ASD_PK_OPROJ, fl_row * qd * c.d_model);
             ok = ok && launch_pf_gemm<PF_RAW>(e, e->pf.cfg[PF_C_O], how.gemm[PF_C_O], o, n_chunks);
@@ -1072,7 +1092,7 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
             pr.end();
 
             PfArgs dn = base;
-            dn.W = (const u32x4*)ly.wd; dn.X = (const u32x4*)e->pf_hmid; dn.x_plane = cap * e->KBf * 64; dn.x_chunk = (int64_t)e->KBf * 64;
+            dn.W = (const u32x4*)ly.wd; dn.X = (const u32x4*)e->pf_hmid; dn.x_plane = cap * e->cf_f * 64; dn.x_chunk = e->cf_f * 64;
             wl(dn, e->g_down, c.d_model / 16, e->KBf);
             pr.begin(ASD_PK_DOWN, fl_row * (double)c.d_model * c.d_ffn);
             ok = ok && launch_pf_gemm<PF_RAW>(e, e->pf.cfg[PF_C_DOWN], how.gemm[PF_C_DOWN], dn, n_chunks);
@@ -1176,7 +1196,7 @@ int asd_create(const asd_config* cfg, void* device_arena, size_t arena_bytes, vo
     e->pf_xres = (float*)(A + p.pf_xres); e->pf_raw = (float*)(A + p.pf_raw);
     e->pf_ssq = (float*)(A + p.pf_ssq); e->pf_rscale = (float*)(A + p.pf_rscale); e->pf_cos_rows = (float*)(A + p.pf_cos_rows);
     e->pf_xb = A + p.pf_xb; e->pf_q = A + p.pf_q; e->pf_attn_out = A + p.pf_attn_out; e->pf_hmid = A + p.pf_hmid;
-    e->pf_rows = p.pf_rows;
+    e->pf_rows = p.pf_rows; e->cf_d = p.cf_d; e->cf_q = p.cf_q; e->cf_f = p.cf_f;
     e->tune = cfg->debug_tune ? cfg->debug_tune : "";
     e->c.debug_tune = nullptr;              // (the caller's string is not kept; e->tune is the copy)
     const char* tune = e->tune.empty() ? nullptr : e->tune.c_str();

@@ -7,10 +7,10 @@
 // one (chunk, k-block) fragment is one contiguous KiB that a wave loads with one instruction, and the prompt attention kernels
 // use the decode kernel's fragments.
 //
-// pf_ring_kernel: a tile of up to 24 weight tiles x 8 chunks (16 x 16 for long blocks) per workgroup, both operands brought
+// pf_ring_kernel: a tile of weight tiles x chunks per workgroup (3 x 2 to 16 x 16), both operands brought
 // into an LDS ring by direct-to-LDS loads; see its own comment.  The kernel and tile of a launch are the ones with the
 // smallest estimated time.
-// pf_gemm_kernel (where the ring's tiles are estimated no better, between whole rounds of their workgroups): a workgroup of NW waves owns NW*NA weight tiles (16 output features each) x NC chunks of
+// pf_gemm_kernel (at some lengths between whole rounds of the ring's larger tiles): a workgroup of NW waves owns NW*NA weight tiles (16 output features each) x NC chunks of
 // rows and, with a K split, one slice of K.  Per k-block the waves stage the NC chunks' activation fragments
 // in LDS (double buffered, one barrier per k-block); each wave streams its own NA weight fragments from
 // global memory and feeds NA*NC accumulators.  Workgroups that share weights (same features, other rows)
@@ -245,41 +245,91 @@ __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const
 }
 
 // ---- the LDS ring kernel of the prompt GEMMs
-// What bounds the large bf16 prompt GEMMs: the clock the card keeps under them, and the cycles in which no product issues.  A loop of
-// matrix-core instructions on random operands in registers, nothing else, runs at 2.06 GHz and 2.1 PFLOP/s (on zeros: 2.4 GHz, 2.46
-// PFLOP/s); this kernel keeps the matrix cores busy in 57 to 72 % of the cycles at 2.15 to 1.8 GHz, the busier the lower the clock (2048 rows:
-// 7B gate/up 61 % at 2.15 GHz, 70B gate/up 72 % at 1.84 GHz).  Both are served by moving fewer bytes per product.  So both operands are read once per workgroup into LDS (no fragment passes through a register on
-// its way there), the tile per workgroup is as large as the launch's balance allows, and a wave's tile (NT weight tiles x
-// NC chunks, both planes) reads NT + 2 NC fragments for 2 NT NC products.
-//   FW x RW waves share a k-block, FW over the weight tiles, RW over the chunks.  An output is one wave's sum over its K
-//   slice in k-block order, hi plane before lo plane, as in pf_gemm_kernel: the tile shape does not enter a result.
-// A stage is one k-block; S stages form a ring.  Per stage: wait for this wave's requests of the stage to come, one
-// barrier (everybody's have arrived, and nobody reads the slot to be refilled any more), then the requests of a later stage
-// spread between the products: a direct-to-LDS load holds up its wave for about 64 cycles, which the SIMD's other wave
-// fills with products; issued back to back they cost more than the products themselves.  PF: the next stage's fragments are read into a second
-// set of registers during this stage's products (all tiles but the largest, whose accumulators leave no room).
+// Both operands are read once per workgroup into LDS (no fragment passes through a register on its way there) and every wave
+// takes its fragments from there: a wave's tile (NT weight tiles x NC chunks, both planes) reads NT + 2 NC fragments for
+// 2 NT NC products.  FW x RW waves share a k-block, FW over the weight tiles, RW over the chunks.  An output is one wave's sum
+// over its K slice in k-block order, hi plane before lo plane, as in pf_gemm_kernel: the tile shape does not enter a result.
+//
+// What bounds it goes by the length of the block.  Long blocks: the clock the card keeps under the products (a loop of them on random operands in registers,
+// nothing else, runs at 2.06 GHz and 2.1 PFLOP/s) and the cycles in which none issues; the tile is as large as LDS and registers allow.
+// Short ones: what a compute unit takes in.  It has 32 KiB of requests in flight (its L1), so a fragment from HBM costs it 1/27 us
+// and one from L2 1/92 us, and the two add up: few chunks per tile while the weights weigh more, row blocks that share them otherwise.  In between: how
+// evenly the tiles fill the 256 units, hence the number of shapes.
+//
+// Requests.  A direct-to-LDS load holds its wave up for 16 cycles, times the SIMDs that issue one at the same moment, and the product waves of a
+// workgroup, in step behind their barrier, all did: 64 cycles per load without a product (an 8 x 8 tile: 60 us for the 7B shape's QKV at 144 rows).  So NL waves of their own ask
+// for the fragments and do nothing else (44 us), and the product waves hold only accumulators and fragments.  The largest tile leaves them no
+// registers: there, and in fp32, the product waves request (NL = 0), spread between the products.
+//
+// A stage is one k-block; S stages form a ring.  Per stage one barrier, before which the requesting waves wait until their share of the stage to come has arrived and
+// the product waves until their reads of the slot that is refilled next have.  PF: the next stage's fragments are read into a second
+// set of registers during this stage's products (all tiles but the three largest, whose accumulators leave no room).
 // Products run with one weight fragment held over NC chunks in alternating direction (2 % less time than the other
-// order).  Measured (two planes counted, 7B): QKV 512 rows 95 -> 91 us, gate/up 158 -> 143 us (1.29 PFLOP/s), down 79 -> 71 us;
-// 2048 rows: gate/up 4 x 158 -> 537 us (1.38 PFLOP/s), QKV 4 x 95 -> 305 us, down 4 x 79 -> 250 us (1.48 PFLOP/s; the
-// vendor library's largest square product reaches 1.40 here).
-template <int NP, int NT, int NC, int FW, int RW, int S> struct PfRing {
-    static constexpr int W = FW * RW;                               // waves
+// order).
+template <int NP, int NT, int NC, int FW, int RW, int NL> struct PfRing {
+    static constexpr int W = FW * RW, WAVES = W + NL;               // product waves, waves
+    static constexpr int ASK = NL ? NL : W;                         // waves that request
     static constexpr int FT = FW * NT, RC = RW * NC;                // weight tiles and chunks per workgroup
-    static constexpr int NF = FT + NP * RC;                          // fragments per k-block
+    static constexpr int NF = FT + NP * RC;                         // fragments per k-block
     // requests per wave and stage, the same number from every wave (the wait counts depend on it): where they do not come
     // out even, some waves' last request reads nothing (into a spare KiB)
-    static constexpr int L = (NF + W - 1) / W, LDS = S * NF + (NF % W ? 1 : 0);
-    static_assert(LDS <= 160 && (S - 1) * L < 64, "LDS, and what the request counter can hold");
+    static constexpr int L = (NF + ASK - 1) / ASK, SPARE = NF % ASK ? 1 : 0;
+    static constexpr int FIT = (160 - SPARE) / NF;                  // stages the LDS holds; an even number of them, except three where four do not fit
+    static constexpr int S = FIT == 3 ? 3 : FIT > 16 ? 16 : FIT / 2 * 2;
+    static_assert(S >= 3 && (S - 1) * L < 64, "a ring, and what the request counter can hold");
 };
-template <class T, int EPI, int NT, int NC, int FW, int RW, int S, bool PF>
-__global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kernel(const PfArgs a) {
+// One wave's requests of a stage: fragments j, j + ASK, ... of the stage's FT weight and NP RC chunk fragments.  A tile
+// beyond the last re-reads the last one, a chunk beyond the block's last re-reads that one (the buffers end with it where
+// the block is full and RC does not divide it): their products are never looked at.
+template <class T, class SH, int EPI, int NT> struct PfRequests {
+    static constexpr int NP = T::NP, NA = EPI == PF_GU ? NT / 2 : NT, L = SH::L, NF = SH::NF, FT = SH::FT;
+    const char* src[L];
+    int64_t step[L];
+    int dst[L];                                                     // fragment of slot 0
+    uint32_t bytes[L];
+    int left;                                                       // stages still to ask for; past the last one it is asked for again
+    __device__ __forceinline__ PfRequests(const PfArgs& a, int fb, int rb, int kb0, int n, int j) : left(n) {
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            const int f = (j + SH::ASK * i) % NF, s = f % NT, x = f - FT;
+            const bool real = j + SH::ASK * i < NF;
+            dst[i] = real ? f : SH::S * NF;
+            bytes[i] = real ? 0xffffffffu : 0u;
+            if (f < FT) {
+                const bool up = EPI == PF_GU && s >= NA;
+                const int t = min((fb * (FT / NT) + f / NT) * NA + (up ? s - NA : s), a.n_tiles - 1);
+                src[i] = (const char*)(up ? a.W2 : a.W) + ((int64_t)t * a.w_tile_stride + (int64_t)kb0 * a.w_kb_stride) * 1024;
+                step[i] = a.w_kb_stride * 1024;
+            } else {
+                const int chunk = min(rb * SH::RC + x / NP, (a.rows + 15) / 16 - 1);
+                src[i] = (const char*)a.X + ((int64_t)(x % NP) * a.x_plane + (int64_t)chunk * a.x_chunk) * 16 + (int64_t)kb0 * 1024;
+                step[i] = 1024;
+            }
+        }
+    }
+    // ONCE: no other workgroup reads the weights (where a request is a weight's for every wave)
+    template <bool ONCE> __device__ __forceinline__ void issue(u32x4* sm, const int slot, const int lane) {
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            u32x4* to = &sm[(dst[i] + (SH::SPARE == 0 || bytes[i] ? slot * NF : 0)) * 64];
+            if (ONCE && SH::ASK * (i + 1) <= FT) frag_to_lds<true>(src[i], bytes[i], to, lane);
+            else frag_to_lds(src[i], bytes[i], to, lane);
+        }
+        --left;
+#pragma unroll
+        for (int i = 0; i < L; ++i) src[i] += left > 0 ? step[i] : 0;
+    }
+};
+template <class T, int EPI, int NT, int NC, int FW, int RW, int NL, bool PF>
+__global__ __launch_bounds__((FW * RW + NL) * 64, (FW * RW + NL + 3) / 4) void pf_ring_kernel(const PfArgs a) {
     constexpr int NP = T::NP;
-    using SH = PfRing<NP, NT, NC, FW, RW, S>;
-    constexpr int W = SH::W, FT = SH::FT, RC = SH::RC, NF = SH::NF, L = SH::L;
+    using SH = PfRing<NP, NT, NC, FW, RW, NL>;
+    constexpr int W = SH::W, FT = SH::FT, RC = SH::RC, NF = SH::NF, L = SH::L, S = SH::S;
     constexpr int NA = EPI == PF_GU ? NT / 2 : NT;                  // output tiles per wave
-    __shared__ u32x4 sm[SH::LDS * 64];
+    constexpr int AHEAD = PF ? S : S - 1;                           // stages asked for before the first product
+    static_assert(!PF || S % 2 == 0, "two register sets: stages in pairs");
+    __shared__ u32x4 sm[(S * NF + SH::SPARE) * 64];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int fw = w % FW, rw = w / FW;
     // workgroup -> (feature block, row block, K slice), XCD-first as in pf_gemm_kernel (a mapping that balances the bytes of
     // weights and activations an XCD's running workgroups share, 8 row blocks x 4 feature blocks instead of 16 x 2, measured the same)
     const int Lb = blockIdx.x, inner = a.n_rb * a.ksplit;
@@ -287,40 +337,33 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
     if (fb >= a.n_fb) return;
     const int kb0 = (int)((long)ks * a.KB / a.ksplit), n = (int)((long)(ks + 1) * a.KB / a.ksplit) - kb0;
 
-    // This wave's requests of a stage: fragments w, w + W, ... of the stage's FT weight and NP RC chunk fragments.  A tile
-    // beyond the last re-reads the last one, a chunk beyond the block's last re-reads that one (the buffers end with it where
-    // the block is full and RC does not divide it): their products are never looked at.
-    const char* src[L];
-    int64_t step[L];
-    int dst[L];                                                     // fragment of slot 0
-    uint32_t bytes[L];
+    if constexpr (NL > 0) {
+        if (w >= W) {                                               // a requesting wave
+            PfRequests<T, SH, EPI, NT> q(a, fb, rb, kb0, n, w - W);
+            auto feed = [&](auto once) {
+                constexpr bool ONCE = decltype(once)::value;
 #pragma unroll
-    for (int i = 0; i < L; ++i) {
-        const int f = (w + W * i) % NF, s = f % NT, x = f - FT;
-        const bool real = w + W * i < NF;
-        dst[i] = real ? f : S * NF;
-        bytes[i] = real ? 0xffffffffu : 0u;
-        if (f < FT) {
-            const bool up = EPI == PF_GU && s >= NA;
-            int t = (fb * FW + f / NT) * NA + (up ? s - NA : s);
-            if (t >= a.n_tiles) t = a.n_tiles - 1;
-            src[i] = (const char*)(up ? a.W2 : a.W) + ((int64_t)t * a.w_tile_stride + (int64_t)kb0 * a.w_kb_stride) * 1024;
-            step[i] = a.w_kb_stride * 1024;
-        } else {
-            const int chunk = min(rb * RC + x / NP, (a.rows + 15) / 16 - 1);
-            src[i] = (const char*)a.X + ((int64_t)(x % NP) * a.x_plane + (int64_t)chunk * a.x_chunk) * 16 + (int64_t)kb0 * 1024;
-            step[i] = 1024;
+                for (int b = 0; b < AHEAD; ++b) q.template issue<ONCE>(sm, b, lane);
+                if constexpr (PF) {
+                    wait_vm<(S - 1) * L, false>();
+                    __builtin_amdgcn_s_barrier();
+                }
+                int slot = AHEAD % S;
+                for (int i = 0; i < n; ++i) {
+                    wait_vm<(S - 2) * L, false>();
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    q.template issue<ONCE>(sm, slot, lane);
+                    slot = slot + 1 == S ? 0 : slot + 1;
+                }
+            };
+            // weights that no other row block reads: non-temporal (45 rows: down 70B 92 -> 83 us, QKV 7B 27 -> 26 us); with several row blocks they should stay in L2
+            if (a.n_rb == 1) feed(std::true_type{}); else feed(std::false_type{});
+            wait_vm<0, true>();                                     // no request may outlive the workgroup's LDS
+            return;
         }
     }
-    int asked = 0;
-    auto issue = [&](const int slot) {
-#pragma unroll
-        for (int i = 0; i < L; ++i) frag_to_lds(src[i], bytes[i], &sm[(dst[i] + (NF % W == 0 || bytes[i] ? slot * NF : 0)) * 64], lane);
-        ++asked;                                                    // past the last stage it is asked for again
-#pragma unroll
-        for (int i = 0; i < L; ++i) src[i] += asked < n ? step[i] : 0;
-    };
-
+    const int fw = w % FW, rw = w / FW;
     f32x4 acc[NT][NC];
 #pragma unroll
     for (int s = 0; s < NT; ++s)
@@ -346,53 +389,65 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
                 }
     };
     constexpr int NM = NP * NT * NC * (sizeof(typename T::elem) == 4 ? 4 : 1), ND = NT + NP * NC, TAIL = NM > 16 ? 6 : 0;     // products and fragment reads per stage
-    auto stage = [&](const int slot, const int r) {
-        wait_vm<(S - 2) * L, true>();
+    // issue: the requests of a later stage, where this wave makes them
+    auto stage = [&](const int slot, const int r, auto issue) {
+        wait_vm<NL ? 63 : (S - 2) * L, true>();
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (PF) {
-            issue(slot);                                            // its fragments are in registers since the last stage
+            if constexpr (NL == 0) issue(slot);                     // its fragments are in registers since the last stage
             read((slot + 1) % S, r ^ 1);
             products(r);
 #pragma unroll
             for (int j = 0; j < NM; ++j) {
                 if (j < NM - TAIL && (j * ND) / (NM - TAIL) != ((j - 1) * ND + NM - TAIL) / (NM - TAIL) - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                if ((j * L) / NM != ((j - 1) * L + NM) / NM - 1) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+                if (NL == 0 && (j * L) / NM != ((j - 1) * L + NM) / NM - 1) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
             }
         } else {
             read(slot, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            issue((slot + S - 1) % S);
+            if constexpr (NL == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                issue((slot + S - 1) % S);
+            }
             products(0);
+            if constexpr (NL == 0) {
 #pragma unroll
-            for (int j = 0; j < NM; ++j) {
-                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-                if ((j * L) / NM != ((j - 1) * L + NM) / NM - 1) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+                for (int j = 0; j < NM; ++j) {
+                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                    if ((j * L) / NM != ((j - 1) * L + NM) / NM - 1) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+                }
             }
         }
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
     };
+    auto stages = [&](auto issue) {
+        if constexpr (PF) {
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            read(0, 0);
+        }
+        int i = 0;
+        for (; i + S <= n; i += S) {
 #pragma unroll
-    for (int b = 0; b < (PF ? S : S - 1); ++b) issue(b);
-    if constexpr (PF) {
-        wait_vm<(S - 1) * L, false>();
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        read(0, 0);
+            for (int u = 0; u < S; ++u) stage(u, PF ? u & 1 : 0, issue);
+        }
+#pragma unroll
+        for (int u = 0; u + 1 < S; ++u)
+            if (i + u < n) stage(u, PF ? u & 1 : 0, issue);
+    };
+    if constexpr (NL > 0) {
+        stages([](int) {});
+    } else {
+        PfRequests<T, SH, EPI, NT> q(a, fb, rb, kb0, n, w);
+#pragma unroll
+        for (int b = 0; b < AHEAD; ++b) q.template issue<false>(sm, b, lane);
+        if constexpr (PF) wait_vm<(S - 1) * L, false>();
+        stages([&](const int slot) { q.template issue<false>(sm, slot, lane); });
+        wait_vm<0, true>();                                         // no request may outlive the workgroup's LDS
     }
-    constexpr int U = PF && S % 2 ? 2 * S : S;                      // stages until slot and register set repeat
-    int i = 0;
-    for (; i + U <= n; i += U) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) stage(u % S, PF ? u & 1 : 0);
-    }
-#pragma unroll
-    for (int u = 0; u + 1 < U; ++u)
-        if (i + u < n) stage(u % S, PF ? u & 1 : 0);
-    wait_vm<0, true>();                                             // no request may outlive the workgroup's LDS
 
     int tile[NA];
     bool tval[NA];
@@ -400,6 +455,28 @@ __global__ __launch_bounds__(FW * RW * 64, (FW * RW + 3) / 4) void pf_ring_kerne
     for (int s = 0; s < NA; ++s) { tile[s] = (fb * FW + fw) * NA + s; tval[s] = tile[s] < a.n_tiles; }
     pf_epilogue<T, EPI, NA, NT, NC>(a, acc, tile, tval, rb * RC + rw * NC, ks, lane);
 }
+
+// The bf16 shapes, X(number, weight tiles per wave, chunks per wave, waves over the tiles, waves over the chunks, requesting waves,
+// second register set): for QKV and the raw sums, and for gate/up, whose tiles come in pairs.  Of some 40 shapes measured on the 7B, 13B and 70B matrices at 20 to
+// 2048 rows, the sixteen of each list that leave the least time on the table (under 1 % over all lengths).
+#define PF_RING_SHAPES(X)                                                                                                \
+    X(0, 4, 4, 4, 2, 4, false) X(1, 6, 4, 2, 2, 4, true) X(2, 8, 4, 2, 4, 0, false) X(3, 1, 2, 4, 1, 4, true)            \
+    X(4, 1, 3, 3, 1, 3, true) X(5, 1, 4, 4, 1, 4, true) X(6, 2, 3, 4, 1, 4, true) X(7, 2, 4, 4, 1, 4, true)              \
+    X(8, 2, 4, 3, 1, 3, true) X(9, 4, 3, 2, 2, 4, true) X(10, 4, 4, 2, 2, 4, true) X(11, 4, 5, 2, 2, 4, true)            \
+    X(12, 5, 4, 2, 2, 4, true) X(13, 5, 5, 2, 2, 4, true) X(14, 6, 3, 2, 2, 4, true) X(15, 8, 3, 2, 2, 4, true)
+#define PF_RING_PAIR_SHAPES(X)                                                                                           \
+    X(0, 4, 4, 4, 2, 4, false) X(1, 6, 4, 4, 2, 4, false) X(2, 8, 4, 2, 4, 0, false) X(3, 2, 5, 4, 1, 4, true)           \
+    X(4, 2, 3, 3, 1, 3, true) X(5, 2, 4, 3, 1, 3, true) X(6, 2, 2, 4, 1, 4, true) X(7, 2, 4, 4, 1, 4, true)              \
+    X(8, 4, 4, 4, 1, 4, true) X(9, 4, 3, 2, 2, 4, true) X(10, 4, 4, 2, 2, 4, true) X(11, 4, 5, 2, 2, 4, true)            \
+    X(12, 6, 3, 2, 2, 4, true) X(13, 6, 4, 2, 2, 4, true) X(14, 4, 5, 4, 1, 4, true) X(15, 8, 3, 2, 2, 4, true)
+// In fp32 a product takes eight times as long (128 cycles of a SIMD per fragment pair): the requests hide behind the products, and
+// a prompt pass of a small model, a few k-blocks per launch, pays for every wave more (256 k values, 4 layers, 30 rows: 168 us like this, 203 with
+// requesting waves).  N weight tiles per wave: one, two for gate/up.
+#define PF_RING_F32_SHAPES(X, N)                                                                                         \
+    X(0, 6, 2, 2, 4, 0, true) X(1, 4, 4, 4, 2, 0, true) X(2, 6, 4, 4, 2, 0, true) X(3, 8, 4, 2, 4, 0, false)             \
+    X(4, N, 2, 3, 1, 0, true) X(5, N, 3, 3, 1, 0, true) X(6, N, 4, 3, 1, 0, true) X(7, N, 2, 4, 1, 0, true)              \
+    X(8, N, 3, 4, 1, 0, true) X(9, N, 4, 4, 1, 0, true) X(10, N, 6, 4, 1, 0, true) X(11, N, 8, 4, 1, 0, true)            \
+    X(12, N, 2, 8, 1, 0, true) X(13, N, 3, 8, 1, 0, true) X(14, N, 4, 8, 1, 0, true) X(15, N, 8, 8, 1, 0, true)
 
 // ---------------------------------------------------------------- rows of a block: embedding, residual add + cosine tap
 // What bounds these kernels is memory (per row and sublayer the K slices, the residual row both ways and its normed copy), and two
