@@ -673,25 +673,42 @@ void build_pass(asd_engine* e, int M, int pos_off, const uint8_t* mask, int ctx_
     push(OP_FINISH, ASD_K_FINISH, 1, 0);
 }
 
+// Enqueue what a call starts with: state, zeroed words, at most 16 tokens
+BeginArgs begin_args(const asd_engine* e, int pos, int target = 0, int reset_counts = 0, int index_base = 0, void* zero = nullptr, int n_zero = 0,
+                     const int32_t* tok = nullptr, int n_tok = 0) {
+    BeginArgs a{};
+    a.st = e->st; a.pos = pos; a.target = target; a.reset_counts = reset_counts; a.index_base = index_base;
+    a.zero = (uint32_t*)zero; a.n_zero = n_zero; a.tokbuf = e->tokbuf; a.n_tok = n_tok;
+    for (int i = 0; i < n_tok; ++i) a.tok[i] = tok[i];
+    return a;
+}
+void launch_begin(asd_engine* e, const BeginArgs& a) { begin_kernel<<<1, 256, 0, e->stream>>>(a); }
+
+template <class T> void launch_embed_t(asd_engine* e, const int32_t* d_tokens, int M, const float* gain, float* part, const BeginArgs* begin) {
+    using El = typename T::elem;
+    const size_t plane = (size_t)e->KBd * 64 * e->KE;
+    const dim3 grid(EMBED_SPLIT, M);
+    if (begin) begin_embed_kernel<T><<<grid, EMBED_THREADS, 0, e->stream>>>(*begin, begin->n_tok ? nullptr : d_tokens, (const El*)e->embed, e->c.d_model, e->c.vocab, gain,
+                                                                            e->xres, e->xb, plane, row_stride(e, M), part);
+    else embed_kernel<T><<<grid, EMBED_THREADS, 0, e->stream>>>((const El*)e->embed, d_tokens, e->c.d_model, e->c.vocab, e->st, gain, e->xres, e->xb, plane, row_stride(e, M), part);
+}
+
 // Run a pass as one launch per step.  embedded: the launch before left this pass's embedding; embed_next: the pass is a draft
-// step (FIN_DRAFT) and its last launch embeds the drafted token for the step that follows under the same mask.
+// step (FIN_DRAFT) and its last launch embeds the drafted token for the step that follows under the same mask.  begin: what the
+// pass's first launch sets up (its n_tok ids, if any, are the pass's rows).
 int launch_steps(asd_engine* e, const std::vector<PassOp>& ops, const int32_t* d_tokens, int M, const uint8_t* mask,
-                 Profiler* profiler, int fin_mode, int fin_arg, const PassOut& out, bool embedded = false, bool embed_next = false) {
+                 Profiler* profiler, int fin_mode, int fin_arg, const PassOut& out, bool embedded = false, bool embed_next = false,
+                 const BeginArgs* begin = nullptr) {
     const asd_config& c = e->c;
     Prof pr{profiler, e->stream};
-    const int RS = row_stride(e, M);
     for (const PassOp& op : ops) {
         pr.begin(op.cls, op.bytes);
         bool ok = true;
         switch (op.type) {
             case OP_EMBED:
                 if (embedded) break;
-                if (c.dtype == ASD_DT_BF16)
-                    embed_kernel<BF16><<<dim3(EMBED_SPLIT, M), EMBED_THREADS, 0, e->stream>>>((const uint16_t*)e->embed, d_tokens, c.d_model, c.vocab, e->st,
-                        next_gain(e, mask, -1), e->xres, e->xb, (size_t)e->KBd * 64 * e->KE, RS, out.part);
-                else
-                    embed_kernel<F32><<<dim3(EMBED_SPLIT, M), EMBED_THREADS, 0, e->stream>>>((const float*)e->embed, d_tokens, c.d_model, c.vocab, e->st,
-                        next_gain(e, mask, -1), e->xres, e->xb, (size_t)e->KBd * 64 * e->KE, RS, out.part);
+                if (c.dtype == ASD_DT_BF16) launch_embed_t<BF16>(e, d_tokens, M, next_gain(e, mask, -1), out.part, begin);
+                else launch_embed_t<F32>(e, d_tokens, M, next_gain(e, mask, -1), out.part, begin);
                 break;
             case OP_QKV: ok = launch_gemm<EPI_QKV>(e, qkv_cfg(e, M), op.g); break;
             case OP_OPROJ: ok = launch_gemm<EPI_RES>(e, e->g_o, op.g); break;
@@ -731,11 +748,11 @@ int launch_steps(asd_engine* e, const std::vector<PassOp>& ops, const int32_t* d
 
 int enqueue_forward(asd_engine* e, const int32_t* d_tokens, int M, int pos_off, const uint8_t* mask, int nc,
                     Profiler* profiler, int ctx_for_bytes, int fin_mode = FIN_NONE, int fin_arg = 0, const PassOut* out_or_null = nullptr,
-                    bool embedded = false, bool embed_next = false) {
+                    bool embedded = false, bool embed_next = false, const BeginArgs* begin = nullptr) {
     const PassOut out = out_or_null ? *out_or_null : engine_out(e);
     std::vector<PassOp> ops;
     build_pass(e, M, pos_off, mask, ctx_for_bytes, nc, out, ops);
-    return launch_steps(e, ops, d_tokens, M, mask, profiler, fin_mode, fin_arg, out, embedded, embed_next);
+    return launch_steps(e, ops, d_tokens, M, mask, profiler, fin_mode, fin_arg, out, embedded, embed_next, begin);
 }
 
 bool weights_ready(asd_engine* e) {
@@ -762,16 +779,6 @@ struct HostCopies {
         return hipLaunchKernel((const void*)to_host_kernel, dim3(blocks < 1 ? 1 : blocks > 256 ? 256 : blocks), dim3(256), args, 0, s);
     }
 };
-// Enqueue what a call starts with: state, zeroed words, at most 16 tokens
-void launch_begin(asd_engine* e, int pos, int target = 0, int reset_counts = 0, int index_base = 0, void* zero = nullptr, int n_zero = 0,
-                  const int32_t* tok = nullptr, int n_tok = 0) {
-    BeginArgs a{};
-    a.st = e->st; a.pos = pos; a.target = target; a.reset_counts = reset_counts; a.index_base = index_base;
-    a.zero = (uint32_t*)zero; a.n_zero = n_zero; a.tokbuf = e->tokbuf; a.n_tok = n_tok;
-    for (int i = 0; i < n_tok; ++i) a.tok[i] = tok[i];
-    begin_kernel<<<n_zero > 256 ? (n_zero + 255) / 256 : 1, 256, 0, e->stream>>>(a);
-}
-
 // After a synchronisation: did a kernel meet a token id outside the vocabulary, or a row of logits without a finite
 // maximum?  (st: a host copy of the decoding state.)
 int check_pass_error(asd_engine* e, const DevState* st) {
@@ -1000,11 +1007,11 @@ template <class T> void launch_pf_attn_t(asd_engine* e, const PfAttnArgs& a, int
     if (H == 128) pf_attn_kernel<T, 128><<<grid, 256, 0, e->stream>>>(a);
 }
 
-template <class T> void launch_pf_embed_t(asd_engine* e, const int32_t* tokens, int rows, int n_chunks) {
+template <class T> void launch_pf_embed_t(asd_engine* e, const int32_t* tokens, int rows, int n_chunks, const BeginArgs& begin) {
     const asd_config& c = e->c;
     pf_embed_kernel<T><<<pf_row_grid(n_chunks), 256, 0, e->stream>>>((const typename T::elem*)e->embed, tokens, rows, n_chunks, c.d_model, e->layers[0].g_attn,
         e->pf_xres, e->pf_xb, (e->pf_rows / 16) * e->cf_d * 64 * e->KE, e->cf_d * 64 * e->KE, e->pf_ssq, e->pf_rscale,
-        1.f / (float)c.d_model, c.rms_eps);
+        1.f / (float)c.d_model, c.rms_eps, begin);
 }
 template <class T> void launch_pf_resid_t(asd_engine* e, int rows, int n_chunks, int ksplit, const float* gain, float* cos_row) {
     const asd_config& c = e->c;
@@ -1032,14 +1039,15 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
     const int block = pf_block_rows(e->pf, n);
     const int64_t cap = e->pf_rows / 16;                // chunks per activation plane
     memcpy(e->h_tok, tokens, (size_t)n * 4);             // (the embedding reads them from there; n <= capacity)
-    launch_begin(e, 0, 0, 0, 0, e->cos_acc, 4 * L);
+    BeginArgs begin = begin_args(e, 0, 0, 0, 0, e->cos_acc, 4 * L);
     int rows = 0;
     for (int r0 = 0; r0 < n; r0 += rows) {
         rows = n - r0 < block ? n - r0 : block;
         const int n_chunks = (rows + 15) / 16;
         const PfBlock how = pf_block(e->pf, rows);
         pr.begin(ASD_PK_ROWS, 0);
-        if (bf) launch_pf_embed_t<BF16>(e, e->h_tok + r0, rows, n_chunks); else launch_pf_embed_t<F32>(e, e->h_tok + r0, rows, n_chunks);
+        if (bf) launch_pf_embed_t<BF16>(e, e->h_tok + r0, rows, n_chunks, begin); else launch_pf_embed_t<F32>(e, e->h_tok + r0, rows, n_chunks, begin);
+        begin.st = nullptr;
         pr.end();
         // flops of each contraction over this block's rows (every weight multiply-add counted once), causal attention
         const double fl_row = 2.0 * rows, ctx_sum = (double)rows * r0 + 0.5 * rows * (rows + 1.0);
@@ -1467,8 +1475,8 @@ int asd_admg(const float* C, int32_t L, float alpha, int32_t m, int32_t n, int32
 
 // run rows [tokens, tokens+n) at the current cache end; results stay on the device (first: the running cosine sums start anew)
 static int forward_rows(asd_engine* e, const int32_t* tokens, int n, const uint8_t* mask, bool first) {
-    launch_begin(e, e->kv_len, 0, 0, 0, e->cos_acc, first ? 4 * e->c.n_layers : 0, tokens, n);
-    return enqueue_forward(e, e->tokbuf, n, 0, mask, chunks_for(e->kv_len + n - 1), nullptr, e->kv_len + n);
+    const BeginArgs begin = begin_args(e, e->kv_len, 0, 0, 0, e->cos_acc, first ? 4 * e->c.n_layers : 0, tokens, n);
+    return enqueue_forward(e, nullptr, n, 0, mask, chunks_for(e->kv_len + n - 1), nullptr, e->kv_len + n, FIN_NONE, 0, nullptr, false, false, &begin);
 }
 
 int asd_forward(asd_engine* e, const int32_t* tokens, int32_t n_rows, int32_t pos0, const uint8_t* mask, int32_t commit,
@@ -1547,9 +1555,10 @@ int asd_forward_noalloc(asd_engine* e, const int32_t* d_tokens, int32_t n_rows, 
     if (d_argmax) out.argmax = d_argmax;
     // what must start at zero: the running cosine sums and the heads' arrival counters (neighbours in the layout)
     const int nz = (int)(((unsigned char*)out.amax_part - (unsigned char*)out.cos_acc) / 4);
-    launch_begin(e, e->kv_len, 0, 0, 0, out.cos_acc, nz);
+    const BeginArgs begin = begin_args(e, e->kv_len, 0, 0, 0, out.cos_acc, nz);
     out.d_cos = d_cos;
-    const int rc = enqueue_forward(e, d_tokens, n_rows, 0, mask, chunks_for(e->kv_len + n_rows - 1), nullptr, e->kv_len + n_rows, FIN_NONE, 0, &out);
+    const int rc = enqueue_forward(e, d_tokens, n_rows, 0, mask, chunks_for(e->kv_len + n_rows - 1), nullptr, e->kv_len + n_rows, FIN_NONE, 0, &out,
+                                   false, false, &begin);
     if (rc) return rc;
     const hipError_t r = hipGetLastError();
     if (r != hipSuccess) return fail(e, ASD_E_HIP, "kernel launch: %s", hipGetErrorString(r));
@@ -1691,7 +1700,7 @@ int asd_spec_sample(asd_engine* e, const float* q_logits, const float* p_logits,
     if (index0 < 0 || index0 > (1 << 30)) return fail(e, ASD_E_INVAL, "index0 out of range");
     const size_t V = e->c.vocab;
     const SampleArgs sa = sample_args(e, temperature, seed);
-    launch_begin(e, e->kv_len, kk + 1, 1, (int)index0);
+    launch_begin(e, begin_args(e, e->kv_len, kk + 1, 1, (int)index0));
     for (int j = 0; j < kk; ++j) {                 // each draft row takes the place a draft step's logits would have
         CK(e, hipMemcpyAsync(e->logits, q_logits + (size_t)j * V, V * 4, hipMemcpyHostToDevice, e->stream));
         launch_sample_draft(e, sa, j);
@@ -1780,7 +1789,7 @@ int asd_decode(asd_engine* e, int32_t last_token, int32_t n_more, const asd_gen_
     const auto t0 = std::chrono::steady_clock::now();
     const bool sampled = p->temperature > 0.f;
     const SampleArgs sa = sampled ? sample_args(e, p->temperature, p->seed) : SampleArgs{};
-    launch_begin(e, e->kv_len, n_more, 1, sampled ? (int)p->sample_index0 : 0, nullptr, 0, &last_token, 1);
+    launch_begin(e, begin_args(e, e->kv_len, n_more, 1, sampled ? (int)p->sample_index0 : 0, nullptr, 0, &last_token, 1));
     const bool graphs = p->use_graphs != 0;
     if (sampled && (e->graph_T != p->temperature || e->graph_seed != p->seed)) {        // both are baked into captured launches
         drop_graphs(e); e->graph_T = p->temperature; e->graph_seed = p->seed;
@@ -1940,7 +1949,7 @@ int asd_generate(asd_engine* e, const int32_t* prompt, int32_t n_prompt, int32_t
 static int bench_tokens(asd_engine* e, int n_rows) {
     int32_t t[ASD_ROWS];
     for (int i = 0; i < n_rows; ++i) t[i] = (int32_t)((1 + 7919 * i) % e->c.vocab);
-    launch_begin(e, e->kv_len, 0, 0, 0, nullptr, 0, t, n_rows);
+    launch_begin(e, begin_args(e, e->kv_len, 0, 0, 0, nullptr, 0, t, n_rows));
     CK(e, hipStreamSynchronize(e->stream));
     return ASD_OK;
 }

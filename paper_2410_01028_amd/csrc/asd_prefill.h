@@ -23,6 +23,7 @@
 #pragma once
 #include <type_traits>
 #include "asd_gemm.h"
+#include "asd_misc.h"
 
 // A block holds up to 512, 1024 or 2048 rows, whatever the engine's workspace has room for (PF_MIN_ROWS always fits);
 // the raw partial sums of a block take slices x rows <= PF_RAW_ROWS rows of d_model.
@@ -542,14 +543,15 @@ __device__ __forceinline__ void pf_block_sum2(float& u, float& v, float2* red) {
     }
 }
 
-// grid = pf_row_grid; rows of the last chunk at or beyond `rows` are zero-filled
+// grid = pf_row_grid; rows of the last chunk at or beyond `rows` are zero-filled.  begin: what a call sets up first (st NULL: a later block)
 template <class T>
 __global__ __launch_bounds__(256) void pf_embed_kernel(const typename T::elem* E, const int32_t* tokens, int rows, int n_chunks, int d, const float* g_first,
                                                        float* xres, void* xb, int64_t xb_plane, int64_t xb_chunk, float* ssq, float* rscale,
-                                                       float inv_d, float eps) {
+                                                       float inv_d, float eps, const BeginArgs begin) {
     using El = typename T::elem;
     __shared__ float2 red[256];
     const int r = pf_row_of_block(blockIdx.x), tid = threadIdx.x;
+    if (begin.st && blockIdx.x == 0) begin_state(begin, tid, 256, 0);
     if (r >= n_chunks * 16) return;
     const bool valid = r < rows;
     const El* src = E + (size_t)(valid ? tokens[r] : 0) * d;
