@@ -321,43 +321,54 @@ template <int NP, int NT, int NC, int FW, int RW, int NL> struct PfRing {
 // One wave's requests of a stage: fragments j, j + ASK, ... of the stage's FT weight and NP RC chunk fragments.  A tile
 // beyond the last re-reads the last one, a chunk beyond the block's last re-reads that one (the buffers end with it where
 // the block is full and RC does not divide it): their products are never looked at.
+// A wave keeps one address per request and nothing else of its own: places in LDS follow from j, weights share one step and chunks another, and
+// only the last request can be one that reads nothing.  (With step, place and length kept per request and the first stages unrolled the compiler spilled up
+// to 293 scalar registers, and the first request of a workgroup waited for 160 to 420 instructions.)
 template <class T, class SH, int EPI, int NT> struct PfRequests {
     static constexpr int NP = T::NP, NA = EPI == PF_GU ? NT / 2 : NT, L = SH::L, NF = SH::NF, FT = SH::FT;
     const char* src[L];
-    int64_t step[L];
-    int dst[L];                                                     // fragment of slot 0
-    uint32_t bytes[L];
+    int64_t w_step;                                                 // to a weight tile's next k-block (a chunk's: 1 KiB)
+    int x_step, j;
+    int last;                                                       // the last request's fragment of slot 0
+    uint32_t last_bytes;
     int left;                                                       // stages still to ask for; past the last one it is asked for again
-    __device__ __forceinline__ PfRequests(const PfArgs& a, int fb, int rb, int kb0, int n, int j) : left(n) {
+    __device__ __forceinline__ PfRequests(const PfArgs& a, int fb, int rb, int kb0, int n, int j) : w_step(a.w_kb_stride * 1024), x_step(1024), j(j), left(n) {
+        const bool real = j + SH::ASK * (L - 1) < NF;
+        last = real ? j + SH::ASK * (L - 1) : SH::S * NF;
+        last_bytes = real ? 0xffffffffu : 0u;
+        const int wt = (int)a.w_tile_stride, xc = (int)a.x_chunk;       // fragments: a tensor of 2^31 of them would be 2 TiB
+        const char* const X = (const char*)a.X + (int64_t)kb0 * 1024;
+        const int64_t w0 = kb0 * a.w_kb_stride;
+        const int last_chunk = (a.rows + 15) / 16 - 1;
 #pragma unroll
         for (int i = 0; i < L; ++i) {
-            const int f = (j + SH::ASK * i) % NF, s = f % NT, x = f - FT;
-            const bool real = j + SH::ASK * i < NF;
-            dst[i] = real ? f : SH::S * NF;
-            bytes[i] = real ? 0xffffffffu : 0u;
-            if (f < FT) {
+            const int f = min(j + SH::ASK * i, NF - 1), s = f % NT, x = f - FT;
+            if (is_weight(i, f)) {
                 const bool up = EPI == PF_GU && s >= NA;
                 const int t = min((fb * (FT / NT) + f / NT) * NA + (up ? s - NA : s), a.n_tiles - 1);
-                src[i] = (const char*)(up ? a.W2 : a.W) + ((int64_t)t * a.w_tile_stride + (int64_t)kb0 * a.w_kb_stride) * 1024;
-                step[i] = a.w_kb_stride * 1024;
+                src[i] = (const char*)(up ? a.W2 : a.W) + ((int64_t)t * wt + w0) * 1024;
             } else {
-                const int chunk = min(rb * SH::RC + x / NP, (a.rows + 15) / 16 - 1);
-                src[i] = (const char*)a.X + ((int64_t)(x % NP) * a.x_plane + (int64_t)chunk * a.x_chunk) * 16 + (int64_t)kb0 * 1024;
-                step[i] = 1024;
+                src[i] = X + ((x % NP ? a.x_plane : 0) + (int64_t)min(rb * SH::RC + x / NP, last_chunk) * xc) * 16;
             }
         }
     }
+    // fragment f, the wave's i-th request (which of the two it is is known when compiling for all i but one)
+    static __device__ __forceinline__ bool is_weight(const int i, const int f) { return SH::ASK * (i + 1) <= FT || (SH::ASK * i < FT && f < FT); }
+    // Called once per trip of a loop whose slots are known when compiling: keeps the compiler from holding every slot's places in registers.
+    __device__ __forceinline__ void next_trip() { asm volatile("" : "+s"(j), "+s"(last)); }
     // ONCE: no other workgroup reads the weights (where a request is a weight's for every wave)
     template <bool ONCE> __device__ __forceinline__ void issue(u32x4* sm, const int slot, const int lane) {
-#pragma unroll
-        for (int i = 0; i < L; ++i) {
-            u32x4* to = &sm[(dst[i] + (SH::SPARE == 0 || bytes[i] ? slot * NF : 0)) * 64];
-            if (ONCE && SH::ASK * (i + 1) <= FT) frag_to_lds<true>(src[i], bytes[i], to, lane);
-            else frag_to_lds(src[i], bytes[i], to, lane);
-        }
+        u32x4* const to = sm + (slot * NF + j) * 64;
         --left;
 #pragma unroll
-        for (int i = 0; i < L; ++i) src[i] += left > 0 ? step[i] : 0;
+        for (int i = 0; i < L; ++i) {
+            const bool odd = SH::SPARE && i == L - 1;
+            const uint32_t bytes = odd ? last_bytes : 0xffffffffu;
+            u32x4* const at = odd ? &sm[(last + (slot * NF & (int)last_bytes)) * 64] : to + SH::ASK * i * 64;
+            if (ONCE && SH::ASK * (i + 1) <= FT) frag_to_lds<true>(src[i], bytes, at, lane);
+            else frag_to_lds(src[i], bytes, at, lane);
+            src[i] += left <= 0 ? 0 : is_weight(i, j + SH::ASK * i) ? w_step : x_step;
+        }
     }
 };
 template <class T, int EPI, int NT, int NC, int FW, int RW, int NL, bool PF>
@@ -375,14 +386,14 @@ __global__ __launch_bounds__((FW * RW + NL) * 64, (FW * RW + NL + 3) / 4) void p
     const int Lb = blockIdx.x, inner = a.n_rb * a.ksplit;
     const int fb = ((Lb >> 3) / inner) * 8 + (Lb & 7), in = (Lb >> 3) % inner, rb = in % a.n_rb, ks = in / a.n_rb;
     if (fb >= a.n_fb) return;
-    const int kb0 = (int)((long)ks * a.KB / a.ksplit), n = (int)((long)(ks + 1) * a.KB / a.ksplit) - kb0;
+    const int kb0 = ks * a.KB / a.ksplit, n = (ks + 1) * a.KB / a.ksplit - kb0;      // (at most eight slices: far inside 32 bits)
 
     if constexpr (NL > 0) {
         if (w >= W) {                                               // a requesting wave
             PfRequests<T, SH, EPI, NT> q(a, fb, rb, kb0, n, w - W);
             auto feed = [&](auto once) {
                 constexpr bool ONCE = decltype(once)::value;
-#pragma unroll
+#pragma unroll 1
                 for (int b = 0; b < AHEAD; ++b) q.template issue<ONCE>(sm, b, lane);
                 if constexpr (PF) {
                     wait_vm<(S - 1) * L, false>();
@@ -463,7 +474,7 @@ __global__ __launch_bounds__((FW * RW + NL) * 64, (FW * RW + NL + 3) / 4) void p
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
     };
-    auto stages = [&](auto issue) {
+    auto stages = [&](auto issue, auto next_trip) {
         if constexpr (PF) {
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
@@ -471,6 +482,7 @@ __global__ __launch_bounds__((FW * RW + NL) * 64, (FW * RW + NL + 3) / 4) void p
         }
         int i = 0;
         for (; i + S <= n; i += S) {
+            next_trip();
 #pragma unroll
             for (int u = 0; u < S; ++u) stage(u, PF ? u & 1 : 0, issue);
         }
@@ -479,13 +491,13 @@ __global__ __launch_bounds__((FW * RW + NL) * 64, (FW * RW + NL + 3) / 4) void p
             if (i + u < n) stage(u, PF ? u & 1 : 0, issue);
     };
     if constexpr (NL > 0) {
-        stages([](int) {});
+        stages([](int) {}, [] {});
     } else {
         PfRequests<T, SH, EPI, NT> q(a, fb, rb, kb0, n, w);
 #pragma unroll
         for (int b = 0; b < AHEAD; ++b) q.template issue<false>(sm, b, lane);
         if constexpr (PF) wait_vm<(S - 1) * L, false>();
-        stages([&](const int slot) { q.template issue<false>(sm, slot, lane); });
+        stages([&](const int slot) { q.template issue<false>(sm, slot, lane); }, [&] { q.next_trip(); });
         wait_vm<0, true>();                                         // no request may outlive the workgroup's LDS
     }
 
