@@ -86,8 +86,8 @@ __device__ __forceinline__ void quad_transpose(float (&v)[4], const int q) {
     }
 }
 // Epilogues of the prompt GEMMs, straight from the accumulators: lane 16g + m holds features 4g..4g+3 of each tile for
-// row m of each chunk.  PF_GU: acc[0 .. NA-1] gate, acc[NA .. 2NA-1] up.
-template <class T, int EPI, int NA, int NAT, int NC>
+// row m of each chunk.  PF_GU: acc[0 .. NA-1] gate, acc[NA .. 2NA-1] up.  RD: PF_QKV's (tile, chunk) pairs whose rotary factors are held.
+template <class T, int EPI, int RD, int NA, int NAT, int NC>
 __device__ __forceinline__ void pf_epilogue(const PfArgs& a, const f32x4 (&acc)[NAT][NC], const int (&tile)[NA], const bool (&tval)[NA],
                                             const int chunk0, const int ks, const int lane) {
     using E = typename T::elem;
@@ -131,9 +131,10 @@ __device__ __forceinline__ void pf_epilogue(const PfArgs& a, const f32x4 (&acc)[
     if constexpr (EPI == PF_QKV) {
         // tile j of a head: rows 0..7 = head dims 8j..8j+7, rows 8..15 = the same dims + h/2 (rotary partners):
         // lane groups 0,1 hold the first halves, groups 2,3 their partners, 32 lanes away.
-        // A workgroup has its compute unit to itself, so what this waits for nobody hides: the rotary factors are requested RD (tile, chunk)
+        // A workgroup of the ring kernel has its compute unit to itself, so what this waits for nobody hides: the rotary factors are requested RD - 1 (tile, chunk)
         // pairs ahead (read between the stores they cost a memory round trip per pair), the rows' pages and scales once.
-        // 7B, 2048 rows: the launch 350 -> 332 us, with V^T's 2-byte stores, one per row and dim, made 8-byte ones below.
+        // 7B, 2048 rows, the ring kernel's launch: 350 -> 332 us, with V^T's 2-byte stores, one per row and dim, made 8-byte ones below.  The four-wave kernel shares its
+        // unit and hides these waits: with eight chunks, which fill its registers, it asks for a pair as it needs it (three ahead spilled 57 registers).
         const int hpt = a.h / 16, hh = a.h / 2, PT = a.page_tokens;
         float rs[NC];
         int page[NC];
@@ -142,7 +143,6 @@ __device__ __forceinline__ void pf_epilogue(const PfArgs& a, const f32x4 (&acc)[
             rs[c] = rv[c] ? a.rscale[row[c]] : 0.f;
             page[c] = a.page_table[(a.pos0 + min(row[c], a.rows - 1)) / PT];      // (a quad's lanes beyond the last row store for those before it)
         }
-        constexpr int RD = 4;
         f32x4 rope[RD][2];                                // (cos, sin) of four dims
         auto rotary = [&](const int i) {
             const int s = i / NC, c = i % NC, head = tile[s] / hpt;
@@ -180,12 +180,14 @@ __device__ __forceinline__ void pf_epilogue(const PfArgs& a, const f32x4 (&acc)[
                     // four lanes of a quad (rows m & ~3 .. m | 3; a block starts at a multiple of 16, so they are neighbours in a fragment)
                     E* base = kvp + (size_t)(head - a.n_h - a.n_kv) * 2 * PT * a.h;
                     quad_transpose(own, m & 3);
-                    if ((row[c] | 3) < a.rows) {
+                    int rows = a.rows;                        // (compared anew for every tile: the masks of all chunks held side by side spilled 50 scalar registers)
+                    asm("" : "+s"(rows));
+                    if ((row[c] | 3) < rows) {
                         store_elem4<T>(base + kv_v_off<T>(slot & ~3, dim + (m & 3), a.h), own);
                     } else {
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
-                            if ((row[c] & ~3) + k < a.rows) base[kv_v_off<T>((slot & ~3) + k, dim + (m & 3), a.h)] = T::from_f32(own[k]);
+                            if ((row[c] & ~3) + k < rows) base[kv_v_off<T>((slot & ~3) + k, dim + (m & 3), a.h)] = T::from_f32(own[k]);
                     }
                 }
             }
@@ -281,7 +283,7 @@ __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const
     for (int p = 0; p + 1 < PD; ++p)                    // the last, partial round: nothing further to request
         if (kb0 + n_full + p < kb1) k_block(p, kb0 + n_full + p, std::false_type{});
 
-    pf_epilogue<T, EPI, NA, NAT, NC>(a, acc, tile, tval, chunk0, ks, lane);
+    pf_epilogue<T, EPI, NC == 8 ? 1 : 4, NA, NAT, NC>(a, acc, tile, tval, chunk0, ks, lane);
 }
 
 // ---- the LDS ring kernel of the prompt GEMMs
@@ -505,7 +507,7 @@ __global__ __launch_bounds__((FW * RW + NL) * 64, (FW * RW + NL + 3) / 4) void p
     bool tval[NA];
 #pragma unroll
     for (int s = 0; s < NA; ++s) { tile[s] = (fb * FW + fw) * NA + s; tval[s] = tile[s] < a.n_tiles; }
-    pf_epilogue<T, EPI, NA, NT, NC>(a, acc, tile, tval, rb * RC + rw * NC, ks, lane);
+    pf_epilogue<T, EPI, 4, NA, NT, NC>(a, acc, tile, tval, rb * RC + rw * NC, ks, lane);
 }
 
 // The bf16 shapes, X(number, weight tiles per wave, chunks per wave, waves over the tiles, waves over the chunks, requesting waves,

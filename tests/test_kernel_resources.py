@@ -51,3 +51,13 @@ def spills(table, prefix):
 @pytest.mark.parametrize("dtype", ["BF16", "F32"])
 def test_ring_kernel_spills_nothing(table, dtype, epilogue):
     assert spills(table, f"pf_ring_kernel<{dtype}, {epilogue},") == {}
+
+
+@pytest.mark.parametrize("dtype", ["BF16", "F32"])
+def test_qkv_epilogue_spills_nothing(table, dtype):
+    assert spills(table, f"pf_ring_kernel<{dtype}, 0,") == {}
+    four_wave = spills(table, f"pf_gemm_kernel<{dtype}, 0,")
+    # eight chunks fill the registers of the bf16 kernel's main loop (the raw sums' spills as many vector registers), nothing else does
+    full = spills(table, f"pf_gemm_kernel<{dtype}, 1,").get(f"pf_gemm_kernel<{dtype}, 1, 4, 8, 4, 2>", (0, 0))
+    assert {n: s for n, s in four_wave.items() if "4, 8, 4, 2>" not in n} == {}
+    assert four_wave.get(f"pf_gemm_kernel<{dtype}, 0, 4, 8, 4, 2>", (0, 0)) <= full
