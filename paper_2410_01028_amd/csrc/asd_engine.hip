@@ -870,12 +870,12 @@ template <class T, int EPI> bool launch_pf_gemm_t(hipStream_t s, const PfCfg& g,
 // k-block: us0 + us1 x the share of the chip that is busy (the clock falls and L2 fills with the workgroups that run).
 struct PfRingTile { int FT, RC; float us0, us1; };
 constexpr int kPfRings = 16;
-constexpr float kPfRawUs[kPfRings][2] = {{0.477f, 0.217f}, {0.300f, 0.222f}, {0.864f, 0.368f}, {0.104f, 0.f}, {0.106f, 0.023f}, {0.127f, 0.026f},
-                                         {0.209f, 0.f}, {0.197f, 0.053f}, {0.193f, 0.f}, {0.199f, 0.124f}, {0.224f, 0.171f}, {0.262f, 0.230f},
-                                         {0.298f, 0.154f}, {0.333f, 0.208f}, {0.253f, 0.158f}, {0.327f, 0.181f}};
-constexpr float kPfPairUs[kPfRings][2] = {{0.520f, 0.180f}, {0.785f, 0.227f}, {0.837f, 0.443f}, {0.233f, 0.060f}, {0.180f, 0.f}, {0.212f, 0.f},
-                                          {0.174f, 0.f}, {0.246f, 0.f}, {0.386f, 0.f}, {0.229f, 0.087f}, {0.263f, 0.115f}, {0.293f, 0.166f},
-                                          {0.396f, 0.003f}, {0.425f, 0.073f}, {0.426f, 0.027f}, {0.410f, 0.110f}};
+constexpr float kPfRawUs[kPfRings][2] = {{0.470f, 0.217f}, {0.300f, 0.222f}, {0.877f, 0.371f}, {0.104f, 0.f}, {0.106f, 0.023f}, {0.127f, 0.026f},
+                                         {0.206f, 0.015f}, {0.197f, 0.053f}, {0.193f, 0.f}, {0.189f, 0.118f}, {0.224f, 0.171f}, {0.273f, 0.221f},
+                                         {0.289f, 0.148f}, {0.343f, 0.208f}, {0.253f, 0.158f}, {0.332f, 0.184f}};
+constexpr float kPfPairUs[kPfRings][2] = {{0.511f, 0.176f}, {0.785f, 0.170f}, {0.837f, 0.418f}, {0.238f, 0.062f}, {0.180f, 0.f}, {0.212f, 0.f},
+                                          {0.174f, 0.f}, {0.246f, 0.f}, {0.398f, 0.f}, {0.229f, 0.087f}, {0.263f, 0.115f}, {0.293f, 0.166f},
+                                          {0.393f, 0.006f}, {0.425f, 0.073f}, {0.426f, 0.027f}, {0.410f, 0.110f}};
 #define PFR(v, nt, nc, fw, rw, nl, pf) {nt * fw, nc * rw, kPfRawUs[v][0], kPfRawUs[v][1]},
 constexpr PfRingTile kPfRing[kPfRings] = {PF_RING_SHAPES(PFR)};
 #undef PFR
@@ -897,17 +897,19 @@ const PfRingTile& pf_ring_tile(bool f32, bool pairs, int v) { return f32 ? (pair
 // The kernel, shape and K slices with the least estimated time.  pf_ring_kernel: rounds of workgroups (one to a compute unit) on the busiest XCD, times
 // a workgroup's k-blocks at the shape's rate, but no less than the weights take from HBM at 6.1 TB/s; 4 us per round for filling the ring and the epilogue; for
 // split-K launches the partial sums, 0.5 us per MB (written, read back).  pf_gemm_kernel: up to three workgroups share a compute unit, so its time grows with the load
-// and not by rounds, which is where it has the better of the ring: between whole rounds of the larger tiles (7B gate/up at 300 rows 108 us against 117,
-// at 700 rows 197 against 204; 13B O at 448 rows 49 against 55).  The bf16 rates are fitted to some 8000 measurements on the 7B, 13B and 70B matrices (20 to 256 rows: each shape by itself; 272 to 2048 rows: inside prompt passes that
-// follow each other, at the clock that such passes keep): near the best time the estimate is off by 3 to 10 %, and what it takes costs 1 % more than the best on average, at worst 18 %
-// (7B gate/up, 300 rows: 127 us against 108; 13B down, 160 rows: 68 against 58; 1700 rows: 440 against 381).
+// and not by rounds, which is where it has the better of the ring: between whole rounds of the larger tiles (7B gate/up at 300 rows 113 us against 119 of the best
+// shape, QKV at 1600 rows 279 against 301).  It streams weights at 5.3 TB/s and so is not the one for few rows (70B gate/up at 45 rows 172 us against 152).
+// The bf16 rates are fitted to some 10000 measurements on the 7B, 13B and 70B matrices at 70 lengths (20 to 2048 rows), up to 480 rows of a launch inside passes, beyond
+// of whole passes that follow each other with one launch's shape exchanged: the clock there goes by what all launches move, so a shape with much traffic slows down the
+// launches behind it (70B at 1600 rows, two layers, gate/up on an 8 x 6 or a 12 x 8 tile: 2361 and 2371 us alone, the pass 9290 and 8815 us).  What the estimate takes costs 0.8 % of a
+// launch more than the best on average, at worst 15 % (7B O, 1050 rows: 78 us against 67; 13B down, 1450 rows: 386 against 340; 70B QKV, 100 rows: 67 against 60).
 // In fp32 two waves on one SIMD are priced as if each had it alone, and the four-wave kernel's constant (1.1 us per k-block) is that of one workgroup to a unit: from
 // 100 rows on the choice costs up to half again what the best tile would (7B down at 144 rows 167 us against 115), and at 200 rows QKV takes 244 us where the four-wave
 // kernel needs 216; a whole prompt is faster at every length measured (17 to 1100 rows) than it was on the four-wave kernel alone.
 // Up to PF_FIXED_SLICES chunks (640 rows) the K slices are the same for every choice, so that the order of the sums,
-// hence every bit, of a contraction depends neither on the kernel nor on its tile.  It is not the fastest count everywhere: 13B down at 48 rows 39 us, with six slices 32, at
-// 80 rows 61, with three 44; 7B down at 48 rows 24 us, with eight 22.5, at 300 rows 63 us and nothing better.  Longer blocks take what the estimate says
-// (13B at 1003 rows, O and down: 94 and 227 us with two slices, 120 and 300 us with four).
+// hence every bit, of a contraction depends neither on the kernel nor on its tile.  It is not the fastest count everywhere: 13B down at 48 rows 34 us, with six slices 31, at
+// 80 rows 45, with eight 35; 7B down at 48 rows 24 us, with eight 22, at 300 rows 49 us and nothing better, at 512 rows 80, with two 73 (O 42 and 35).  Longer blocks take
+// what the estimate says (13B at 1003 rows, O and down: 92 and 225 us with one slice, 98 and 239 with two, 123 and 277 with four).
 constexpr int PF_FIXED_SLICES = 40;
 PfPick pf_pick_gemm(const PfRules& r, int cls, int n_chunks) {
     const PfCfg& g = r.cfg[cls];
@@ -922,8 +924,8 @@ PfPick pf_pick_gemm(const PfRules& r, int cls, int n_chunks) {
         const int na = pairs ? 2 : cls == PF_C_QKV ? pf_qkv_na(g, n_tiles, n_chunks) : 4, per = PF_NW * na;
         const float load = (float)(((n_tiles + per - 1) / per + 7) / 8 * ((n_chunks + g.NC - 1) / g.NC) * ks4) / units;
         const float on_unit = load > 2.f ? load : ceilf(load), frags = PF_NW * (pairs ? 2 * na : na) + F32::NP * g.NC;
-        const float kb_us = f32 ? fmaxf(1.1f, on_unit * frags / 57.f) : pairs ? 0.154f + 0.390f * fmaxf(load, 1.f) : 0.08f + 0.096f * na * fmaxf(load, 1.f);
-        best_us = 4.f + fmaxf((float)KB / ks4 * kb_us, hbm_us) + ks4 * slice_us;
+        const float kb_us = f32 ? fmaxf(1.1f, on_unit * frags / 57.f) : pairs ? 0.154f + 0.390f * fmaxf(load, 1.f) : 0.088f + 0.097f * na * fmaxf(load, 1.f);
+        best_us = 4.f + fmaxf((float)KB / ks4 * kb_us, f32 ? hbm_us : hbm_us * (6.1f / 5.3f)) + ks4 * slice_us;
     }
     for (int v = 0; v < kPfRings; ++v) {
         const PfRingTile& T = pf_ring_tile(f32, pairs, v);

@@ -68,3 +68,16 @@ def test_short_prompts_and_bad_lengths():
     cfg.d_model = 100
     with pytest.raises(asd.AsdError):
         asd.plan_prompt(cfg, 20)
+
+
+@pytest.mark.parametrize("name,n,gemm,tiles", [
+    # the kernels and shapes within 5 % of the best measured (up to 480 rows: the launch; beyond: the whole pass with this launch exchanged)
+    ("7b", 272, "gateup", {-1}), ("7b", 300, "gateup", {-1, 12}), ("7b", 320, "gateup", {-1}),       # ring's best 119, 119, 121 us against 112, 113, 114
+    ("7b", 1600, "qkv", {-1}),                                                                       # 279 us, the ring's best 301
+    ("70b", 20, "gateup", {8, 14, 15}), ("70b", 45, "gateup", {8, 14, 15}),                          # 145 and 152 us, four-wave 170 and 172
+    ("13b", 45, "oproj", {8}), ("13b", 45, "down", {8}), ("13b", 160, "down", {14, 15}),             # 18, 35, 59 us; the former choices 22, 39, 68
+    ("70b", 300, "oproj", {11}),
+    ("13b", 1700, "down", {1, 12}), ("13b", 1900, "down", {11, 12}), ("70b", 1600, "gateup", {1, 2}),
+], ids=lambda v: str(v) if isinstance(v, (int, str)) else "")
+def test_the_estimate_takes_what_was_measured_faster(name, n, gemm, tiles):
+    assert asd.plan_prompt(asd.make_config(si.SHAPES[name], n), n)[0]["tile"][gemm] in tiles
