@@ -348,11 +348,11 @@ Plan make_plan(const asd_config& c) {
     // Longer blocks (fewer, better balanced launches) are laid out over the staging region too, which only a weight
     // upload or read-back uses, and only if they fit into what 512 rows and the staging region take anyway (the arena does
     // not grow) and no activation has k padding (padding is cleared once, when the engine is created, and an upload
-    // would leave other bytes there).
+    // would leave other bytes there).  512 rows move there too where that makes room for the extra KiB per chunk:
     // Fragments (KiB) from a chunk to the next: the k-blocks, made odd.  A workgroup asks for the same k-block of all its chunks
     // at once, and an XCD's L2 spreads addresses over its channels every 4 KiB: with 128 or 256 k-blocks between chunks
     // (d_model 4096, 8192) all of them fall on the same quarter of the channels.  QKV at 512 rows, tile 15 and tile 12: 70B 135 -> 138 and
-    // 144 -> 126 us, 7B at 300 rows with tile 11 73 -> 62 us.  Long blocks that fit only without the extra KiB do without.
+    // 144 -> 126 us, 7B at 300 rows with tile 11 73 -> 62 us.  Blocks that fit only without the extra KiB do without.
     // In fp32, whose products hide the requests, it gains nothing (256 k values, 4 layers, 30 rows: 173 us with it, 168 without).
     auto take_pf = [&](size_t R, int odd) {
         p.pf_rows = (int)R;
@@ -367,11 +367,11 @@ Plan make_plan(const asd_config& c) {
         p.pf_attn_out = take(R / 16 * p.cf_q * frag * NPL);
         p.pf_hmid = take(R / 16 * p.cf_f * frag * NPL);
     };
-    take_pf(PF_MIN_ROWS, c.dtype == ASD_DT_BF16);
+    take_pf(PF_MIN_ROWS, 0);
     const size_t end = off;
     if (c.dtype == ASD_DT_BF16 && c.d_model % kblk == 0 && qd % kblk == 0 && c.d_ffn % kblk == 0) {
         bool fits = false;
-        for (size_t R = PF_MAX_ROWS; R > PF_MIN_ROWS && !fits; R /= 2)
+        for (size_t R = PF_MAX_ROWS; R >= PF_MIN_ROWS && !fits; R /= 2)
             for (int odd = 1; odd >= 0 && !fits; --odd) {
                 const Plan keep = p;
                 off = p.staging;

@@ -43,6 +43,12 @@ def test_long_blocks_need_room_in_the_staging_region_and_no_padding():
     assert [most(s) for s in SHAPES] == [512, 2048, 2048, 2048, 512, 1024, 2048, 512, 512, 512, 512]
 
 
+def test_prompt_workspace_does_not_make_the_arena_larger():
+    """An arena of the size that 512 rows of activations without extra space between their chunks need is enough for every shape."""
+    sizes = [93562112, 18176713728, 33246890240, 141454589696, 19984384, 29615104, 46308352, 15901952, 62781184, 45114368, 80845824]
+    assert [asd.arena_bytes(asd.make_config(s, 8192)) for s in SHAPES] == sizes
+
+
 def test_overrides_are_honoured_or_fall_back_as_stated():
     plan = lambda shape, n, tune: asd.plan_prompt(asd.make_config(shape, n, debug_tune=tune), n)[0]
     for v in range(16):
