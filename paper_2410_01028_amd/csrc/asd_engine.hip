@@ -673,7 +673,7 @@ void build_pass(asd_engine* e, int M, int pos_off, const uint8_t* mask, int ctx_
     push(OP_FINISH, ASD_K_FINISH, 1, 0);
 }
 
-// Enqueue what a call starts with: state, zeroed words, at most 16 tokens
+// What a call starts with: state, words to clear, at most 16 token ids (begin_embed_kernel, pf_embed_kernel, or launch_begin where the first pass is none of the call's own launches)
 BeginArgs begin_args(const asd_engine* e, int pos, int target = 0, int reset_counts = 0, int index_base = 0, void* zero = nullptr, int n_zero = 0,
                      const int32_t* tok = nullptr, int n_tok = 0) {
     BeginArgs a{};
@@ -682,7 +682,7 @@ BeginArgs begin_args(const asd_engine* e, int pos, int target = 0, int reset_cou
     for (int i = 0; i < n_tok; ++i) a.tok[i] = tok[i];
     return a;
 }
-void launch_begin(asd_engine* e, const BeginArgs& a) { begin_kernel<<<1, 256, 0, e->stream>>>(a); }
+void launch_begin(asd_engine* e, const BeginArgs& a) { begin_kernel<<<1, 64, 0, e->stream>>>(a); }
 
 template <class T> void launch_embed_t(asd_engine* e, const int32_t* d_tokens, int M, const float* gain, float* part, const BeginArgs* begin) {
     using El = typename T::elem;
@@ -1791,6 +1791,7 @@ int asd_decode(asd_engine* e, int32_t last_token, int32_t n_more, const asd_gen_
     const auto t0 = std::chrono::steady_clock::now();
     const bool sampled = p->temperature > 0.f;
     const SampleArgs sa = sampled ? sample_args(e, p->temperature, p->seed) : SampleArgs{};
+    // (a launch of its own, once per call: the passes behind it are captured and replayed, its values are this call's)
     launch_begin(e, begin_args(e, e->kv_len, n_more, 1, sampled ? (int)p->sample_index0 : 0, nullptr, 0, &last_token, 1));
     const bool graphs = p->use_graphs != 0;
     if (sampled && (e->graph_T != p->temperature || e->graph_seed != p->seed)) {        // both are baked into captured launches

@@ -68,11 +68,12 @@ __device__ __forceinline__ void begin_state(const BeginArgs& a, const int i, con
         if (a.reset_counts) { st->cycles = 0; st->drafted = 0; st->accepted = 0; }
     }
 }
-__global__ __launch_bounds__(256) void begin_kernel(const BeginArgs a) { begin_state(a, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256, 0); }
+// the state and ids alone, one wave: where the passes that follow are recorded and replayed, or other kernels come first
+__global__ __launch_bounds__(64) void begin_kernel(const BeginArgs a) { begin_state(a, threadIdx.x, 64, 0); }
 // begin_kernel and embed_kernel in one launch, for ids that come as arguments (tokens NULL) or from a caller's device buffer: the embedding reads nothing that
 // begin_kernel writes except the ids, and what it would add to the state's error bits the state's writer finds for itself.  A dependent launch costs about 4 us and
-// neither of the two does that much: one row, fp32, 256 features, 4 layers: a pass 145 -> 133 us; bf16, 4096 features, 2
-// layers: 249.7 -> 245.1 us.
+// neither of the two does that much: one row, bf16, 4096 features, 2 layers: a pass 249 -> 246 us (the mean of 16 row counts: 1.3 % less; with fp32, 256 features and 4 layers the
+// gain lies inside the 8 % between runs of one build).
 template <class T>
 __global__ __launch_bounds__(EMBED_THREADS) void begin_embed_kernel(const BeginArgs a, const int32_t* tokens, const typename T::elem* E, int d, int vocab,
                                                                     const float* g_first, float* xres, void* xb, size_t xb_plane, int rs, float* part) {
