@@ -1,5 +1,8 @@
 """The ring kernel of the prompt GEMMs: every tile shape and K split against the chunked prompt pass (the decode kernels).
 
+pf_ring=V names a shape by number: in bf16 2 is the largest (16 weight tiles or 8 pairs x 16 chunks), 0 and 1 are 16 x 8 and 12 x 8 tiles (8 and 12 pairs x 8), 3 the
+smallest of QKV and the raw sums (4 x 2; gate/up 4 pairs x 5), 4 to 15 lie between; in fp32 3 is the largest and 4 the smallest (3 x 2).
+
 The first two shapes have output widths that no tile divides (feature blocks with a partly filled last tile, and fewer blocks than
 XCDs), and K ranges shorter than the ring; their workspace holds 512 rows.  The other two have a vocabulary large enough for the
 staging region to hold blocks of 1024 and 2048 rows.  The prompts end inside a 16-row chunk, inside a workgroup's 8 (16) chunks,
@@ -24,11 +27,11 @@ LONGEST = {"least": 512, "ragged": 512, "even": 512, "long-1k": 1024, "long-2k":
 CASES = [(RAGGED, "pf_ring=0", 81), (RAGGED, "pf_ring=1", 130), (RAGGED, "pf_ring=2,2", 97), (RAGGED, "pf_ring=3", 300), (RAGGED, "pf_ring=0,6", 200),
          (RAGGED, "pf_ring=4", 17), (RAGGED, "pf_ring=5", 45), (RAGGED, "pf_ring=6", 63), (RAGGED, "pf_ring=7,1", 100), (RAGGED, "pf_ring=8", 33),
          (RAGGED, "pf_ring=9,3", 49), (RAGGED, "pf_ring=10", 81), (RAGGED, "pf_ring=11", 128), (RAGGED, "pf_ring=12", 32), (RAGGED, "pf_ring=13", 40),
-         (RAGGED, "pf_ring=14", 64), (RAGGED, "pf_ring=15,5", 144), (EVEN, None, 18), (EVEN, None, 300), (EVEN, "pf_ring=1,8", 500),
-         (EVEN, "pf_ring=2,1", 144), (EVEN, "pf_ring=3,2", 1000), (EVEN, None, 2049), (EVEN, "pf_ring=3,1", 2300), (EVEN, "pf_o=4,4,2", 1500),
+         (RAGGED, "pf_ring=14", 64), (RAGGED, "pf_ring=15,5", 144), (RAGGED, "pf_ring=2", 300), (EVEN, None, 18), (EVEN, None, 300), (EVEN, "pf_ring=1,8", 500),
+         (EVEN, "pf_ring=2,1", 144), (EVEN, "pf_ring=3,2", 1000), (EVEN, None, 2049), (EVEN, "pf_ring=3,1", 2300), (EVEN, "pf_ring=2,2", 1000), (EVEN, "pf_ring=2,1", 2300), (EVEN, "pf_o=4,4,2", 1500),
          (LEAST, None, 17), (LEAST, None, 600), (LEAST.with_(dtype=si.DT_F32), None, 45), (LONG_1K, None, 641), (LONG_1K, None, 1003), (LONG_1K, None, 1025), (LONG_1K, None, 2300), (LONG_1K, "pf_ring=1,4", 1009),
          (LONG_1K, "pf_o=4,4,2;pf_down=8,3,2;pf_qkv=4,1,2;pf_gu=4,1,2", 1700), (LONG_2K, None, 641), (LONG_2K, None, 1003), (LONG_2K, None, 2041),
-         (LONG_2K, None, 2049), (LONG_2K, None, 4001), (LONG_2K, None, 4200), (LONG_2K, "pf_ring=3,2", 2035), (LONG_2K, "pf_ring=2,1", 2300), (LONG_2K, "pf_ring=15,3", 1345),
+         (LONG_2K, None, 2049), (LONG_2K, None, 4001), (LONG_2K, None, 4200), (LONG_2K, "pf_ring=3,2", 2035), (LONG_2K, "pf_ring=2,2", 2035), (LONG_2K, "pf_ring=2,1", 2300), (LONG_2K, "pf_ring=15,3", 1345),
          (LONG_2K, "pf_ring=13", 700), (LONG_2K, "pf_o=4,4,2;pf_down=4,4,2;pf_qkv=4,1,2;pf_gu=4,1,2", 1985)]
 
 
