@@ -901,11 +901,11 @@ const PfRingTile& pf_ring_tile(bool f32, bool pairs, int v) { return f32 ? (pair
 // shape, QKV at 1600 rows 279 against 301).  It streams weights at 5.3 TB/s and so is not the one for few rows (70B gate/up at 45 rows 172 us against 152).
 // The bf16 rates are fitted to some 10000 measurements on the 7B, 13B and 70B matrices at 70 lengths (20 to 2048 rows), up to 480 rows of a launch inside passes, beyond
 // of whole passes that follow each other with one launch's shape exchanged: the clock there goes by what all launches move, so a shape with much traffic slows down the
-// launches behind it (70B at 1600 rows, two layers, gate/up on an 8 x 6 or a 12 x 8 tile: 2361 and 2371 us alone, the pass 9290 and 8815 us).  What the estimate takes costs 0.8 % of a
+// launches behind it (70B at 1600 rows, two layers, gate/up on an 8 x 6 or a 12 x 8 tile: 2361 and 2371 us launch by launch, the pass 9290 and 8815 us).  What the estimate takes costs 0.8 % of a
 // launch more than the best on average, at worst 15 % (7B O, 1050 rows: 78 us against 67; 13B down, 1450 rows: 386 against 340; 70B QKV, 100 rows: 67 against 60).
 // In fp32 two waves on one SIMD are priced as if each had it alone, and the four-wave kernel's constant (1.1 us per k-block) is that of one workgroup to a unit: from
-// 100 rows on the choice costs up to half again what the best tile would (7B down at 144 rows 167 us against 115), and at 200 rows QKV takes 244 us where the four-wave
-// kernel needs 216; a whole prompt is faster at every length measured (17 to 1100 rows) than it was on the four-wave kernel alone.
+// 100 rows on the choice costs up to 1.4 times what the best tile would (7B at 144 rows: down 169 us against 119, gate/up 355 against 258), and at 200 rows QKV takes 246 us where the four-wave
+// kernel needs 212; a whole prompt is faster at every length measured (17 to 1100 rows) than it was on the four-wave kernel alone.
 // Up to PF_FIXED_SLICES chunks (640 rows) the K slices are the same for every choice, so that the order of the sums,
 // hence every bit, of a contraction depends neither on the kernel nor on its tile.  It is not the fastest count everywhere: 13B down at 48 rows 34 us, with six slices 31, at
 // 80 rows 45, with eight 35; 7B down at 48 rows 24 us, with eight 22, at 300 rows 49 us and nothing better, at 512 rows 80, with two 73 (O 42 and 35).  Longer blocks take

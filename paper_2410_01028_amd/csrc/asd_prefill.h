@@ -7,7 +7,7 @@
 // one (chunk, k-block) fragment is one contiguous KiB that a wave loads with one instruction, and the prompt attention kernels
 // use the decode kernel's fragments.
 //
-// pf_ring_kernel: a tile of weight tiles x chunks per workgroup (3 x 2 to 16 x 16), both operands brought
+// pf_ring_kernel: a tile of weight tiles x chunks per workgroup (3 x 2 to 24 x 8 and 16 x 16), both operands brought
 // into an LDS ring by direct-to-LDS loads; see its own comment.  The kernel and tile of a launch are the ones with the
 // smallest estimated time.
 // pf_gemm_kernel (at some lengths between whole rounds of the ring's larger tiles): a workgroup of NW waves owns NW*NA weight tiles (16 output features each) x NC chunks of
@@ -294,13 +294,13 @@ __global__ __launch_bounds__(NW * 64, PD >= 2 ? 2 : 1) void pf_gemm_kernel(const
 //
 // What bounds it goes by the length of the block.  Long blocks: the clock the card keeps under the products (a loop of them on random operands in registers,
 // nothing else, runs at 2.06 GHz and 2.1 PFLOP/s) and the cycles in which none issues; the tile is as large as LDS and registers allow.
-// Short ones: what a compute unit takes in.  It has 32 KiB of requests in flight (its L1), so a fragment from HBM costs it 1/27 us
-// and one from L2 1/92 us, and the two add up: few chunks per tile while the weights weigh more, row blocks that share them otherwise.  In between: how
+// Short ones: what a compute unit takes in.  With all units busy a fragment from HBM costs it 1/23 us (non-temporal 1/25) and one from L2 about 1/110 us
+// (one weight fragment and 0, 1, 2, 4 shared ones: 44, 48, 58, 80 ns): few chunks per tile while the weights weigh more, row blocks that share them otherwise.  In between: how
 // evenly the tiles fill the 256 units, hence the number of shapes.
 //
-// Requests.  A direct-to-LDS load holds its wave up for 16 cycles, times the SIMDs that issue one at the same moment, and the product waves of a
-// workgroup, in step behind their barrier, all did: 64 cycles per load without a product (an 8 x 8 tile: 60 us for the 7B shape's QKV at 144 rows).  So NL waves of their own ask
-// for the fragments and do nothing else (44 us), and the product waves hold only accumulators and fragments.  The largest tile leaves them no
+// Requests.  A direct-to-LDS load holds its wave up for 55 cycles, for 78 while one wave on each SIMD asks and 114 while two do, and the product waves of a
+// workgroup, in step behind their barrier, all did, without a product meanwhile (7B QKV at 144 rows 60 us).  So NL waves of their own ask
+// for the fragments and do nothing else (47 us), and the product waves hold only accumulators and fragments.  The largest tile leaves them no
 // registers: there, and in fp32, the product waves request (NL = 0), spread between the products.
 //
 // A stage is one k-block; S stages form a ring.  Per stage one barrier, before which the requesting waves wait until their share of the stage to come has arrived and
@@ -512,7 +512,7 @@ __global__ __launch_bounds__((FW * RW + NL) * 64, (FW * RW + NL + 3) / 4) void p
 
 // The bf16 shapes, X(number, weight tiles per wave, chunks per wave, waves over the tiles, waves over the chunks, requesting waves,
 // second register set): for QKV and the raw sums, and for gate/up, whose tiles come in pairs.  Of some 40 shapes measured on the 7B, 13B and 70B matrices at 20 to
-// 2048 rows, the sixteen of each list that leave the least time on the table (under 1 % over all lengths).
+// 2048 rows, the sixteen of each list that left the least time on the table (under 1 % over all lengths).  Over 1500 configurations of other widths the estimate takes each of them somewhere.
 #define PF_RING_SHAPES(X)                                                                                                \
     X(0, 4, 4, 4, 2, 4, false) X(1, 6, 4, 2, 2, 4, true) X(2, 8, 4, 2, 4, 0, false) X(3, 1, 2, 4, 1, 4, true)            \
     X(4, 1, 3, 3, 1, 3, true) X(5, 1, 4, 4, 1, 4, true) X(6, 2, 3, 4, 1, 4, true) X(7, 2, 4, 4, 1, 4, true)              \
@@ -525,7 +525,7 @@ __global__ __launch_bounds__((FW * RW + NL) * 64, (FW * RW + NL + 3) / 4) void p
     X(12, 6, 3, 2, 2, 4, true) X(13, 6, 4, 2, 2, 4, true) X(14, 4, 5, 4, 1, 4, true) X(15, 8, 3, 2, 2, 4, true)
 // In fp32 a product takes eight times as long (128 cycles of a SIMD per fragment pair): the requests hide behind the products, and
 // a prompt pass of a small model, a few k-blocks per launch, pays for every wave more (256 k values, 4 layers, 30 rows: 168 us like this, 203 with
-// requesting waves).  N weight tiles per wave: one, two for gate/up.
+// requesting waves).  N weight tiles per wave: one, two for gate/up.  The estimate takes 2, 3 and 10 on no width tried (1500 configurations): a tuning string reaches them.
 #define PF_RING_F32_SHAPES(X, N)                                                                                         \
     X(0, 6, 2, 2, 4, 0, true) X(1, 4, 4, 4, 2, 0, true) X(2, 6, 4, 4, 2, 0, true) X(3, 8, 4, 2, 4, 0, false)             \
     X(4, N, 2, 3, 1, 0, true) X(5, N, 3, 3, 1, 0, true) X(6, N, 4, 3, 1, 0, true) X(7, N, 2, 4, 1, 0, true)              \
