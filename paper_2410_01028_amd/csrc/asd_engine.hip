@@ -9,6 +9,7 @@
 #include "asd_pass.h"
 #include "asd_prefill.h"
 #include "asd_sample.h"
+#include "asd_small.h"
 
 #include <chrono>
 #include <cmath>
@@ -135,6 +136,7 @@ struct asd_engine {
     bool sample_mem = false;            // ASD_DBG_SAMPLE_MEM: sampling kernels that re-read memory instead of holding their segments
     bool att_gh1 = false;               // ASD_DBG_ATT_GH1: one query head per attention workgroup also for grouped-query models
     bool force_att_w4 = false;          // ASD_DBG_ATT_W4: always launch the four-waves-per-SIMD attention variant
+    bool small = false;                 // decode passes as one launch per sublayer (small_shape)
     bool rs_pow2 = false;               // ASD_DBG_RS_POW2: activation row stride = next power of two
     float graph_T = 0.f;
     uint64_t graph_seed = 0;
@@ -693,6 +695,20 @@ template <class T> void launch_embed_t(asd_engine* e, const int32_t* d_tokens, i
     else embed_kernel<T><<<grid, EMBED_THREADS, 0, e->stream>>>((const El*)e->embed, d_tokens, e->c.d_model, e->c.vocab, e->st, gain, e->xres, e->xb, plane, row_stride(e, M), part);
 }
 
+// The launch behind a pass's LM head
+void launch_finish(asd_engine* e, int M, const uint8_t* mask, int fin_mode, int fin_arg, const PassOut& out) {
+    const asd_config& c = e->c;
+    const AmaxCand* cand = (const AmaxCand*)out.amax_part;
+    if (fin_mode == FIN_SKIP) return;
+    if (out.d_cos) {
+        MaskBits mb{};
+        for (int j = 0; j < 2 * c.n_layers; ++j) if (mask && mask[j]) mb.w[j >> 5] |= 1u << (j & 31);
+        finish_cos_kernel<<<1, 64 * M, 0, e->stream>>>(cand, e->g_lm.grid, M, c.vocab, out.argmax, e->st, out.cos_acc, 2 * c.n_layers, mb, out.d_cos);
+        return;
+    }
+    finish_kernel<<<1, 64 * M, 0, e->stream>>>(cand, e->g_lm.grid, M, c.vocab, out.argmax, fin_mode, fin_arg, e->st, e->tokbuf, e->out_tokens);
+}
+
 // Run a pass as one launch per step.  embedded: the launch before left this pass's embedding; embed_next: the pass is a draft
 // step (FIN_DRAFT) and its last launch embeds the drafted token for the step that follows under the same mask.  begin: what the
 // pass's first launch sets up (its n_tok ids, if any, are the pass's rows).
@@ -717,14 +733,6 @@ int launch_steps(asd_engine* e, const std::vector<PassOp>& ops, const int32_t* d
             case OP_LM: ok = launch_gemm<EPI_LM>(e, e->g_lm, op.g); break;
             case OP_ATTN: launch_attn(e, op.t); break;
             case OP_FINISH:
-                if (fin_mode == FIN_SKIP) break;
-                if (out.d_cos) {
-                    MaskBits mb{};
-                    for (int j = 0; j < 2 * c.n_layers; ++j) if (mask && mask[j]) mb.w[j >> 5] |= 1u << (j & 31);
-                    finish_cos_kernel<<<1, 64 * M, 0, e->stream>>>((const AmaxCand*)out.amax_part, e->g_lm.grid, M, c.vocab, out.argmax, e->st, out.cos_acc,
-                                                                   2 * c.n_layers, mb, out.d_cos);
-                    break;
-                }
                 if (embed_next) {
                     if (c.dtype == ASD_DT_BF16)
                         finish_embed_kernel<BF16><<<EMBED_SPLIT, EMBED_THREADS, 0, e->stream>>>((const AmaxCand*)out.amax_part, e->g_lm.grid, out.argmax, fin_arg, e->tokbuf,
@@ -734,8 +742,7 @@ int launch_steps(asd_engine* e, const std::vector<PassOp>& ops, const int32_t* d
                             (const float*)e->embed, c.d_model, c.vocab, e->st, next_gain(e, mask, -1), e->xres, e->xb, (size_t)e->KBd * 64 * e->KE, out.part);
                     break;
                 }
-                finish_kernel<<<1, 64 * M, 0, e->stream>>>((const AmaxCand*)out.amax_part, e->g_lm.grid, M, c.vocab, out.argmax, fin_mode, fin_arg,
-                                                           e->st, e->tokbuf, e->out_tokens);
+                launch_finish(e, M, mask, fin_mode, fin_arg, out);
                 break;
         }
         pr.end();
@@ -746,13 +753,105 @@ int launch_steps(asd_engine* e, const std::vector<PassOp>& ops, const int32_t* d
     return ASD_OK;
 }
 
+// ------------------------------------------------------------------ small fp32 models: one launch per sublayer (asd_small.h)
+// Shapes the kernels take: fp32, one KV head per query head, a residual projection's K slice (an eighth) inside one head, 256 features, 256 query dims and 768 hidden
+// features at most (a slice's weights in one workgroup's registers, all requested ahead), and the launch shapes whose order of sums they follow (all of them the default's).
+bool small_shape(const asd_config& c, const Plan& p) {
+    const int qd = c.n_heads * c.head_dim;
+    auto is = [](const GemmCfg& g, int nw, int kmajor) { return g.NW == nw && g.kmajor == kmajor && g.kint == kmajor; };
+    return c.dtype == ASD_DT_F32 && c.n_kv_heads == c.n_heads && c.d_model <= SM_D && qd <= SM_Q && qd % (16 * SM_SLICES) == 0 &&
+           SM_SLICES % c.n_heads == 0 && c.d_ffn <= SM_FFN_TILES * SM_SLICES * 16 && c.d_ffn >= SM_SLICES * 16 &&
+           is(p.g_qkv, 4, 1) && is(p.g_o, 8, 0) && p.g_o.TN == 1 && is(p.g_gu, 8, 0) && is(p.g_down, 8, 1) && p.g_down.TN == 1 && is(p.g_lm, 8, 1) && p.g_lm.TN == 2;
+}
+// A pass of M rows over nc chunks of context goes this way.  The chains' time grows with the rows in eight compute units, hardly at all in the five launches' many.  256 features, 4 layers,
+// one launch per sublayer / five per layer, us: 1 row 61 / 99 (context 20), 75 / 114 (context 700); 2 rows 72 / 100; 4 rows 78 / 100; 5 rows 88 / 101 and 105 / 117; 6 rows 94 / 102 and
+// 113 / 117; 8 rows 102 / 102 and 121 / 117; 9 rows 139 / 106.  Contexts beyond SM_CHUNKS chunks need more waves than the workgroup has.
+bool small_pass(const asd_engine* e, int M, int nc) { return e->small && M <= SM_ROWS && nc <= SM_CHUNKS; }
+
+// kernel instances by row count: f(4-row groups in matrix instructions, a row beside them)
+template <class F> void sm_by_rows(int M, F f) {
+    using std::integral_constant;
+    if (M == 1) f(integral_constant<int, 0>{}, integral_constant<int, 1>{});
+    else if (M <= 4) f(integral_constant<int, 1>{}, integral_constant<int, 0>{});
+    else if (M == 5) f(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+    else f(integral_constant<int, 2>{}, integral_constant<int, 0>{});
+}
+
+// pending: the draft whose token the pass before left to this one's first launch (-1: none); leave_finish: leave this draft's to the next
+int enqueue_small(asd_engine* e, const int32_t* d_tokens, int M, int pos_off, const uint8_t* mask, int nc, int fin_mode, int fin_arg, const PassOut& out, int pending,
+                  bool leave_finish, const BeginArgs* begin) {
+    const asd_config& c = e->c;
+    const int d = c.d_model, qd = c.n_heads * c.head_dim;
+    // the stream's and the slices' two buffers: workspace of the five-launch path and of prompt blocks
+    float* xbuf[2] = {e->xres, (float*)e->xb};
+    const size_t part_n = (size_t)SM_SLICES * SM_ROWS * d;
+    static_assert(2 * SM_SLICES * SM_ROWS <= PF_RAW_ROWS, "the slices fit the prompt blocks' partial sums");
+    float* pbuf[2] = {e->pf_raw, e->pf_raw + part_n};
+#define SM_IN in.part, in.xin, in.gain, in.d | (M << 16)
+    int n = 0, open_sub = -1;               // launches so far; sublayer whose projection is open
+    const BeginArgs first = begin ? *begin : BeginArgs{};
+    SmallIn in{};
+    in.d = d; in.M = M; in.inv_d = 1.f / (float)d; in.eps = c.rms_eps; in.ssq = out.ssq;
+    in.E = (const float*)e->embed; in.tokens = d_tokens; in.argmax = out.argmax; in.tokbuf = e->tokbuf; in.st = e->st;
+    in.vocab = c.vocab; in.P = e->g_lm.grid;
+    auto input = [&](const float* gain, bool keep) {
+        in.embed = n == 0; in.gain = gain;
+        in.xin = xbuf[(n + 1) & 1]; in.part = pbuf[(n + 1) & 1]; in.xout = keep ? xbuf[n & 1] : nullptr;
+        in.cand = n == 0 && pending >= 0 ? (const AmaxCand*)out.amax_part : nullptr; in.draft = pending;
+        in.has_begin = n == 0 && begin;
+        in.fin_cos_rows = open_sub >= 0 ? out.cos_rows + (size_t)open_sub * ASD_ROWS : nullptr;
+        in.fin_cos_acc = open_sub >= 0 ? out.cos_acc + open_sub : nullptr;
+    };
+    for (int l = 0; l < c.n_layers; ++l) {
+        const Layer& ly = e->layers[l];
+        if (!(mask && mask[2 * l])) {
+            SmallAttn a{};
+            a.Wo = (const float*)ly.wo; a.part_out = pbuf[n & 1];
+            a.kv = (float*)(e->kv + (size_t)l * e->kv_layer_bytes); a.page_table = e->page_table;
+            a.pos_off = pos_off; a.page_tokens = c.page_tokens; a.nc = nc; a.scale = 1.f / sqrtf((float)c.head_dim);
+            int s_log = 0;
+            while ((c.n_heads << s_log) < SM_SLICES) ++s_log;
+            const int heads = c.n_heads | (s_log << 8) | ((qd == SM_Q ? 5 : 4) << 16);
+            input(ly.g_attn, true);
+            sm_by_rows(M, [&](auto rm, auto rv) {
+                constexpr int RM = decltype(rm)::value, RV = decltype(rv)::value;
+#define ATT(h) if (c.head_dim == h) sm_attn_kernel<h, RM, RV><<<SM_SLICES, SM_NT, 0, e->stream>>>(SM_IN, heads, (const float*)ly.wqkv, e->st, e->rope, in, first, a);
+                ATT(32) ATT(64) ATT(128)
+#undef ATT
+            });
+            ++n; open_sub = 2 * l;
+        }
+        if (!(mask && mask[2 * l + 1])) {
+            float* const part_out = pbuf[n & 1];
+            input(ly.g_mlp, true);
+            sm_by_rows(M, [&](auto rm, auto rv) {
+                sm_mlp_kernel<decltype(rm)::value, decltype(rv)::value><<<SM_SLICES, SM_NT, 0, e->stream>>>(
+                    SM_IN, c.d_ffn / 16, (const float*)ly.wg, (const float*)ly.wu, (const float*)ly.wd, in, first, part_out);
+            });
+            ++n; open_sub = 2 * l + 1;
+        }
+    }
+    input(e->g_final, false);
+    sm_by_rows(M, [&](auto rm, auto rv) {
+        sm_lm_kernel<decltype(rm)::value, decltype(rv)::value><<<(c.vocab + 63) / 64, SM_LM_NW * 64, 0, e->stream>>>(
+            SM_IN, c.vocab, (const float*)e->lm, in, first, out.logits, out.amax_part);
+    });
+#undef SM_IN
+    if (!leave_finish) launch_finish(e, M, mask, fin_mode, fin_arg, out);
+    const hipError_t r = hipGetLastError();
+    if (r != hipSuccess) return fail(e, ASD_E_HIP, "kernel launch: %s", hipGetErrorString(r));
+    return ASD_OK;
+}
+
+// pending (>= 0): the pass before was draft step `pending` under the same mask and left its end to this one; leave_finish: this draft step does so
 int enqueue_forward(asd_engine* e, const int32_t* d_tokens, int M, int pos_off, const uint8_t* mask, int nc,
                     Profiler* profiler, int ctx_for_bytes, int fin_mode = FIN_NONE, int fin_arg = 0, const PassOut* out_or_null = nullptr,
-                    bool embedded = false, bool embed_next = false, const BeginArgs* begin = nullptr) {
+                    int pending = -1, bool leave_finish = false, const BeginArgs* begin = nullptr) {
     const PassOut out = out_or_null ? *out_or_null : engine_out(e);
+    if (small_pass(e, M, nc) && !profiler) return enqueue_small(e, d_tokens, M, pos_off, mask, nc, fin_mode, fin_arg, out, pending, leave_finish, begin);
     std::vector<PassOp> ops;
     build_pass(e, M, pos_off, mask, ctx_for_bytes, nc, out, ops);
-    return launch_steps(e, ops, d_tokens, M, mask, profiler, fin_mode, fin_arg, out, embedded, embed_next, begin);
+    return launch_steps(e, ops, d_tokens, M, mask, profiler, fin_mode, fin_arg, out, pending >= 0, leave_finish, begin);
 }
 
 bool weights_ready(asd_engine* e) {
@@ -1217,6 +1316,9 @@ int asd_create(const asd_config* cfg, void* device_arena, size_t arena_bytes, vo
     e->sample_mem = (cfg->debug_flags & ASD_DBG_SAMPLE_MEM) != 0;
     e->force_att_w4 = (cfg->debug_flags & ASD_DBG_ATT_W4) != 0;
     e->rs_pow2 = (cfg->debug_flags & ASD_DBG_RS_POW2) != 0;
+    int sm_on[1] = {1};
+    tune_entry(tune, "small", sm_on, 1);
+    e->small = sm_on[0] && small_shape(*cfg, p) && !(cfg->debug_flags & (ASD_DBG_ATT_GH1 | ASD_DBG_ATT_W4 | ASD_DBG_RS_POW2));
     e->kv_len = 0;
     e->acs.assign(2 * (size_t)cfg->n_layers, 0.f);
     e->acs_sum.assign(2 * (size_t)cfg->n_layers, 0.0);
@@ -1478,7 +1580,7 @@ int asd_admg(const float* C, int32_t L, float alpha, int32_t m, int32_t n, int32
 // run rows [tokens, tokens+n) at the current cache end; results stay on the device (first: the running cosine sums start anew)
 static int forward_rows(asd_engine* e, const int32_t* tokens, int n, const uint8_t* mask, bool first) {
     const BeginArgs begin = begin_args(e, e->kv_len, 0, 0, 0, e->cos_acc, first ? 4 * e->c.n_layers : 0, tokens, n);
-    return enqueue_forward(e, nullptr, n, 0, mask, chunks_for(e->kv_len + n - 1), nullptr, e->kv_len + n, FIN_NONE, 0, nullptr, false, false, &begin);
+    return enqueue_forward(e, nullptr, n, 0, mask, chunks_for(e->kv_len + n - 1), nullptr, e->kv_len + n, FIN_NONE, 0, nullptr, -1, false, &begin);
 }
 
 int asd_forward(asd_engine* e, const int32_t* tokens, int32_t n_rows, int32_t pos0, const uint8_t* mask, int32_t commit,
@@ -1560,7 +1662,7 @@ int asd_forward_noalloc(asd_engine* e, const int32_t* d_tokens, int32_t n_rows, 
     const BeginArgs begin = begin_args(e, e->kv_len, 0, 0, 0, out.cos_acc, nz);
     out.d_cos = d_cos;
     const int rc = enqueue_forward(e, d_tokens, n_rows, 0, mask, chunks_for(e->kv_len + n_rows - 1), nullptr, e->kv_len + n_rows, FIN_NONE, 0, &out,
-                                   false, false, &begin);
+                                   -1, false, &begin);
     if (rc) return rc;
     const hipError_t r = hipGetLastError();
     if (r != hipSuccess) return fail(e, ASD_E_HIP, "kernel launch: %s", hipGetErrorString(r));
@@ -1633,13 +1735,14 @@ int asd_prefill_chunked(asd_engine* e, const int32_t* tokens, int32_t n, int32_t
 
 static int enqueue_drafts(asd_engine* e, int kk, const uint8_t* mask, int nc, int32_t ctx) {
     for (int j = 0; j < kk; ++j) {
-        int rc = enqueue_forward(e, e->tokbuf + j, 1, j, mask, nc, nullptr, ctx, FIN_DRAFT, j, nullptr, j > 0, j + 1 < kk);
+        // (the last step's token: found by the verification's first launch where passes take one launch per sublayer)
+        int rc = enqueue_forward(e, e->tokbuf + j, 1, j, mask, nc, nullptr, ctx, FIN_DRAFT, j, nullptr, j - 1, j + 1 < kk || small_pass(e, kk + 1, nc));
         if (rc) return rc;
     }
     return ASD_OK;
 }
 static int enqueue_verify(asd_engine* e, int kk, int nc, int32_t ctx) {
-    return enqueue_forward(e, e->tokbuf, kk + 1, 0, nullptr, nc, nullptr, ctx, FIN_ACCEPT, kk);
+    return enqueue_forward(e, e->tokbuf, kk + 1, 0, nullptr, nc, nullptr, ctx, FIN_ACCEPT, kk, nullptr, small_pass(e, kk + 1, nc) ? kk - 1 : -1);
 }
 
 // sampling stream key: the synthetic-input generator's stream derivation for tensor id 102

@@ -1,0 +1,95 @@
+"""Decode passes of small fp32 models (one launch per sublayer) against the same passes as one launch per step (`small=0`): the
+order of every sum is the same, so the bits are."""
+import numpy as np
+import pytest
+
+import asd_inputs as si
+import paper_2410_01028_amd as asd
+
+pytestmark = pytest.mark.gpu
+
+# edges of what the kernels take: features 64 .. 256 (odd numbers of tiles, a ragged last group of 64), 1 .. 8 heads of each size (16 and 32 dims per
+# slice), hidden tiles that do not divide by the eight slices, a vocabulary whose last 64 and last 32 logits are not whole
+SHAPES = [si.SHAPES["tiny"],
+          si.Shape("one-head", 2, 64, 1, 1, 128, 128, 48, si.DT_F32, 8, 8, 2),
+          si.Shape("two-heads", 2, 240, 2, 2, 128, 768, 336, si.DT_F32, 8, 8, 2),
+          si.Shape("narrow", 3, 112, 4, 4, 32, 208, 400, si.DT_F32, 8, 8, 2),
+          si.Shape("eight-heads", 2, 256, 8, 8, 32, 400, 1024, si.DT_F32, 8, 8, 2),
+          si.Shape("two-small-heads", 1, 16, 2, 2, 64, 752, 16, si.DT_F32, 8, 8, 2)]
+
+
+def engines(s, max_seq=1024):
+    W = list(si.all_tensors(s, 5, gain_std=0.1))
+    return [asd.Engine(asd.make_config(s, max_seq, page_tokens=64, debug_tune=t)).load(W) for t in (None, "small=0")]
+
+
+def same(a, b, what):
+    for k in a:
+        assert np.array_equal(np.asarray(a[k]).view(np.int32), np.asarray(b[k]).view(np.int32)), (what, k)
+
+
+@pytest.mark.parametrize("s", SHAPES, ids=lambda s: s.name)
+def test_passes_have_the_bits_of_one_launch_per_step(s):
+    """Every row count, over the edges of chunks, of the groups of 256 keys, and past the longest context of these kernels (768)."""
+    new, old = engines(s)
+    rng = np.random.default_rng(3)
+    toks = rng.integers(0, s.vocab, 1024, dtype=np.int32)
+    mask = np.zeros(2 * s.n_layers, np.uint8)
+    for start, rows in ((0, (1, 2, 5, 9, 16, 3)), (57, (6, 4, 1)), (250, (3, 8, 1)), (505, (13, 1, 4)), (751, (16, 1, 4, 1))):
+        for e in (new, old):
+            e.reset()
+            for p in range(0, start, 16):
+                e.forward(toks[p:min(start, p + 16)], p, want_logits=False)
+        pos = start
+        for n in rows:
+            for skip in (None, mask):
+                if skip is not None:
+                    skip[:] = rng.integers(0, 2, skip.size)
+                a, b = (e.forward(toks[pos:pos + n], pos, skip, commit=False) for e in (new, old))
+                same(a, b, (start, pos, n, skip))
+            a, b = (e.forward(toks[pos:pos + n], pos) for e in (new, old))
+            same(a, b, (start, pos, n))
+            pos += n
+        for layer in range(s.n_layers):
+            for x, y in zip(new.get_kv(layer, 0, pos), old.get_kv(layer, 0, pos)):
+                assert np.array_equal(x.view(np.int32), y.view(np.int32)), (start, layer)
+    new.close(), old.close()
+
+
+@pytest.mark.parametrize("options", [dict(draft_len=4), dict(draft_len=0), dict(draft_len=15), dict(draft_len=3, use_graphs=False), dict(draft_len=4, refresh=True),
+                                     dict(draft_len=4, exit_mode=1, gamma0=0.0011), dict(draft_len=4, temperature=0.8, seed=3), dict(draft_len=0, temperature=0.8, seed=3)],
+                         ids=lambda o: "-".join(f"{k}{v}" for k, v in o.items()))
+def test_loops_emit_the_same(options):
+    """The drafts' ends left to the next pass's first launch, in every form of the loop; the cache crosses a group of 256 keys and the end of these
+    kernels' contexts (where a cycle goes back to one launch per step)."""
+    s = si.SHAPES["tiny"]
+    new, old = engines(s)
+    rng = np.random.default_rng(4)
+    for n_prompt, n_new in ((9, 40), (241, 32), (745, 40)):
+        prompt = rng.integers(0, s.vocab, n_prompt, dtype=np.int32)
+        for masked in (dict(alpha=0.985, m=2, n=1), dict(fixed_mask=np.array([1, 0, 0, 1, 1, 1, 0, 0], np.uint8))):
+            if "refresh" in options and "fixed_mask" in masked:
+                continue
+            (ta, sa, ma), (tb, sb, mb) = (e.generate(prompt, n_new, **options, **masked) for e in (new, old))
+            assert np.array_equal(ta, tb) and np.array_equal(ma, mb), (n_prompt, masked)
+            assert all(sa[k] == sb[k] for k in ("cycles", "drafted", "accepted", "emitted", "mask_changes", "gamma"))
+    new.close(), old.close()
+
+
+def test_a_token_outside_the_vocabulary_is_reported():
+    import torch
+    s = si.SHAPES["tiny"]
+    new, old = engines(s, 128)
+    for e in (new, old):
+        for ids in ([5, s.vocab, 7], [-1]):
+            t = torch.tensor(ids, dtype=torch.int32, device="cuda:0")
+            lg = torch.zeros((len(ids), s.vocab), device="cuda:0")
+            torch.cuda.synchronize()
+            e.forward_noalloc(t, 0, commit=False, d_logits=lg)
+            with pytest.raises(asd.AsdError):
+                e.check()
+        t = torch.tensor([5], dtype=torch.int32, device="cuda:0")
+        torch.cuda.synchronize()
+        e.forward_noalloc(t, 0, commit=False)
+        e.check()
+    new.close(), old.close()
