@@ -81,10 +81,12 @@ typedef struct {
  * debug_tune: "name=a,b,c,d;..." with name in {qkv, o, gu, down, lm}: tiles per workgroup, waves per
  * workgroup, k-major layout (0/1), interleaved k-blocks (0/1); and name in {pf_qkv, pf_o, pf_gu,
  * pf_down}: 16-row chunks per workgroup, K slices[, prefetch depth[, tiles per wave (pf_qkv: 3..5)]] of the prompt-block GEMMs;
- * "pf_ring=V[,S]": tile shape V (0..15) of the ring kernel of the prompt-block GEMMs and K slices S of its residual-add
+ * "pf_ring=V[,S]": tile shape V (0..15; in fp32 2: a kernel without a ring) of the ring kernel of the prompt-block GEMMs and K
+ * slices S of its residual-add
  * launches (default: by estimated time; a pf_* entry takes its class back to the other kernel, and so does an S that a
  * launch cannot have: more slices than k-blocks, or more than the partial-sum buffer holds, 4096 rows over all slices);
- * "qkv_rows=N": tiles per QKV workgroup in passes of five rows and more (default: by balance).  A
+ * "qkv_rows=N": tiles per QKV workgroup in passes of five rows and more (default: by balance);
+ * "small=0": the decode passes of small fp32 models as one launch per step instead of one per sublayer.  A
  * layout override changes how weights are tiled in the arena, never their values.  The string is
  * copied by asd_create.
  */
@@ -369,8 +371,8 @@ int asd_copy_bench(asd_engine* e, size_t nbytes, int32_t reps, double* ms_avg);
  * How asd_prefill runs a prompt of n tokens under a configuration (host arithmetic, no engine; for the compute units of the
  * current device, 256 where none is visible): block number
  * `block` (0 ..) of n_blocks, its first row and rows, the query rows per attention workgroup (16 or 128: two kernels), and
- * for the layer's contractions QKV, O, gate/up, down the tile shape of the ring kernel (-1: the four-wave kernel) and
- * the K slices.  n <= max_rows: n_blocks is 0 (one pass of the decode kernels).  ASD_E_INVAL: no such block, n outside
+ * for the layer's contractions QKV, O, gate/up, down the tile shape of the ring kernel (-1: the four-wave kernel; in fp32 2: the
+ * kernel without a ring) and the K slices.  n <= max_rows: n_blocks is 0 (one pass of the decode kernels).  ASD_E_INVAL: no such block, n outside
  * [1, capacity], or an invalid configuration.
  */
 typedef struct {

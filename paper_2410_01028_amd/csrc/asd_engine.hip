@@ -987,11 +987,22 @@ constexpr float pf_f32_us(int tiles, int chunks, int waves) {
     const float mfma = tiles * chunks * 0.061f / waves, in = (tiles + F32::NP * chunks) / 43.f;
     return mfma > in ? mfma : in;
 }
-constexpr PfRingTile kPfRingF32[kPfRings] = {PF_RING_F32_SHAPES(PFR, 1)};
+// pf_direct_kernel: fitted at 16 and 32 k-blocks beside the ring's figures
+#define PFD(v) {4, 1, 0.131f, 0.f},
+constexpr PfRingTile kPfRingF32[kPfRings] = {PF_RING_F32_SHAPES(PFR, PFD, 1)};
 #undef PFR
 #define PFR(v, nt, nc, fw, rw, nl, pf) {nt * fw / 2, nc * rw, pf_f32_us(nt * fw, nc * rw, fw * rw), 0.f},
-constexpr PfRingTile kPfRingPairsF32[kPfRings] = {PF_RING_F32_SHAPES(PFR, 2)};
+#undef PFD
+#define PFD(v) {4, 1, 0.238f, 0.f},
+constexpr PfRingTile kPfRingPairsF32[kPfRings] = {PF_RING_F32_SHAPES(PFR, PFD, 2)};
 #undef PFR
+#undef PFD
+#define PFR(v, nt, nc, fw, rw, nl, pf)
+#define PFD(v) constexpr int kPfDirect = v;
+PF_RING_F32_SHAPES(PFR, PFD, 1)
+#undef PFR
+#undef PFD
+constexpr int PF_DIRECT_MAX_KB = 64;                // most k-blocks of a slice: its requests wait for each other every PF_DIRECT_KB, the ring's do not
 const PfRingTile& pf_ring_tile(bool f32, bool pairs, int v) { return f32 ? (pairs ? kPfRingPairsF32 : kPfRingF32)[v] : (pairs ? kPfRingPairs : kPfRing)[v]; }
 // The kernel, shape and K slices with the least estimated time.  pf_ring_kernel: rounds of workgroups (one to a compute unit) on the busiest XCD, times
 // a workgroup's k-blocks at the shape's rate, but no less than the weights take from HBM at 6.1 TB/s; 4 us per round for filling the ring and the epilogue; for
@@ -1029,13 +1040,16 @@ PfPick pf_pick_gemm(const PfRules& r, int cls, int n_chunks) {
     for (int v = 0; v < kPfRings; ++v) {
         const PfRingTile& T = pf_ring_tile(f32, pairs, v);
         if (r.ring_tile >= 0 && r.ring_tile != v) continue;
+        const bool direct = f32 && v == kPfDirect;
         const int n_fb = (n_tiles + T.FT - 1) / T.FT, n_rb = (n_chunks + T.RC - 1) / T.RC;
         for (int ks = 1; ks <= PF_MAX_KSPLIT; ++ks) {
             if (ks > 1 && (!raw || ks * n_chunks * 16 > PF_RAW_ROWS || ks > KB)) break;
             if (raw && (r.ring_ks > 0 ? ks != r.ring_ks : n_chunks <= PF_FIXED_SLICES && ks != ks4)) continue;
             const int wgs = (n_fb + 7) / 8 * n_rb * ks, full = wgs / units, rest = wgs % units;
+            // (one workgroup per compute unit: with more the ring is faster; tiny O, 100 rows, 28 workgroups on the busiest XCD 6.3 us either way, 144 rows, 36: 7.1 against 6.3)
+            if (direct && r.ring_tile < 0 && (wgs > units || KB > PF_DIRECT_MAX_KB * ks)) continue;
             const float kb_us = full * (T.us0 + T.us1) + (rest ? T.us0 + T.us1 * rest / units : 0.f);
-            const float us = (full + (rest ? 1 : 0)) * 4.f + fmaxf((float)KB / ks * kb_us, hbm_us) + ks * slice_us;
+            const float us = (full + (rest ? 1 : 0)) * (direct ? 2.5f : 4.f) + fmaxf((float)KB / ks * kb_us, hbm_us) + ks * slice_us;
             if (us < best_us) { best = {v, ks}; best_us = us; }
         }
     }
@@ -1049,10 +1063,12 @@ template <class T, int EPI> bool launch_pf_ring(hipStream_t s, const PfPick& p, 
     a.ksplit = p.ks;
     const unsigned grid = (unsigned)((a.n_fb + 7) / 8 * 8 * a.n_rb * a.ksplit);
 #define PFR(v, nt, nc, fw, rw, nl, pf) case v: pf_ring_kernel<T, EPI, nt, nc, fw, rw, nl, pf><<<grid, (fw * rw + nl) * 64, 0, s>>>(a); return true;
-    if constexpr (f32) { switch (p.tile) { PF_RING_F32_SHAPES(PFR, EPI == PF_GU ? 2 : 1) } }
+#define PFD(v) case v: pf_direct_kernel<T, EPI><<<grid, 256, 0, s>>>(a); return true;
+    if constexpr (f32) { switch (p.tile) { PF_RING_F32_SHAPES(PFR, PFD, EPI == PF_GU ? 2 : 1) } }
     else if constexpr (EPI == PF_GU) { switch (p.tile) { PF_RING_PAIR_SHAPES(PFR) } }
     else { switch (p.tile) { PF_RING_SHAPES(PFR) } }
 #undef PFR
+#undef PFD
     return false;
 }
 template <int EPI> bool launch_pf_gemm(asd_engine* e, const PfCfg& g, const PfPick& p, const PfArgs& a, int n_chunks) {

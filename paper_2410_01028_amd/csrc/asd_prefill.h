@@ -510,6 +510,51 @@ __global__ __launch_bounds__((FW * RW + NL) * 64, (FW * RW + NL + 3) / 4) void p
     pf_epilogue<T, EPI, 4, NA, NT, NC>(a, acc, tile, tval, rb * RC + rw * NC, ks, lane);
 }
 
+// ---- fp32, short K ranges: a wave on its own
+// A wave takes one weight tile (gate/up: a pair) and one chunk, and asks for the fragments of PF_DIRECT_KB k-blocks at once, straight into registers: no ring to fill, no
+// barrier.  A few k-blocks in fp32 last as long as one wave's products (32 cycles each, two chunks in a wave of the smallest ring tile): here a wave has half
+// as many, and there are waves for all compute units.  Every wave reads its own fragments, which L2 serves.  256 features, 17 to 200 rows (to 100 for O and
+// down), ring / this, us between events: QKV 8.3 / 7.2, gate/up 10.3 / 8.5, O 6.3 / 6.2, down 6.8 / 6.3; 512 features: 10.4 / 9.3, 14.2 / 12.3, 6.5 / 6.2, 8.3 / 7.9.  Two chunks per wave: 9.2 and 10.5
+// us for the first two.  An output is one wave's sum over its K slice in k-block order, as everywhere.
+#define PF_DIRECT_KB 16
+template <class T, int EPI>
+__global__ __launch_bounds__(256) void pf_direct_kernel(const PfArgs a) {
+    static_assert(T::NP == 1, "one plane");
+    constexpr int NAT = EPI == PF_GU ? 2 : 1, B = PF_DIRECT_KB;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int Lb = blockIdx.x, inner = a.n_rb * a.ksplit;          // as in pf_gemm_kernel
+    const int fb = ((Lb >> 3) / inner) * 8 + (Lb & 7), in = (Lb >> 3) % inner, rb = in % a.n_rb, ks = in / a.n_rb;
+    const int tile[1] = {fb * 4 + w};
+    if (tile[0] >= a.n_tiles) return;
+    const int kb0 = ks * a.KB / a.ksplit, n = (ks + 1) * a.KB / a.ksplit - kb0;
+    const u32x4* A[NAT];
+#pragma unroll
+    for (int s = 0; s < NAT; ++s) A[s] = (s ? a.W2 : a.W) + (tile[0] * a.w_tile_stride + kb0 * a.w_kb_stride) * ASD_WAVE;
+    const u32x4* const X = a.X + (size_t)rb * a.x_chunk + (size_t)kb0 * ASD_WAVE;
+    f32x4 acc[NAT][1];
+#pragma unroll
+    for (int s = 0; s < NAT; ++s) acc[s][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < n; b += B) {
+        u32x4 wf[B][NAT], xf[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) {                              // (past the end the last k-block again: the wait counts are exact only without conditions)
+            const int kb = min(b + i, n - 1);
+            xf[i] = X[(size_t)kb * ASD_WAVE + lane];
+#pragma unroll
+            for (int s = 0; s < NAT; ++s) wf[i][s] = A[s][kb * a.w_kb_stride * ASD_WAVE + lane];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < B; ++i)
+            if (b + i < n) {
+#pragma unroll
+                for (int s = 0; s < NAT; ++s) mma16<T>(acc[s][0], wf[i][s], xf[i]);
+            }
+    }
+    const bool tval[1] = {true};
+    pf_epilogue<T, EPI, 1, 1, NAT, 1>(a, acc, tile, tval, rb, ks, lane);
+}
+
 // The bf16 shapes, X(number, weight tiles per wave, chunks per wave, waves over the tiles, waves over the chunks, requesting waves,
 // second register set): for QKV and the raw sums, and for gate/up, whose tiles come in pairs.  Of some 40 shapes measured on the 7B, 13B and 70B matrices at 20 to
 // 2048 rows, the sixteen of each list that left the least time on the table (under 1 % over all lengths).  Over 1500 configurations of other widths the estimate takes each of them somewhere.
@@ -525,9 +570,9 @@ __global__ __launch_bounds__((FW * RW + NL) * 64, (FW * RW + NL + 3) / 4) void p
     X(12, 6, 3, 2, 2, 4, true) X(13, 6, 4, 2, 2, 4, true) X(14, 4, 5, 4, 1, 4, true) X(15, 8, 3, 2, 2, 4, true)
 // In fp32 a product takes eight times as long (128 cycles of a SIMD per fragment pair): the requests hide behind the products, and
 // a prompt pass of a small model, a few k-blocks per launch, pays for every wave more (256 k values, 4 layers, 30 rows: 168 us like this, 203 with
-// requesting waves).  N weight tiles per wave: one, two for gate/up.  The estimate takes 2, 3 and 10 on no width tried (1500 configurations): a tuning string reaches them.
-#define PF_RING_F32_SHAPES(X, N)                                                                                         \
-    X(0, 6, 2, 2, 4, 0, true) X(1, 4, 4, 4, 2, 0, true) X(2, 6, 4, 4, 2, 0, true) X(3, 8, 4, 2, 4, 0, false)             \
+// requesting waves).  N weight tiles per wave: one, two for gate/up.  D(number): pf_direct_kernel.  The estimate takes 3 and 10 on no width tried (1500 configurations): a tuning string reaches them.
+#define PF_RING_F32_SHAPES(X, D, N)                                                                                      \
+    X(0, 6, 2, 2, 4, 0, true) X(1, 4, 4, 4, 2, 0, true) D(2) X(3, 8, 4, 2, 4, 0, false)                                  \
     X(4, N, 2, 3, 1, 0, true) X(5, N, 3, 3, 1, 0, true) X(6, N, 4, 3, 1, 0, true) X(7, N, 2, 4, 1, 0, true)              \
     X(8, N, 3, 4, 1, 0, true) X(9, N, 4, 4, 1, 0, true) X(10, N, 6, 4, 1, 0, true) X(11, N, 8, 4, 1, 0, true)            \
     X(12, N, 2, 8, 1, 0, true) X(13, N, 3, 8, 1, 0, true) X(14, N, 4, 8, 1, 0, true) X(15, N, 8, 8, 1, 0, true)

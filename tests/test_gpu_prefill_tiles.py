@@ -196,3 +196,23 @@ def test_fp32_tile_shapes_give_the_same_bits(n):
     for g in got[1:]:
         assert all(np.array_equal(x, y) for x, y in zip(got[0], g))
     assert np.abs(got[0][1] - ref[1]).max() < COS_TOL and rel_err(got[0][2], ref[2]) < TOL[si.DT_F32]
+
+
+@pytest.mark.parametrize("d,ffn,n", [(16, 16, 17), (256, 688, 200), (272, 592, 45), (1024, 1040, 33)], ids=str)
+def test_fp32_waves_on_their_own_give_the_same_bits(d, ffn, n):
+    """pf_direct_kernel at one k-block, at a whole batch of requests, one past it and at four batches, with tiles that do not fill its workgroups, against the
+    four-wave kernel; the estimate takes it where the launch has a compute unit per workgroup and not beyond."""
+    shape = si.Shape("direct", 2, d, 3, 3, 32, ffn, 320, si.DT_F32, 8, 8, 2)
+    toks = si.prompt(n, n, shape.vocab)
+    W = list(si.all_tensors(shape, 3, 0.1))
+    got = []
+    for tune in ("pf_qkv=4,1,2;pf_o=4,4,2;pf_gu=4,1,2;pf_down=4,4,2", None, "pf_ring=2"):
+        cfg = asd.make_config(shape, n + 16, debug_tune=tune)
+        tiles = asd.plan_prompt(cfg, n)[0]["tile"]
+        if tune is None:
+            assert tiles["qkv"] == 2 and (tiles["oproj"] == 2) == (n < 200)
+        eng = asd.Engine(cfg).load(W)
+        got.append((*eng.prefill(toks, want_logits=True), *eng.get_kv(1, 0, n)))
+        eng.close()
+    for g in got[1:]:
+        assert all(np.array_equal(x, y) for x, y in zip(got[0], g))
