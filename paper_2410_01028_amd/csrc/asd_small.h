@@ -18,8 +18,8 @@
 // groups' fragments, j = 0..3) and the waves' sums in order.  Here a lane runs that chain for its weight row: with v_fma for one row, with
 // 4x4x1 matrix instructions (64 weight rows x 4 activation rows, one k per instruction: the same chain) for more.
 //
-// What bounds a launch is latency.  One row, 256 features, 64 head dims, context 45, ns from a workgroup's first instruction: input whole 2250 (the arguments, then the slices from
-// other XCDs' L2s), q/K/V rows 3250, rotated 3650, attention 5050, merged 5700, done 6100; the MLP 2700, 3500, 3950, 4750.  A pass (4 layers) 99 -> 61 us for one row, 101 -> 88 for five.
+// What bounds a launch is latency.  One row, 256 features, 64 head dims, context 45, ns from a workgroup's first instruction: input whole 1150 (the arguments, then the slices from
+// other XCDs' L2s), q/K/V rows 2700, rotated 3100, attention 4800, merged 5300, done 5700; the MLP 1750, 3100, 3500, 4300.  A pass (4 layers) 99 -> 55 us for one row, 101 -> 78 for five.
 #pragma once
 #include "asd_attn.h"
 #include "asd_gemm.h"
@@ -163,46 +163,46 @@ template <int NR> struct SmInLds {
     float yy[16], xy[16];
     int tok[16];
 };
-// Thread -> element: feature tid % 256 of rows tid / 256, + NT / 256, ...
-// The loads of this thread's first element, requested before the weights' (loads return in order) and without a condition (the
-// compiler's wait counts are exact only then).
-template <int NI> struct SmFirst { float x[NI], g, p[NI][SM_SLICES]; };
-template <int NR, int NT> constexpr int sm_ahead() { return NR > NT / SM_D ? 2 : 1; }      // rounds of rows requested ahead
-template <int NT, int NI> __device__ __forceinline__ void sm_request(const SmallIn& a, SmFirst<NI>& f, int m0, int n) {
-    n = min(n, a.d - 1);
+// Wave m takes row m, lane l its features 4 l .. 4 l + 3.  The loads are requested before the weights' (loads return in order).  What bounds the stage is the issue of loads: a
+// compute unit takes one of 1 KiB in about 16 cycles, its oldest waves' first, and a wave gets to its input when all its own are issued.  Hence 16 bytes per lane, the
+// oldest waves, and only the first of a wave's weights before it (a feature per thread and all weights before it: the input was whole at 2250 ns instead of 1150, in the MLP at 2700
+// instead of 1750; a pass 60 -> 55 us for one row, 77 -> 69 for four, 87 -> 78 for five).
+struct SmFirst { f32x4 x, g, p[SM_SLICES]; };
+__device__ __forceinline__ void sm_request(const SmallIn& a, SmFirst& f, int w, int lane) {
+    if (w >= a.M) return;                                         // (the same for a whole wave)
+    const int n = min(4 * lane, a.d - 4);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int m = min(m0 + i * (NT / SM_D), a.M - 1);
-#pragma unroll
-        for (int s = 0; s < SM_SLICES; ++s) f.p[i][s] = a.part[(s * a.M + m) * a.d + n];
-        f.x[i] = a.xin[m * a.d + n];
-    }
-    f.g = a.gain[n];
+    for (int s = 0; s < SM_SLICES; ++s) f.p[s] = *(const f32x4*)(a.part + (s * a.M + w) * a.d + n);
+    f.x = *(const f32x4*)(a.xin + w * a.d + n);
+    f.g = *(const f32x4*)(a.gain + n);
 }
 // y = x + the eight slices in order, into LDS as y * gain with the products of the cosine's sums; x is whole after the next barrier
-template <int NT, int NR, int NI> __device__ __forceinline__ void sm_input(const SmallIn& a, const BeginArgs& begin, SmFirst<NI>& f, SmInLds<NR>& l, int tid) {
+template <int NT, int NR> __device__ __forceinline__ void sm_input(const SmallIn& a, const BeginArgs& begin, const SmFirst& f, SmInLds<NR>& l, int tid, int w, int lane) {
 #pragma clang fp contract(off)
-    const int n = tid % SM_D;
+    static_assert(NT / 64 >= SM_ROWS, "a wave per row");
     if (!a.embed) {
-        for (int m0 = tid / SM_D; m0 < a.M; m0 += NI * (NT / SM_D)) {
-            if (m0 >= NI * (NT / SM_D)) sm_request<NT>(a, f, m0, n);
+        const int n = 4 * lane;
+        if (w >= a.M) return;
+        f32x4 y, xg, yy, xy;
 #pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                const int m = m0 + i * (NT / SM_D);
-                float v = 0.f;
+        for (int i = 0; i < 4; ++i) {
+            float v = 0.f;
 #pragma unroll
-                for (int s = 0; s < SM_SLICES; ++s) v += f.p[i][s];
-                const float y = f.x[i] + v;
-                if (n < a.d && m < a.M) {
-                    l.x[m][n] = y * f.g;
-                    l.pyy[m][n] = y * y;
-                    l.pxy[m][n] = f.x[i] * y;
-                    if (blockIdx.x == 0 && a.xout) a.xout[m * a.d + n] = y;
-                }
-            }
+            for (int s = 0; s < SM_SLICES; ++s) v += f.p[s][i];
+            y[i] = f.x[i] + v;
+            xg[i] = y[i] * f.g[i];
+            yy[i] = y[i] * y[i];
+            xy[i] = f.x[i] * y[i];
+        }
+        if (n < a.d) {
+            *(f32x4*)&l.x[w][n] = xg;
+            *(f32x4*)&l.pyy[w][n] = yy;
+            *(f32x4*)&l.pxy[w][n] = xy;
+            if (blockIdx.x == 0 && a.xout) *(f32x4*)(a.xout + w * a.d + n) = y;
         }
         return;
     }
+    const int n = tid % SM_D;
     // the tokens of the pass
     if (tid < 64) {
         float conf;
@@ -337,8 +337,8 @@ __global__ __launch_bounds__(SM_NT) void sm_attn_kernel(SM_IN_PARAMS, int32_t he
     const int KB = in.d / 16, M = in.M;
     const int st_pos = st->pos;
 
-    SmFirst<sm_ahead<NR, SM_NT>()> first;
-    sm_request<SM_NT>(in, first, tid / SM_D, tid % SM_D);
+    SmFirst first;
+    sm_request(in, first, w, lane);
 
     // weight row of local row lr: the head's H query rows, its H key rows (tile row order), then HS value dims
     auto row_of = [&](int lr, int* tile, int* r) {
@@ -349,19 +349,17 @@ __global__ __launch_bounds__(SM_NT) void sm_attn_kernel(SM_IN_PARAMS, int32_t he
             *tile = (2 * n_h + head) * HB + i / 8; *r = (i & 7) + (dim >= H / 2 ? 8 : 0);
         }
     };
-    // task t: rows of group t >> 2, K split t & 3 (k-blocks split, split + 4, ...); the first task's requests go out now
+    // task t: rows of group t >> 2, K split t & 3 (k-blocks split, split + 4, ...); the first task's requests go out in two parts (see sm_request)
     f32x4 wq[4][4], kf[PB][4];
     int tile, r;
     row_of((w >> 2) * 64 + lane, &tile, &r);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sm_load(wq[i], Wqkv + (min((w & 3) + 4 * i, KB - 1) * qkv_tiles + tile) * 256, r);
-    // rotary factors of this thread's first pair
+    auto load_q = [&](int i) { sm_load(wq[i], Wqkv + (min((w & 3) + 4 * i, KB - 1) * qkv_tiles + tile) * 256, r); };
+    load_q(0);
     constexpr int np = H / 2;
     const int rp = min(tid, M * np - 1), pos0 = (in.has_begin ? begin.pos : st_pos) + a.pos_off;
-    const float2 rot = *(const float2*)(rope + ((size_t)(pos0 + rp / np) * np + rp % np) * 2);
 
-    sm_input<SM_NT>(in, begin, first, l.in, tid);
-    // this wave's 64-key chunk of the cache.  Its K rows are requested here and its V^T rows once the weights are used, where registers allow; else one step later each.
+    sm_input<SM_NT>(in, begin, first, l.in, tid, w, lane);
+    // this wave's 64-key chunk of the cache.  Its K rows are requested once the weights are used, its V^T rows with them where registers allow, else one step later.
     constexpr bool EARLY = RM == 0 && HB <= PB;
     const int PT = a.page_tokens;
     const float* chunk = a.kv;
@@ -376,8 +374,11 @@ __global__ __launch_bounds__(SM_NT) void sm_attn_kernel(SM_IN_PARAMS, int32_t he
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) sm_load(vf[ks], chunk + kv_v_frag_off<F32>(vd >> 4, ks, H), vd & 15);
     };
-    if (EARLY && have) load_k(0);
     __syncthreads();
+#pragma unroll
+    for (int i = 1; i < 4; ++i) load_q(i);
+    // rotary factors of this thread's first pair
+    const float2 rot = *(const float2*)(rope + ((size_t)(pos0 + rp / np) * np + rp % np) * 2);
     sm_norms(in, l.in, tid);
 #pragma unroll
     for (int t0 = 0; t0 < L::NG * 4; t0 += SM_NW) {
@@ -395,7 +396,8 @@ __global__ __launch_bounds__(SM_NT) void sm_attn_kernel(SM_IN_PARAMS, int32_t he
     }
     f32x4 vf[4][4];
     if (have) {
-        if constexpr (EARLY) load_v(vf); else load_k(0);
+        load_k(0);
+        if constexpr (EARLY) load_v(vf);
     }
     __syncthreads();
 
@@ -482,14 +484,17 @@ __global__ __launch_bounds__(SM_NT) void sm_attn_kernel(SM_IN_PARAMS, int32_t he
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        for (int n = max(0, key0 - pos0); n < M && pos0 + n < key0 + 64; ++n) {       // (none unless the chunk is fresh)
-            const int kk = pos0 + n - key0;
-            const float v = l.v[n][lane & (HS - 1)];
+        if (fresh) {                                              // the new positions' V, four keys a piece
+            const int n0 = key0 - pos0;                           // row of the chunk's first key
 #pragma unroll
             for (int q = 0; q < 16; ++q)
-                if ((kk >> 2) == q) {
+                if (n0 + 4 * q + 3 >= 0 && n0 + 4 * q < M) {      // (the same in every lane)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) vf[q >> 2][q & 3][i] = (kk & 3) == i ? v : vf[q >> 2][q & 3][i];
+                    for (int i = 0; i < 4; ++i) {
+                        const int n = n0 + 4 * q + i;
+                        const float v = l.v[min(max(n, 0), M - 1)][lane & (HS - 1)];
+                        vf[q >> 2][q & 3][i] = n >= 0 && n < M ? v : vf[q >> 2][q & 3][i];
+                    }
                 }
         }
         // the output, and beside it the chunk's sums of probabilities: lane group g's keys 16 ks + 4 g + j in order, then the groups in pairs
@@ -542,22 +547,26 @@ __global__ __launch_bounds__(SM_NT) void sm_attn_kernel(SM_IN_PARAMS, int32_t he
         for (int gr = 0; gr < SM_CHUNKS / ATT_GW; ++gr) {
             gm[gr] = -INFINITY; gl[gr] = ga[gr] = 0.f;
             if (gr >= n_groups) continue;
-            float gmax = -INFINITY, mx[ATT_GW];
+            // (read without a condition, so that the reads are on their way together: a chunk past the context is left out by its maximum)
+            float gmax = -INFINITY, mx[ATT_GW], ml[ATT_GW], v[ATT_GW];
 #pragma unroll
             for (int ww = 0; ww < ATT_GW; ++ww) {
                 const int ch = gr * ATT_GW + ww;
-                mx[ww] = ch < n_c ? l.ml[ch][m][0] : -INFINITY;
+                mx[ww] = l.ml[ch][m][0]; ml[ww] = l.ml[ch][m][1]; v[ww] = l.att.o[ch][m][i];
+            }
+#pragma unroll
+            for (int ww = 0; ww < ATT_GW; ++ww) {
+                const bool on = gr * ATT_GW + ww < n_c;
+                mx[ww] = on ? mx[ww] : -INFINITY; ml[ww] = on ? ml[ww] : 0.f; v[ww] = on ? v[ww] : 0.f;
                 gmax = fmaxf(gmax, mx[ww]);
             }
             float Lg = 0.f, acc = 0.f;
             if (gmax != -INFINITY) {
 #pragma unroll
                 for (int ww = 0; ww < ATT_GW; ++ww) {
-                    const int ch = gr * ATT_GW + ww;
                     const float wgt = __expf(mx[ww] - gmax);
-                    const float v = ch < n_c ? l.att.o[ch][m][i] : 0.f;
-                    Lg += (ch < n_c ? l.ml[ch][m][1] : 0.f) * wgt;
-                    acc += v * wgt;
+                    Lg += ml[ww] * wgt;
+                    acc += v[ww] * wgt;
                 }
             }
             gm[gr] = gmax; gl[gr] = Lg; ga[gr] = acc;
@@ -608,11 +617,11 @@ __global__ __launch_bounds__(SM_NT) void sm_mlp_kernel(SM_IN_PARAMS, int32_t n_h
     const int slice = blockIdx.x, KB = in.d / 16, M = in.M;
     const int n_t = (n_hid - slice + SM_SLICES - 1) / SM_SLICES;           // hidden tiles slice, slice + 8, ...
     const int n_rg = (2 * n_t + 3) / 4, n_og = (in.d + 63) / 64;           // 64-row groups
-    SmFirst<sm_ahead<NR, SM_NT>()> first;
-    sm_request<SM_NT>(in, first, tid / SM_D, tid % SM_D);
+    SmFirst first;
+    sm_request(in, first, w, lane);
     // wave w < 8: K slice w (as gemm_kernel's wave w) of the row groups; waves 8 ..: row groups of the down-projection
     const int kb0 = w * KB / 8, nk = (w + 1) * KB / 8 - kb0;               // at most two k-blocks (d <= 256)
-    // (indexes past the end are clamped, not skipped: see sm_request)
+    // (indexes past the end are clamped, not skipped: the compiler's wait counts are exact only without conditions)
     auto gate_frag = [&](int gr, int kb) {
         const int ti = min(gr * 4 + (lane >> 4), 2 * n_t - 1), hid = slice + SM_SLICES * (ti < n_t ? ti : ti - n_t);
         return (ti < n_t ? Wg : Wu) + (hid * KB + kb) * 256;
@@ -622,21 +631,24 @@ __global__ __launch_bounds__(SM_NT) void sm_mlp_kernel(SM_IN_PARAMS, int32_t n_h
     };
     f32x4 wt[SM_FFN_TILES][4];                                    // (two k-blocks x three tasks, or a down row group's six k-blocks)
     static_assert(SM_FFN_TILES == 2 * PT_, "one register set for both roles");
+    auto load_gate = [&](int t) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) sm_load(wt[t * 2 + i], gate_frag(t, min(kb0 + i, KB - 1)), lane & 15);
+    };
+    if (w < GW) load_gate(0);
+    sm_input<SM_NT>(in, begin, first, l.in, tid, w, lane);
     if (w < GW) {
 #pragma unroll
-        for (int t = 0; t < PT_; ++t)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-                sm_load(wt[t * 2 + i], gate_frag(t, min(kb0 + i, KB - 1)), lane & 15);
-    } else {
+        for (int t = 1; t < PT_; ++t) load_gate(t);
+    }
+    __syncthreads();
+    // (the norms' sums in the waves without a product to wait for; their weights, needed last, are requested behind the others')
+    if (w >= GW) {
 #pragma unroll
         for (int i = 0; i < SM_FFN_TILES; ++i)
             sm_load(wt[i], down_frag(w - GW, min(i, n_t - 1)), lane & 15);
+        sm_norms(in, l.in, tid - GW * 64);
     }
-    sm_input<SM_NT>(in, begin, first, l.in, tid);
-    __syncthreads();
-    // (the norms' sums in the waves without a product to wait for)
-    if (w >= GW) sm_norms(in, l.in, tid - GW * 64);
     if (w < GW) {
 #pragma unroll
         for (int t = 0; t < PT_; ++t) {
@@ -684,14 +696,14 @@ __global__ __launch_bounds__(SM_LM_NW * 64) void sm_lm_kernel(SM_IN_PARAMS, int3
     SM_IN_ARGS(in, in0)
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KB = in.d / 16, M = in.M, tiles = V / 16, n0 = blockIdx.x * 64;
-    SmFirst<sm_ahead<NR, NT>()> first;
-    sm_request<NT>(in, first, tid / SM_D, tid % SM_D);
+    SmFirst first;
+    sm_request(in, first, w, lane);
     f32x4 wt[2][4];                                               // k-blocks w, w + 8 (d <= 256)
     const int tile = min((int)blockIdx.x * 4 + (lane >> 4), tiles - 1);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
         sm_load(wt[i], W + ((size_t)min(w + 8 * i, KB - 1) * tiles + tile) * 256, lane & 15);
-    sm_input<NT>(in, begin, first, l.in, tid);
+    sm_input<NT>(in, begin, first, l.in, tid, w, lane);
     __syncthreads();
     sm_norms(in, l.in, tid);
     {
