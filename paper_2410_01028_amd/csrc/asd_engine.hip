@@ -1130,21 +1130,16 @@ template <class T> void launch_pf_embed_t(asd_engine* e, const int32_t* tokens, 
         e->pf_xres, e->pf_xb, (e->pf_rows / 16) * e->cf_d * 64 * e->KE, e->cf_d * 64 * e->KE, e->pf_ssq, e->pf_rscale,
         1.f / (float)c.d_model, c.rms_eps, begin);
 }
-template <class T> void launch_pf_resid_t(asd_engine* e, int rows, int n_chunks, int ksplit, const float* gain, float* cos_row) {
+template <class T> void launch_pf_resid_t(asd_engine* e, int rows, int n_chunks, int ksplit, const float* gain, float* cos_row, const PfLastRow& out) {
     const asd_config& c = e->c;
 #define PFS(ks) case ks: pf_resid_kernel<T, ks><<<pf_row_grid(n_chunks), 256, 0, e->stream>>>(e->pf_raw, n_chunks * 16, rows, c.d_model, e->pf_xres, e->pf_xb, \
-        (e->pf_rows / 16) * e->cf_d * 64 * e->KE, e->cf_d * 64 * e->KE, gain, e->pf_ssq, e->pf_rscale, cos_row, 1.f / (float)c.d_model, c.rms_eps); break;
+        (e->pf_rows / 16) * e->cf_d * 64 * e->KE, e->cf_d * 64 * e->KE, gain, e->pf_ssq, e->pf_rscale, cos_row, 1.f / (float)c.d_model, c.rms_eps, out); break;
     switch (ksplit) { PFS(1) PFS(2) PFS(3) PFS(4) PFS(5) PFS(6) PFS(7) PFS(8) }
 #undef PFS
 }
-template <class T> void launch_pf_tail_t(asd_engine* e, int rows) {
-    const asd_config& c = e->c;
-    pf_tail_kernel<T><<<2 * c.n_layers + (c.d_model + 255) / 256, 256, 0, e->stream>>>(e->pf_cos_rows, e->pf_rows, rows, e->cos_acc, 2 * c.n_layers, e->pf_xres,
-        e->pf_ssq, c.d_model, e->g_final, e->xres, e->xb, (int64_t)e->KBd * 64 * e->KE, e->part);
-}
 // The whole prompt, block by block and layer by layer; leaves the last row's logits / greedy token in row 0 of the
-// decode buffers and the cosine sums of all rows in cos_acc.  Enqueue only.
-int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profiler = nullptr) {
+// decode buffers and the cosine sums of all rows in cos_acc, and what host names in pinned memory.  Enqueue only.
+int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, const PfHost& host, Profiler* profiler = nullptr) {
     const asd_config& c = e->c;
     const int L = c.n_layers, KE = e->KE;
     const bool bf = c.dtype == ASD_DT_BF16;
@@ -1177,7 +1172,8 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
         base.hmid = e->pf_hmid; base.hmid_plane = cap * e->cf_f * 64 * KE; base.hmid_chunk = e->cf_f * 64 * KE;
         auto resid = [&](int ksplit, const float* gain, int sub) {
             float* cr = e->pf_cos_rows + (size_t)sub * e->pf_rows;
-            if (bf) launch_pf_resid_t<BF16>(e, rows, n_chunks, ksplit, gain, cr); else launch_pf_resid_t<F32>(e, rows, n_chunks, ksplit, gain, cr);
+            const PfLastRow out{sub + 1 == 2 * L && r0 + rows == n ? rows - 1 : -1, e->xb, (int64_t)e->KBd * 64 * KE, e->part};
+            if (bf) launch_pf_resid_t<BF16>(e, rows, n_chunks, ksplit, gain, cr, out); else launch_pf_resid_t<F32>(e, rows, n_chunks, ksplit, gain, cr, out);
         };
         for (int l = 0; l < L; ++l) {
             const Layer& ly = e->layers[l];
@@ -1227,12 +1223,11 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
             pr.end();
             if (!ok) return fail(e, ASD_E_STATE, "no prompt GEMM instance for this launch shape");
         }
-        if (r0 + rows < n) pf_cos_sum_kernel<<<2 * L, 256, 0, e->stream>>>(e->pf_cos_rows, e->pf_rows, rows, e->cos_acc);      // (the last block's: pf_tail_kernel)
+        if (r0 + rows < n) pf_cos_sum_kernel<<<2 * L, 256, 0, e->stream>>>(e->pf_cos_rows, e->pf_rows, rows, e->cos_acc);      // (the last block's: pf_finish_kernel)
         e->kv_len = r0 + rows;
     }
     // the last prompt row through the final norm and the LM head, as row 0 of a one-row pass
     pr.begin(ASD_PK_LMHEAD, 2.0 * c.d_model * c.vocab);
-    if (bf) launch_pf_tail_t<BF16>(e, rows); else launch_pf_tail_t<F32>(e, rows);
     std::vector<PassOp> ops;
     build_pass(e, 1, 0, nullptr, n, chunks_for(n - 1), engine_out(e), ops);
     for (PassOp& op : ops) {
@@ -1240,7 +1235,9 @@ int prefill_blocks(asd_engine* e, const int32_t* tokens, int n, Profiler* profil
         op.g.part_in = e->part; op.g.P_in = 1; op.g.fin_cos_rows = nullptr; op.g.fin_cos_acc = nullptr;
         if (!launch_gemm<EPI_LM>(e, e->g_lm, op.g)) return fail(e, ASD_E_STATE, "no kernel instance for the LM head");
     }
-    finish_kernel<<<1, 64, 0, e->stream>>>((const AmaxCand*)e->amax_part, e->g_lm.grid, 1, c.vocab, e->argmax, FIN_NONE, 0, e->st, e->tokbuf, e->out_tokens);
+    const int copies = !host.logits ? 0 : c.vocab < 256 * 1024 ? (c.vocab + 1023) / 1024 : 256;
+    pf_finish_kernel<<<2 * L + 1 + copies, 256, 0, e->stream>>>(e->pf_cos_rows, e->pf_rows, rows, e->cos_acc, 2 * L, (const AmaxCand*)e->amax_part, e->g_lm.grid, c.vocab, e->argmax,
+                                                                e->st, e->logits, host);
     pr.end();
     hipError_t r = hipGetLastError();
     if (r != hipSuccess) return fail(e, ASD_E_HIP, "kernel launch: %s", hipGetErrorString(r));
@@ -1706,7 +1703,7 @@ static int prefill_impl(asd_engine* e, const int32_t* tokens, int32_t n, int32_t
     e->kv_len = 0; e->acs_valid = false;
     int last_row = 0;
     if (blocks) {
-        rc = prefill_blocks(e, tokens, n);
+        rc = prefill_blocks(e, tokens, n, PfHost{e->h_st, e->h_argmax, e->h_cos_acc, last_logits ? e->h_logits : nullptr});
         if (rc) return rc;
     } else {
         int rows = 0;
@@ -1719,12 +1716,14 @@ static int prefill_impl(asd_engine* e, const int32_t* tokens, int32_t n, int32_t
         last_row = rows - 1;
     }
     e->last_logits_row = last_row;
-    HostCopies out;
-    out.add(e->st, e->h_st, sizeof(DevState));
-    out.add(e->argmax, e->h_argmax, ASD_ROWS * 4);
-    out.add(e->cos_acc, e->h_cos_acc, (size_t)L2 * 8);
-    if (last_logits) out.add(e->logits + (size_t)last_row * e->c.vocab, e->h_logits, (size_t)e->c.vocab * 4);
-    CK(e, out.launch(e->stream));
+    if (!blocks) {                                     // (a prompt in blocks: its last launch)
+        HostCopies out;
+        out.add(e->st, e->h_st, sizeof(DevState));
+        out.add(e->argmax, e->h_argmax, ASD_ROWS * 4);
+        out.add(e->cos_acc, e->h_cos_acc, (size_t)L2 * 8);
+        if (last_logits) out.add(e->logits + (size_t)last_row * e->c.vocab, e->h_logits, (size_t)e->c.vocab * 4);
+        CK(e, out.launch(e->stream));
+    }
     CK(e, hipStreamSynchronize(e->stream));
     rc = check_pass_error(e, e->h_st);
     if (rc) return rc;
@@ -2171,11 +2170,11 @@ int asd_profile_prefill(asd_engine* e, const int32_t* tokens, int32_t n, asd_pre
     if (rc) return rc;
     const int L2 = 2 * e->c.n_layers;
     e->kv_len = 0; e->acs_valid = false;
-    rc = prefill_blocks(e, tokens, n);                 // warm-up
+    rc = prefill_blocks(e, tokens, n, PfHost{});       // warm-up
     if (rc) return rc;
     e->kv_len = 0;
     Profiler pf;
-    rc = prefill_blocks(e, tokens, n, &pf);
+    rc = prefill_blocks(e, tokens, n, PfHost{}, &pf);
     hipError_t r2 = hipStreamSynchronize(e->stream);
     memset(out, 0, sizeof *out);
     if (!rc && r2 == hipSuccess) {
