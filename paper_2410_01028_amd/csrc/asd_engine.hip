@@ -1780,6 +1780,15 @@ static void launch_sample_draft(asd_engine* e, const SampleArgs& sa, int j) {
     if (sample_in_registers(e)) sample_draft_kernel<SAMPLE_TILES><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, j);
     else sample_draft_kernel<0><<<1, SAMPLE_THREADS, 0, e->stream>>>(sa, j);
 }
+// ... and the embedding for the draft step that follows under the same mask
+static void launch_sample_draft_embed(asd_engine* e, const SampleArgs& sa, int j, const float* gain) {
+#define SDE(T, El, tiles) sample_draft_embed_kernel<T, tiles><<<EMBED_SPLIT, SAMPLE_THREADS, 0, e->stream>>>(sa, j, (const El*)e->embed, e->c.d_model, gain, e->xres, e->xb, \
+                                                                                                            (size_t)e->KBd * 64 * e->KE, e->part)
+    const bool regs = sample_in_registers(e);
+    if (e->c.dtype == ASD_DT_BF16) { if (regs) SDE(BF16, uint16_t, SAMPLE_TILES); else SDE(BF16, uint16_t, 0); }
+    else { if (regs) SDE(F32, float, SAMPLE_TILES); else SDE(F32, float, 0); }
+#undef SDE
+}
 static void launch_sample_accept(asd_engine* e, const SampleArgs& sa, int kk) {
     if (sample_in_registers(e)) {
         sample_stats_kernel<SAMPLE_TILES><<<kk + 1, SAMPLE_THREADS, 0, e->stream>>>(sa);
@@ -1796,10 +1805,12 @@ static void launch_sample_plain(asd_engine* e, const SampleArgs& sa, int row, in
 
 // one sampled draft / verify / accept cycle, enqueue only
 static int enqueue_sampled_drafts(asd_engine* e, int kk, const uint8_t* mask, int nc, int32_t ctx, const SampleArgs& sa) {
+    const bool steps = !small_pass(e, 1, nc);          // (a pass of one launch per sublayer embeds its token itself)
     for (int j = 0; j < kk; ++j) {
-        int rc = enqueue_forward(e, e->tokbuf + j, 1, j, mask, nc, nullptr, ctx, FIN_SKIP, 0);
+        int rc = enqueue_forward(e, e->tokbuf + j, 1, j, mask, nc, nullptr, ctx, FIN_SKIP, 0, nullptr, steps ? j - 1 : -1);
         if (rc) return rc;
-        launch_sample_draft(e, sa, j);
+        if (!steps || j + 1 == kk) launch_sample_draft(e, sa, j);
+        else launch_sample_draft_embed(e, sa, j, next_gain(e, mask, -1));
     }
     return ASD_OK;
 }

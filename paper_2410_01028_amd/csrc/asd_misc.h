@@ -13,7 +13,7 @@ __device__ __forceinline__ void embed_block(const typename T::elem* E, const int
                                             float* xres, void* xb, size_t xb_plane, int rs, float* part, const int sp, const int m, float* red,
                                             const int token = 0) {
     using El = typename T::elem;
-    const int tid = threadIdx.x, nt = EMBED_THREADS;
+    const int tid = threadIdx.x, nt = EMBED_THREADS;              // (a larger workgroup's other threads: the barriers alone)
     // a token id that is not a row of the table (possible when the ids come from device memory the host never saw)
     // must not become an address: it reads row 0 and raises the state's error bit (st NULL: somebody else looks at the ids)
     int tok = tokens ? tokens[m] : token;
@@ -24,13 +24,13 @@ __device__ __forceinline__ void embed_block(const typename T::elem* E, const int
     const El* row = E + (size_t)tok * d;
     const int per = (d + EMBED_SPLIT - 1) / EMBED_SPLIT, lo = sp * per, hi = min(d, lo + per);
     float ss = 0.f;
-    for (int i = lo + tid; i < hi; i += nt) {
+    for (int i = tid < nt ? lo + tid : hi; i < hi; i += nt) {
         const float x = T::to_f32(row[i]);
         xres[(size_t)m * d + i] = x;
         store_act<T>(xb, xb_plane, rs, i, m, x * g_first[i]);
         ss += x * x;
     }
-    red[tid] = ss;
+    if (tid < nt) red[tid] = ss;
     __syncthreads();
     for (int s = nt / 2; s > 0; s >>= 1) {
         if (tid < s) red[tid] += red[tid + s];

@@ -526,7 +526,7 @@ __global__ __launch_bounds__(SM_NT) void sm_attn_kernel(SM_IN_PARAMS, int32_t he
 #pragma unroll
         for (int cg = 0; cg < RM; ++cg)
             if (lane < 4) l.ml[c][cg * 4 + lane][1] = (lv[cg][0] + lv[cg][1]) + (lv[cg][2] + lv[cg][3]);
-        if (RV != 0 && lane == 0) l.ml[c][4 * RM][1] = (ls[0] + ls[1]) + (ls[2] + ls[3]);
+        if constexpr (RV != 0) { if (lane == 0) l.ml[c][4 * RM][1] = (ls[0] + ls[1]) + (ls[2] + ls[3]); }
         sm_put(o, &l.att.o[c][0][0], L::VS, lane, HS);
     }
     f32x4 wo[2][4];                                               // the O-projection's weights, on their way while the chunks are merged

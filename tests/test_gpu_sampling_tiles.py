@@ -76,3 +76,25 @@ def test_rows_with_nan_draw_their_last_positive_weight(V):
         masked[:, 3:] = -np.inf                                                   # ordinary masked rows: only what is left
         assert all(eng.spec_sample(np.zeros((0, V), np.float32), masked, 0.8, s, 0)[2] < 3 for s in range(20))
         eng.close()
+
+
+@pytest.mark.parametrize("flags", [0, asd.DBG_SAMPLE_MEM], ids=["registers", "memory"])
+@pytest.mark.parametrize("dtype", [si.DT_BF16, si.DT_F32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("drafts", [1, 2, 5])
+def test_the_drawn_token_is_the_next_draft_steps_input(dtype, drafts, flags):
+    """A draw between two draft steps embeds its token itself.  Drafts of the whole model are its own draws: the same bits in the
+    draft step and the verification, hence all kept, unless a step had another token's embedding."""
+    s = si.Shape("d", 2, 272, 2, 1, 64, 304, 1040, dtype, 4, 4, 2)
+    eng = asd.Engine(asd.make_config(s, 192, debug_flags=flags, debug_tune="small=0"))
+    eng.init_synthetic(5)
+    first = eng.prefill(si.prompt(2, 40, s.vocab))[0]
+    kw = dict(temperature=0.9, seed=11, fixed_mask=np.zeros(2 * s.n_layers, np.uint8))
+    got = []
+    for graphs in (False, True):
+        eng.reset()
+        assert eng.prefill(si.prompt(2, 40, s.vocab))[0] == first
+        toks, st, _ = eng.decode(first, 24, drafts, use_graphs=graphs, **kw)
+        assert st["accepted"] == st["drafted"] > 0
+        got.append(toks)
+    assert np.array_equal(got[0], got[1])
+    eng.close()
