@@ -764,8 +764,9 @@ bool small_shape(const asd_config& c, const Plan& p) {
            is(p.g_qkv, 4, 1) && is(p.g_o, 8, 0) && p.g_o.TN == 1 && is(p.g_gu, 8, 0) && is(p.g_down, 8, 1) && p.g_down.TN == 1 && is(p.g_lm, 8, 1) && p.g_lm.TN == 2;
 }
 // A pass of M rows over nc chunks of context goes this way.  The chains' time grows with the rows in eight compute units, hardly at all in the five launches' many.  256 features, 4 layers,
-// one launch per sublayer / five per layer, us: 1 row 61 / 99 (context 20), 75 / 114 (context 700); 2 rows 72 / 100; 4 rows 78 / 100; 5 rows 88 / 101 and 105 / 117; 6 rows 94 / 102 and
-// 113 / 117; 8 rows 102 / 102 and 121 / 117; 9 rows 139 / 106.  Contexts beyond SM_CHUNKS chunks need more waves than the workgroup has.
+// one launch per sublayer / five per layer, us: 1 row 55 / 99 (context 45), 67 / 114 (context 600); 2 rows 64 / 100; 4 rows 69 / 100; 5 rows, contexts 20 and 700, 79 / 99 and 95 / 118; 6 rows 84 / 100 and
+// 105 / 118; 8 rows 88 / 100 and 109 / 118.  A ninth would begin a third group of four (139 / 106 with requests in an earlier order, 15 % slower at eight).  Contexts beyond SM_CHUNKS
+// chunks need more waves than the workgroup has.
 bool small_pass(const asd_engine* e, int M, int nc) { return e->small && M <= SM_ROWS && nc <= SM_CHUNKS; }
 
 // kernel instances by row count: f(4-row groups in matrix instructions, a row beside them)

@@ -32,7 +32,7 @@
 #define SM_Q 256                    // most query dims (heads x head_dim)
 #define SM_FFN_TILES 6              // most hidden tiles per slice (d_ffn <= 768)
 #define SM_CHUNKS SM_NW             // most 64-key chunks of the context: one per wave
-#define SM_ROWS 6                   // most rows of a pass (the caller's rule)
+#define SM_ROWS 8                   // most rows of a pass (the caller's rule)
 #define SM_LM_NW 8
 
 struct SmallIn {                    // a sublayer's input

@@ -35,7 +35,7 @@ def test_passes_have_the_bits_of_one_launch_per_step(s):
     rng = np.random.default_rng(3)
     toks = rng.integers(0, s.vocab, 1024, dtype=np.int32)
     mask = np.zeros(2 * s.n_layers, np.uint8)
-    for start, rows in ((0, (1, 2, 5, 9, 16, 3)), (57, (6, 4, 1)), (250, (3, 8, 1)), (505, (13, 1, 4)), (751, (16, 1, 4, 1))):
+    for start, rows in ((0, (1, 2, 5, 9, 16, 3)), (57, (6, 7, 4, 1)), (250, (3, 8, 1)), (505, (13, 1, 4)), (751, (16, 1, 4, 1))):
         for e in (new, old):
             e.reset()
             for p in range(0, start, 16):
