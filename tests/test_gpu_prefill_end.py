@@ -11,6 +11,7 @@ from test_gpu_parity import BF_GQA, COS_TOL, TOL, build_pair, rel_err
 
 pytestmark = pytest.mark.gpu
 
+
 @pytest.mark.parametrize("shape", [si.SHAPES["tiny"], BF_GQA], ids=lambda s: s.name)
 @pytest.mark.parametrize("n", [17, 32, 33, 513])
 def test_last_row_sums_and_results(shape, n):
