@@ -778,6 +778,13 @@ template <class F> void sm_by_rows(int M, F f) {
     else f(integral_constant<int, 2>{}, integral_constant<int, 0>{});
 }
 
+// Whether a draft step of this mask may leave its token to the next one's first launch: that launch reads the candidates, and with every sublayer left out it is the
+// LM head's, which writes them
+bool drafts_hand_over(const asd_engine* e, const uint8_t* mask) {
+    for (int j = 0; j < 2 * e->c.n_layers; ++j) if (!(mask && mask[j])) return true;
+    return false;
+}
+
 // pending: the draft whose token the pass before left to this one's first launch (-1: none); leave_finish: leave this draft's to the next
 int enqueue_small(asd_engine* e, const int32_t* d_tokens, int M, int pos_off, const uint8_t* mask, int nc, int fin_mode, int fin_arg, const PassOut& out, int pending,
                   bool leave_finish, const BeginArgs* begin) {
@@ -1750,9 +1757,11 @@ int asd_prefill_chunked(asd_engine* e, const int32_t* tokens, int32_t n, int32_t
 #define DECODE_BURST 16      // draft-free decode cycles enqueued between two looks at the device state
 
 static int enqueue_drafts(asd_engine* e, int kk, const uint8_t* mask, int nc, int32_t ctx) {
+    const bool hand_over = !small_pass(e, 1, nc) || drafts_hand_over(e, mask);         // (one launch per step: the finish embeds for the next step in a launch of its own)
     for (int j = 0; j < kk; ++j) {
         // (the last step's token: found by the verification's first launch where passes take one launch per sublayer)
-        int rc = enqueue_forward(e, e->tokbuf + j, 1, j, mask, nc, nullptr, ctx, FIN_DRAFT, j, nullptr, j - 1, j + 1 < kk || small_pass(e, kk + 1, nc));
+        int rc = enqueue_forward(e, e->tokbuf + j, 1, j, mask, nc, nullptr, ctx, FIN_DRAFT, j, nullptr, hand_over ? j - 1 : -1,
+                                 j + 1 < kk ? hand_over : small_pass(e, kk + 1, nc));
         if (rc) return rc;
     }
     return ASD_OK;

@@ -76,6 +76,27 @@ def test_loops_emit_the_same(options):
     new.close(), old.close()
 
 
+@pytest.mark.parametrize("vocab", [1024, 40000])
+@pytest.mark.parametrize("silent", [True, False], ids=["silent", "ordinary"])
+def test_drafts_without_any_sublayer(vocab, silent):
+    """A draft step under a mask that leaves out every sublayer is the LM head alone, a launch that needs the token of the step before and writes the next
+    candidates.  40000 entries: more LM-head workgroups than run at once.  silent: the sublayers' output projections are zero, so the full model says what the
+    draft model says and every draft of a greedy loop is kept, if each step took the token of the step before."""
+    s = si.SHAPES["tiny"].with_(vocab=vocab)
+    W = [(t, l, 0 * w if silent and t in (si.T_WO, si.T_WD) else w) for t, l, w in si.all_tensors(s, 5, gain_std=0.1)]
+    new, old = (asd.Engine(asd.make_config(s, 128, page_tokens=64, debug_tune=t)).load(W) for t in (None, "small=0"))
+    prompt = np.random.default_rng(6).integers(0, vocab, 12, dtype=np.int32)
+    for options in (dict(draft_len=2), dict(draft_len=4), dict(draft_len=4, use_graphs=False), dict(draft_len=9), dict(draft_len=4, exit_mode=1),
+                    dict(draft_len=4, temperature=0.8, seed=3)):
+        for masked in (dict(fixed_mask=np.ones(2 * s.n_layers, np.uint8)), dict(alpha=0.985, m=1, n=0)):
+            (ta, sa, ma), (tb, sb, mb) = (e.generate(prompt, 40, **options, **masked) for e in (new, old))
+            assert ma.all() and mb.all(), (options, masked)
+            assert np.array_equal(ta, tb), (options, masked)
+            assert all(sa[k] == sb[k] for k in ("cycles", "drafted", "accepted", "emitted")), (options, masked)
+            assert not silent or "temperature" in options or sa["accepted"] == sa["drafted"] > 0, (options, masked)
+    new.close(), old.close()
+
+
 def test_a_token_outside_the_vocabulary_is_reported():
     import torch
     s = si.SHAPES["tiny"]
