@@ -43,7 +43,7 @@ def run_everything(shape, fill):
     return out
 
 
-@pytest.mark.parametrize("shape", [BF_GQA, SMALL_GQA], ids=["bf16-gqa", "fp32-gqa"])
+@pytest.mark.parametrize("shape", [BF_GQA, SMALL_GQA, si.SHAPES["tiny"]], ids=["bf16-gqa", "fp32-gqa", "fp32-one-launch-per-sublayer"])
 def test_arena_of_ff_bytes_gives_the_same_bits_as_an_arena_of_zeros(shape):
     clean = run_everything(shape, 0x00)
     dirty = run_everything(shape, 0xFF)
