@@ -1010,7 +1010,11 @@ constexpr PfRingTile kPfRingPairsF32[kPfRings] = {PF_RING_F32_SHAPES(PFR, PFD, 2
 PF_RING_F32_SHAPES(PFR, PFD, 1)
 #undef PFR
 #undef PFD
-constexpr int PF_DIRECT_MAX_KB = 64;                // most k-blocks of a slice: its requests wait for each other every PF_DIRECT_KB, the ring's do not
+// Most k-blocks of a slice that pf_direct_kernel takes, by class.  Its requests wait for each other every PF_DIRECT_KB, the ring's do not, and the wait is longer where the weights come from HBM
+// than where the last pass left them in the 256 MB behind the L2s.  Ring / direct, us, 17 to 64 rows, weights from HBM (16 k-blocks: as well for 256 features, 112 layers): QKV 16 8.8 / 7.6, 32
+// 10.7 / 10.2, 48 12.6 / 12.4, 64 14.4 / 14.6 (out of the cache 13.9 / 12.8); gate/up 16 11.0 / 9.4, 32 15.1 / 14.1, 48 19.2 / 18.9, 64 23.2 / 23.8 (21.8 / 19.6); the residual adds 8 7.1 / 6.7,
+// 11 7.3 / 6.7, 16 8.0 / 7.1, 18 8.2 / 8.4, 20 8.4 / 8.6, 24 9.1 / 9.0, 32 9.9 / 9.8 (768 features) and 9.9 / 10.1 (2048), 38 10.7 / 11.3, 48 11.6 / 12.1, 54 12.4 / 13.5, 64 13.6 / 14.3.
+constexpr int kPfDirectKb[PF_CLASSES] = {64, 16, 48, 16};
 const PfRingTile& pf_ring_tile(bool f32, bool pairs, int v) { return f32 ? (pairs ? kPfRingPairsF32 : kPfRingF32)[v] : (pairs ? kPfRingPairs : kPfRing)[v]; }
 // The kernel, shape and K slices with the least estimated time.  pf_ring_kernel: rounds of workgroups (one to a compute unit) on the busiest XCD, times
 // a workgroup's k-blocks at the shape's rate, but no less than the weights take from HBM at 6.1 TB/s; 4 us per round for filling the ring and the epilogue; for
@@ -1055,7 +1059,7 @@ PfPick pf_pick_gemm(const PfRules& r, int cls, int n_chunks) {
             if (raw && (r.ring_ks > 0 ? ks != r.ring_ks : n_chunks <= PF_FIXED_SLICES && ks != ks4)) continue;
             const int wgs = (n_fb + 7) / 8 * n_rb * ks, full = wgs / units, rest = wgs % units;
             // (one workgroup per compute unit: with more the ring is faster; tiny O, 100 rows, 28 workgroups on the busiest XCD 6.3 us either way, 144 rows, 36: 7.1 against 6.3)
-            if (direct && r.ring_tile < 0 && (wgs > units || KB > PF_DIRECT_MAX_KB * ks)) continue;
+            if (direct && r.ring_tile < 0 && (wgs > units || KB > kPfDirectKb[cls] * ks)) continue;
             const float kb_us = full * (T.us0 + T.us1) + (rest ? T.us0 + T.us1 * rest / units : 0.f);
             const float us = (full + (rest ? 1 : 0)) * (direct ? 2.5f : 4.f) + fmaxf((float)KB / ks * kb_us, hbm_us) + ks * slice_us;
             if (us < best_us) { best = {v, ks}; best_us = us; }

@@ -87,3 +87,15 @@ def test_short_prompts_and_bad_lengths():
 ], ids=lambda v: str(v) if isinstance(v, (int, str)) else "")
 def test_the_estimate_takes_what_was_measured_faster(name, n, gemm, tiles):
     assert asd.plan_prompt(asd.make_config(si.SHAPES[name], n), n)[0]["tile"][gemm] in tiles
+
+
+@pytest.mark.parametrize("d,ffn,n,direct", [
+    # fp32, k-blocks per slice against the kernel without a ring (tile 2): waves whose requests wait for each other lose to the ring over long slices, in the residual adds first
+    (256, 688, 45, "qkv oproj gateup down"), (512, 1408, 45, "qkv oproj gateup"), (768, 2048, 45, "qkv oproj gateup"),
+    (896, 2432, 32, "qkv oproj"), (1024, 2752, 45, "qkv oproj"), (1024, 4096, 17, "qkv oproj"),       # gate/up of 64 k-blocks 23.2 us on the ring, 23.8 without
+    (1152, 3072, 17, ""), (1280, 3456, 17, ""), (1536, 4096, 32, ""),                                  # down of 48, 54 and 64: 11.4, 12.3, 13.5 us, without 11.9, 13.5, 14.4
+], ids=str)
+def test_fp32_launches_without_a_ring_where_they_are_not_slower(d, ffn, n, direct):
+    s = si.Shape("fp32", 8, d, d // 64, d // 64, 64, ffn, 1024, si.DT_F32, 8, 8, 2)
+    tiles = asd.plan_prompt(asd.make_config(s, 256), n)[0]["tile"]
+    assert {g for g in tiles if tiles[g] == 2} == set(direct.split())
