@@ -347,15 +347,16 @@ typedef struct {
  * current kv_len with the given mask, over reps back-to-back repetitions bracketed
  * by HIP events on the engine's stream (as a captured graph when use_graph != 0);
  * *bytes (optional) = algorithmic bytes one such pass must read.
- * asd_profile_forward: one such pass with an event pair around every launch.
+ * asd_profile_forward: one such pass with an event pair around every launch.  Small fp32 models whose pass is one launch per
+ * sublayer: an attention sublayer counts as ASD_K_ATTN, an MLP sublayer as ASD_K_GATEUP, with the bytes of all it contains.
  * asd_time_step_class: the steps of one kernel class (ASD_K_QKV .. ASD_K_LMHEAD, one per kept layer) of a full-model
  * pass launched back to back, reps rounds, bracketed by one pair of HIP events on the engine's stream: average
  * microseconds per launch (weights differ from launch to launch, so no launch finds its weights cached) and the
  * algorithmic bytes one launch must read.  The steps run out of their usual order: the pass's activations are
- * scratch afterwards.
+ * scratch afterwards.  The steps are those of a pass as one launch per step, also where decoding takes one per sublayer.
  * asd_profile_prefill: the prompt pass in blocks over n > max_rows tokens (host array), once untimed and once with
  * an event pair around every launch; ASD_PK_ROWS collects the row-wise kernels (embedding, residual add + cosine
- * tap), ASD_PK_LMHEAD the last row's hand-over, LM head and argmax.  Resets the cache (kv_len 0 afterwards).
+ * tap), ASD_PK_LMHEAD the LM head and the launch behind it.  Resets the cache (kv_len 0 afterwards).
  * asd_copy_bench: average milliseconds of a plain device copy kernel moving
  * nbytes (read nbytes + write nbytes) inside the arena's scratch region; used to
  * calibrate byte counters and to report the achievable HBM rate.

@@ -785,9 +785,10 @@ bool drafts_hand_over(const asd_engine* e, const uint8_t* mask) {
     return false;
 }
 
-// pending: the draft whose token the pass before left to this one's first launch (-1: none); leave_finish: leave this draft's to the next
-int enqueue_small(asd_engine* e, const int32_t* d_tokens, int M, int pos_off, const uint8_t* mask, int nc, int fin_mode, int fin_arg, const PassOut& out, int pending,
-                  bool leave_finish, const BeginArgs* begin) {
+// pending: the draft whose token the pass before left to this one's first launch (-1: none); leave_finish: leave this draft's to the next.  profiler: an attention
+// sublayer counts as ASD_K_ATTN, an MLP sublayer as ASD_K_GATEUP, each with the bytes of all its steps
+int enqueue_small(asd_engine* e, const int32_t* d_tokens, int M, int pos_off, const uint8_t* mask, int nc, Profiler* profiler, int ctx_for_bytes, int fin_mode, int fin_arg,
+                  const PassOut& out, int pending, bool leave_finish, const BeginArgs* begin) {
     const asd_config& c = e->c;
     const int d = c.d_model, qd = c.n_heads * c.head_dim;
     // the stream's and the slices' two buffers: workspace of the five-launch path and of prompt blocks
@@ -797,6 +798,9 @@ int enqueue_small(asd_engine* e, const int32_t* d_tokens, int M, int pos_off, co
     float* pbuf[2] = {e->pf_raw, e->pf_raw + part_n};
 #define SM_IN in.part, in.xin, in.gain, in.d | (M << 16)
     int n = 0, open_sub = -1;               // launches so far; sublayer whose projection is open
+    Prof pr{profiler, e->stream};
+    double bytes[ASD_K_COUNT];
+    pass_bytes(e, nullptr, ctx_for_bytes, bytes);
     const BeginArgs first = begin ? *begin : BeginArgs{};
     SmallIn in{};
     in.d = d; in.M = M; in.inv_d = 1.f / (float)d; in.eps = c.rms_eps; in.ssq = out.ssq;
@@ -821,31 +825,41 @@ int enqueue_small(asd_engine* e, const int32_t* d_tokens, int M, int pos_off, co
             while ((c.n_heads << s_log) < SM_SLICES) ++s_log;
             const int heads = c.n_heads | (s_log << 8) | ((qd == SM_Q ? 5 : 4) << 16);
             input(ly.g_attn, true);
+            pr.begin(ASD_K_ATTN, (bytes[ASD_K_QKV] + bytes[ASD_K_ATTN] + bytes[ASD_K_OPROJ]) / c.n_layers);
             sm_by_rows(M, [&](auto rm, auto rv) {
                 constexpr int RM = decltype(rm)::value, RV = decltype(rv)::value;
 #define ATT(h) if (c.head_dim == h) sm_attn_kernel<h, RM, RV><<<SM_SLICES, SM_NT, 0, e->stream>>>(SM_IN, heads, (const float*)ly.wqkv, e->st, e->rope, in, first, a);
                 ATT(32) ATT(64) ATT(128)
 #undef ATT
             });
+            pr.end();
             ++n; open_sub = 2 * l;
         }
         if (!(mask && mask[2 * l + 1])) {
             float* const part_out = pbuf[n & 1];
             input(ly.g_mlp, true);
+            pr.begin(ASD_K_GATEUP, (bytes[ASD_K_GATEUP] + bytes[ASD_K_DOWN]) / c.n_layers);
             sm_by_rows(M, [&](auto rm, auto rv) {
                 sm_mlp_kernel<decltype(rm)::value, decltype(rv)::value><<<SM_SLICES, SM_NT, 0, e->stream>>>(
                     SM_IN, c.d_ffn / 16, (const float*)ly.wg, (const float*)ly.wu, (const float*)ly.wd, in, first, part_out);
             });
+            pr.end();
             ++n; open_sub = 2 * l + 1;
         }
     }
     input(e->g_final, false);
+    pr.begin(ASD_K_LMHEAD, bytes[ASD_K_LMHEAD]);
     sm_by_rows(M, [&](auto rm, auto rv) {
         sm_lm_kernel<decltype(rm)::value, decltype(rv)::value><<<(c.vocab + 63) / 64, SM_LM_NW * 64, 0, e->stream>>>(
             SM_IN, c.vocab, (const float*)e->lm, in, first, out.logits, out.amax_part);
     });
 #undef SM_IN
-    if (!leave_finish) launch_finish(e, M, mask, fin_mode, fin_arg, out);
+    pr.end();
+    if (!leave_finish) {
+        pr.begin(ASD_K_FINISH, 0);
+        launch_finish(e, M, mask, fin_mode, fin_arg, out);
+        pr.end();
+    }
     const hipError_t r = hipGetLastError();
     if (r != hipSuccess) return fail(e, ASD_E_HIP, "kernel launch: %s", hipGetErrorString(r));
     return ASD_OK;
@@ -856,7 +870,7 @@ int enqueue_forward(asd_engine* e, const int32_t* d_tokens, int M, int pos_off, 
                     Profiler* profiler, int ctx_for_bytes, int fin_mode = FIN_NONE, int fin_arg = 0, const PassOut* out_or_null = nullptr,
                     int pending = -1, bool leave_finish = false, const BeginArgs* begin = nullptr) {
     const PassOut out = out_or_null ? *out_or_null : engine_out(e);
-    if (small_pass(e, M, nc) && !profiler) return enqueue_small(e, d_tokens, M, pos_off, mask, nc, fin_mode, fin_arg, out, pending, leave_finish, begin);
+    if (small_pass(e, M, nc)) return enqueue_small(e, d_tokens, M, pos_off, mask, nc, profiler, ctx_for_bytes, fin_mode, fin_arg, out, pending, leave_finish, begin);
     std::vector<PassOp> ops;
     build_pass(e, M, pos_off, mask, ctx_for_bytes, nc, out, ops);
     return launch_steps(e, ops, d_tokens, M, mask, profiler, fin_mode, fin_arg, out, pending >= 0, leave_finish, begin);

@@ -114,3 +114,22 @@ def test_a_token_outside_the_vocabulary_is_reported():
         e.forward_noalloc(t, 0, commit=False)
         e.check()
     new.close(), old.close()
+
+
+def test_the_profiled_pass_is_the_pass_that_runs():
+    """One launch per kept sublayer, the LM head and the finish, with the bytes of all steps; the launches of one launch per step where that is what runs."""
+    s = si.SHAPES["tiny"]
+    new, old = engines(s, 128)
+    skip = np.array([1, 0, 0, 1, 1, 1, 0, 0], np.uint8)
+    for e in (new, old):
+        e.prefill(np.arange(20, dtype=np.int32))
+    for rows, mask in ((1, None), (5, skip), (8, np.ones(8, np.uint8)), (9, skip)):
+        a, b = (e.profile_forward(rows, mask) for e in (new, old))
+        kept = np.zeros(8, np.uint8) if mask is None else mask
+        launches = {k: v["launches"] for k, v in a.items() if k != "ms_total" and v["launches"]}
+        att, mlp = int((kept[0::2] == 0).sum()), int((kept[1::2] == 0).sum())
+        want = dict(attn=att, gateup=mlp, lmhead=1, finish=1) if rows <= 8 else dict(embed=1, qkv=att, attn=att, oproj=att, gateup=mlp, down=mlp, lmhead=1, finish=1)
+        assert launches == {k: v for k, v in want.items() if v}, rows
+        total = lambda p: sum(v["bytes"] for k, v in p.items() if k != "ms_total")
+        assert abs(total(a) - total(b)) <= 1e-12 * total(b) and total(b) == pytest.approx(e.time_pass(rows, mask, 1)[1], rel=1e-12), rows
+    new.close(), old.close()
