@@ -276,8 +276,9 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_draft_kernel(const Samp
     draft_draw<TILES>(a, j, true, red, ired);
 }
 // Between two draft steps: the draw and the embedding of the token, in one launch of EMBED_SPLIT workgroups, each of which draws for itself (the draw is one workgroup's latency,
-// and the logits come to eight nearly as fast as to one; see finish_embed_kernel).  Vocabulary 32000, 4096 features: 13.0 + 4.6 us and the gap between them -> 15.2 us; a sampled decode of
-// 24 tokens 16.99 -> 16.85 ms.
+// and the logits come to eight nearly as fast as to one; see finish_embed_kernel).  Vocabulary 32000, 4096 features: 13.0 + 4.6 us and the gap between them -> 15.2 us.  Calls
+// that sample 24 tokens with four or eight drafts (7B, 13B and 512-feature fp32 widths, one to four layers, vocabularies of 1024 to 128256), four processes of each build in turn: 1.001 to
+// 1.008x, runs of one build within 0.7 % (13B width, 8 drafts: 5126 -> 5099 us; 512 features: 2846 -> 2824; vocabulary 128256, re-read by every workgroup: 8713 -> 8701).
 template <class T, int TILES>
 __global__ __launch_bounds__(SAMPLE_THREADS) void sample_draft_embed_kernel(const SampleArgs a, int j, const typename T::elem* E, int d, const float* g_first,
                                                                             float* xres, void* xb, size_t xb_plane, float* part) {

@@ -1,6 +1,6 @@
 // Decode passes of small fp32 models: one launch per sublayer instead of five per layer.
 //
-// A pass of such a model is a chain of launches of 3 to 6 us each that hardly compute: 256 features, 4 layers: 22 launches, 95 us.
+// A pass of such a model is a chain of launches of 3 to 6 us each that hardly compute: 256 features, 4 layers: 22 launches, 99 us.
 // Here a sublayer is one launch of SM_SLICES workgroups, one per K slice of its residual projection (the slices that the
 // eight waves of gemm_kernel<EPI_RES> take): the workgroup computes everything that its slice of the projection needs, so nothing
 // is exchanged inside the launch:
