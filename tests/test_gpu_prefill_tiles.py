@@ -201,7 +201,7 @@ def test_fp32_tile_shapes_give_the_same_bits(n):
 @pytest.mark.parametrize("d,ffn,n", [(16, 16, 17), (256, 688, 200), (272, 592, 45), (1024, 1040, 33)], ids=str)
 def test_fp32_waves_on_their_own_give_the_same_bits(d, ffn, n):
     """pf_direct_kernel at one k-block, at a whole batch of requests, one past it and at four batches, with tiles that do not fill its workgroups, against the
-    four-wave kernel; the estimate takes it where the launch has a compute unit per workgroup and not beyond."""
+    four-wave kernel; the estimate takes it where the slices are short and the launch has a compute unit per workgroup, and not beyond."""
     shape = si.Shape("direct", 2, d, 3, 3, 32, ffn, 320, si.DT_F32, 8, 8, 2)
     toks = si.prompt(n, n, shape.vocab)
     W = list(si.all_tensors(shape, 3, 0.1))
